@@ -2,7 +2,7 @@
 // kernel entry points. See include/blink.h for the contract of every exported function.
 #include "../../include/blink.h"
 #include "blink_device.h"
-#include "phases.h"
+#include "phase_kernels.h"
 
 #include <algorithm>
 #include <atomic>
@@ -26,61 +26,33 @@ __global__ void __launch_bounds__(BLK_THREADS) k_sched(DevCtx c) {
 // speculative decoding: the drafts of the running greedy requests, ahead of the scheduler step that feeds them
 __global__ void __launch_bounds__(BLK_THREADS) k_spec_draft(DevCtx c) { spec_draft(c, blockIdx.x, gridDim.x); }
 
-// one named kernel per phase so that profiles attribute time to the step of the forward pass. Two workgroups per
-// compute unit (at most 256 registers per lane): the start and the end of one workgroup overlap the other's streaming.
-#define PHASE_KERNEL(name, PH)                                                   \
-  __global__ void __launch_bounds__(BLK_THREADS, 2) name(DevCtx c, u32 layer) {  \
-    __shared__ PhaseSharedOf<PH>::type sh;                                       \
-    run_phase(c, PH, layer, &sh, blockIdx.x, gridDim.x);                         \
-  }
-PHASE_KERNEL(k_embed, PH_EMBED)
-PHASE_KERNEL(k_norm1, PH_NORM1)
-// The projections with few output rows (QKV, attention output, FFN down) run eight waves per workgroup on the bf16
-// path so that K is split eight ways and enough weight bytes are in flight; the fp32 path keeps four.
-#define PHASE_KERNEL8(name, PH)                                                  \
-  __global__ void __launch_bounds__(512) name(DevCtx c, u32 layer) {             \
-    __shared__ PhaseSharedOf<PH>::type sh;                                       \
-    run_phase(c, PH, layer, &sh, blockIdx.x, gridDim.x);                         \
-  }
-PHASE_KERNEL8(k_qkv, PH_QKV)
-PHASE_KERNEL(k_rope_kvwrite, PH_ROPE)
-PHASE_KERNEL8(k_attention, PH_ATTN)
-PHASE_KERNEL8(k_oproj, PH_OPROJ)
-PHASE_KERNEL(k_norm2, PH_NORM2)
-PHASE_KERNEL(k_gateup, PH_GATEUP)
-PHASE_KERNEL8(k_down, PH_DOWN)
-PHASE_KERNEL(k_final_norm, PH_FINAL_NORM)
-PHASE_KERNEL(k_lm_head, PH_LM_HEAD)
-PHASE_KERNEL(k_sample_publish, PH_SAMPLE)
-PHASE_KERNEL(k_attention_combine, PH_ATTN_COMBINE)
-PHASE_KERNEL(k_qkv_reduce, PH_QKV_RED)
-PHASE_KERNEL(k_oproj_reduce, PH_OPROJ_RED)
-PHASE_KERNEL(k_down_reduce, PH_DOWN_RED)
-PHASE_KERNEL(k_moe_router, PH_ROUTER)
-PHASE_KERNEL(k_moe_route, PH_ROUTE)
-PHASE_KERNEL(k_moe_gateup, PH_MOE_GATEUP)
-PHASE_KERNEL(k_moe_down, PH_MOE_DOWN)
-PHASE_KERNEL(k_moe_combine, PH_MOE_COMBINE)
-PHASE_KERNEL(k_moe_permute, PH_MOE_PERMUTE)
-
 typedef void (*phase_kernel_t)(DevCtx, u32);
-static phase_kernel_t phase_kernel(int ph) {
+static phase_kernel_t phase_kernel(int ph, bool f32) {
+  if (f32) {
+    switch (ph) {
+      case PH_EMBED: return k_embed_f32;
+      case PH_NORM1: return k_norm1_f32;
+      case PH_QKV: return k_qkv_f32;
+      case PH_ROPE: return k_rope_kvwrite_f32;
+      case PH_ATTN: return k_attention_f32;
+      case PH_OPROJ: return k_oproj_f32;
+      case PH_NORM2: return k_norm2_f32;
+      case PH_GATEUP: return k_gateup_f32;
+      case PH_DOWN: return k_down_f32;
+      case PH_FINAL_NORM: return k_final_norm_f32;
+      case PH_LM_HEAD: return k_lm_head_f32;
+      default: return k_sample_publish_f32;
+    }
+  }
   switch (ph) {
     case PH_EMBED: return k_embed;
-    case PH_NORM1: return k_norm1;
     case PH_QKV: return k_qkv;
-    case PH_ROPE: return k_rope_kvwrite;
     case PH_ATTN: return k_attention;
     case PH_OPROJ: return k_oproj;
-    case PH_NORM2: return k_norm2;
     case PH_GATEUP: return k_gateup;
     case PH_DOWN: return k_down;
-    case PH_FINAL_NORM: return k_final_norm;
     case PH_LM_HEAD: return k_lm_head;
     case PH_ATTN_COMBINE: return k_attention_combine;
-    case PH_QKV_RED: return k_qkv_reduce;
-    case PH_OPROJ_RED: return k_oproj_reduce;
-    case PH_DOWN_RED: return k_down_reduce;
     case PH_ROUTER: return k_moe_router;
     case PH_ROUTE: return k_moe_route;
     case PH_MOE_GATEUP: return k_moe_gateup;
@@ -418,7 +390,7 @@ static int init_impl(const blink_config* cfg, blink_engine* e) {
       };
       auto pack = [&](u64 src_off, u32 N, u32 K, u32 pair_rows, u32 perm_hd, const f16_t** dst) -> int {
         f16_t* p;
-        const u64 elems = (u64)((N + 15) / 16) * 16 * K;
+        const u64 elems = (u64)((N + 15) / 16) * gemm_k_tiles(K) * 512;
         if (int rc = dalloc(e, &p, elems, false)) return rc;
         if (int rc = pack_to(p, src_off, 0, N, K, pair_rows, perm_hd)) return rc;
         *dst = p;
@@ -427,16 +399,16 @@ static int init_impl(const blink_config* cfg, blink_engine* e) {
       };
       // the experts of one layer: packed one after the other (2F x d gate/up pairs, then d x F down matrices)
       auto pack_experts = [&](u64 off_g, u64 off_u, u64 off_d, LayerWP& lp_l) -> int {
-        const u64 E = c.n_experts;
+        const u64 E = c.n_experts, gu = (2 * F / 16) * gemm_k_tiles(c.d) * 512, dn = (d / 16) * gemm_k_tiles(c.F) * 512;   // elements of one expert
         f16_t *pgu, *pd;
-        if (int rc = dalloc(e, &pgu, E * 2 * F * d, false)) return rc;
-        if (int rc = dalloc(e, &pd, E * d * F, false)) return rc;
+        if (int rc = dalloc(e, &pgu, E * gu, false)) return rc;
+        if (int rc = dalloc(e, &pd, E * dn, false)) return rc;
         for (u64 x = 0; x < E; ++x) {
-          if (int rc = pack_to(pgu + x * 2 * F * d, off_g + x * 2 * F * d, off_u + x * 2 * F * d, 2 * c.F, c.d, c.F, 0)) return rc;
-          if (int rc = pack_to(pd + x * d * F, off_d + x * 2 * d * F, 0, c.d, c.F, 0, 0)) return rc;
+          if (int rc = pack_to(pgu + x * gu, off_g + x * 2 * F * d, off_u + x * 2 * F * d, 2 * c.F, c.d, c.F, 0)) return rc;
+          if (int rc = pack_to(pd + x * dn, off_d + x * 2 * d * F, 0, c.d, c.F, 0, 0)) return rc;
         }
         lp_l.wgu = pgu; lp_l.wd = pd;
-        e->weight_bytes += E * 3 * F * d * 2;
+        e->weight_bytes += E * (gu + dn) * 2;
         return 0;
       };
       auto all = [&]() -> int {
@@ -504,15 +476,16 @@ static int init_impl(const blink_config* cfg, blink_engine* e) {
   c.TBS = ((c.maxT + 255) / 256) * 16;   // whole 256-token workgroup tiles
   if (c.dtype == 1) {
     const u64 tile_tokens = (u64)c.TBS * 16;
-    if (int rc = dalloc(e, &c.xq, tile_tokens * c.d)) return rc;
-    if (int rc = dalloc(e, &c.aq, tile_tokens * c.nq * c.hd)) return rc;
+    auto k_pad = [](u32 K) { return (u64)gemm_k_tiles(K) * 32; };      // (the padding stays zero)
+    if (int rc = dalloc(e, &c.xq, tile_tokens * k_pad(c.d))) return rc;
+    if (int rc = dalloc(e, &c.aq, tile_tokens * k_pad(c.nq * c.hd))) return rc;
     if (c.n_experts) {
       // every (token, selected expert) pair is a column of the grouped GEMMs; the columns of one expert start at a
       // multiple of 16, and a workgroup tile may read up to 255 columns past the last one
       const u64 cols = (u64)c.maxT * c.n_active + 16ull * c.n_experts + 256 + 16;
       c.moe_TBS = (u32)((cols + 15) / 16);
-      if (int rc = dalloc(e, &c.hq_moe, (u64)c.moe_TBS * 16 * c.F)) return rc;
-      if (int rc = dalloc(e, &c.xq_moe, (u64)c.moe_TBS * 16 * c.d)) return rc;
+      if (int rc = dalloc(e, &c.hq_moe, (u64)c.moe_TBS * 16 * k_pad(c.F))) return rc;
+      if (int rc = dalloc(e, &c.xq_moe, (u64)c.moe_TBS * 16 * k_pad(c.d))) return rc;
       if (int rc = dalloc(e, &c.y_moe, (u64)c.moe_TBS * 16 * c.d, false)) return rc;
       if (int rc = dalloc(e, &c.moe_logits, (u64)c.maxT * c.n_experts, false)) return rc;
       if (int rc = dalloc(e, &c.moe_count, c.n_experts)) return rc;
@@ -521,15 +494,9 @@ static int init_impl(const blink_config* cfg, blink_engine* e) {
       if (int rc = dalloc(e, &c.moe_pos, (u64)c.maxT * c.n_active)) return rc;
       if (int rc = dalloc(e, &c.moe_w, (u64)c.maxT * c.n_active)) return rc;
       if (int rc = dalloc(e, &c.moe_rstd, c.maxT)) return rc;
-    } else if (int rc = dalloc(e, &c.hq, tile_tokens * c.F)) return rc;
+    } else if (int rc = dalloc(e, &c.hq, tile_tokens * k_pad(c.F))) return rc;
     if (int rc = dalloc(e, &c.ssq, tile_tokens * (c.d / 16))) return rc;
     if (int rc = dalloc(e, &c.qbuf, (u64)c.maxT * c.nq * c.hd)) return rc;
-    if (c.max_batch > 64 && ((cfg->tune >> 28) & 3u) == 2u) {   // the chain with K split across workgroups: up to eight K slices of the widest split GEMM at 256 tokens
-      c.splitk_ok = 1;
-      const u64 rows = ((std::max<u64>(c.qkv_n, c.d) + 127) / 128) * 128;
-      c.gemm_part_cap = 8ull * rows * 256;
-      if (int rc = dalloc(e, &c.gemm_part, c.gemm_part_cap, false)) return rc;
-    }
     {
       c.chunk_cap = c.max_batch * ((c.max_seq_len + ATTN_CHUNK_TOKENS - 1) / ATTN_CHUNK_TOKENS);
       if (int rc = dalloc(e, &c.chunk_rec, 2ull * c.chunk_cap)) return rc;
@@ -691,8 +658,6 @@ extern "C" int blink_submit(blink_engine* e, const int32_t* prompt, uint32_t n_p
 // The host thread is a pump: it enqueues the fixed kernel chain of one iteration, several iterations ahead,
 // and never reads a result the device waits for. Every decision (what runs, on which shapes, when the window
 // ends) is taken on the device; an iteration enqueued after the window has ended costs a few empty kernels.
-static bool has_split_chain(const blink_engine* e) { return e->ctx.dtype == 1 && e->ctx.splitk_ok != 0; }
-
 static bool phase_per_layer(int ph) { return (ph >= PH_LAYER_FIRST && ph <= PH_LAYER_LAST) || ph >= PH_ATTN_COMBINE; }
 
 static int launch_phase(blink_engine* e, const DevCtx& ctx, hipStream_t st, int ph, u32 layer, u64 enq_index) {
@@ -705,25 +670,21 @@ static int launch_phase(blink_engine* e, const DevCtx& ctx, hipStream_t st, int 
     b = e->phase_ev[2 * slot + 1];
     HIPCHK(hipEventRecord(a, st));
   }
-  // (bit 31 of the tuning word: the narrow projections run four waves per workgroup like the other GEMMs)
-  const bool wide = ph == PH_ATTN || ((ph == PH_QKV || ph == PH_OPROJ || ph == PH_DOWN) && !(e->cfg.tune & 0x80000000u));
-  const u32 threads = (wide && e->ctx.dtype == 1) ? 512u : (u32)BLK_THREADS;
-  hipLaunchKernelGGL(phase_kernel(ph), dim3(e->grid), dim3(threads), 0, st, ctx, layer);
+  // the GEMMs of a bf16 model run one eight-wave workgroup per compute unit
+  const bool gemm = ph == PH_QKV || ph == PH_OPROJ || ph == PH_GATEUP || ph == PH_DOWN || ph == PH_LM_HEAD || ph == PH_MOE_GATEUP || ph == PH_MOE_DOWN;
+  const bool bf16 = e->ctx.dtype == 1;
+  const u32 threads = bf16 && (gemm || ph == PH_ATTN) ? 512u : (u32)BLK_THREADS;
+  hipLaunchKernelGGL(phase_kernel(ph, !bf16), dim3(bf16 && gemm ? (u32)e->n_cu : e->grid), dim3(threads), 0, st, ctx, layer);
   if (timed) HIPCHK(hipEventRecord(b, st));
   return 0;
 }
 
-// The kernel chain of one iteration. An engine made with bits 28-29 of blink_config.tune = 2 runs the chain that lets
-// the narrow GEMMs split K across workgroups when the iteration has 65..256 tokens; it carries a reduce kernel behind
-// each of them (three more launches per layer, which do nothing in other iterations). Measured on the llama3_8b shape at
-// 256 tokens, the second kernel costs what the split saves (QKV 60 -> 32 + 21 us, attention output 32 -> 26 + 14 us,
-// down 69 -> 54 + 14 us), so the default chain does not split.
+// The kernel chain of one iteration.
 // whole_chain: the chain for iterations whose decode attention takes whole contexts as its items. The scheduler step
 // of this chain is told to make them so whatever the batch (bit 22 of its tuning word), no item leaves a partial
 // result, and the merge kernel behind every attention launch is left out: 32 launches less per iteration on a
 // 32-layer model (an empty kernel costs 4-5 us here, the gap before the next one 2-3 us).
 static int enqueue_iteration_kernels(blink_engine* e, hipStream_t st, u64 enq_index, bool whole_chain) {
-  const bool split = has_split_chain(e);
   DevCtx c = e->ctx;
   if (whole_chain) c.tune_nw |= 0x400000u;
   if (c.spec_k) hipLaunchKernelGGL(k_spec_draft, dim3((c.max_batch + 3) / 4), dim3(BLK_THREADS), 0, st, c);
@@ -739,9 +700,8 @@ static int enqueue_iteration_kernels(blink_engine* e, hipStream_t st, u64 enq_in
         continue;
       }
       if (int rc = launch_phase(e, c, st, ph, l, enq_index)) return rc;
-      const int after = ph == PH_ATTN ? PH_ATTN_COMBINE : ph == PH_QKV ? PH_QKV_RED : ph == PH_OPROJ ? PH_OPROJ_RED : ph == PH_DOWN ? PH_DOWN_RED : -1;
-      if (c.dtype == 1 && after >= 0 && (after == PH_ATTN_COMBINE ? !whole_chain : split))
-        if (int rc = launch_phase(e, c, st, after, l, enq_index)) return rc;
+      if (c.dtype == 1 && ph == PH_ATTN && !whole_chain)
+        if (int rc = launch_phase(e, c, st, PH_ATTN_COMBINE, l, enq_index)) return rc;
     }
   if (int rc = launch_phase(e, c, st, PH_FINAL_NORM, 0, enq_index)) return rc;
   if (int rc = launch_phase(e, c, st, PH_LM_HEAD, 0, enq_index)) return rc;

@@ -264,7 +264,7 @@ struct DevCtx {
   f16_t* hq;            // packed half(silu(gate)*up), inner dimension F
   float* ssq;           // [token][d/16] partial sums of squares of the residual stream
   u32 TBS;              // token-block stride of the packed activation buffers
-  u32 tune_nw;          // tuning knob of the streaming GEMM (0: automatic)
+  u32 tune_nw;          // tuning word (MfmaGemmArgs::tune_nw)
   // mixture of experts
   float* moe_logits;    // [maxT][n_experts] router logits
   u32* moe_count;       // [n_experts] tokens routed to every expert in the current layer
@@ -277,10 +277,6 @@ struct DevCtx {
   f16_t* hq_moe;        // packed silu(gate)*up of all pairs, columns grouped by expert (groups padded to 16), inner dimension F
   float* y_moe;         // [columns][d] expert outputs of all pairs
   u32 moe_TBS;          // token-block stride of hq_moe
-  // GEMMs with K split across workgroups (decode iterations of 65..256 tokens): the slices' fp32 partial sums
-  float* gemm_part;
-  u64 gemm_part_cap;    // floats
-  u32 splitk_ok;        // 1: the engine's kernel chain carries the reduce kernels (a chain without them never splits)
   // decode attention: partial (max, sum, output) of every chunk of a context longer than one chunk
   float* attn_part_o;   // [chunk][kv head][G][hd]
   float* attn_part_ml;  // [chunk][kv head][G][2]

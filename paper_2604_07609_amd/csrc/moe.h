@@ -1,14 +1,14 @@
 // Mixture-of-experts FFN of a bf16 model (the second workload of the paper's evaluation, section 6, is such a model):
 // router GEMM -> per-token selection of the n_active largest router logits (ties to the lower expert id) and softmax over
 // them -> one list of tokens per expert -> the normalised inputs of all (token, expert) pairs gathered into columns grouped
-// by expert -> grouped gate/up and down GEMMs (an expert's columns as independent wave items or as one GEMM of the tile
-// schedules) -> weighted sum of a token's expert outputs in selection order + residual + next norm's operand.
+// by expert -> grouped gate/up and down GEMMs (an expert's columns as independent wave items or as tiles of one
+// stream of tiles over all such experts) -> weighted sum of a token's expert outputs in selection order + residual + next norm's operand.
 // The expert lists are filled with atomic counters: the order of the tokens inside a list depends on timing, but a
 // token's result does not depend on its place in the list (every GEMM column is accumulated on its own, in an order fixed
 // by the schedule), and the per-token sum over its experts runs in selection order, so results are reproducible.
 #pragma once
 #include "blink_device.h"
-#include "mfma_gemm.h"
+#include "gemm_dma.h"
 #include "sampler.h"
 
 #define MOE_MAX_EXPERTS 256
@@ -16,48 +16,73 @@
 
 #define MOE_WAVE_MAX_TOKENS 64   // experts with at most this many tokens are run by independent waves (see moe_wave_item)
 
-struct MoeShared {
-  MfmaShared mfma;
+struct MoeLists {
   u32 cnt[MOE_MAX_EXPERTS];
   u32 off[MOE_MAX_EXPERTS + 1];   // first column of every expert's group: counts padded to whole 16-token blocks
+};
+struct MoeShared {
+  MoeLists l;
   u32 small_e[MOE_MAX_EXPERTS];   // experts with 1..MOE_WAVE_MAX_TOKENS tokens, and the first wave item of each
   u32 small_base[MOE_MAX_EXPERTS + 1];
-  u32 big_e[MOE_MAX_EXPERTS];     // experts with more tokens: one GEMM of the workgroup schedules each
-  u32 big_start[MOE_MAX_EXPERTS]; // workgroup that takes the first tile of that GEMM: the tiles of all such GEMMs go round the grid
-  u32 n_small, n_big;
-  float wrstd[4][64];             // per wave: norm scales of the tokens of its current item
+  u32 big_e[MOE_MAX_EXPERTS];     // experts with more tokens, and the blocks of tokens of all of them before each
+  u32 big_base[MOE_MAX_EXPERTS + 1];
+  u32 n_small, n_big, shape;      // shape: workgroup tile of the big experts' GEMMs (DMA_SHAPES)
+  float wrstd[8][64];             // per wave: norm scales of the tokens of its current item
+  DmaShared dma;
 };
 
-// counts -> LDS, offsets by a serial prefix sum (at most 256 terms); every workgroup of the grouped kernels does this.
-// NT > 0 (row tiles of an expert's matrix): also the split of the experts into those run by independent waves, with their
-// wave items (moe_wave_rows row tiles each), and the rest.
+// row tiles of a wave item
 __device__ __forceinline__ u32 moe_wave_rows(u32 n_tokens) { return n_tokens <= 32 ? 4u : 2u; }
 
-__device__ __forceinline__ void moe_offsets(const DevCtx& c, MoeShared& sh, u32 NT = 0, u32 nwg = 1) {
-  for (u32 e = threadIdx.x; e < c.n_experts; e += blockDim.x) sh.cnt[e] = c.moe_count[e];
+// counts -> LDS, offsets by a serial prefix sum (at most 256 terms); every workgroup of the grouped kernels does this.
+__device__ __forceinline__ void moe_offsets(const DevCtx& c, MoeLists& l) {
+  for (u32 e = threadIdx.x; e < c.n_experts; e += blockDim.x) l.cnt[e] = c.moe_count[e];
   __syncthreads();
   if (threadIdx.x == 0) {
-    u32 o = 0, ns = 0, nb = 0, base = 0, tiles = 0;
+    u32 o = 0;
     for (u32 e = 0; e < c.n_experts; ++e) {
-      const u32 n = sh.cnt[e];
-      sh.off[e] = o;
-      o += (n + 15u) & ~15u;
-      if (NT && n) {
-        if (n <= MOE_WAVE_MAX_TOKENS) {
-          const u32 nw = moe_wave_rows(n);
-          sh.small_e[ns] = e; sh.small_base[ns] = base; base += (NT + nw - 1) / nw; ++ns;
-        }
-        else {
-          // workgroup tiles of the expert's GEMM at the tile width moe_grouped forces: 128 rows x (all tokens up to 192, else 256)
-          sh.big_e[nb] = e;
-          sh.big_start[nb++] = tiles % nwg;
-          tiles += ((NT + 7) / 8) * (n <= 192 ? 1u : (n + 255) / 256);
-        }
+      l.off[e] = o;
+      o += (l.cnt[e] + 15u) & ~15u;
+    }
+    l.off[c.n_experts] = o;
+  }
+  __syncthreads();
+}
+
+// The split of the experts for a grouped GEMM of N rows and inner dimension K: those run by independent waves, with their wave
+// items (moe_wave_rows row tiles each), and the rest, whose tiles have the shape that takes the least time for all of
+// them together (bits 12-14 of the tuning word force it).
+__device__ __forceinline__ void moe_split(const DevCtx& c, MoeShared& sh, u32 N, u32 K, u32 nwg) {
+  moe_offsets(c, sh.l);
+  if (threadIdx.x == 0) {
+    const u32 NT = N / 16;
+    u32 ns = 0, nb = 0, base = 0, b64 = 0, b128 = 0, b192 = 0, b256 = 0;
+    for (u32 e = 0; e < c.n_experts; ++e) {
+      const u32 n = sh.l.cnt[e];
+      if (n == 0) continue;
+      if (n <= MOE_WAVE_MAX_TOKENS) {
+        const u32 nw = moe_wave_rows(n);
+        sh.small_e[ns] = e; sh.small_base[ns] = base; base += (NT + nw - 1) / nw; ++ns;
+      } else {
+        sh.big_e[nb++] = e;
+        b64 += (n + 63) / 64; b128 += (n + 127) / 128; b192 += (n + 191) / 192; b256 += (n + 255) / 256;
       }
     }
-    sh.off[c.n_experts] = o;
     sh.small_base[ns] = base;
     sh.n_small = ns; sh.n_big = nb;
+    u32 best = (c.tune_nw >> 12) & 7u, width = 0, bt_of_best = 256;
+    const bool forced = best != 0 && best != 5;
+    float least = INFINITY;
+#define OFFER(id, bn, bt, lone, full, fixed) {                                                                             \
+      width = bt == 64 ? b64 : bt == 128 ? b128 : bt == 192 ? b192 : b256;                                                 \
+      const float t = dma_cost((N + bn - 1) / bn * width, K, lone, full, fixed, nwg);                                      \
+      if (forced ? best == id : t < least) { least = t; best = id; bt_of_best = bt; } }
+    DMA_SHAPES(OFFER)
+#undef OFFER
+    sh.shape = best;
+    u32 o = 0;
+    for (u32 b = 0; b < nb; ++b) { sh.big_base[b] = o; o += (sh.l.cnt[sh.big_e[b]] + bt_of_best - 1) / bt_of_best; }
+    sh.big_base[nb] = o;
   }
   __syncthreads();
 }
@@ -118,7 +143,7 @@ __device__ __forceinline__ void moe_route(const DevCtx& c, u32 layer, u32 wg, u3
 // fp32 values of the residual stream of column c's token, applies the norm's gain and scale and rounds once to half
 // precision. Gathering the tokens here, once, lets the grouped GEMMs read whole operand tiles instead of sixteen-byte
 // pieces of sixteen different tokens per load. Columns past an expert's count (its group is padded to 16) get zeros.
-__device__ __forceinline__ void moe_permute(const DevCtx& c, u32 layer, MoeShared& sh, u32 wg, u32 nwg) {
+__device__ __forceinline__ void moe_permute(const DevCtx& c, u32 layer, MoeLists& sh, u32 wg, u32 nwg) {
   moe_offsets(c, sh);
   const u32 lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6, E = c.n_experts;
   const u32 nblk = sh.off[E] / 16, KT = c.d / 32, lc = lane & 15, kg = lane >> 4;
@@ -169,9 +194,9 @@ __device__ __forceinline__ void moe_wave_item(const DevCtx& c, const LayerWP* P,
   constexpr int NW = TW <= 2 ? 4 : 2, U = 2;
   constexpr int EPI = GATEUP ? EPI_SILU_GATE : EPI_SCALED_STORE;
   const u32 lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const u32 cnt = sh.cnt[e], col0 = sh.off[e];
-  const u32 K = GATEUP ? c.d : c.F, N = GATEUP ? 2 * c.F : c.d, KT = K / 32, NT = N / 16;
-  const f16_t* Wp = GATEUP ? P->wgu + (u64)e * (2 * c.F) * c.d : P->wd + (u64)e * c.d * c.F;
+  const u32 cnt = sh.l.cnt[e], col0 = sh.l.off[e];
+  const u32 K = GATEUP ? c.d : c.F, N = GATEUP ? 2 * c.F : c.d, KT = gemm_k_tiles(K), NT = N / 16;
+  const f16_t* Wp = (GATEUP ? P->wgu : P->wd) + (u64)e * NT * KT * 512;
   const f16_t* wp[NW];
 #pragma unroll
   for (int i = 0; i < NW; ++i) wp[i] = Wp + (u64)min(g * NW + i, NT - 1) * KT * 512 + lane * 8;
@@ -225,13 +250,38 @@ __device__ __forceinline__ void moe_wave_item(const DevCtx& c, const LayerWP* P,
     }
 }
 
-// Experts with more tokens run as one GEMM of the workgroup schedules each (shared operand tiles in LDS); every GEMM
-// starts at the workgroup behind the previous one's last tile, so the tiles of all of them go round the grid evenly.
+// Experts with more tokens: one stream of workgroup tiles (gemm_dma) over the tiles of all of them, expert by expert, so that a
+// workgroup fetches the first operands of an expert's tile while it stores the previous expert's, and all tiles go round
+// the grid evenly. (One GEMM after the other, staged through registers, 2100 tokens on 128 experts of width 768: gate/up
+// 558 us, down 404 us per layer.)
+template <bool GATEUP>
+struct MoeItems {
+  const MoeShared& sh;
+  const f16_t *W, *X;
+  u32 nblocks, expert_elems, total;
+  __device__ __forceinline__ void at(u32 i, MfmaGemmArgs& a, u32& nb, u32& tb) const {
+    u32 lo = 0, hi = sh.n_big;                       // the expert of item i: last b with nblocks * big_base[b] <= i
+    while (hi - lo > 1) {
+      const u32 mid = (lo + hi) >> 1;
+      if (nblocks * sh.big_base[mid] <= i) lo = mid; else hi = mid;
+    }
+    lo = (u32)__builtin_amdgcn_readfirstlane(lo);
+    const u32 e = (u32)__builtin_amdgcn_readfirstlane(sh.big_e[lo]), base = (u32)__builtin_amdgcn_readfirstlane(sh.big_base[lo]);
+    const u32 width = (u32)__builtin_amdgcn_readfirstlane(sh.big_base[lo + 1]) - base, rem = i - nblocks * base;
+    nb = rem / width;                                // the expert's blocks of tokens vary fastest: they share the weight rows
+    tb = rem % width;
+    a.T = (u32)__builtin_amdgcn_readfirstlane(sh.l.cnt[e]);
+    a.col0 = (u32)__builtin_amdgcn_readfirstlane(sh.l.off[e]);
+    a.Wp = W + (u64)e * expert_elems;
+    a.Xp = X + (u64)(a.col0 / 16) * 512;
+  }
+};
+
 template <bool GATEUP>
 __device__ __forceinline__ void moe_grouped(const DevCtx& c, u32 layer, MoeShared& sh, u32 wg, u32 nwg) {
   const LayerWP* P = c.players + layer;
-  const u32 Fe = c.F, N = GATEUP ? 2 * Fe : c.d;
-  moe_offsets(c, sh, N / 16, nwg);
+  const u32 Fe = c.F, N = GATEUP ? 2 * Fe : c.d, K = GATEUP ? c.d : Fe;
+  moe_split(c, sh, N, K, nwg);
   const u32 lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
   sh.wrstd[w][lane] = W_SCALE_INV;                   // the operands are normalised already; each wave reads only its own row
   const u32 total = sh.small_base[sh.n_small];
@@ -242,30 +292,32 @@ __device__ __forceinline__ void moe_grouped(const DevCtx& c, u32 layer, MoeShare
       if (sh.small_base[mid] <= i) lo = mid; else hi = mid;
     }
     const u32 e = sh.small_e[lo], g = i - sh.small_base[lo];
-    switch ((sh.cnt[e] + 15) / 16) {
+    switch ((sh.l.cnt[e] + 15) / 16) {
       case 1: moe_wave_item<GATEUP, 1>(c, P, sh, e, g); break;
       case 2: moe_wave_item<GATEUP, 2>(c, P, sh, e, g); break;
       case 3: moe_wave_item<GATEUP, 3>(c, P, sh, e, g); break;
       default: moe_wave_item<GATEUP, 4>(c, P, sh, e, g); break;
     }
   }
-  for (u32 b = 0; b < sh.n_big; ++b) {
-    const u32 e = sh.big_e[b];
-    MfmaGemmArgs a{};
-    a.T = sh.cnt[e]; a.eps = c.eps; a.tune_nw = c.tune_nw; a.col0 = sh.off[e];
-    // the other experts' GEMMs fill the chip: take the widest tile the expert's tokens fill instead of a narrower one
-    // that would spread this one GEMM over more workgroups (bits 12-14 of the tuning word, unless the caller forces them)
-    if (((a.tune_nw >> 12) & 7u) == 0)
-      a.tune_nw |= (a.T <= 64 ? 2u : a.T <= 96 ? 3u : a.T <= 128 ? 4u : a.T <= 192 ? 6u : 7u) << 12;
-    if (GATEUP) {
-      a.TBS = c.moe_TBS; a.Wp = P->wgu + (u64)e * (2 * Fe) * c.d; a.Xp = c.xq_moe + (u64)(sh.off[e] / 16) * 512; a.N = 2 * Fe; a.K = c.d;
-      a.Hp = c.hq_moe;
-      gemm_mfma<EPI_SILU_GATE, false>(a, sh.mfma, (wg + nwg - sh.big_start[b]) % nwg, nwg);
-    } else {
-      a.TBS = c.moe_TBS; a.Wp = P->wd + (u64)e * c.d * Fe; a.Xp = c.hq_moe + (u64)(sh.off[e] / 16) * 512; a.N = c.d; a.K = Fe;
-      a.out = c.y_moe; a.ldo = c.d;
-      gemm_mfma<EPI_SCALED_STORE, false>(a, sh.mfma, (wg + nwg - sh.big_start[b]) % nwg, nwg);
-    }
+  if (sh.n_big == 0) return;
+  MfmaGemmArgs a{};
+  a.eps = c.eps; a.tune_nw = c.tune_nw; a.TBS = c.moe_TBS; a.N = N; a.K = K;
+  if (GATEUP) a.Hp = c.hq_moe;
+  else { a.out = c.y_moe; a.ldo = c.d; }
+  constexpr int EPI = GATEUP ? EPI_SILU_GATE : EPI_SCALED_STORE;
+  MoeItems<GATEUP> items{sh, GATEUP ? P->wgu : P->wd, GATEUP ? c.xq_moe : c.hq_moe, 0, (N / 16) * gemm_k_tiles(K) * 512, 0};
+  auto shaped = [&](u32 bn) -> const MoeItems<GATEUP>& {
+    items.nblocks = (N + bn - 1) / bn;
+    items.total = items.nblocks * sh.big_base[sh.n_big];
+    return items;
+  };
+  switch (sh.shape) {
+    case 1: gemm_dma<EPI, 4, 1, 2, 2, false>(a, shaped(64), sh.dma, wg, nwg); break;
+    case 2: gemm_dma<EPI, 2, 4, 1, 2, false>(a, shaped(128), sh.dma, wg, nwg); break;
+    case 3: gemm_dma<EPI, 2, 4, 2, 2, false>(a, shaped(128), sh.dma, wg, nwg); break;
+    case 4: gemm_dma<EPI, 4, 4, 4, 2, false>(a, shaped(256), sh.dma, wg, nwg); break;
+    case 6: gemm_dma<EPI, 4, 4, 6, 1, false>(a, shaped(256), sh.dma, wg, nwg); break;
+    default: gemm_dma<EPI, 4, 4, 8, 1, false>(a, shaped(256), sh.dma, wg, nwg); break;
   }
 }
 
@@ -277,7 +329,7 @@ __device__ __forceinline__ void moe_down(const DevCtx& c, u32 layer, MoeShared& 
 }
 
 // ---- x[t] += sum_j w_j * y[column of (t, j)], in selection order; packed operand and norm partials of the next GEMM ----
-__device__ __forceinline__ void moe_combine(const DevCtx& c, u32 layer, MoeShared& sh, u32 wg, u32 nwg) {
+__device__ __forceinline__ void moe_combine(const DevCtx& c, u32 layer, MoeLists& sh, u32 wg, u32 nwg) {
   moe_offsets(c, sh);
   const u32 T = c.meta->n_tokens, d = c.d, per_row = d / 16, k = c.n_active;
   const float* g = layer + 1 < c.n_layers ? c.layers[layer + 1].g1 : c.gf;
