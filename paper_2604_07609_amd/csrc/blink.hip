@@ -31,15 +31,11 @@ static phase_kernel_t phase_kernel(int ph, bool f32) {
   if (f32) {
     switch (ph) {
       case PH_EMBED: return k_embed_f32;
-      case PH_NORM1: return k_norm1_f32;
       case PH_QKV: return k_qkv_f32;
-      case PH_ROPE: return k_rope_kvwrite_f32;
       case PH_ATTN: return k_attention_f32;
       case PH_OPROJ: return k_oproj_f32;
-      case PH_NORM2: return k_norm2_f32;
       case PH_GATEUP: return k_gateup_f32;
       case PH_DOWN: return k_down_f32;
-      case PH_FINAL_NORM: return k_final_norm_f32;
       case PH_LM_HEAD: return k_lm_head_f32;
       default: return k_sample_publish_f32;
     }
@@ -520,11 +516,9 @@ static int init_impl(const blink_config* cfg, blink_engine* e) {
   // ---- activations ----
   if (int rc = dalloc(e, &c.x, (u64)c.maxT * c.d)) return rc;
   if (c.dtype == 0) {
-    if (int rc = dalloc(e, &c.h, (u64)c.maxT * c.d)) return rc;
     if (int rc = dalloc(e, &c.qkv, (u64)c.maxT * c.qkv_n)) return rc;
     if (int rc = dalloc(e, &c.attn, (u64)c.maxT * c.nq * c.hd)) return rc;
     if (int rc = dalloc(e, &c.gu, (u64)c.maxT * 2 * c.F)) return rc;
-    if (int rc = dalloc(e, &c.hlast, rows_cap * c.d)) return rc;
   }
   if (int rc = dalloc(e, &c.logits, rows_cap * c.V)) return rc;
   HIPCHK(hipStreamSynchronize(e->compute));
@@ -661,7 +655,7 @@ extern "C" int blink_submit(blink_engine* e, const int32_t* prompt, uint32_t n_p
 static bool phase_per_layer(int ph) { return (ph >= PH_LAYER_FIRST && ph <= PH_LAYER_LAST) || ph >= PH_ATTN_COMBINE; }
 
 static int launch_phase(blink_engine* e, const DevCtx& ctx, hipStream_t st, int ph, u32 layer, u64 enq_index) {
-  if (e->ctx.dtype == 1 && (ph == PH_NORM1 || ph == PH_NORM2 || ph == PH_FINAL_NORM || ph == PH_ROPE)) return 0;   // fused into the GEMMs
+  if (ph == PH_NORM1 || ph == PH_NORM2 || ph == PH_FINAL_NORM || ph == PH_ROPE) return 0;   // fused into the GEMMs
   const bool timed = e->timed_phase == ph && enq_index != ~0ull;
   hipEvent_t a = nullptr, b = nullptr;
   if (timed) {

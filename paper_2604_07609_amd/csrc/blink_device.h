@@ -249,11 +249,9 @@ struct DevCtx {
   u64 kv_kv_stride;     // elements between the K and the V half of a layer
   // activations
   float* x;             // [maxT][d] residual stream
-  float* h;             // [maxT][d] normalised input of a GEMM
   float* qkv;           // [maxT][qkv_n]
   float* attn;          // [maxT][nq*hd]
   float* gu;            // [maxT][2F]
-  float* hlast;         // [max_batch][d]
   float* logits;        // [max_batch][V]
   // bf16 path: packed weights and packed activation operands
   const LayerWP* players;

@@ -1,5 +1,4 @@
-// Forward pass of the Llama-style decoder over paged KV: generic phases (fp32 weights, and the
-// reference-quality path for bf16 weights). Each phase is a device function that loops over its work
+// Forward pass of the Llama-style decoder over paged KV: the embedding and, for fp32 models, the attention. Each phase is a device function that loops over its work
 // items with a workgroup stride, reading the batch shape from the device-resident metadata, so the
 // same code runs from a host-enqueued kernel sequence and from the resident loop kernel. The model is
 // the decoder that the paper's engine treats as opaque (section 4.3); shapes come from the workloads.
@@ -102,125 +101,6 @@ __device__ __forceinline__ void phase_embed_packed(const DevCtx& c, u32 wg, u32 
       *(uint4*)(c.xq + packed_act_off(t, k0 + 8 * h, c.TBS)) = make_uint4(w[0], w[1], w[2], w[3]);
     }
     c.ssq[(u64)t * per_row + nt] = ss;
-  }
-}
-
-// ---- RMSNorm: out[r] = in[row(r)] * g / sqrt(mean(in^2) + eps); one workgroup per row -------------------------
-// rows == nullptr: row(r) = r, n_rows = n_tokens; else row(r) = rows[r], n_rows = sampling sequences (their last positions).
-__device__ __forceinline__ void phase_rmsnorm(const DevCtx& c, const float* in, const float* g, float* out, const u32* rows, float* red,
-                              u32 wg, u32 nwg) {
-  const u32 n = rows ? c.meta->n_samples : c.meta->n_tokens, d = c.d;
-  for (u32 r = wg; r < n; r += nwg) {
-    const float* x = in + (u64)(rows ? rows[r] : r) * d;
-    float ss = 0.f;
-    for (u32 j = threadIdx.x; j < d; j += BLK_THREADS) ss += x[j] * x[j];
-    ss = block_sum_f(ss, red);
-    const float rstd = 1.0f / sqrtf(ss / (float)d + c.eps);
-    for (u32 j = threadIdx.x; j < d; j += BLK_THREADS) out[(u64)r * d + j] = x[j] * rstd * g[j];
-  }
-}
-
-// ---- generic GEMM: out[t][n] (+)= sum_k a(t,k) * W[n][k] ---------------------------------------------------------
-// 32 x 64 output tile per workgroup, K in steps of 32 through LDS, 2 x 4 outputs per thread, fp32 FMA.
-#define GA_PLAIN 0
-#define GA_SILU_MUL 1   // a(t,k) = silu(A[t][k]) * A[t][K + k]   (A has 2K columns: gate | up)
-#define GE_STORE 0
-#define GE_ADD 1        // out += result (residual connection, in place)
-#define G_BM 32
-#define G_BN 64
-#define G_BK 32
-struct GemmShared {
-  float As[G_BK][G_BM + 1];
-  float Ws[G_BK][G_BN + 4];
-};
-
-template <typename WT, int AMODE, int EMODE>
-__device__ __forceinline__ void phase_gemm(const float* A, u32 lda, const WT* W, float* out, u32 ldo, u32 T, u32 N, u32 K, GemmShared& sh,
-                           u32 wg, u32 nwg) {
-  const u32 tid = threadIdx.x;
-  const u32 mt = (T + G_BM - 1) / G_BM, nt = (N + G_BN - 1) / G_BN;
-  const u32 tm = tid / 16, tn = tid % 16;
-  for (u32 tile = wg; tile < mt * nt; tile += nwg) {
-    const u32 t0 = (tile % mt) * G_BM, n0 = (tile / mt) * G_BN;
-    float acc[2][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-    for (u32 k0 = 0; k0 < K; k0 += G_BK) {
-      {  // A tile: thread -> row tid/8, 4 consecutive k
-        const u32 r = tid / 8, kk = (tid % 8) * 4;
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (t0 + r < T) {
-          const float* ap = A + (u64)(t0 + r) * lda + k0 + kk;
-          v = *(const float4*)ap;
-          if (AMODE == GA_SILU_MUL) {
-            const float4 u = *(const float4*)(ap + K);
-            v.x = v.x / (1.f + __expf(-v.x)) * u.x;
-            v.y = v.y / (1.f + __expf(-v.y)) * u.y;
-            v.z = v.z / (1.f + __expf(-v.z)) * u.z;
-            v.w = v.w / (1.f + __expf(-v.w)) * u.w;
-          }
-        }
-        sh.As[kk][r] = v.x; sh.As[kk + 1][r] = v.y; sh.As[kk + 2][r] = v.z; sh.As[kk + 3][r] = v.w;
-      }
-      {  // W tile: thread -> row tid/4, 8 consecutive k
-        const u32 r = tid / 4, kk = (tid % 4) * 8;
-        float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        if (n0 + r < N) WLoad<WT>::load8(W + (u64)(n0 + r) * K + k0 + kk, v);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) sh.Ws[kk + i][r] = v[i];
-      }
-      __syncthreads();
-#pragma unroll
-      for (int k = 0; k < G_BK; ++k) {
-        const float a0 = sh.As[k][tm * 2], a1 = sh.As[k][tm * 2 + 1];
-        const float4 w = *(const float4*)&sh.Ws[k][tn * 4];
-        acc[0][0] += a0 * w.x; acc[0][1] += a0 * w.y; acc[0][2] += a0 * w.z; acc[0][3] += a0 * w.w;
-        acc[1][0] += a1 * w.x; acc[1][1] += a1 * w.y; acc[1][2] += a1 * w.z; acc[1][3] += a1 * w.w;
-      }
-      __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const u32 t = t0 + tm * 2 + i;
-      if (t >= T) continue;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const u32 n = n0 + tn * 4 + j;
-        if (n >= N) continue;
-        float* o = out + (u64)t * ldo + n;
-        if (EMODE == GE_ADD) *o += acc[i][j]; else *o = acc[i][j];
-      }
-    }
-  }
-}
-
-// ---- rotary embedding on q and k (rotate-half pairing), K/V write through the slot mapping --------------------
-template <typename WT>
-__device__ __forceinline__ void phase_rope_kvwrite(const DevCtx& c, u32 layer, u32 wg, u32 nwg) {
-  const u32 T = c.meta->n_tokens, hd = c.hd, half = hd / 2, nh = c.nq + 2 * c.nkv;
-  WT* Kc = (WT*)c.kv + (u64)layer * c.kv_layer_stride;
-  WT* Vc = Kc + c.kv_kv_stride;
-  const u64 total = (u64)T * nh * half;
-  for (u64 i = (u64)wg * BLK_THREADS + threadIdx.x; i < total; i += (u64)nwg * BLK_THREADS) {
-    const u32 p = (u32)(i % half), hh = (u32)((i / half) % nh), t = (u32)(i / ((u64)half * nh));
-    float* q = c.qkv + (u64)t * c.qkv_n + (u64)hh * hd;
-    const float a = q[p], b = q[p + half];
-    if (hh < c.nq + c.nkv) {
-      const float2 cs = c.rope_tab[(u64)c.positions[t] * half + p];
-      const float ra = a * cs.x - b * cs.y, rb = b * cs.x + a * cs.y;
-      if (hh < c.nq) {
-        q[p] = ra;
-        q[p + half] = rb;
-      } else {
-        const u32 slot = (u32)c.slot_mapping[t], g = hh - c.nq;
-        const u64 o = (((u64)(slot / c.bs) * c.nkv + g) * c.bs + slot % c.bs) * hd;
-        WLoad<WT>::put(Kc, o + p, ra);
-        WLoad<WT>::put(Kc, o + p + half, rb);
-      }
-    } else {
-      const u32 slot = (u32)c.slot_mapping[t], g = hh - c.nq - c.nkv;
-      const u64 o = (((u64)(slot / c.bs) * c.nkv + g) * c.bs + slot % c.bs) * hd;
-      WLoad<WT>::put(Vc, o + p, a);
-      WLoad<WT>::put(Vc, o + p + half, b);
-    }
   }
 }
 

@@ -2,14 +2,10 @@
 #include "../phase_kernels.h"
 
 PHASE_KERNEL_F32(k_embed_f32, PH_EMBED)
-PHASE_KERNEL_F32(k_norm1_f32, PH_NORM1)
 PHASE_KERNEL_F32(k_qkv_f32, PH_QKV)
-PHASE_KERNEL_F32(k_rope_kvwrite_f32, PH_ROPE)
 PHASE_KERNEL_F32(k_attention_f32, PH_ATTN)
 PHASE_KERNEL_F32(k_oproj_f32, PH_OPROJ)
-PHASE_KERNEL_F32(k_norm2_f32, PH_NORM2)
 PHASE_KERNEL_F32(k_gateup_f32, PH_GATEUP)
 PHASE_KERNEL_F32(k_down_f32, PH_DOWN)
-PHASE_KERNEL_F32(k_final_norm_f32, PH_FINAL_NORM)
 PHASE_KERNEL_F32(k_lm_head_f32, PH_LM_HEAD)
 PHASE_KERNEL_F32(k_sample_publish_f32, PH_SAMPLE)

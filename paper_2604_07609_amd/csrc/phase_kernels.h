@@ -32,14 +32,10 @@ PHASE_KERNEL_DECL(k_moe_combine)
 PHASE_KERNEL_DECL(k_moe_permute)
 // fp32 models
 PHASE_KERNEL_DECL(k_embed_f32)
-PHASE_KERNEL_DECL(k_norm1_f32)
 PHASE_KERNEL_DECL(k_qkv_f32)
-PHASE_KERNEL_DECL(k_rope_kvwrite_f32)
 PHASE_KERNEL_DECL(k_attention_f32)
 PHASE_KERNEL_DECL(k_oproj_f32)
-PHASE_KERNEL_DECL(k_norm2_f32)
 PHASE_KERNEL_DECL(k_gateup_f32)
 PHASE_KERNEL_DECL(k_down_f32)
-PHASE_KERNEL_DECL(k_final_norm_f32)
 PHASE_KERNEL_DECL(k_lm_head_f32)
 PHASE_KERNEL_DECL(k_sample_publish_f32)

@@ -6,6 +6,7 @@
 #include "sched.h"
 #include "forward.h"
 #include "gemm_dma.h"
+#include "gemm_f32.h"
 #include "attention_mfma.h"
 #include "sampler.h"
 #include "moe.h"
@@ -25,7 +26,6 @@ enum {
 // LDS of a phase kernel of a bf16 model, and of an fp32 model (the GEMMs and the attention have kernels of their own per kind of
 // model, so that neither is charged the other's LDS and registers)
 struct NoShared {};
-struct RedShared { float red[8]; };
 template <int PH, bool F32> struct PhaseSharedOf { typedef NoShared type; };
 template <> struct PhaseSharedOf<PH_QKV, false> { typedef GemmShared8 type; };
 template <> struct PhaseSharedOf<PH_OPROJ, false> { typedef GemmShared8 type; };
@@ -39,44 +39,48 @@ template <> struct PhaseSharedOf<PH_MOE_GATEUP, false> { typedef MoeShared type;
 template <> struct PhaseSharedOf<PH_MOE_DOWN, false> { typedef MoeShared type; };
 template <> struct PhaseSharedOf<PH_MOE_COMBINE, false> { typedef MoeLists type; };
 template <> struct PhaseSharedOf<PH_MOE_PERMUTE, false> { typedef MoeLists type; };
-template <> struct PhaseSharedOf<PH_NORM1, true> { typedef RedShared type; };
-template <> struct PhaseSharedOf<PH_NORM2, true> { typedef RedShared type; };
-template <> struct PhaseSharedOf<PH_FINAL_NORM, true> { typedef RedShared type; };
-template <> struct PhaseSharedOf<PH_QKV, true> { typedef GemmShared type; };
-template <> struct PhaseSharedOf<PH_OPROJ, true> { typedef GemmShared type; };
-template <> struct PhaseSharedOf<PH_GATEUP, true> { typedef GemmShared type; };
-template <> struct PhaseSharedOf<PH_DOWN, true> { typedef GemmShared type; };
-template <> struct PhaseSharedOf<PH_LM_HEAD, true> { typedef GemmShared type; };
+template <> struct PhaseSharedOf<PH_QKV, true> { typedef F32GemmShared type; };
+template <> struct PhaseSharedOf<PH_OPROJ, true> { typedef F32GemmShared type; };
+template <> struct PhaseSharedOf<PH_GATEUP, true> { typedef F32GemmShared type; };
+template <> struct PhaseSharedOf<PH_DOWN, true> { typedef F32GemmShared type; };
+template <> struct PhaseSharedOf<PH_LM_HEAD, true> { typedef F32GemmShared type; };
 template <> struct PhaseSharedOf<PH_ATTN, true> { typedef AttnShared type; };
 template <> struct PhaseSharedOf<PH_SAMPLE, true> { typedef SamplerShared type; };
 
+// fp32 path: the norms, the SiLU gate, the residual adds and the rotary embedding + KV write are fused into the GEMMs here too
 template <int PH>
 __device__ __forceinline__ void run_phase_f32(const DevCtx& c, u32 layer, typename PhaseSharedOf<PH, true>::type& sh, u32 wg, u32 nwg) {
-  typedef float WT;
   const IterMeta* m = c.meta;
-  const u32 T = m->n_tokens, B = m->n_samples;     // B: the sequences that sample in this iteration (rows of the logits)
   const LayerW* L = c.layers + layer;
+  F32GemmArgs a{};
+  a.T = m->n_tokens;
+  a.eps = c.eps;
   switch (PH) {
-    case PH_EMBED: phase_embed<WT>(c, wg, nwg); break;
-    case PH_NORM1: phase_rmsnorm(c, c.x, L->g1, c.h, nullptr, ((RedShared*)&sh)->red, wg, nwg); break;
+    case PH_EMBED: phase_embed<float>(c, wg, nwg); break;
     case PH_QKV:
-      phase_gemm<WT, GA_PLAIN, GE_STORE>(c.h, c.d, (const WT*)L->wqkv, c.qkv, c.qkv_n, T, c.qkv_n, c.d, *(GemmShared*)&sh, wg, nwg);
+      a.A = c.x; a.lda = c.d; a.gain = L->g1; a.W = (const float*)L->wqkv; a.out = c.qkv; a.ldo = c.qkv_n; a.N = c.qkv_n; a.K = c.d;
+      a.positions = c.positions; a.slot_mapping = c.slot_mapping; a.rope_tab = c.rope_tab;
+      a.Kc = (float*)c.kv + (u64)layer * c.kv_layer_stride; a.Vc = a.Kc + c.kv_kv_stride;
+      a.nq = c.nq; a.nkv = c.nkv; a.hd = c.hd; a.bs = c.bs;
+      gemm_f32<FA_NORM, FE_ROPE>(a, *(F32GemmShared*)&sh, wg, nwg);
       break;
-    case PH_ROPE: phase_rope_kvwrite<WT>(c, layer, wg, nwg); break;
-    case PH_ATTN: phase_attention<WT, false>(c, layer, *(AttnShared*)&sh, wg, nwg); break;
+    case PH_ATTN: phase_attention<float, false>(c, layer, *(AttnShared*)&sh, wg, nwg); break;
     case PH_OPROJ:
-      phase_gemm<WT, GA_PLAIN, GE_ADD>(c.attn, c.nq * c.hd, (const WT*)L->wo, c.x, c.d, T, c.d, c.nq * c.hd, *(GemmShared*)&sh, wg, nwg);
+      a.A = c.attn; a.lda = c.nq * c.hd; a.W = (const float*)L->wo; a.out = c.x; a.ldo = c.d; a.N = c.d; a.K = c.nq * c.hd;
+      gemm_f32<FA_PLAIN, FE_ADD>(a, *(F32GemmShared*)&sh, wg, nwg);
       break;
-    case PH_NORM2: phase_rmsnorm(c, c.x, L->g2, c.h, nullptr, ((RedShared*)&sh)->red, wg, nwg); break;
     case PH_GATEUP:
-      phase_gemm<WT, GA_PLAIN, GE_STORE>(c.h, c.d, (const WT*)L->wgu, c.gu, 2 * c.F, T, 2 * c.F, c.d, *(GemmShared*)&sh, wg, nwg);
+      a.A = c.x; a.lda = c.d; a.gain = L->g2; a.W = (const float*)L->wgu; a.out = c.gu; a.ldo = 2 * c.F; a.N = 2 * c.F; a.K = c.d;
+      gemm_f32<FA_NORM, FE_STORE>(a, *(F32GemmShared*)&sh, wg, nwg);
       break;
     case PH_DOWN:
-      phase_gemm<WT, GA_SILU_MUL, GE_ADD>(c.gu, 2 * c.F, (const WT*)L->wd, c.x, c.d, T, c.d, c.F, *(GemmShared*)&sh, wg, nwg);
+      a.A = c.gu; a.lda = 2 * c.F; a.W = (const float*)L->wd; a.out = c.x; a.ldo = c.d; a.N = c.d; a.K = c.F;
+      gemm_f32<FA_SILU_MUL, FE_ADD>(a, *(F32GemmShared*)&sh, wg, nwg);
       break;
-    case PH_FINAL_NORM: phase_rmsnorm(c, c.x, c.gf, c.hlast, c.last_idx, ((RedShared*)&sh)->red, wg, nwg); break;
-    case PH_LM_HEAD:
-      phase_gemm<WT, GA_PLAIN, GE_STORE>(c.hlast, c.d, (const WT*)c.lm, c.logits, c.V, B, c.V, c.d, *(GemmShared*)&sh, wg, nwg);
+    case PH_LM_HEAD:      // one row per sampling sequence (its last token)
+      a.T = m->n_samples; a.rows = c.last_idx; a.A = c.x; a.lda = c.d; a.gain = c.gf; a.W = (const float*)c.lm; a.out = c.logits; a.ldo = c.V;
+      a.N = c.V; a.K = c.d;
+      gemm_f32<FA_NORM, FE_STORE>(a, *(F32GemmShared*)&sh, wg, nwg);
       break;
     case PH_SAMPLE:
       if (c.spec_k) phase_sample_publish_spec(c, *(SamplerShared*)&sh, wg, nwg);
