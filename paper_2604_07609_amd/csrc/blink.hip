@@ -127,6 +127,35 @@ __global__ void k_clock_probe(HostMirror* m) {
   __hip_atomic_store(&m->clock_probe, dev_now_ns(), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// One request into its ring slot (the frontend's write of section 4.4): payload first, then, behind a system-scope fence, the state
+// word. Reads the staged descriptor, status and prompt from pinned host memory; one workgroup.
+__global__ void __launch_bounds__(BLK_THREADS) k_ring_write(const SlotDesc* desc_in, const i32* prompt_in, u32 n_prompt, SlotStatus st, SlotDesc* desc, i32* prompt,
+                                                            SlotStatus* status) {
+  for (u32 i = threadIdx.x; i < n_prompt; i += BLK_THREADS) prompt[i] = prompt_in[i];
+  if (threadIdx.x < sizeof(SlotDesc) / 4) ((u32*)desc)[threadIdx.x] = ((const u32*)desc_in)[threadIdx.x];
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    status->gen_count = st.gen_count; status->ticket_lo = st.ticket_lo; status->flags = st.flags;
+    __hip_atomic_store(&status->state, st.state, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
+
+// The token reader's fetch (section 4.4): the new records of every picked slot into one pinned array, a workgroup per slot; a slot
+// whose last record this is goes back to EMPTY behind them.
+struct OutPick { u32 slot, from, n, at, completed, pad[3]; };
+__global__ void __launch_bounds__(64) k_fetch_outputs(const OutPick* picks, const OutRec* out_arena, u32 max_seq_len, OutRec* to, SlotStatus* status) {
+  const OutPick p = picks[blockIdx.x];
+  const uint4* src = (const uint4*)(out_arena + (u64)p.slot * max_seq_len + p.from);
+  uint4* dst = (uint4*)(to + p.at);
+  for (u32 i = threadIdx.x; i < p.n; i += 64) dst[i] = src[i];
+  if (p.completed && threadIdx.x == 0) {
+    SlotStatus* st = status + p.slot;
+    st->gen_count = 0; st->ticket_lo = 0; st->flags = 0;
+    __hip_atomic_store(&st->state, (u32)BLINK_SLOT_EMPTY, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
+
 __global__ void k_open_window(SchedState* ss, u64 iter_limit) {
   ss->stopped = 0;
   ss->iter_limit = iter_limit;
@@ -171,7 +200,8 @@ struct blink_engine {
   SlotStatus* stage_status = nullptr;  // pinned [ring_slots]
   OutRec* stage_out = nullptr;         // pinned
   u64 stage_out_cap = 0;
-  SlotStatus* stage_empty = nullptr;   // pinned zero status
+  OutPick* stage_picks = nullptr;      // pinned [ring_slots]
+  u64 iter_limit = 0;                  // of the current window (0: none)
   // loop
   std::thread launcher;
   hipGraphExec_t iter_graph = nullptr;        // the kernel chain of one iteration
@@ -281,7 +311,7 @@ static int init_impl(const blink_config* cfg, blink_engine* e) {
   if (int rc = halloc(e, &e->stage_status, c.ring_slots)) return rc;
   e->stage_out_cap = 1u << 16;
   if (int rc = halloc(e, &e->stage_out, e->stage_out_cap)) return rc;
-  if (int rc = halloc(e, &e->stage_empty, 1)) return rc;
+  if (int rc = halloc(e, &e->stage_picks, c.ring_slots)) return rc;
   e->delivered.assign(c.ring_slots, 0);
   e->slot_ticket.assign(c.ring_slots, 0);
   for (auto& s : e->shadow_state) s.store(0);
@@ -635,13 +665,13 @@ extern "C" int blink_submit(blink_engine* e, const int32_t* prompt, uint32_t n_p
   d->top_p = sp->top_p; d->seed = sp->seed;
   memcpy(ptoks, prompt, (u64)n_prompt * 4);
   st->state = BLINK_SLOT_PREFILL_PENDING; st->gen_count = 0; st->ticket_lo = (u32)t; st->flags = 0;
-  HIPCHK(hipMemcpyAsync(c.in_arena + (u64)slot * c.max_seq_len, ptoks, (u64)n_prompt * 4, hipMemcpyHostToDevice, e->s_in));
-  HIPCHK(hipMemcpyAsync(c.desc + slot, d, sizeof *d, hipMemcpyHostToDevice, e->s_in));
-  HIPCHK(hipStreamSynchronize(e->s_in));
   e->slot_ticket[slot] = t;
   e->delivered[slot] = 0;
   e->shadow_state[slot].store(1, std::memory_order_release);
-  HIPCHK(hipMemcpyAsync(c.status + slot, st, sizeof *st, hipMemcpyHostToDevice, e->s_in));
+  // one small kernel writes all three in order and is waited for once (three copies and two waits: 35-49 us a call)
+  hipLaunchKernelGGL(k_ring_write, dim3(1), dim3(BLK_THREADS), 0, e->s_in, (const SlotDesc*)d, (const i32*)ptoks, n_prompt, *st, c.desc + slot,
+                     c.in_arena + (u64)slot * c.max_seq_len, c.status + slot);
+  HIPCHK(hipGetLastError());
   HIPCHK(hipStreamSynchronize(e->s_in));
   e->next_ticket = t + 1;
   if (request_id_out) *request_id_out = t;
@@ -767,11 +797,17 @@ static void pump_loop(blink_engine* e) {
   int rc = 0;
   if (hipSetDevice(e->cfg.device) != hipSuccess) rc = BLINK_ERR_DEVICE;
   const u32 depth = (u32)e->events.size();
-  u64 enq = 0;
+  u64 enq = 0, done = 0;                         // iterations enqueued, and waited for
   while (rc == 0) {
-    if (enq >= depth) {   // wait for the iteration enqueued `depth` ago: bounds the work in flight
-      if (hipEventSynchronize(e->events[enq % depth]) != hipSuccess) { rc = BLINK_ERR_DEVICE; break; }
-      harvest_phase_times(e, enq - depth);
+    // `depth` iterations in flight, but no more than the window still lacks: behind its last iteration a chain is a row of
+    // empty kernels (60-500 us for the eight of them) that the end of the window would wait for. The mirrored count is the
+    // device's own, written by the scheduler step of every chain; at worst it lags by the chains in flight.
+    const u64 limit = e->iter_limit, ran = *(volatile const u64*)&e->hmirror->iteration;
+    const bool enough = limit != 0 && enq - done >= (limit > ran ? limit - ran : 0);
+    if (enq - done >= depth || (enough && enq > done)) {   // wait for the oldest one
+      if (hipEventSynchronize(e->events[done % depth]) != hipSuccess) { rc = BLINK_ERR_DEVICE; break; }
+      harvest_phase_times(e, done);
+      ++done;
       if (e->hmirror->error) { rc = BLINK_ERR_DEVICE; break; }
       if (__atomic_load_n(&e->hmirror->stopped, __ATOMIC_ACQUIRE)) break;
       if (e->host_step_bytes) {   // the previous iteration has ended: its tokens to the host, a batch description back
@@ -783,13 +819,15 @@ static void pump_loop(blink_engine* e) {
           break;
         }
       }
+      continue;
     }
+    if (enough) break;                           // the window's iterations have run
     rc = enqueue_iteration(e, enq);
     if (rc == 0 && hipEventRecord(e->events[enq % depth], e->compute) != hipSuccess) rc = BLINK_ERR_DEVICE;
     ++enq;
   }
   if (hipStreamSynchronize(e->compute) != hipSuccess && rc == 0) rc = BLINK_ERR_DEVICE;
-  if (rc == 0) for (u64 i = enq > depth ? enq - depth : 0; i < enq; ++i) harvest_phase_times(e, i);
+  if (rc == 0) for (u64 i = done; i < enq; ++i) harvest_phase_times(e, i);
   if (rc == 0 && e->hmirror->error) rc = BLINK_ERR_DEVICE;
   e->loop_rc.store(rc);
   e->loop_active.store(false, std::memory_order_release);
@@ -804,6 +842,7 @@ extern "C" int blink_run(blink_engine* e, uint64_t max_iterations) {
   HIPCHK(hipSetDevice(e->cfg.device));
   if (e->hmirror->error) return fail(BLINK_ERR_DEVICE, "device loop error %u", e->hmirror->error);
   const u64 iter_limit = max_iterations ? e->hmirror->iteration + max_iterations : 0;
+  e->iter_limit = iter_limit;
   e->hmirror->stopped = 0;
   hipLaunchKernelGGL(k_open_window, dim3(1), dim3(1), 0, e->compute, e->ctx.ss, iter_limit);
   HIPCHK(hipGetLastError());
@@ -843,8 +882,7 @@ extern "C" int blink_poll_outputs(blink_engine* e, blink_event* buf, uint32_t ca
   // one bulk read of the slot metadata (section 4.4 "Token reader")
   HIPCHK(hipMemcpyAsync(e->stage_status, c.status, sizeof(SlotStatus) * c.ring_slots, hipMemcpyDeviceToHost, e->s_out));
   HIPCHK(hipStreamSynchronize(e->s_out));
-  struct Pick { u32 slot, from, n, stage_off; bool completed; };
-  std::vector<Pick> picks;
+  u32 n_picks = 0;
   u64 staged = 0;
   u32 budget = cap;
   for (u32 slot = 0; slot < c.ring_slots && budget > 0; ++slot) {
@@ -856,19 +894,25 @@ extern "C" int blink_poll_outputs(blink_engine* e, blink_event* buf, uint32_t ca
     u32 n = std::min(gen - have, budget);
     if (staged + n > e->stage_out_cap) n = (u32)(e->stage_out_cap - staged);
     if (n == 0) break;
-    picks.push_back({slot, have, n, (u32)staged, st.state == BLINK_SLOT_DECODE_COMPLETED && have + n == gen});
-    HIPCHK(hipMemcpyAsync(e->stage_out + staged, c.out_arena + (u64)slot * c.max_seq_len + have, sizeof(OutRec) * n,
-                          hipMemcpyDeviceToHost, e->s_out));
+    OutPick& p = e->stage_picks[n_picks++];
+    p = OutPick{};
+    p.slot = slot; p.from = have; p.n = n; p.at = (u32)staged;
+    p.completed = st.state == BLINK_SLOT_DECODE_COMPLETED && have + n == gen;
     staged += n;
     budget -= n;
   }
-  if (picks.empty()) return BLINK_OK;
+  if (n_picks == 0) return BLINK_OK;
+  // one kernel fetches the records of all slots and returns the completed slots to EMPTY (the frontend's edge of the life cycle);
+  // a copy per slot cost 3 us each, and another for every completed one
+  hipLaunchKernelGGL(k_fetch_outputs, dim3(n_picks), dim3(64), 0, e->s_out, (const OutPick*)e->stage_picks, c.out_arena, c.max_seq_len, e->stage_out, c.status);
+  HIPCHK(hipGetLastError());
   HIPCHK(hipStreamSynchronize(e->s_out));
   // events across requests ordered by (iteration, ring slot); per request by index
   u32 w = 0;
-  for (const Pick& p : picks)
+  for (u32 k = 0; k < n_picks; ++k) {
+    const OutPick p = e->stage_picks[k];
     for (u32 i = 0; i < p.n; ++i) {
-      const OutRec& r = e->stage_out[p.stage_off + i];
+      const OutRec& r = e->stage_out[p.at + i];
       blink_event& ev = buf[w++];
       ev.request_id = e->slot_ticket[p.slot];
       ev.index = p.from + i;
@@ -877,20 +921,11 @@ extern "C" int blink_poll_outputs(blink_engine* e, blink_event* buf, uint32_t ca
       ev.iteration = r.iteration;
       ev.device_ns = r.device_ns;
     }
-  // completed slots go back to EMPTY (the frontend's edge of the life cycle), then become reusable
-  bool any_done = false;
-  for (const Pick& p : picks) {
     e->delivered[p.slot] = p.from + p.n;
-    if (p.completed) {
-      HIPCHK(hipMemcpyAsync(c.status + p.slot, e->stage_empty, sizeof(SlotStatus), hipMemcpyHostToDevice, e->s_out));
-      any_done = true;
-    }
   }
-  if (any_done) {
-    HIPCHK(hipStreamSynchronize(e->s_out));
-    for (const Pick& p : picks)
-      if (p.completed) e->shadow_state[p.slot].store(0, std::memory_order_release);
-  }
+  // completed slots are EMPTY on the device now, and become reusable here
+  for (u32 k = 0; k < n_picks; ++k)
+    if (e->stage_picks[k].completed) e->shadow_state[e->stage_picks[k].slot].store(0, std::memory_order_release);
   *n_out = w;
   return BLINK_OK;
 }
