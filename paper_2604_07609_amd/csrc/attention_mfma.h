@@ -12,7 +12,7 @@
 // Softmax is the online form (running maximum and sum per column), all in fp32.
 #pragma once
 #include "blink_device.h"
-#include "mfma_gemm.h"
+#include "gemm_dma.h"
 
 typedef _Float16 f16x4_t __attribute__((ext_vector_type(4)));
 
@@ -133,8 +133,16 @@ struct AttnMfmaShared {
   float m[ATTN_WAVES][16], l[ATTN_WAVES][16];
   float o[ATTN_WAVES][16][128];  // [wave][q head of the group (decode) or query of the tile (prefill)][dim]
   u32 cu_chunks[ATTN_META_MAX + 1], tok[ATTN_META_MAX], ctx[ATTN_META_MAX], bslot[ATTN_META_MAX], pos0[ATTN_META_MAX];
-  u32 next_item;   // decode items taken through the work counter: the item after the next one
+  u32 next_item;   // items taken through a work counter: the next one (prompts), the one after it (decode)
 };
+
+// Prompt attention with shared KV tiles: a ring of stages of four KV blocks (64 keys), and where every sequence's items begin.
+#define ATTN_RING_BYTES (128u * 1024u)
+struct AttnPromptShared {
+  unsigned char ring[ATTN_RING_BYTES];
+  u32 cu_items[ATTN_META_MAX + 1], wave_sum[ATTN_WAVES], next_item;
+};
+union AttnShared8 { AttnMfmaShared m; AttnPromptShared p; };
 
 // ---- decode: one workgroup per (sequence, kv head); its waves take the KV blocks round-robin ----------------------
 template <int HD>
@@ -609,6 +617,221 @@ __device__ __forceinline__ void attn_prefill(const DevCtx& c, u32 layer, AttnMfm
   }
 }
 
+// ---- prompts of 32 tokens and more: the KV tiles of a kv head shared by a workgroup through LDS ---------------------------
+// One workgroup (eight waves) per (sequence, kv head, QT tiles of 16 queries): QT x G / CT waves' worth of (query tile, CT q
+// heads), eight in all, walk the KV blocks together, 64 keys per step, from 0 to the last visible key. What bounded the
+// wave-per-tile kernel above was the path from the L2s: every wave fetched its own 8 KB per 16 keys and used them for
+// 32 query rows. Here a step's 32 KB (four blocks, head dimension 128) come once per workgroup, straight into LDS, three
+// steps ahead. Each lane of a fetch picks the 16 bytes that lands at its place, so that every read of an operand is 16
+// bytes per lane from 16 different groups of banks: with V read as it lies (8 bytes every 32) two thirds of the cycles of
+// the LDS were bank conflicts. Scores S[key][query] = K q, with the rows of two blocks shared out between two products so
+// that a lane's registers hold eight consecutive keys: the operand of a 16x16x32 product O^T[dim][query] += V^T P^T, whose columns are the lanes' own queries: the
+// running maximum, sum and rescaling of a query stay in its lane (a rescale only when some maximum moved; the sum crosses
+// lanes once, at the end). 64 keys per step rather than 32 halve the barriers and the reductions and give the matrix
+// cores sixteen independent chains. Waves skip the steps behind their own last key. Items are handed out through a
+// counter, the last queries of the last prompt first.
+// Per launch at 32 q / 8 kv heads of 128, wave-per-tile kernel -> this one: two prompts of 4000 tokens 1130 -> 363 us
+// (of 262 GFLOP: 0.72 PFLOP/s; 530 with 32 keys per step, 515 with 64, 387 without bank conflicts, 363 with the order of the
+// two waves of a SIMD), three of 350-790 tokens 76 -> 40, one of 509 32 -> 30, a chunk of 1850 tokens beside 190 decoding
+// sequences 441 -> 268. Now bound by the softmax's vector instructions beside the matrix instructions.
+template <int HD, int CT>
+__device__ __forceinline__ void attn_prompt(const DevCtx& c, u32 layer, AttnPromptShared& sh, u32 wg, u32 nwg, bool mixed) {
+  const u32 ncu = max(1u, nwg / 2);              // one workgroup per compute unit is resident; the launch has two
+  if (wg >= ncu) return;
+  constexpr u32 BLK = 16 * HD * 2, NB = 4, STAGE = 2 * NB * BLK;   // bytes of a block's K (or V); blocks of a stage, its bytes
+  constexpr u32 NS = ATTN_RING_BYTES / STAGE > 6 ? 6 : ATTN_RING_BYTES / STAGE, TPW = BLK / 1024;   // stages; 1 KB tiles a wave fetches per stage (a block's K or V)
+  const u32 B = c.meta->n_seqs, G = c.nq / c.nkv, groups = G / CT, QT = 8 / groups;
+  const u32 lane = threadIdx.x & 63, w = (u32)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lg = lane >> 4, lc = lane & 15;
+  const f16_t* const Kc = (const f16_t*)c.kv + (u64)layer * c.kv_layer_stride;
+  const f16_t* const Vc = Kc + c.kv_kv_stride;
+  // items of every sequence (a decoding one has none): prefix sums over the batch
+  {
+    const u32 i = threadIdx.x;
+    u32 n = 0;
+    if (i < B) n = (c.cu_qtiles[i + 1] - c.cu_qtiles[i] + QT - 1) / QT;
+    u32 v = n;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) { const u32 x = __shfl_up(v, o); if (lane >= (u32)o) v += x; }
+    if (lane == 63) sh.wave_sum[w] = v;
+    __syncthreads();
+    u32 before = 0;
+    for (u32 k = 0; k < w; ++k) before += sh.wave_sum[k];
+    if (i == 0) sh.cu_items[0] = 0;
+    if (i < B) sh.cu_items[i + 1] = before + v;
+    __syncthreads();
+  }
+  const u32 total = sh.cu_items[B] * c.nkv;
+  const u32 qt = w / groups, hg = w % groups;    // this wave's query tile of the item and group of heads
+  const u32 lds0 = (u32)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)sh.ring;
+  // fetching: stage = K of the four blocks, then V; waves 0-3 fetch the K of a block each, waves 4-7 the V
+  const bool fk = w < 4;
+  const u32 fb = w & 3u, f_lds = lds0 + w * BLK;
+  u32 voff[TPW];
+#pragma unroll
+  for (u32 r = 0; r < TPW; ++r)
+    voff[r] = fk ? ((lc & 4) * 2 + (lc & 3) + (((lc >> 3) ^ fb) & 1u) * 4) * (HD * 2) + r * 64 + lg * 16
+                 : (r * 32 + (lg >> 1) * 16 + lc) * 32 + (lg & 1) * 16;
+  // reading: operand 0 / 1 of a pair of blocks holds the keys lg * 8 + 0..3 / + 4..7 of its 32, V the keys lg * 8 + 0..7
+  const u32 k_at[2] = {(lc >> 3) * BLK + lg * 256 + (lc >> 3) * 128 + (lc & 7) * 16, (lc >> 3) * BLK + lg * 256 + ((lc >> 3) ^ 1u) * 128 + (lc & 7) * 16};
+  const u32 v_at = NB * BLK + (lg >> 1) * BLK + (lg & 1) * 256 + lc * 16;
+  typedef const __attribute__((address_space(4))) u32 const_u32;
+  constexpr float L2E = 1.44269504088896340736f;
+  // The barrier of every step would keep the two waves of a SIMD in the same part of it, both at the matrix cores, then
+  // both at the softmax: one of them goes first.
+  if (w >= 4) __builtin_amdgcn_s_setprio(1);
+  // (beside decode items a workgroup may come here late: then its first item comes from the counter too)
+  u32 item = wg;
+  if (mixed) {
+    if (threadIdx.x == 0) sh.next_item = atomicAdd(c.attn_ctr + c.n_layers + layer, 1u);
+    __syncthreads();
+    item = (u32)__builtin_amdgcn_readfirstlane(sh.next_item);
+    __syncthreads();
+  }
+  while (item < total) {
+    u32 t0, P, p0, a0, bslot, g;
+    {
+      const u32 gi = sh.cu_items[B] - 1 - item / c.nkv;       // the last queries (the longest walks) first
+      g = item % c.nkv;
+      u32 lo = 0, hi = B;                                    // the sequence of group gi: last s with cu_items[s] <= gi
+      while (hi - lo > 1) {
+        const u32 mid = (lo + hi) / 2;
+        if (sh.cu_items[mid] <= gi) lo = mid; else hi = mid;
+      }
+      const u32 s = (u32)__builtin_amdgcn_readfirstlane(lo);
+      t0 = c.cu_seqlens[s];
+      P = c.cu_seqlens[s + 1] - t0;
+      bslot = c.seq_bslot[s];
+      p0 = (gi - sh.cu_items[s]) * QT * 16;                  // first query of the item within the sequence's tokens of this iteration
+      a0 = c.seq_pos0[s];
+    }
+    t0 = (u32)__builtin_amdgcn_readfirstlane(t0); P = (u32)__builtin_amdgcn_readfirstlane(P); bslot = (u32)__builtin_amdgcn_readfirstlane(bslot);
+    p0 = (u32)__builtin_amdgcn_readfirstlane(p0); a0 = (u32)__builtin_amdgcn_readfirstlane(a0); g = (u32)__builtin_amdgcn_readfirstlane(g);
+    const u32 last_block = (a0 + min(p0 + QT * 16, P) - 1) / 16, steps = last_block / NB + 1;
+    const_u32* const bt = (const_u32*)(u64)uniform_ptr(c.block_tables + (u64)bslot * c.max_blocks_per_seq);
+    u32 id = bt[min(fb, last_block)];                        // (a block id is read a stage ahead of its use)
+    auto fetch = [&](u32 s) {                                // stage s (past the last: the last block again, not used)
+      const unsigned char* src = (const unsigned char*)uniform_ptr((fk ? Kc : Vc) + ((u64)id * c.nkv + g) * (16 * HD));
+      const u32 at = f_lds + (s % NS) * STAGE;
+#pragma unroll
+      for (u32 r = 0; r < TPW; ++r) dma_tile<false>(at + r * 1024, src, voff[r]);
+      id = bt[min(NB * (s + 1) + fb, last_block)];
+    };
+#pragma unroll 1
+    for (u32 s = 0; s < NS - 1; ++s) fetch(s);
+    // this wave's queries (columns past the prompt's end repeat its last token; they see key 0 only and are not stored)
+    const u32 q0 = p0 + qt * 16;
+    const bool live = q0 < P;                                // (uniform in the wave)
+    const bool colv = q0 + lc < P;
+    const u32 lim = colv ? a0 + q0 + lc + 1 : 1, qrow = t0 + min(q0 + lc, P - 1);
+    const u32 w_last = live ? a0 + min(q0 + 15, P - 1) : 0;  // last key of the tile
+    f16x8_t q[CT][HD / 32];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+      for (int st = 0; st < HD / 32; ++st) q[ct][st] = ld_tile(c.qbuf + ((u64)qrow * c.nq + g * G + hg * CT + ct) * HD + st * 32 + lg * 8);
+    floatx4_t o[CT][HD / 16];
+    float m[CT], l[CT];                                      // running maximum, this lane's share of the sum
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+      m[ct] = -INFINITY; l[ct] = 0.f;
+#pragma unroll
+      for (int d = 0; d < HD / 16; ++d) o[ct][d] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+    }
+    for (u32 s = 0; s < steps; ++s) {
+      wait_dma_barrier<(int)((NS - 2) * TPW)>();             // stage s is in LDS for everyone, stage s - 1 has been read by everyone
+      fetch(s + NS - 1);
+      if (!live || s * (NB * 16) > w_last) continue;
+      const unsigned char* const st0 = sh.ring + (s % NS) * STAGE;
+      floatx4_t sc[CT][NB];
+#pragma unroll
+      for (u32 b = 0; b < NB; ++b) {
+        f16x8_t ka[HD / 32];
+#pragma unroll
+        for (int st = 0; st < HD / 32; ++st) ka[st] = as_f16x8(*(const uint4*)(st0 + (b & 2) * BLK + st * 1024 + k_at[b & 1]));
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) sc[ct][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ka[0], q[ct][0], floatx4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+        for (int st = 1; st < HD / 32; ++st)
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct) sc[ct][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ka[st], q[ct][st], sc[ct][b], 0, 0, 0);
+      }
+      if (s * (NB * 16) + NB * 16 > a0 + q0 + 1 || !colv) {  // the step reaches behind some query's last key (or a column is padding)
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+          for (u32 b = 0; b < NB; ++b)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (s * (NB * 16) + (b & 2) * 16 + lg * 8 + (b & 1) * 4 + i >= lim) sc[ct][b][i] = -INFINITY;
+      }
+      f16x8_t pb[CT][NB / 2];
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        float bm = -INFINITY;
+#pragma unroll
+        for (u32 b = 0; b < NB; ++b) bm = fmaxf(bm, fmaxf(fmaxf(sc[ct][b][0], sc[ct][b][1]), fmaxf(sc[ct][b][2], sc[ct][b][3])));
+        bm = quad_max(bm);
+        const float mn = fmaxf(m[ct], bm);                   // finite: every column sees key 0 in step 0
+        if (__ballot(mn > m[ct])) {
+          const float corr = __builtin_amdgcn_exp2f((m[ct] - mn) * L2E);
+          l[ct] *= corr;
+#pragma unroll
+          for (int d = 0; d < HD / 16; ++d) o[ct][d] *= corr;
+          m[ct] = mn;
+        }
+        const float nm = -mn * L2E;
+        float ps = 0.f;
+#pragma unroll
+        for (u32 b = 0; b < NB; ++b)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[ct][b][i], L2E, nm));   // exp2(-inf) = 0 for masked keys
+            ps += p;
+            pb[ct][b / 2][(b & 1) * 4 + i] = (_Float16)p;
+          }
+        l[ct] += ps;
+      }
+#pragma unroll
+      for (int d = 0; d < HD / 16; ++d)
+#pragma unroll
+        for (u32 h = 0; h < NB / 2; ++h) {
+          const f16x8_t va = as_f16x8(*(const uint4*)(st0 + 2 * h * BLK + (d >> 1) * 1024 + (d & 1) * 512 + v_at));
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct) o[ct][d] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va, pb[ct][h], o[ct][d], 0, 0, 0);
+        }
+    }
+    if (threadIdx.x == 0) sh.next_item = (mixed ? 0u : ncu) + atomicAdd(c.attn_ctr + c.n_layers + layer, 1u);
+    if (colv) {
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        const float inv = 1.0f / quad_sum(l[ct]);
+#pragma unroll
+        for (int d = 0; d < HD / 16; ++d)
+          *(uint2*)(c.aq + packed_off(t0 + q0 + lc, (g * G + hg * CT + ct) * HD + d * 16 + lg * 4, c.TBS)) =
+              make_uint2(pack_f16x2(o[ct][d][0] * inv, o[ct][d][1] * inv), pack_f16x2(o[ct][d][2] * inv, o[ct][d][3] * inv));
+      }
+    }
+    wait_dma_barrier<0>();                                   // no fetch of this item is on its way any more, and next_item is there
+    item = (u32)__builtin_amdgcn_readfirstlane(sh.next_item);
+    __syncthreads();                                         // (read by everyone before it is written again)
+  }
+  __builtin_amdgcn_s_setprio(0);
+}
+
+// Which kernel an iteration's prompt tokens take. Short runs of tokens (speculative decoding's few per sequence, the rest of a cached
+// prompt) would leave most of a shared item's waves without queries while the whole context is walked by one item:
+// they stay with the wave-per-tile kernel, which splits a tile's keys between waves.
+__device__ __forceinline__ bool attn_prompt_ok(const DevCtx& c) { return c.meta->max_q_len >= 32 && ((c.tune_nw >> 16) & 15u) == 0; }   // (bits 16-19 of the tuning word ask for the other kernel)
+
+template <int HD>
+__device__ __forceinline__ void attn_prompt_hd(const DevCtx& c, u32 layer, AttnPromptShared& sh, u32 wg, u32 nwg, bool mixed) {
+  switch (c.nq / c.nkv) {
+    case 1: attn_prompt<HD, 1>(c, layer, sh, wg, nwg, mixed); break;
+    case 3: case 6: attn_prompt<HD, 3>(c, layer, sh, wg, nwg, mixed); break;
+    default: attn_prompt<HD, 2>(c, layer, sh, wg, nwg, mixed); break;   // 2, 4, 8
+  }
+}
+
 template <int HD>
 __device__ __forceinline__ void attn_prefill_hd(const DevCtx& c, u32 layer, AttnMfmaShared& sh, u32 wg, u32 nwg) {
   const u32 G = c.nq / c.nkv;
@@ -623,10 +846,18 @@ __device__ __forceinline__ void attn_prefill_hd(const DevCtx& c, u32 layer, Attn
   }
 }
 
+__device__ __forceinline__ void attn_prompt_part(const DevCtx& c, u32 layer, AttnShared8& u, u32 wg, u32 nwg, bool mixed) {
+  if (attn_prompt_ok(c)) {
+    if (c.hd == 64) attn_prompt_hd<64>(c, layer, u.p, wg, nwg, mixed); else attn_prompt_hd<128>(c, layer, u.p, wg, nwg, mixed);
+  } else {
+    if (c.hd == 64) attn_prefill_hd<64>(c, layer, u.m, wg, nwg); else attn_prefill_hd<128>(c, layer, u.m, wg, nwg);
+  }
+}
+
 // The sequences of an iteration that decode (one token, work items = chunks of their context) and those that process
 // prompt tokens (work items = tiles of 16 queries) each have their kernel part; a mixed iteration (chunked prefill) runs
 // both in the one launch, every workgroup first its share of the decode items, then of the query tiles.
-__device__ __forceinline__ void phase_attention_mfma(const DevCtx& c, u32 layer, AttnMfmaShared& sh, u32 wg, u32 nwg) {
+__device__ __forceinline__ void phase_attention_mfma(const DevCtx& c, u32 layer, AttnShared8& u, u32 wg, u32 nwg) {
   const u32 B = c.meta->n_seqs;
   const bool dec = c.cu_chunks[B] != 0, pre = c.cu_qtiles[B] != 0;
   // In a mixed iteration every other workgroup takes its query tiles first: the decode items stream the KV cache from
@@ -634,19 +865,17 @@ __device__ __forceinline__ void phase_attention_mfma(const DevCtx& c, u32 layer,
   // of all workgroups hitting HBM first and L2 afterwards.
   const bool pre_first = dec && pre && (wg & 1u) && !(c.tune_nw & 0x40000000u);   // bit 30 of the tuning word: decode part first everywhere (A/B)
   if (pre_first) {
-    if (c.hd == 64) attn_prefill_hd<64>(c, layer, sh, wg, nwg); else attn_prefill_hd<128>(c, layer, sh, wg, nwg);
+    attn_prompt_part(c, layer, u, wg, nwg, true);
     __syncthreads();
   }
   if (dec) {
     // bit 23 of the tuning word (A/B): static items, one batch of loads per item, instead of the items taken through the work counter
     if (c.tune_nw & 0x800000u) {
-      if (c.hd == 64) attn_decode<64>(c, layer, sh, wg, nwg); else attn_decode<128>(c, layer, sh, wg, nwg);
+      if (c.hd == 64) attn_decode<64>(c, layer, u.m, wg, nwg); else attn_decode<128>(c, layer, u.m, wg, nwg);
     } else {
-      if (c.hd == 64) attn_decode_dyn<64>(c, layer, sh, wg, nwg); else attn_decode_dyn<128>(c, layer, sh, wg, nwg);
+      if (c.hd == 64) attn_decode_dyn<64>(c, layer, u.m, wg, nwg); else attn_decode_dyn<128>(c, layer, u.m, wg, nwg);
     }
   }
-  if (dec && pre && !pre_first) __syncthreads();   // the batch metadata in LDS is staged again for the other part
-  if (pre && !pre_first) {
-    if (c.hd == 64) attn_prefill_hd<64>(c, layer, sh, wg, nwg); else attn_prefill_hd<128>(c, layer, sh, wg, nwg);
-  }
+  if (dec && pre && !pre_first) __syncthreads();   // the other part uses the same LDS
+  if (pre && !pre_first) attn_prompt_part(c, layer, u, wg, nwg, dec);
 }

@@ -526,7 +526,7 @@ static int init_impl(const blink_config* cfg, blink_engine* e) {
     {
       c.chunk_cap = c.max_batch * ((c.max_seq_len + ATTN_CHUNK_TOKENS - 1) / ATTN_CHUNK_TOKENS);
       if (int rc = dalloc(e, &c.chunk_rec, 2ull * c.chunk_cap)) return rc;
-      if (int rc = dalloc(e, &c.attn_ctr, c.n_layers)) return rc;
+      if (int rc = dalloc(e, &c.attn_ctr, 2ull * c.n_layers)) return rc;
     }
     {
       const u64 chunks = (u64)c.max_batch * ((c.max_seq_len + ATTN_CHUNK_TOKENS - 1) / ATTN_CHUNK_TOKENS), G = c.nq / c.nkv;

@@ -230,7 +230,7 @@ struct DevCtx {
   u32* cu_qtiles;       // [max_batch+1] prefix sum of ceil(tokens/16) per sequence of the iteration
   ChunkRec* chunk_rec;  // [2 * chunk_cap] (bf16 models; null otherwise)
   u32 chunk_cap;        // max_batch * chunks of the longest context
-  u32* attn_ctr;        // [n_layers] work counters of the decode attention launches, zeroed by the scheduler step
+  u32* attn_ctr;        // [2][n_layers] work counters of the attention launches (decode items; prompt items), zeroed by the scheduler step
   u32* cu_chunks;       // [max_batch+1] prefix sum of ceil(context/ATTN_CHUNK_TOKENS) per sequence (decode attention work items)
   i32* input_ids;       // [maxT]
   i32* positions;       // [maxT]

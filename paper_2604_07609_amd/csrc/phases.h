@@ -33,7 +33,7 @@ template <> struct PhaseSharedOf<PH_GATEUP, false> { typedef GemmShared8 type; }
 template <> struct PhaseSharedOf<PH_DOWN, false> { typedef GemmShared8 type; };
 template <> struct PhaseSharedOf<PH_LM_HEAD, false> { typedef GemmShared8 type; };
 template <> struct PhaseSharedOf<PH_ROUTER, false> { typedef MfmaShared type; };
-template <> struct PhaseSharedOf<PH_ATTN, false> { typedef AttnMfmaShared type; };
+template <> struct PhaseSharedOf<PH_ATTN, false> { typedef AttnShared8 type; };
 template <> struct PhaseSharedOf<PH_SAMPLE, false> { typedef SamplerShared type; };
 template <> struct PhaseSharedOf<PH_MOE_GATEUP, false> { typedef MoeShared type; };
 template <> struct PhaseSharedOf<PH_MOE_DOWN, false> { typedef MoeShared type; };
@@ -109,7 +109,7 @@ __device__ __forceinline__ void run_phase_bf16(const DevCtx& c, u32 layer, typen
       a.nq = c.nq; a.nkv = c.nkv; a.hd = c.hd; a.bs = c.bs; a.ordered = c.n_experts;
       gemm_bf16<EPI_QKV_ROPE>(a, *(GemmShared8*)&sh, wg, nwg);
       break;
-    case PH_ATTN: phase_attention_mfma(c, layer, *(AttnMfmaShared*)&sh, wg, nwg); break;
+    case PH_ATTN: phase_attention_mfma(c, layer, *(AttnShared8*)&sh, wg, nwg); break;
     case PH_ATTN_COMBINE: attn_decode_combine(c, wg, nwg); break;
     case PH_ROUTER:     // router logits of every token; its first workgroup also clears the experts' counters for this layer
       if (wg == 0)

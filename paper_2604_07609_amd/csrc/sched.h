@@ -891,7 +891,7 @@ __device__ void sched_step(const DevCtx& c, SchedShared& sh) {
 
   // ---- write back ------------------------------------------------------------------------------------------
   if (c.attn_ctr)
-    for (u32 l = tid; l < c.n_layers; l += BLK_THREADS) c.attn_ctr[l] = 0;     // work counters of this iteration's decode attention launches
+    for (u32 l = tid; l < 2 * c.n_layers; l += BLK_THREADS) c.attn_ctr[l] = 0; // work counters of this iteration's attention launches
   if (tid == 0) {
     const u64 now = dev_now_ns();
     ss->free_top = top;
