@@ -139,7 +139,7 @@ struct AttnMfmaShared {
 // Prompt attention with shared KV tiles: a ring of stages of four KV blocks (64 keys), and where every sequence's items begin.
 #define ATTN_RING_BYTES (128u * 1024u)
 struct AttnPromptShared {
-  unsigned char ring[ATTN_RING_BYTES];
+  alignas(256) unsigned char ring[ATTN_RING_BYTES];
   u32 cu_items[ATTN_META_MAX + 1], wave_sum[ATTN_WAVES], next_item;
 };
 union AttnShared8 { AttnMfmaShared m; AttnPromptShared p; };

@@ -13,7 +13,9 @@
 
 #define DMA_RING_BYTES (144u * 1024u)
 struct DmaShared {
-  unsigned char ring[DMA_RING_BYTES];   // k-steps in flight: of each the weight tiles, then the activation tiles (1 KB each)
+  // k-steps in flight: of each the weight tiles, then the activation tiles (1 KB each). Aligned: 8 bytes off, behind the lists
+  // of the grouped GEMMs, every 16-byte read took 60 cycles of the LDS instead of 4 and a launch up to 3.5 times as long.
+  alignas(256) unsigned char ring[DMA_RING_BYTES];
   float rstd[256];                      // norm scales of the tokens of the workgroup's tile
 };
 
