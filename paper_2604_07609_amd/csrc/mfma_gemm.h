@@ -336,7 +336,7 @@ struct StreamBuf {
 // NW consecutive 16-row weight tiles per workgroup: every activation tile a wave loads is used for NW MFMAs, which
 // divides the L2 traffic of the activation operand by NW (it is TW/NW times the weight bytes).
 // k-tiles per batch of loads (two batches are in flight per wave). Measured on MI355X under the budget of 256 registers
-// per lane that lets two four-wave workgroups share a compute unit: the widest variants keep fewer k-tiles per batch.
+// per lane (an eight-wave workgroup per compute unit): the widest variants keep fewer k-tiles per batch.
 // GRID2D (64 < T <= 256, four token blocks per item): the work items are (tile group, group of 64 tokens) pairs, the
 // token group varying fastest and the items of one round dealt to the XCDs in runs, so that the workgroups running
 // together share weight rows in L2; the weight loads are ordinary (cached) ones then.
@@ -437,7 +437,7 @@ __device__ __forceinline__ void gemm_stream(const MfmaGemmArgs& a, MfmaShared& s
         pre_cs[i] = *(const float4*)(a.rope_tab + (u64)(rot ? pos : 0u) * half + (rot ? (n0 % a.hd) >> 1 : 0u));
       }
     }
-    // reduce the four K-quarters through LDS, one weight tile of the group at a time
+    // reduce the waves' shares of K through LDS, one weight tile of the group at a time
 #pragma unroll
     for (int i = 0; i < NW; ++i) {
       __syncthreads();   // the previous reduction has been read
