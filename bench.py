@@ -537,7 +537,7 @@ def claim_latency(B, e, vocab, n=24):
                 submit_return_to_scheduled_us=dict(median=med(ret), p90=round(float(np.percentile(ret, 90)), 1)),
                 clock_mapping_uncertainty_us=med(unc),
                 note="idle engine, one 8-token request at a time; 'scheduled' = end of the scheduler step that admitted it (claim, block "
-                     "allocation and batch metadata done); blink_submit is two synchronous copies (payload, then the state word), so the "
+                     "allocation and batch metadata done); blink_submit is one small kernel (payload, then the state word) and one wait, so the "
                      "device may claim the request before the call returns")
 
 
