@@ -211,6 +211,7 @@ struct blink_engine {
   u64 host_step_bytes = 0;
   int timed_phase = -1;                 // phase whose launches are bracketed by HIP events (-1: none)
   std::vector<hipEvent_t> phase_ev;     // [depth][n_layers][2]
+  std::vector<char> phase_rec;          // [depth][n_layers]: the pair has been recorded and not yet read
   std::vector<float> phase_ms;          // per enqueued iteration of the current window: summed duration
   std::vector<hipEvent_t> events;
   std::atomic<bool> loop_active{false};
@@ -568,6 +569,7 @@ static int init_impl(const blink_config* cfg, blink_engine* e) {
     for (u32 i = 0; i < depth; ++i) HIPCHK(hipEventCreateWithFlags(&e->events[i], hipEventDisableTiming));
     e->phase_ev.resize((u64)depth * c.n_layers * 2);
     for (auto& ev : e->phase_ev) HIPCHK(hipEventCreate(&ev));
+    e->phase_rec.assign((u64)depth * c.n_layers, 0);
   }
   if (int rc = build_graph(e)) return rc;
   return 0;
@@ -692,6 +694,7 @@ static int launch_phase(blink_engine* e, const DevCtx& ctx, hipStream_t st, int 
     const u64 slot = (enq_index % e->events.size()) * e->ctx.n_layers + (phase_per_layer(ph) ? layer : 0);
     a = e->phase_ev[2 * slot];
     b = e->phase_ev[2 * slot + 1];
+    e->phase_rec[slot] = 1;
     HIPCHK(hipEventRecord(a, st));
   }
   // the GEMMs of a bf16 model run one eight-wave workgroup per compute unit
@@ -779,7 +782,9 @@ static int enqueue_iteration(blink_engine* e, u64 enq_index) {
   return enqueue_iteration_kernels(e, e->compute, enq_index, whole);
 }
 
-// durations of the timed phase for the iteration enqueued at enq_index (its events have completed)
+// durations of the timed phase for the iteration enqueued at enq_index (its events have completed). A phase without kernels in
+// that iteration's chain counts as 0: its events are not asked (the error of an event that was never recorded would stay behind
+// for the next launch's check, which then ends the loop).
 static void harvest_phase_times(blink_engine* e, u64 enq_index) {
   if (e->timed_phase < 0) return;
   const bool per_layer = phase_per_layer(e->timed_phase);
@@ -788,6 +793,8 @@ static void harvest_phase_times(blink_engine* e, u64 enq_index) {
   for (u32 l = 0; l < n; ++l) {
     const u64 slot = (enq_index % e->events.size()) * e->ctx.n_layers + l;
     float ms = 0.f;
+    if (!e->phase_rec[slot]) continue;
+    e->phase_rec[slot] = 0;
     if (hipEventElapsedTime(&ms, e->phase_ev[2 * slot], e->phase_ev[2 * slot + 1]) == hipSuccess) sum += ms;
   }
   e->phase_ms.push_back(sum);
