@@ -13,6 +13,7 @@
 #include <mutex>
 #include <string>
 #include <thread>
+#include <tuple>
 #include <vector>
 
 // ================================================================================================
@@ -226,6 +227,17 @@ struct blink_engine {
   explicit blink_engine(u32 slots) : shadow_state(slots) {}
 };
 
+// Launches a kernel and returns the launch's own result. (hipGetLastError also reports what any earlier HIP call of the same thread
+// has left behind, the caller's own included.)
+template <typename... P, typename... A>
+static hipError_t launch(void (*kernel)(P...), u32 grid, u32 block, hipStream_t st, A... args) {
+  std::tuple<P...> as_declared(args...);
+  return std::apply([&](auto&... a) {
+    void* argv[] = {(void*)&a...};
+    return hipLaunchKernel((const void*)kernel, dim3(grid), dim3(block), argv, 0, st);
+  }, as_declared);
+}
+
 template <typename T>
 static int dalloc(blink_engine* e, T** p, u64 count, bool zero = true) {
   void* q = nullptr;
@@ -410,8 +422,7 @@ static int init_impl(const blink_config* cfg, blink_engine* e) {
         } else {
           HIPCHK(hipMemcpy(stage, hsrc + src_off, (u64)N * K * 2, hipMemcpyHostToDevice));
         }
-        hipLaunchKernelGGL(k_pack_weights, dim3(2048), dim3(BLK_THREADS), 0, e->compute, (const bf16_t*)stage, p, N, K, pair_rows, perm_hd);
-        HIPCHK(hipGetLastError());
+        HIPCHK(launch(k_pack_weights, 2048, BLK_THREADS, e->compute, (const bf16_t*)stage, p, N, K, pair_rows, perm_hd));
         HIPCHK(hipStreamSynchronize(e->compute));          // the staging buffer is reused by the next matrix
         return 0;
       };
@@ -495,8 +506,7 @@ static int init_impl(const blink_config* cfg, blink_engine* e) {
     float2* tab;
     if (int rc = dalloc(e, &tab, (u64)c.max_seq_len * (c.hd / 2), false)) return rc;
     const u64 n = (u64)c.max_seq_len * (c.hd / 2);
-    hipLaunchKernelGGL(k_rope_table, dim3((u32)((n + 255) / 256)), dim3(256), 0, e->compute, tab, c.max_seq_len, c.hd / 2, (double)c.theta);
-    HIPCHK(hipGetLastError());
+    HIPCHK(launch(k_rope_table, (u32)((n + 255) / 256), 256, e->compute, tab, c.max_seq_len, c.hd / 2, (double)c.theta));
     c.rope_tab = tab;
   }
   // ---- bf16 model: packed activation operands between the GEMMs, decode attention partials ----
@@ -671,9 +681,7 @@ extern "C" int blink_submit(blink_engine* e, const int32_t* prompt, uint32_t n_p
   e->delivered[slot] = 0;
   e->shadow_state[slot].store(1, std::memory_order_release);
   // one small kernel writes all three in order and is waited for once (three copies and two waits: 35-49 us a call)
-  hipLaunchKernelGGL(k_ring_write, dim3(1), dim3(BLK_THREADS), 0, e->s_in, (const SlotDesc*)d, (const i32*)ptoks, n_prompt, *st, c.desc + slot,
-                     c.in_arena + (u64)slot * c.max_seq_len, c.status + slot);
-  HIPCHK(hipGetLastError());
+  HIPCHK(launch(k_ring_write, 1, BLK_THREADS, e->s_in, d, ptoks, n_prompt, *st, c.desc + slot, c.in_arena + (u64)slot * c.max_seq_len, c.status + slot));
   HIPCHK(hipStreamSynchronize(e->s_in));
   e->next_ticket = t + 1;
   if (request_id_out) *request_id_out = t;
@@ -701,7 +709,7 @@ static int launch_phase(blink_engine* e, const DevCtx& ctx, hipStream_t st, int 
   const bool gemm = ph == PH_QKV || ph == PH_OPROJ || ph == PH_GATEUP || ph == PH_DOWN || ph == PH_LM_HEAD || ph == PH_MOE_GATEUP || ph == PH_MOE_DOWN;
   const bool bf16 = e->ctx.dtype == 1;
   const u32 threads = bf16 && (gemm || ph == PH_ATTN) ? 512u : (u32)BLK_THREADS;
-  hipLaunchKernelGGL(phase_kernel(ph, !bf16), dim3(bf16 && gemm ? (u32)e->n_cu : e->grid), dim3(threads), 0, st, ctx, layer);
+  HIPCHK(launch(phase_kernel(ph, !bf16), bf16 && gemm ? (u32)e->n_cu : e->grid, threads, st, ctx, layer));
   if (timed) HIPCHK(hipEventRecord(b, st));
   return 0;
 }
@@ -714,8 +722,8 @@ static int launch_phase(blink_engine* e, const DevCtx& ctx, hipStream_t st, int 
 static int enqueue_iteration_kernels(blink_engine* e, hipStream_t st, u64 enq_index, bool whole_chain) {
   DevCtx c = e->ctx;
   if (whole_chain) c.tune_nw |= 0x400000u;
-  if (c.spec_k) hipLaunchKernelGGL(k_spec_draft, dim3((c.max_batch + 3) / 4), dim3(BLK_THREADS), 0, st, c);
-  hipLaunchKernelGGL(k_sched, dim3(1), dim3(BLK_THREADS), 0, st, c);
+  if (c.spec_k) HIPCHK(launch(k_spec_draft, (c.max_batch + 3) / 4, BLK_THREADS, st, c));
+  HIPCHK(launch(k_sched, 1, BLK_THREADS, st, c));
   if (int rc = launch_phase(e, c, st, PH_EMBED, 0, enq_index)) return rc;
   for (u32 l = 0; l < c.n_layers; ++l)
     for (int ph = PH_LAYER_FIRST; ph <= PH_LAYER_LAST; ++ph) {
@@ -732,9 +740,7 @@ static int enqueue_iteration_kernels(blink_engine* e, hipStream_t st, u64 enq_in
     }
   if (int rc = launch_phase(e, c, st, PH_FINAL_NORM, 0, enq_index)) return rc;
   if (int rc = launch_phase(e, c, st, PH_LM_HEAD, 0, enq_index)) return rc;
-  if (int rc = launch_phase(e, c, st, PH_SAMPLE, 0, enq_index)) return rc;
-  HIPCHK(hipGetLastError());
-  return 0;
+  return launch_phase(e, c, st, PH_SAMPLE, 0, enq_index);
 }
 
 static int capture_chain(blink_engine* e, bool whole_chain, hipGraphExec_t* out) {
@@ -851,8 +857,7 @@ extern "C" int blink_run(blink_engine* e, uint64_t max_iterations) {
   const u64 iter_limit = max_iterations ? e->hmirror->iteration + max_iterations : 0;
   e->iter_limit = iter_limit;
   e->hmirror->stopped = 0;
-  hipLaunchKernelGGL(k_open_window, dim3(1), dim3(1), 0, e->compute, e->ctx.ss, iter_limit);
-  HIPCHK(hipGetLastError());
+  HIPCHK(launch(k_open_window, 1, 1, e->compute, e->ctx.ss, iter_limit));
   e->loop_active.store(true, std::memory_order_release);
   e->loop_rc.store(0);
   e->windows.fetch_add(1);
@@ -911,8 +916,7 @@ extern "C" int blink_poll_outputs(blink_engine* e, blink_event* buf, uint32_t ca
   if (n_picks == 0) return BLINK_OK;
   // one kernel fetches the records of all slots and returns the completed slots to EMPTY (the frontend's edge of the life cycle);
   // a copy per slot cost 3 us each, and another for every completed one
-  hipLaunchKernelGGL(k_fetch_outputs, dim3(n_picks), dim3(64), 0, e->s_out, (const OutPick*)e->stage_picks, c.out_arena, c.max_seq_len, e->stage_out, c.status);
-  HIPCHK(hipGetLastError());
+  HIPCHK(launch(k_fetch_outputs, n_picks, 64, e->s_out, e->stage_picks, c.out_arena, c.max_seq_len, e->stage_out, c.status));
   HIPCHK(hipStreamSynchronize(e->s_out));
   // events across requests ordered by (iteration, ring slot); per request by index
   u32 w = 0;
@@ -1106,8 +1110,7 @@ extern "C" int blink_calibration_copy(blink_engine* e, uint64_t bytes) {
   const u64 cap = e->calib_bytes;
   if (bytes == 0 || bytes > cap || (bytes & 15)) return fail(BLINK_ERR_INVAL, "bytes must be a multiple of 16 in (0, %llu]", (unsigned long long)cap);
   HIPCHK(hipSetDevice(e->cfg.device));
-  hipLaunchKernelGGL(k_copy_calibration, dim3(e->grid * 4), dim3(BLK_THREADS), 0, e->compute, (const uint4*)src, (uint4*)dst, bytes / 16);
-  HIPCHK(hipGetLastError());
+  HIPCHK(launch(k_copy_calibration, e->grid * 4, BLK_THREADS, e->compute, (const uint4*)src, (uint4*)dst, bytes / 16));
   HIPCHK(hipStreamSynchronize(e->compute));
   return BLINK_OK;
 }
@@ -1127,7 +1130,7 @@ extern "C" int blink_calibration_rates(blink_engine* e, double* copy_gbs, double
     if (src) (void)hipFree(src);
     (void)hipEventDestroy(t0);
     (void)hipEventDestroy(t1);
-    (void)hipGetLastError();
+    (void)hipGetLastError();             // (the caller's next look must not find this one)
     return fail(BLINK_ERR_DEVICE, "no room for the two 1 GiB copy buffers");
   }
   const u32 rounds = 4096, wgs = e->grid * 2;        // the MFMA loop writes one float per lane: 1 MiB of the 64 MiB buffer
@@ -1136,15 +1139,15 @@ extern "C" int blink_calibration_rates(blink_engine* e, double* copy_gbs, double
   for (int rep = 0; rep < 4 && rc == BLINK_OK; ++rep) {   // the first repetition warms up; the best of the rest counts
     float ms = 0.f;
     if (hipEventRecord(t0, e->compute) != hipSuccess) { rc = BLINK_ERR_DEVICE; break; }
-    hipLaunchKernelGGL(k_copy_calibration, dim3(e->grid * 4), dim3(BLK_THREADS), 0, e->compute, (const uint4*)src, (uint4*)dst, n16);
+    if (launch(k_copy_calibration, e->grid * 4, BLK_THREADS, e->compute, (const uint4*)src, (uint4*)dst, n16) != hipSuccess) { rc = BLINK_ERR_DEVICE; break; }
     if (hipEventRecord(t1, e->compute) != hipSuccess || hipEventSynchronize(t1) != hipSuccess || hipEventElapsedTime(&ms, t0, t1) != hipSuccess) { rc = BLINK_ERR_DEVICE; break; }
     if (rep && (best_copy == 0.f || ms < best_copy)) best_copy = ms;
     if (hipEventRecord(t0, e->compute) != hipSuccess) { rc = BLINK_ERR_DEVICE; break; }
-    hipLaunchKernelGGL(k_mfma_calibration, dim3(wgs), dim3(BLK_THREADS), 0, e->compute, (float*)e->calib_dst, rounds);
+    if (launch(k_mfma_calibration, wgs, BLK_THREADS, e->compute, (float*)e->calib_dst, rounds) != hipSuccess) { rc = BLINK_ERR_DEVICE; break; }
     if (hipEventRecord(t1, e->compute) != hipSuccess || hipEventSynchronize(t1) != hipSuccess || hipEventElapsedTime(&ms, t0, t1) != hipSuccess) { rc = BLINK_ERR_DEVICE; break; }
     if (rep && (best_mfma == 0.f || ms < best_mfma)) best_mfma = ms;
     if (hipEventRecord(t0, e->compute) != hipSuccess) { rc = BLINK_ERR_DEVICE; break; }
-    hipLaunchKernelGGL(k_read_calibration, dim3(e->grid), dim3(BLK_THREADS), 0, e->compute, (const uint4*)src, (u32*)e->calib_dst, n16);
+    if (launch(k_read_calibration, e->grid, BLK_THREADS, e->compute, (const uint4*)src, (u32*)e->calib_dst, n16) != hipSuccess) { rc = BLINK_ERR_DEVICE; break; }
     if (hipEventRecord(t1, e->compute) != hipSuccess || hipEventSynchronize(t1) != hipSuccess || hipEventElapsedTime(&ms, t0, t1) != hipSuccess) { rc = BLINK_ERR_DEVICE; break; }
     if (rep && (best_read == 0.f || ms < best_read)) best_read = ms;
   }
@@ -1153,7 +1156,7 @@ extern "C" int blink_calibration_rates(blink_engine* e, double* copy_gbs, double
   (void)hipFree(dst);
   (void)hipEventDestroy(t0);
   (void)hipEventDestroy(t1);
-  if (rc != BLINK_OK || hipGetLastError() != hipSuccess) return fail(BLINK_ERR_DEVICE, "calibration kernels failed");
+  if (rc != BLINK_OK) return fail(BLINK_ERR_DEVICE, "calibration kernels failed");
   *copy_gbs = 2.0 * (double)(n16 * 16) / ((double)best_copy * 1e-3) / 1e9;   // bytes read + bytes written
   *read_gbs = (double)(n16 * 16) / ((double)best_read * 1e-3) / 1e9;
   *mfma_bf16_tflops = (double)wgs * (BLK_THREADS / 64) * rounds * 16.0 * (2.0 * 16 * 16 * 32) / ((double)best_mfma * 1e-3) / 1e12;
@@ -1174,8 +1177,7 @@ extern "C" int blink_clock_sync(blink_engine* e, uint64_t* device_ns, uint64_t* 
   for (int rep = 0; rep < 8; ++rep) {
     __atomic_store_n(&e->hmirror->clock_probe, 0ull, __ATOMIC_RELEASE);
     const u64 h0 = host_now_ns();
-    hipLaunchKernelGGL(k_clock_probe, dim3(1), dim3(1), 0, e->s_in, e->hmirror);   // not the compute stream: the loop may be running there
-    HIPCHK(hipGetLastError());
+    HIPCHK(launch(k_clock_probe, 1, 1, e->s_in, e->hmirror));   // not the compute stream: the loop may be running there
     u64 dv = 0, h1 = h0;
     while ((dv = __atomic_load_n(&e->hmirror->clock_probe, __ATOMIC_ACQUIRE)) == 0) {
       h1 = host_now_ns();
@@ -1224,9 +1226,8 @@ static int sample_rows_on(char* dev, hipStream_t st, const float* logits, uint32
   HIPCHK(hipMemcpyAsync(dev, logits, (u64)n_rows * vocab * 4, hipMemcpyHostToDevice, st));
   HIPCHK(hipMemcpyAsync(dev + s.params, params, (u64)n_rows * sizeof(blink_sampling), hipMemcpyHostToDevice, st));
   HIPCHK(hipMemcpyAsync(dev + s.index, token_index, (u64)n_rows * 4, hipMemcpyHostToDevice, st));
-  hipLaunchKernelGGL(k_sample_rows, dim3(std::min<u32>(n_rows, 1024u)), dim3(BLK_THREADS), 0, st, (const float*)dev, n_rows, vocab,
-                     (const SampleRowParams*)(dev + s.params), (const u32*)(dev + s.index), (i32*)(dev + s.tokens));
-  HIPCHK(hipGetLastError());
+  HIPCHK(launch(k_sample_rows, std::min<u32>(n_rows, 1024u), BLK_THREADS, st, (const float*)dev, n_rows, vocab,
+                (const SampleRowParams*)(dev + s.params), (const u32*)(dev + s.index), (i32*)(dev + s.tokens)));
   HIPCHK(hipMemcpyAsync(tokens_out, dev + s.tokens, (u64)n_rows * 4, hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
   return BLINK_OK;
