@@ -1,6 +1,7 @@
 """The host side of the ABI on the GPU: what a call does when a phase has no kernels, when another library's HIP call has failed
 on the same thread, and while long kernels run."""
 import ctypes
+import time
 
 import numpy as np
 import pytest
@@ -60,3 +61,40 @@ def test_an_error_of_an_earlier_hip_call_is_not_taken_for_the_engine_s_own(lib):
             assert lib.sample_rows(row, [dict(temperature=0.0, top_k=0, top_p=1.0, seed=0)], [0])[0] == 99
     finally:
         e.shutdown()
+
+
+def test_submit_and_poll_beside_long_kernels(lib):
+    """Submit and poll need a place on the chip for a moment and must not wait for the GEMM launch that occupies it to end.
+    Prefill iterations of 8192 tokens at the widths of the llama3_8b shape: launches of 0.4 to 1.5 ms one behind the other, so
+    that a call which waited for the end of one would take about half a millisecond at the median; 25 to 35 us without the wait."""
+    cfg = dict(synth.model_config("llama3_8b"), n_layers=2, vocab=1024)
+    eng = dict(synth.engine_config("llama3_8b"), kv_num_blocks=60 * 260, max_batch=64, max_seq_len=4112, max_prefill_tokens=8192, ring_slots=256)
+    d, hd = cfg["d_model"], cfg["head_dim"]
+    layer = 2 * 4 * d + 2 * ((cfg["n_q_heads"] + 2 * cfg["n_kv_heads"]) * hd * d + d * cfg["n_q_heads"] * hd + 3 * d * cfg["d_ffn"])
+    blob = np.zeros(2 * 2 * cfg["vocab"] * d + cfg["n_layers"] * layer + 4 * d, dtype=np.uint8)
+    e = lib.Engine(cfg, eng, blob)
+    rng = np.random.default_rng(1)
+    took = {"submit": [], "poll": []}
+    try:
+        for _ in range(60):
+            e.submit(np.zeros(4096, np.int32), 1)
+        e.run(0)
+        end = time.perf_counter() + 0.1
+        while time.perf_counter() < end:
+            t0 = time.perf_counter()
+            e.poll()
+            t1 = time.perf_counter()
+            time.sleep(rng.uniform(0, 1e-3))
+            t2 = time.perf_counter()
+            e.submit(np.zeros(16, np.int32), 1)
+            took["poll"].append(t1 - t0)
+            took["submit"].append(time.perf_counter() - t2)
+            time.sleep(rng.uniform(0, 1e-3))
+        e.stop()
+        st = e.stats()
+    finally:
+        e.shutdown()
+    for name, v in took.items():
+        print(name, "median %.0f us of %d calls" % (np.median(v) * 1e6, len(v)), "prefill iterations", st["prefill_iterations"])
+    assert st["prefill_iterations"] >= 5 and st["next_ticket"] < 60 + len(took["submit"])      # prefills ran all along
+    assert np.median(took["submit"]) < 150e-6 and np.median(took["poll"]) < 150e-6
