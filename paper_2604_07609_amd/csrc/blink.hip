@@ -189,6 +189,8 @@ struct blink_engine {
   u64 stage_out_cap = 0;
   OutPick* stage_picks = nullptr;      // pinned [ring_slots]
   u64 iter_limit = 0;                  // of the current window (0: none)
+  u64 iter_before = 0;                 // iterations and chains run before the current window
+  u32 chains_before = 0;
   // loop
   std::thread launcher;
   hipGraphExec_t iter_graph = nullptr;        // the kernel chain of one iteration
@@ -803,10 +805,14 @@ static void pump_loop(blink_engine* e) {
   u64 enq = 0, done = 0;                         // iterations enqueued, and waited for
   while (rc == 0) {
     // `depth` iterations in flight, but no more than the window still lacks: behind its last iteration a chain is a row of
-    // empty kernels (60-500 us for the eight of them) that the end of the window would wait for. The mirrored count is the
-    // device's own, written by the scheduler step of every chain; at worst it lags by the chains in flight.
-    const u64 limit = e->iter_limit, ran = *(volatile const u64*)&e->hmirror->iteration;
-    const bool enough = limit != 0 && enq - done >= (limit > ran ? limit - ran : 0);
+    // empty kernels (60-500 us for the eight of them) that the end of the window would wait for. What it lacks are the
+    // iterations that have not begun, and what is on its way to them are the chains whose scheduler step has not run: the device
+    // mirrors both counts in one word. (Chains not waited for are one more, the one that runs: counted like that,
+    // the last chain was enqueued only behind the end of the one before it.)
+    const u64 limit = e->iter_limit, progress = *(volatile const u64*)&e->hmirror->progress;
+    const u64 lacking = limit - e->iter_before - ((u32)progress - (u32)e->iter_before);
+    const u32 coming = (u32)enq - ((u32)(progress >> 32) - e->chains_before);
+    const bool enough = limit != 0 && coming >= lacking;
     if (enq - done >= depth || (enough && enq > done)) {   // wait for the oldest one
       if (hipEventSynchronize(e->events[done % depth]) != hipSuccess) { rc = BLINK_ERR_DEVICE; break; }
       harvest_phase_times(e, done);
@@ -844,8 +850,10 @@ extern "C" int blink_run(blink_engine* e, uint64_t max_iterations) {
   if (e->launcher.joinable()) e->launcher.join();
   HIPCHK(hipSetDevice(e->cfg.device));
   if (e->hmirror->error) return fail(BLINK_ERR_DEVICE, "device loop error %u", e->hmirror->error);
-  const u64 iter_limit = max_iterations ? e->hmirror->iteration + max_iterations : 0;
+  e->iter_before = e->hmirror->iteration;
+  const u64 iter_limit = max_iterations ? e->iter_before + max_iterations : 0;
   e->iter_limit = iter_limit;
+  e->chains_before = (u32)(e->hmirror->progress >> 32);
   e->hmirror->stopped = 0;
   HIPCHK(launch(k_open_window, 1, 1, e->compute, e->ctx.ss, iter_limit));
   e->loop_active.store(true, std::memory_order_release);

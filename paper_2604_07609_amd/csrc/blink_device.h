@@ -151,6 +151,7 @@ struct HostMirror {
   u32 n_running;
   u32 idle;
   u64 clock_probe;      // device clock written by the clock probe kernel
+  u64 progress;         // chains whose scheduler step has run (upper half) and iterations begun (lower half), one store
 };
 
 // host -> device control words (pinned host memory, read by the scheduler with system-scope loads)

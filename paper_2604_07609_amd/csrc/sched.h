@@ -277,6 +277,7 @@ __device__ void sched_step(const DevCtx& c, SchedShared& sh) {
       ss->stopped = 1;
       c.meta->skip = 1;
       c.hmirror->iteration = ss->iteration;
+      c.hmirror->progress = (ss->chains << 32) | (u32)ss->iteration;
       c.hmirror->tokens_out = ss->tokens_out;
       c.hmirror->n_running = ss->n_running;
       c.hmirror->error = ss->error;
@@ -954,6 +955,7 @@ __device__ void sched_step(const DevCtx& c, SchedShared& sh) {
       }
     }
     c.hmirror->iteration = ss->iteration;
+    c.hmirror->progress = (ss->chains << 32) | (u32)ss->iteration;
     c.hmirror->tokens_out = ss->tokens_out;
     c.hmirror->n_running = nrun;
     c.hmirror->error = ss->error;

@@ -98,3 +98,26 @@ def test_submit_and_poll_beside_long_kernels(lib):
         print(name, "median %.0f us of %d calls" % (np.median(v) * 1e6, len(v)), "prefill iterations", st["prefill_iterations"])
     assert st["prefill_iterations"] >= 5 and st["next_ticket"] < 60 + len(took["submit"])      # prefills ran all along
     assert np.median(took["submit"]) < 150e-6 and np.median(took["poll"]) < 150e-6
+
+
+def test_the_last_iteration_of_a_window_is_enqueued_ahead(lib):
+    """Device time from the end of an iteration to the scheduler step of the next: no longer before the second and last
+    iteration of a window of two than inside a window of six (15 us each; 21 when the launcher waited for the first of two to end)."""
+    cfg, eng = synth.model_config("mini_churn"), dict(synth.engine_config("mini_churn"), max_batch=4, max_seq_len=1000, kv_num_blocks=256)
+    e = lib.Engine(cfg, eng, synth.pack_blob(cfg, synth.make_weights(cfg, 49)), flags=lib.FLAG_TRACE)
+    gaps = {2: [], 6: []}
+    try:
+        e.submit(np.arange(50), 900)
+        e.run(1)
+        e.wait()
+        for i in range(50):
+            for n, g in gaps.items():
+                e.run(n)
+                e.wait()
+                t = e.trace(n)
+                g.append((t["t_sched_begin_ns"][-1].astype(np.int64) - t["t_publish_end_ns"][-2].astype(np.int64)) / 1e3)
+    finally:
+        e.shutdown()
+    short, long = (np.median(gaps[n][5:]) for n in (2, 6))
+    print("gap before the last iteration of 2: %.1f us, of 6: %.1f us" % (short, long))
+    assert short < long + 3.0
