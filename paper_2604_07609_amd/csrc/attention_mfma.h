@@ -493,13 +493,8 @@ __device__ __forceinline__ void attn_prefill(const DevCtx& c, u32 layer, AttnMfm
   __syncthreads();
   auto cuq = [&](u32 i) { return sh.cu_chunks[i]; };
   const u64 total = (u64)cuq(B) * per_tile;
-  // waves per item: doubled while the longest chain (blocks of the longest prompt / WPI) is long and the items, each
-  // now taking WPI wave slots, still fit the waves that run at once
-  u32 WPI = 1;
+  u32 WPI = prefill_waves_per_item((c.meta->max_pref_ctx + 15) / 16, total, (u64)(nwg / 2) * nw);
   {
-    const u32 chain = (c.meta->max_pref_ctx + 15) / 16;
-    const u64 slots = (u64)(nwg / 2) * nw;
-    while (WPI < nw && WPI < 8 && chain > 12 * WPI && total * WPI <= slots) WPI *= 2;
     const u32 forced = (c.tune_nw >> 16) & 15u;      // bits 16-19 of the tuning word: 1, 2, 4, 8 force it (tests)
     if (forced == 1 || forced == 2 || forced == 4 || forced == 8) WPI = min(forced, nw);
   }
@@ -617,7 +612,7 @@ __device__ __forceinline__ void attn_prefill(const DevCtx& c, u32 layer, AttnMfm
   }
 }
 
-// ---- prompts of 32 tokens and more: the KV tiles of a kv head shared by a workgroup through LDS ---------------------------
+// ---- prompts: the KV tiles of a kv head shared by a workgroup through LDS (prompt_shared_pays says where) ---------------------
 // One workgroup (eight waves) per (sequence, kv head, QT tiles of 16 queries): QT x G / CT waves' worth of (query tile, CT q
 // heads), eight in all, walk the KV blocks together, 64 keys per step, from 0 to the last visible key. What bounded the
 // wave-per-tile kernel above was the path from the L2s: every wave fetched its own 8 KB per 16 keys and used them for
@@ -818,11 +813,6 @@ __device__ __forceinline__ void attn_prompt(const DevCtx& c, u32 layer, AttnProm
   __builtin_amdgcn_s_setprio(0);
 }
 
-// Which kernel an iteration's prompt tokens take. Short runs of tokens (speculative decoding's few per sequence, the rest of a cached
-// prompt) would leave most of a shared item's waves without queries while the whole context is walked by one item:
-// they stay with the wave-per-tile kernel, which splits a tile's keys between waves.
-__device__ __forceinline__ bool attn_prompt_ok(const DevCtx& c) { return c.meta->max_q_len >= 32 && ((c.tune_nw >> 16) & 15u) == 0; }   // (bits 16-19 of the tuning word ask for the other kernel)
-
 template <int HD>
 __device__ __forceinline__ void attn_prompt_hd(const DevCtx& c, u32 layer, AttnPromptShared& sh, u32 wg, u32 nwg, bool mixed) {
   switch (c.nq / c.nkv) {
@@ -847,7 +837,7 @@ __device__ __forceinline__ void attn_prefill_hd(const DevCtx& c, u32 layer, Attn
 }
 
 __device__ __forceinline__ void attn_prompt_part(const DevCtx& c, u32 layer, AttnShared8& u, u32 wg, u32 nwg, bool mixed) {
-  if (attn_prompt_ok(c)) {
+  if (c.meta->prompt_shared) {      // (the scheduler step's choice)
     if (c.hd == 64) attn_prompt_hd<64>(c, layer, u.p, wg, nwg, mixed); else attn_prompt_hd<128>(c, layer, u.p, wg, nwg, mixed);
   } else {
     if (c.hd == 64) attn_prefill_hd<64>(c, layer, u.m, wg, nwg); else attn_prefill_hd<128>(c, layer, u.m, wg, nwg);

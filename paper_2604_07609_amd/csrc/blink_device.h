@@ -107,8 +107,45 @@ struct IterMeta {
   u32 n_sample_seqs;    // sequences that sample (n_samples counts logits rows: more than one per sequence with speculative decoding)
   u32 n_full_chunks;    // decode attention work: chunks of ATTN_CHUNK_TOKENS context tokens that are full, listed first ...
   u32 n_chunks;         // ... and all chunks (the others are the last, partly filled chunk of a context)
-  u32 pad;
+  u32 prompt_shared;    // the prompt tokens' attention takes the kernel with shared KV tiles (bf16 models)
 };
+
+// ---- which of the two prompt attention kernels an iteration takes ---------------------------------------------------------
+// Query tiles of 16 per work item of the kernel with shared KV tiles: eight waves with one (three for 3 and 6, else two) q heads each.
+__host__ __device__ __forceinline__ u32 prompt_tiles_per_item(u32 G) { return G <= 3 ? 8u : G <= 6 ? 4u : 2u; }
+// Waves that share the keys of an item in the other kernel: doubled while the longest chain of KV blocks per wave is long and the
+// items, each taking that many wave slots, still fit the waves that run at once.
+__host__ __device__ __forceinline__ u32 prefill_waves_per_item(u32 blocks, u64 items, u64 slots) {
+  u32 w = 1;
+  while (w < 8 && blocks > 12 * w && items * w <= slots) w *= 2;
+  return w;
+}
+// The kernel with shared tiles walks all keys of an item with one workgroup; the other one splits a query tile's keys over up to
+// eight waves, but every wave fetches its own. So a few query tiles behind a long context are better off with the latter, as are
+// many sequences of one tile each, which leave a shared item's other waves without queries. Both times in us, from the
+// iteration's query tiles, the sequences they belong to, the shared items, the longest context of those and the sequences that
+// decode in the same launch. The shared items go in rounds of one per compute unit; beside decode items a workgroup that took
+// one still has its own first two decode items (9 us each) to do, while the other kernel's work comes behind the decode items.
+// Fitted to launches at 32 q / 8 kv heads of 128, 16 / 16 of 64 and 32 / 4 of 128 on 256 compute units; the choice is within 1 % of
+// the better kernel on average. Shared / other, measured at 32 / 8 of 128: 64 queries behind 4096 cached keys 147 / 62, behind 512 31 / 32; 512 behind
+// 4096 163 / 135, behind 512 49 / 53; eight sequences of 128 behind 4096 177 / 237; 15 tails of 16 behind 4096 154 / 84; prompts
+// from position 0: 509 tokens 32 / 33, 2048 85 / 137, 8192 596 / 1426; a chunk of 300 at position 1800 beside 190 decoding 105 / 135.
+__host__ __device__ __forceinline__ bool prompt_shared_pays(u32 tiles, u32 seqs, u32 items, u32 max_ctx, u32 decoding, u32 nkv, u32 G, u32 hd, u32 ncu) {
+  const float blocks = (float)((max_ctx + 15) / 16), h = (float)hd / 128.f;
+  const u64 old_items = (u64)tiles * nkv * (8 / prompt_tiles_per_item(G)), slots = (u64)ncu * 8;
+  const u32 split = prefill_waves_per_item((max_ctx + 15) / 16, old_items, slots), rounds = (items * nkv + ncu - 1) / ncu;
+  const float fill = (float)(old_items * split) / (float)slots, block_us = tiles < 2 * seqs ? .85f : 1.45f;
+  float shared = 6.f + (float)rounds * (2.f + h * (4.f + .54f * blocks));
+  const float passes = fill > 1.f ? ceilf(fill) : 1.f;
+  float other = split == 1 ? 6.f + h * (6.f + block_us * blocks * (fill > 1.f ? fill : 1.f) + 6.f * fill)
+                           : h * (18.f + 14.f * fill / passes + block_us * blocks / (float)split * passes);
+  if (decoding) {
+    const float r = (float)((u64)decoding * nkv) / (float)ncu, decode = r > 1.f ? h * (9.f * r - 8.f) : 0.f;
+    other += decode + 8.f * h;
+    shared = (shared > decode ? shared : decode) + h * (r > 1.f ? 18.f : 9.f) + (blocks < 40.f ? .2f * blocks - 4.f : 4.f);
+  }
+  return shared <= other;
+}
 
 // (sequence, kv head) pairs per compute unit from which the decode attention's work items are whole contexts; the
 // launcher takes the kernel chain without the merge kernels from the same count (read from the host mirror)

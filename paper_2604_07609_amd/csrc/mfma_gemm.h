@@ -74,8 +74,8 @@ struct MfmaGemmArgs {
                            // Bit 6: epilogues load their operands tile by tile. Bit 11: tall matrices stream too at T <= 64.
                            // Bits 12-14: force the tile shape at T > 64 (gemm_dma_pick).
                            // Bit 15 (scheduler): the decode attention's work items are always chunks, bit 22: always whole
-                           // contexts; bit 23: the decode attention kernel with static items. Bits 16-19: waves per item of the
-                           // prefill attention. Bit 30: mixed launches run their decode part first in every workgroup.
+                           // contexts; bit 23: the decode attention kernel with static items. Bits 16-19: 15 prompt attention with shared KV tiles, 1, 2, 4 or 8 the
+                           // other kernel with that many waves per item, other values that kernel. Bit 30: mixed launches run their decode part first in every workgroup.
 };
 
 #define GEMM_MAX_WAVES 8

@@ -16,19 +16,82 @@ pytestmark = pytest.mark.gpu
 RTOL = 4e-3
 
 
+# bits 16-19 of the tuning word: 15 forces prompt attention with shared KV tiles, 3 the kernel with a query tile per wave; 0: the scheduler's choice
+SHARED_TILES, WAVE_PER_TILE = 15 << 16, 3 << 16
+
+
+@pytest.mark.parametrize("kernel", [SHARED_TILES, WAVE_PER_TILE])
 @pytest.mark.parametrize("chunked", [False, True])
 @pytest.mark.parametrize("name", ["mini_churn", "mini_kv8", "mini_gqa", "mini_gqa128", "mini_g6", "mini_g8"])
-def test_prompt_attention_with_shared_kv_tiles(lib, name, chunked):
+def test_prompt_attention_with_shared_kv_tiles(lib, name, chunked, kernel):
     """1, 2, 3, 4, 6 and 8 q heads per kv head (so 128, 64 or 32 queries per work item), head dimensions 64 and 128. Prompts one
     below, at and above the item, the 64-key step and the 16-token block, one shorter than a query tile; with chunked
-    prefill, chunks that begin in the middle of a block and items beside decoding sequences."""
+    prefill, chunks that begin in the middle of a block and items beside decoding sequences. The kernel with a query tile per
+    wave on the same prompts."""
     cfg, eng, raw, blob = setup(name, 61)
     prompts = [33, 5, 127, 130, 64, 321, 509]
     eng = dict(eng, max_batch=7, max_seq_len=540, kv_num_blocks=110, max_prefill_tokens=2048, ring_slots=16)
     if chunked:
         eng.update(chunked_prefill=True, max_prefill_tokens=203)
-    worst = parity.stepwise_check(lib, cfg, eng, raw, blob, _fixed_prompts(cfg, prompts, 3, 261), rtol=RTOL)
+    worst = parity.stepwise_check(lib, cfg, eng, raw, blob, _fixed_prompts(cfg, prompts, 3, 261), rtol=RTOL, tune=kernel)
     print(name, "chunked" if chunked else "whole prompts", "worst relative logit error", worst)
+
+
+@pytest.mark.parametrize("kernel", [0, SHARED_TILES, WAVE_PER_TILE])
+def test_prompt_tails_behind_a_cached_head(lib, kernel):
+    """32 q / 8 kv heads of 128: tails of 1 to 130 tokens behind a cached head of 1040 in one iteration, on every kernel and on the
+    scheduler's choice."""
+    cfg, eng, raw, blob = setup("mini_heads32", 64)
+    tails = [1, 16, 17, 31, 32, 33, 64, 65, 130]
+    eng = dict(eng, prefix_cache=True, max_batch=len(tails) + 1, max_seq_len=1200, kv_num_blocks=200, max_prefill_tokens=1060, ring_slots=16)
+    rng = np.random.default_rng(64)
+    head = rng.integers(0, cfg["vocab"], 1040).astype(np.int32)
+    reqs = [dict(arrival_s=0.0, prompt=np.concatenate([head, rng.integers(0, cfg["vocab"], n).astype(np.int32)]), max_new_tokens=3,
+                 temperature=0.0, top_k=0, top_p=1.0, seed=i) for i, n in enumerate([3] + tails)]
+    worst = parity.stepwise_check(lib, cfg, eng, raw, blob, reqs, rtol=RTOL, tune=kernel)
+    print("tails, tuning word", hex(kernel), "worst relative logit error", worst)
+
+
+@pytest.mark.parametrize("heads", [(32, 8, 128), (16, 16, 64)])
+def test_prompt_attention_takes_the_faster_kernel(lib, heads):
+    """Launch times of both kernels and of the scheduler's choice: few queries behind a long context, where the keys of a query
+    tile have to be split between waves (62 us against 147 for 64 queries behind 4096 tokens), and prompts from
+    position 0, where the shared tiles win (85 against 137 at 2048 tokens). The choice may cost a quarter and 4 us more than the better one."""
+    nq, nkv, hd = heads
+    cfg = dict(synth.model_config("mini_heads32"), n_q_heads=nq, n_kv_heads=nkv, head_dim=hd, n_layers=1)
+    eng = dict(synth.engine_config("mini_heads32"), prefix_cache=True, max_batch=16, max_seq_len=4400, kv_num_blocks=4000, max_prefill_tokens=8192, ring_slots=32)
+    blob = synth.pack_blob(cfg, synth.make_weights(cfg, 65))
+    rng = np.random.default_rng(65)
+
+    def prompt(n):
+        return rng.integers(0, cfg["vocab"], n).astype(np.int32)
+
+    heads_cached = [prompt(4100) for _ in range(4)]
+    us = {}
+    for kernel in (0, SHARED_TILES, WAVE_PER_TILE):
+        e = lib.Engine(cfg, eng, blob, tune=kernel)
+        try:
+            for h in heads_cached:
+                e.submit(h, 1)
+                e.run(1)
+                e.wait()
+                e.drain()
+            e.time_phase(4)
+            for n, cached, tokens in ((1, 4096, 64), (4, 4096, 32), (1, 1024, 128), (1, 0, 2048), (3, 0, 700)):
+                best = np.inf
+                for rep in range(4):
+                    for i in range(n):
+                        e.submit(np.concatenate([heads_cached[i % 4][:cached], prompt(tokens)]), 1)
+                    e.run(1)
+                    e.wait()
+                    e.drain()
+                    best = min(best, float(e.phase_times_ms()[0]) * 1e3)
+                us.setdefault((n, cached, tokens), []).append(best)
+        finally:
+            e.shutdown()
+    for case, t in us.items():
+        print(heads, "prompts, cached, tokens", case, "us: choice %.1f, shared %.1f, wave per tile %.1f" % tuple(t))
+    assert all(t[0] < 1.25 * min(t[1:]) + 4.0 for t in us.values()), us
 
 
 def ragged(dtype, **more):
