@@ -206,13 +206,15 @@ __device__ __forceinline__ void gemm_dma_dense(const MfmaGemmArgs& a, DmaShared&
 }
 
 // ---- choice of the workgroup tile -----------------------------------------------------------------------------------
-// Time of a launch with tiles of one shape, in microseconds, from the number of rounds of workgroups: a k-step takes `lone` while
-// few compute units are busy (then it waits for weights from HBM, 25 to 40 GB/s per compute unit) and `full` with all
-// of them (shared L2s and the clock under load), and an item `fixed` for its first operands, its norm scales and its
-// epilogue. Fits, within 15 %, to launches of 4096 x 14336, 28672 x 4096 and 6144 x 4096 weights that come from HBM, at 100 to
-// 8000 tokens. 4096 x 14336 at 256 / 509 / 1700 tokens: 70 us (64 x 64), 108 us (128 x 64), 185 us (256 x 128), where the
-// register-staged tiles took 102, 111 and 283 us; 28672 x 4096 at 8000 tokens in the engine 1513 us = 1.24 PFLOP/s (256 x 256)
-// against 2040 us.
+// Time of a launch with tiles of one shape, in microseconds (without the launch itself), from the number of rounds of workgroups: a
+// k-step takes `lone` while few compute units are busy and `full` with all of them (shared L2s and the clock under load), and an
+// item `fixed` for its first operands, its norm scales and its epilogue. The epilogue differs by what follows the GEMM, and with
+// one workgroup per compute unit nothing runs beside it: of a 256 x 256 tile on 4096 k (128 k-steps) the rotary embedding and KV
+// write make 187 us, the residual add 145, the gate 108. So the constants are fitted per kind of epilogue, to launches with every shape forced
+// of 2 to 7 matrices each (1024 to 28672 rows, k 1024 to 14336, weights from HBM) at 65 to 8000 tokens; the fits are within 4 to 11 % (rms) of
+// them, and the shape they choose is within 3 % of the fastest one (5 % at sizes between those fitted). (One set for all epilogues, within 15 % for down and gate/up, took
+// 256 x 256 tiles where 256 x 128 are faster: QKV 6144 x 4096 at 8000 tokens 561 us instead of 464, 5120 x 2048 347 instead of 228, 2048 x 4096 at 6000
+// tokens 147 instead of 117.)
 __device__ __forceinline__ float dma_cost(u32 total, u32 K, float lone, float full, float fixed, u32 ncu) {
   const u32 rounds = total / ncu, rest = total % ncu;
   const float f = (float)rest / (float)ncu, kt = (float)(K / 32);
@@ -220,8 +222,12 @@ __device__ __forceinline__ float dma_cost(u32 total, u32 K, float lone, float fu
 }
 
 // The shapes: number, rows x tokens of the workgroup tile, constants.
-#define DMA_SHAPES(X) X(1, 64, 64, .136f, .142f, 4.f) X(2, 128, 64, .210f, .215f, 5.f) X(3, 128, 128, .265f, .280f, 7.f) \
-                      X(4, 256, 128, .385f, .420f, 9.f) X(6, 256, 192, .450f, .660f, 12.f) X(7, 256, 256, .525f, .750f, 14.f)
+#define DMA_SHAPES_STORE(X) X(1, 64, 64, .193f, .116f, 1.7f) X(2, 128, 64, .287f, .194f, 1.4f) X(3, 128, 128, .285f, .261f, 4.f) \
+                            X(4, 256, 128, .455f, .419f, 5.6f) X(6, 256, 192, .518f, .591f, 8.8f) X(7, 256, 256, .576f, .735f, 13.7f)
+#define DMA_SHAPES_RESIDUAL(X) X(1, 64, 64, .124f, .110f, 2.2f) X(2, 128, 64, .196f, .192f, 2.8f) X(3, 128, 128, .223f, .270f, 5.9f) \
+                               X(4, 256, 128, .356f, .449f, 11.2f) X(6, 256, 192, .430f, .688f, 17.f) X(7, 256, 256, .532f, .960f, 29.1f)
+#define DMA_SHAPES_ROPE(X) X(1, 64, 64, .363f, .255f, .7f) X(2, 128, 64, .258f, .204f, 4.3f) X(3, 128, 128, .303f, .309f, 8.4f) \
+                           X(4, 256, 128, .419f, .474f, 14.3f) X(6, 256, 192, .532f, .740f, 24.8f) X(7, 256, 256, .629f, 1.082f, 53.7f)
 
 // T > 64 tokens. (Bits 12-14 of the tuning word force a shape by its number.)
 template <int EPI>
@@ -231,7 +237,9 @@ __device__ __forceinline__ void gemm_dma_pick(const MfmaGemmArgs& a, DmaShared& 
     float least = INFINITY;
 #define OFFER(id, bn, bt, lone, full, fixed) \
     { const float t = dma_cost(DenseItems(a, bn, bt).total, a.K, lone, full, fixed, nwg); if (t < least) { least = t; best = id; } }
-    DMA_SHAPES(OFFER)
+    if (EPI == EPI_QKV_ROPE) { DMA_SHAPES_ROPE(OFFER) }
+    else if (EPI == EPI_RESIDUAL) { DMA_SHAPES_RESIDUAL(OFFER) }
+    else { DMA_SHAPES_STORE(OFFER) }
 #undef OFFER
   }
   switch (best) {
@@ -257,10 +265,12 @@ union GemmShared8 { MfmaShared mfma; DmaShared dma; };
 //     where the matrix has few enough of them. A decode iteration's sums are then taken in the order in which they have
 //     been taken all along (K in eight slices): in another order they round otherwise, and tokens with two nearly equal router
 //     logits go to another expert. The tiles would win 1 % of a decode iteration at 96 sequences of the moe_30b_a3b shape.
+//     The same schedule for the QKV projection of any model at up to 128 tokens, where it is the fastest: 6144 x 4096 at
+//     65 / 128 tokens 34 / 34 us against 39 / 45 (128 x 64 tiles) and 51 (64 x 64).
 template <int EPI>
 __device__ __forceinline__ void gemm_bf16(const MfmaGemmArgs& a, GemmShared8& sh, u32 wg, u32 nwg) {
   if (a.T == 0) return;
-  if (a.ordered && a.T > 64 && a.T <= 256 && ((a.N + 127) / 128) * ((a.T + 127) / 128) * 4 <= nwg) gemm_stream<EPI, 4, 4, 1, true>(a, sh.mfma, wg, nwg);
+  if (a.T > 64 && (a.ordered ? a.T <= 256 : EPI == EPI_QKV_ROPE && a.T <= 128) && !(a.tune_nw & 0x7000u) && ((a.N + 127) / 128) * ((a.T + 127) / 128) * 4 <= nwg) gemm_stream<EPI, 4, 4, 1, true>(a, sh.mfma, wg, nwg);
   else if (a.T > 64) gemm_dma_pick<EPI>(a, sh.dma, wg, nwg);
   else if (((a.N + 127) / 128) * 4 >= nwg * 3 && !(a.tune_nw & 0x807u)) {   // (not where bits 0-2 or 11 of the tuning word ask for streaming)
     if (a.T <= 16) gemm_dma_dense<EPI, 8, 1, 1, 2, true>(a, sh.dma, wg, nwg);        // 128 rows x 16 tokens

@@ -26,7 +26,7 @@ struct MoeShared {
   u32 small_base[MOE_MAX_EXPERTS + 1];
   u32 big_e[MOE_MAX_EXPERTS];     // experts with more tokens, and the blocks of tokens of all of them before each
   u32 big_base[MOE_MAX_EXPERTS + 1];
-  u32 n_small, n_big, shape;      // shape: workgroup tile of the big experts' GEMMs (DMA_SHAPES)
+  u32 n_small, n_big, shape;      // shape: workgroup tile of the big experts' GEMMs (DMA_SHAPES_STORE)
   float wrstd[8][64];             // per wave: norm scales of the tokens of its current item
   DmaShared dma;
 };
@@ -96,7 +96,7 @@ __device__ __forceinline__ void moe_split(const DevCtx& c, MoeShared& sh, u32 N,
       width = bt == 64 ? b64 : bt == 128 ? b128 : bt == 192 ? b192 : b256;                                                 \
       const float t = dma_cost((N + bn - 1) / bn * width, K, lone, full, fixed, nwg);                                      \
       if (forced ? best == id : t < least) { least = t; best = id; bt_of_best = bt; } }
-    DMA_SHAPES(OFFER)
+    DMA_SHAPES_STORE(OFFER)
 #undef OFFER
     u32 blocks = 0;
 #pragma unroll
