@@ -101,3 +101,27 @@ def test_moe_rejects_bad_configs(lib):
             lib.Engine(dict(cfg, **bad), eng, blob)
     with pytest.raises(lib.BlinkError):
         lib.Engine(dict(cfg, dtype=0), eng, blob)
+
+
+def test_few_expert_items_are_spread_over_the_chip(lib):
+    """Gate/up and down of one token at the widths of moe_30b_a3b: 192 and 256 wave items of eight experts. 24 and 15 us a
+    launch with the items spread over the compute units; 50 and 25 with eight neighbouring items in every workgroup (39 and 26 with four)."""
+    cfg = dict(synth.model_config("moe_30b_a3b"), n_layers=1, vocab=1024)
+    eng = dict(synth.engine_config("moe_30b_a3b"), kv_num_blocks=64, max_batch=2, max_seq_len=256, max_prefill_tokens=256, ring_slots=4)
+    d, hd, E = cfg["d_model"], cfg["head_dim"], cfg["n_experts"]
+    layer = 2 * 4 * d + 2 * ((cfg["n_q_heads"] + 2 * cfg["n_kv_heads"]) * hd * d + d * cfg["n_q_heads"] * hd + E * d + E * 3 * d * cfg["d_ffn"])
+    e = lib.Engine(cfg, eng, np.zeros(2 * 2 * cfg["vocab"] * d + layer + 4 * d, dtype=np.uint8))
+    us = {}
+    try:
+        e.submit(np.zeros(4, np.int32), 200)
+        e.run(1)
+        e.wait()
+        for phase in (18, 19):
+            e.time_phase(phase)
+            e.run(20)
+            e.wait()
+            us[phase] = float(np.min(e.phase_times_ms()[:20])) * 1e3
+    finally:
+        e.shutdown()
+    print("one token: gate/up %.1f us, down %.1f us" % (us[18], us[19]))
+    assert us[18] < 34 and us[19] < 22
