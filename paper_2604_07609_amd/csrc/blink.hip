@@ -128,6 +128,34 @@ __global__ void k_clock_probe(HostMirror* m) {
   __hip_atomic_store(&m->clock_probe, dev_now_ns(), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// One request into its ring slot (the frontend's write of section 4.4): payload first, then, behind a system-scope fence, the state
+// word. Reads the staged descriptor and prompt from pinned host memory (16 bytes a load, four of them in flight per thread: the time of the
+// call is that of the reads over the bus); one workgroup.
+__global__ void __launch_bounds__(BLK_THREADS) k_ring_write(const SlotDesc* desc_in, const i32* prompt_in, u32 n_prompt, SlotStatus st, SlotDesc* desc, i32* prompt,
+                                                            SlotStatus* status) {
+  const u32 quads = (n_prompt + 3) / 4;                            // (the staging buffer is padded to whole ones; a slot's prompt is not)
+  for (u32 i0 = threadIdx.x; i0 < quads; i0 += 4 * BLK_THREADS) {
+    int4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = ((const int4*)prompt_in)[min(i0 + u * BLK_THREADS, quads - 1)];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const u32 t = 4 * (i0 + u * BLK_THREADS);
+      if (t < n_prompt) prompt[t] = v[u].x;
+      if (t + 1 < n_prompt) prompt[t + 1] = v[u].y;
+      if (t + 2 < n_prompt) prompt[t + 2] = v[u].z;
+      if (t + 3 < n_prompt) prompt[t + 3] = v[u].w;
+    }
+  }
+  if (threadIdx.x < sizeof(SlotDesc) / 4) ((u32*)desc)[threadIdx.x] = ((const u32*)desc_in)[threadIdx.x];
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    status->gen_count = st.gen_count; status->ticket_lo = st.ticket_lo; status->flags = st.flags;
+    __hip_atomic_store(&status->state, st.state, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
+
 // The token reader's fetch (section 4.4): the new records of every picked slot into one pinned array, a workgroup per slot; a slot
 // whose last record this is goes back to EMPTY behind them.
 struct OutPick { u32 slot, from, n, at, completed, pad[3]; };
@@ -308,7 +336,7 @@ static int init_impl(const blink_config* cfg, blink_engine* e) {
   if (int rc = halloc(e, &e->hctrl, 1)) return rc;
   if (int rc = halloc(e, &e->hmirror, 1)) return rc;
   c.hctrl = e->hctrl; c.hmirror = e->hmirror;
-  if (int rc = halloc(e, &e->stage_in, sizeof(SlotDesc) + sizeof(SlotStatus) + (u64)c.max_seq_len * 4)) return rc;
+  if (int rc = halloc(e, &e->stage_in, sizeof(SlotDesc) + sizeof(SlotStatus) + ((u64)c.max_seq_len + 3) / 4 * 16)) return rc;
   if (int rc = halloc(e, &e->stage_status, c.ring_slots)) return rc;
   e->stage_out_cap = 1u << 16;
   if (int rc = halloc(e, &e->stage_out, e->stage_out_cap)) return rc;
@@ -665,15 +693,14 @@ extern "C" int blink_submit(blink_engine* e, const int32_t* prompt, uint32_t n_p
   d->top_p = sp->top_p; d->seed = sp->seed;
   memcpy(ptoks, prompt, (u64)n_prompt * 4);
   st->state = BLINK_SLOT_PREFILL_PENDING; st->gen_count = 0; st->ticket_lo = (u32)t; st->flags = 0;
-  // Three copies in stream order (the state word is not written before the payload is there) and one wait: 23 us a call on an idle
-  // engine, 28 with a prompt of 4000 tokens. (One small kernel that reads all three from pinned memory: 20 and 44. A wait
-  // of its own for the payload: 33 and 38.)
-  HIPCHK(hipMemcpyAsync(c.in_arena + (u64)slot * c.max_seq_len, ptoks, (u64)n_prompt * 4, hipMemcpyHostToDevice, e->s_in));
-  HIPCHK(hipMemcpyAsync(c.desc + slot, d, sizeof *d, hipMemcpyHostToDevice, e->s_in));
   e->slot_ticket[slot] = t;
   e->delivered[slot] = 0;
   e->shadow_state[slot].store(1, std::memory_order_release);
-  HIPCHK(hipMemcpyAsync(c.status + slot, st, sizeof *st, hipMemcpyHostToDevice, e->s_in));
+  // one small kernel and one wait: 20 us a call on an idle engine, 26 with a prompt of 4000 tokens (read 4 bytes a load: 44), 30 beside
+  // prefill iterations of 8000 tokens (three copies and one wait: 23 / 28 / 37; and a second wait: 33 / 38)
+  const hipError_t launched = launch(k_ring_write, 1, BLK_THREADS, e->s_in, d, ptoks, n_prompt, *st, c.desc + slot, c.in_arena + (u64)slot * c.max_seq_len, c.status + slot);
+  if (launched != hipSuccess) e->shadow_state[slot].store(0, std::memory_order_release);
+  HIPCHK(launched);
   HIPCHK(hipStreamSynchronize(e->s_in));
   e->next_ticket = t + 1;
   if (request_id_out) *request_id_out = t;
