@@ -208,26 +208,27 @@ __device__ __forceinline__ void gemm_dma_dense(const MfmaGemmArgs& a, DmaShared&
 // ---- choice of the workgroup tile -----------------------------------------------------------------------------------
 // Time of a launch with tiles of one shape, in microseconds (without the launch itself), from the number of rounds of workgroups: a
 // k-step takes `lone` while few compute units are busy and `full` with all of them (shared L2s and the clock under load), and an
-// item `fixed` for its first operands, its norm scales and its epilogue. The epilogue differs by what follows the GEMM, and with
-// one workgroup per compute unit nothing runs beside it: of a 256 x 256 tile on 4096 k (128 k-steps) the rotary embedding and KV
-// write make 187 us, the residual add 145, the gate 108. So the constants are fitted per kind of epilogue, to launches with every shape forced
-// of 2 to 7 matrices each (1024 to 28672 rows, k 1024 to 14336, weights from HBM) at 65 to 8000 tokens; the fits are within 4 to 11 % (rms) of
-// them, and the shape they choose is within 3 % of the fastest one (5 % at sizes between those fitted). (One set for all epilogues, within 15 % for down and gate/up, took
-// 256 x 256 tiles where 256 x 128 are faster: QKV 6144 x 4096 at 8000 tokens 561 us instead of 464, 5120 x 2048 347 instead of 228, 2048 x 4096 at 6000
-// tokens 147 instead of 117.)
-__device__ __forceinline__ float dma_cost(u32 total, u32 K, float lone, float full, float fixed, u32 ncu) {
+// item's first operands, norm scales and epilogue take `fixed` alone and `fixed_full` with all of them at it. With one workgroup per
+// compute unit nothing runs beside an epilogue, and what it costs depends on what follows the GEMM: a 256 x 256 tile on 128 k-steps
+// takes 187 us with the rotary embedding and KV write, 150 with the residual add, 108 with the gate. So the constants are
+// fitted per kind of epilogue, to launches with every shape forced of 2 to 6 matrices each (1024 to 28672 rows, k 1024 to 14336, weights from HBM)
+// at 65 to 8000 tokens. The fits are within 5 to 11 % (rms) of them, and the shape they choose takes at most 6 % more than the best.
+// (One set for all epilogues took 256 x 256 tiles where 256 x 128 are faster: QKV 6144 x 4096 at 8000 tokens 561 us instead of 464,
+// 5120 x 2048 347 instead of 228, 2048 x 4096 at 6000 tokens 147 instead of 117.)
+__device__ __forceinline__ float dma_cost(u32 total, u32 K, float lone, float full, float fixed, float fixed_full, u32 ncu) {
   const u32 rounds = total / ncu, rest = total % ncu;
   const float f = (float)rest / (float)ncu, kt = (float)(K / 32);
-  return (float)rounds * (kt * full + fixed) + (rest ? kt * (lone + (full - lone) * f * f * f * f) + fixed : 0.f);
+  return (float)rounds * (kt * full + fixed_full) +
+         (rest ? kt * (lone + (full - lone) * f * f * f * f) + fixed + (fixed_full - fixed) * f * f : 0.f);
 }
 
 // The shapes: number, rows x tokens of the workgroup tile, constants.
-#define DMA_SHAPES_STORE(X) X(1, 64, 64, .193f, .116f, 1.7f) X(2, 128, 64, .287f, .194f, 1.4f) X(3, 128, 128, .285f, .261f, 4.f) \
-                            X(4, 256, 128, .455f, .419f, 5.6f) X(6, 256, 192, .518f, .591f, 8.8f) X(7, 256, 256, .576f, .735f, 13.7f)
-#define DMA_SHAPES_RESIDUAL(X) X(1, 64, 64, .124f, .110f, 2.2f) X(2, 128, 64, .196f, .192f, 2.8f) X(3, 128, 128, .223f, .270f, 5.9f) \
-                               X(4, 256, 128, .356f, .449f, 11.2f) X(6, 256, 192, .430f, .688f, 17.f) X(7, 256, 256, .532f, .960f, 29.1f)
-#define DMA_SHAPES_ROPE(X) X(1, 64, 64, .363f, .255f, .7f) X(2, 128, 64, .258f, .204f, 4.3f) X(3, 128, 128, .303f, .309f, 8.4f) \
-                           X(4, 256, 128, .419f, .474f, 14.3f) X(6, 256, 192, .532f, .740f, 24.8f) X(7, 256, 256, .629f, 1.082f, 53.7f)
+#define DMA_SHAPES_STORE(X) X(1, 64, 64, .117f, .111f, 5.7f, 1.9f) X(2, 128, 64, .193f, .192f, 3.7f, 1.2f) X(3, 128, 128, .222f, .255f, 4.9f, 3.7f) \
+                            X(4, 256, 128, .361f, .390f, 5.8f, 7.6f) X(6, 256, 192, .430f, .558f, 11.5f, 11.3f) X(7, 256, 256, .533f, .671f, 14.3f, 17.9f)
+#define DMA_SHAPES_RESIDUAL(X) X(1, 64, 64, .117f, .111f, 2.5f, 1.9f) X(2, 128, 64, .193f, .192f, 2.5f, 2.1f) X(3, 128, 128, .222f, .255f, 4.8f, 7.6f) \
+                               X(4, 256, 128, .361f, .390f, 9.3f, 20.5f) X(6, 256, 192, .430f, .558f, 14.9f, 39.1f) X(7, 256, 256, .533f, .671f, 26.6f, 75.7f)
+#define DMA_SHAPES_ROPE(X) X(1, 64, 64, .363f, .255f, .7f, .7f) X(2, 128, 64, .258f, .204f, 4.3f, 4.3f) X(3, 128, 128, .303f, .309f, 8.4f, 8.4f) \
+                           X(4, 256, 128, .419f, .474f, 14.3f, 14.3f) X(6, 256, 192, .532f, .740f, 24.8f, 24.8f) X(7, 256, 256, .629f, 1.082f, 53.7f, 53.7f)
 
 // T > 64 tokens. (Bits 12-14 of the tuning word force a shape by its number.)
 template <int EPI>
@@ -235,8 +236,8 @@ __device__ __forceinline__ void gemm_dma_pick(const MfmaGemmArgs& a, DmaShared& 
   u32 best = (a.tune_nw >> 12) & 7u;
   if (best == 0 || best == 5) {
     float least = INFINITY;
-#define OFFER(id, bn, bt, lone, full, fixed) \
-    { const float t = dma_cost(DenseItems(a, bn, bt).total, a.K, lone, full, fixed, nwg); if (t < least) { least = t; best = id; } }
+#define OFFER(id, bn, bt, lone, full, fixed, fixed_full) \
+    { const float t = dma_cost(DenseItems(a, bn, bt).total, a.K, lone, full, fixed, fixed_full, nwg); if (t < least) { least = t; best = id; } }
     if (EPI == EPI_QKV_ROPE) { DMA_SHAPES_ROPE(OFFER) }
     else if (EPI == EPI_RESIDUAL) { DMA_SHAPES_RESIDUAL(OFFER) }
     else { DMA_SHAPES_STORE(OFFER) }

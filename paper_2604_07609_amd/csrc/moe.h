@@ -92,9 +92,9 @@ __device__ __forceinline__ void moe_split(const DevCtx& c, MoeShared& sh, u32 N,
     u32 best = (c.tune_nw >> 12) & 7u, width = 0, bt_of_best = 256;
     const bool forced = best != 0 && best != 5;
     float least = INFINITY;
-#define OFFER(id, bn, bt, lone, full, fixed) {                                                                             \
+#define OFFER(id, bn, bt, lone, full, fixed, fixed_full) {                                                                 \
       width = bt == 64 ? b64 : bt == 128 ? b128 : bt == 192 ? b192 : b256;                                                 \
-      const float t = dma_cost((N + bn - 1) / bn * width, K, lone, full, fixed, nwg);                                      \
+      const float t = dma_cost((N + bn - 1) / bn * width, K, lone, full, fixed, fixed_full, nwg);                          \
       if (forced ? best == id : t < least) { least = t; best = id; bt_of_best = bt; } }
     DMA_SHAPES_STORE(OFFER)
 #undef OFFER

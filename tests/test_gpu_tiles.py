@@ -110,14 +110,14 @@ def wide_engine(lib, tune=0):
 
 
 def test_the_tile_shape_chosen_is_about_the_fastest(lib):
-    """QKV (6144 x 4096) and the attention output projection (4096 x 4096) at 100 to 8000 tokens with every shape forced and with the
+    """QKV (6144 x 4096), the attention output projection (4096 x 4096) and down (4096 x 14336) at 100 to 8000 tokens with every shape forced and with the
     automatic choice, which may cost an eighth more than the best of them (with one set of constants for all epilogues
     it took 51 us against 39 for QKV at 100 tokens, 561 against 464 at 8000)."""
     us = {}
     for shape in (0, 1, 2, 3, 4, 6, 7):
         e = wide_engine(lib, tune=shape << 12)
         try:
-            for phase in (2, 5):
+            for phase in (2, 5, 8):
                 e.time_phase(phase)
                 for tokens in (100, 300, 1000, 2048, 4000, 8000):
                     best = np.inf
