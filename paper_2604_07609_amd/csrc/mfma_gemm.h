@@ -264,8 +264,8 @@ __device__ __forceinline__ void residual_finish(const MfmaGemmArgs& a, floatx4_t
 }
 
 // Epilogue of the TJ accumulator tiles a wave holds for one row tile (tokens t_base + 16 j + lane % 16). The epilogues that
-// read memory (the residual stream, the positions and the rotary table) request the operands of four tiles first and
-// then compute and store tile by tile: written one tile after the other, every tile's loads would wait behind the
+// read memory (the residual stream, the positions and the rotary table) request the operands of four tiles (two, where a wave has
+// six or eight) first and then compute and store tile by tile: written one tile after the other, every tile's loads would wait behind the
 // previous tile's stores (the compiler has to assume that they may alias), a chain of TJ memory latencies per row tile.
 // Tokens behind the last one read the last token's operands (an unconditional load) and store nothing.
 // (Bit 6 of the tuning word: tile by tile, for comparison.)
@@ -276,8 +276,12 @@ __device__ __forceinline__ void epilogue_row(const MfmaGemmArgs& a, const floatx
     for (int j = 0; j < TJ; ++j) epilogue_tile<EPI>(a, acc[j], nt, t_base + j * 16, rstd + j * 16);
     return;
   }
-  constexpr int H = TJ > 4 ? TJ / 2 : TJ;      // tiles whose operands are requested together
-  const u32 lane = threadIdx.x & 63;
+  constexpr int H = TJ > 4 ? 2 : TJ;           // tiles whose operands are requested together
+  // The lane comes anew for every row tile (an empty asm): else the offsets of all token tiles are kept from the first row tile to the
+  // last, and beside 128 accumulators and the next item's operands they end in scratch memory, whose loads wait behind every
+  // store: 4096 x 14336 at 8000 tokens 771 us instead of 753.
+  u32 lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));
   const u32 n0 = nt * 16 + (lane >> 4) * 4;
   const u32 hd = a.hd, half = hd / 2, head = EPI == EPI_QKV_ROPE ? n0 / hd : 0u, p = EPI == EPI_QKV_ROPE ? (n0 % hd) >> 1 : 0u;   // rows: (p, p+half, p+1, p+1+half)
   const bool rot = head < a.nq + a.nkv;
