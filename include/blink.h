@@ -124,7 +124,7 @@ typedef struct {
                                   is admitted by that same kernel */
   uint32_t pump_depth;         /* iterations the launcher thread keeps enqueued ahead of the device (0: 8; at most 1024) */
   uint32_t tune;               /* tests and tuning: forces variants of the GEMM and attention kernels (0: automatic
-                                  choice; the bits are listed in csrc/mfma_gemm.h) */
+                                  choice; the bits are listed in csrc/mfma_gemm.h, others are ignored) */
   /* mixture-of-experts FFN (the second model of the paper's evaluation, section 6, is of this kind); bf16 models only */
   uint32_t n_experts;          /* 0: dense FFN. E > 0 (at most 256): every layer has a router wr[E][d] and E experts of
                                   width d_ffn; the blob then holds, in place of wg wu wd: wr[E][d] wg[E][F][d] wu[E][F][d]

@@ -714,7 +714,6 @@ extern "C" int blink_submit(blink_engine* e, const int32_t* prompt, uint32_t n_p
 static bool phase_per_layer(int ph) { return (ph >= PH_LAYER_FIRST && ph <= PH_LAYER_LAST) || ph >= PH_ATTN_COMBINE; }
 
 static int launch_phase(blink_engine* e, const DevCtx& ctx, hipStream_t st, int ph, u32 layer, u64 enq_index) {
-  if (ph == PH_NORM1 || ph == PH_NORM2 || ph == PH_FINAL_NORM || ph == PH_ROPE) return 0;   // fused into the GEMMs
   const bool timed = e->timed_phase == ph && enq_index != ~0ull;
   hipEvent_t a = nullptr, b = nullptr;
   if (timed) {
@@ -744,20 +743,15 @@ static int enqueue_iteration_kernels(blink_engine* e, hipStream_t st, u64 enq_in
   if (c.spec_k) HIPCHK(launch(k_spec_draft, (c.max_batch + 3) / 4, BLK_THREADS, st, c));
   HIPCHK(launch(k_sched, 1, BLK_THREADS, st, c));
   if (int rc = launch_phase(e, c, st, PH_EMBED, 0, enq_index)) return rc;
+  // the phases of a layer; the norms and the rotary step have no kernels of their own
+  static const int dense[] = {PH_QKV, PH_ATTN, PH_ATTN_COMBINE, PH_OPROJ, PH_GATEUP, PH_DOWN};
+  static const int experts[] = {PH_QKV, PH_ATTN, PH_ATTN_COMBINE, PH_OPROJ, PH_ROUTER, PH_ROUTE, PH_MOE_PERMUTE, PH_MOE_GATEUP, PH_MOE_DOWN, PH_MOE_COMBINE};
+  const int *const chain = c.n_experts ? experts : dense, n = (int)(c.n_experts ? sizeof experts : sizeof dense) / (int)sizeof(int);
   for (u32 l = 0; l < c.n_layers; ++l)
-    for (int ph = PH_LAYER_FIRST; ph <= PH_LAYER_LAST; ++ph) {
-      if (c.n_experts && (ph == PH_GATEUP || ph == PH_DOWN)) {    // mixture of experts: six kernels in place of the two
-        if (ph == PH_DOWN) continue;
-        static const int moe_chain[] = {PH_ROUTER, PH_ROUTE, PH_MOE_PERMUTE, PH_MOE_GATEUP, PH_MOE_DOWN, PH_MOE_COMBINE};
-        for (int mp : moe_chain)
-          if (int rc = launch_phase(e, c, st, mp, l, enq_index)) return rc;
-        continue;
-      }
-      if (int rc = launch_phase(e, c, st, ph, l, enq_index)) return rc;
-      if (c.dtype == 1 && ph == PH_ATTN && !whole_chain)
-        if (int rc = launch_phase(e, c, st, PH_ATTN_COMBINE, l, enq_index)) return rc;
+    for (int i = 0; i < n; ++i) {
+      if (chain[i] == PH_ATTN_COMBINE && (c.dtype == 0 || whole_chain)) continue;
+      if (int rc = launch_phase(e, c, st, chain[i], l, enq_index)) return rc;
     }
-  if (int rc = launch_phase(e, c, st, PH_FINAL_NORM, 0, enq_index)) return rc;
   if (int rc = launch_phase(e, c, st, PH_LM_HEAD, 0, enq_index)) return rc;
   return launch_phase(e, c, st, PH_SAMPLE, 0, enq_index);
 }

@@ -320,12 +320,6 @@ struct DevCtx {
 
 __device__ __forceinline__ u64 dev_now_ns() { return wall_clock64() * 10ull; }  // 100 MHz constant clock
 
-__device__ __forceinline__ float bf16_to_f32(bf16_t b) { return __uint_as_float(((u32)b) << 16); }
-__device__ __forceinline__ bf16_t f32_to_bf16(float f) {  // round to nearest even; inputs are finite
-  u32 u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (bf16_t)(u >> 16);
-}
 // two floats to half precision (round to nearest even), saturating at the largest finite half; low half = a
 __device__ __forceinline__ u32 pack_f16x2(float a, float b) {
   typedef _Float16 half2_t __attribute__((ext_vector_type(2)));

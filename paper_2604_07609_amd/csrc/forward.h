@@ -12,10 +12,8 @@ template <> struct WLoad<float> {
     const float4 a = *(const float4*)p, b = *(const float4*)(p + 4);
     o[0] = a.x; o[1] = a.y; o[2] = a.z; o[3] = a.w; o[4] = b.x; o[5] = b.y; o[6] = b.z; o[7] = b.w;
   }
-  static __device__ __forceinline__ void put(float* p, u64 i, float v) { p[i] = v; }
 };
 template <> struct WLoad<bf16_t> {
-  static __device__ __forceinline__ float get(const bf16_t* p, u64 i) { return bf16_to_f32(p[i]); }
   static __device__ __forceinline__ void load8(const bf16_t* p, float* o) {
     const uint4 a = *(const uint4*)p;
     const u32 w[4] = {a.x, a.y, a.z, a.w};
@@ -25,7 +23,6 @@ template <> struct WLoad<bf16_t> {
       o[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
     }
   }
-  static __device__ __forceinline__ void put(bf16_t* p, u64 i, float v) { p[i] = f32_to_bf16(v); }
 };
 
 __device__ __forceinline__ float wave_sum(float v) {
@@ -113,7 +110,7 @@ struct AttnShared {
   float accred[4][ATT_MAX_G][64];
 };
 
-template <typename WT, bool PACKED_OUT>
+template <typename WT>
 __device__ __forceinline__ void phase_attention(const DevCtx& c, u32 layer, AttnShared& sh, u32 wg, u32 nwg) {
   const u32 T = c.meta->n_tokens, hd = c.hd, G = c.nq / c.nkv, tid = threadIdx.x;
   const WT* Kc = (const WT*)c.kv + (u64)layer * c.kv_layer_stride;
@@ -190,8 +187,7 @@ __device__ __forceinline__ void phase_attention(const DevCtx& c, u32 layer, Attn
           if ((u32)h < G) {
             float a = 0.f;
             for (u32 pp = 0; pp < nparts; ++pp) a += sh.accred[pp][h][slot64];
-            if (PACKED_OUT) c.aq[packed_act_off(t, (g * G + h) * hd + dd, c.TBS)] = f32_to_f16(a / l[h]);
-            else c.attn[(u64)t * (c.nq * hd) + (u64)(g * G + h) * hd + dd] = a / l[h];
+            c.attn[(u64)t * (c.nq * hd) + (u64)(g * G + h) * hd + dd] = a / l[h];
           }
       }
     }

@@ -15,7 +15,7 @@
 // The k dimension of both is padded with zeros to a multiple of 64 (an even number of k-steps).
 //
 // out[t][n] = sum_k X[t][k] * W[n][k]. Every GEMM kernel runs eight waves per workgroup and one workgroup per compute unit. The
-// schedule is chosen per launch from the token count T of the iteration and the shape of the matrix (gemm_dma.h: gemm_eight):
+// schedule is chosen per launch from the token count T of the iteration and the shape of the matrix (gemm_dma.h: gemm_bf16):
 //   tiles whose operands go from memory straight to LDS (gemm_dma.h): T > 64, and tall matrices at any T.
 //   stream (T <= 64 otherwise, decode at small batch): a workgroup owns 1 or 2 16-row weight tiles and all token blocks; its
 //     eight waves split K and keep two batches of 1 KB operand loads in flight each; weight loads are non-temporal;
