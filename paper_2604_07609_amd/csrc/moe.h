@@ -36,8 +36,7 @@ __device__ __forceinline__ u32 moe_wave_rows(u32 n_tokens) { return n_tokens <= 
 
 // counts -> LDS and the offsets, by the first wave: four experts per lane, a prefix sum over the lanes. Every workgroup of the
 // grouped kernels does this before anything else, so it is latency on the path of four kernels per layer: with one
-// thread walking the experts (128 of them, 96 decoding sequences) a gate/up launch took 152 us rather than 147, down 88 rather than 76,
-// permute 12 rather than 10, combine 10 rather than 8.
+// thread walking the experts (128 of them, 96 decoding sequences) a gate/up launch takes 5 us more, down 12, permute and combine 2.
 __device__ __forceinline__ u32 wave_scan(u32 v) {    // inclusive
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) { const u32 x = __shfl_up(v, o); if ((threadIdx.x & 63) >= (u32)o) v += x; }
@@ -289,7 +288,7 @@ __device__ __forceinline__ void moe_wave_item(const DevCtx& c, const LayerWP* P,
 // Experts with more tokens: one stream of workgroup tiles (gemm_dma) over the tiles of all of them, expert by expert, so that a
 // workgroup fetches the first operands of an expert's tile while it stores the previous expert's, and all tiles go round
 // the grid evenly. (One GEMM after the other, staged through registers, 2100 tokens on 128 experts of width 768: gate/up
-// 558 us, down 404 us per layer; now 191 and 132.)
+// 558 us, down 404 us per layer; now 187 and 133.)
 template <bool GATEUP>
 struct MoeItems {
   const MoeShared& sh;
