@@ -657,7 +657,7 @@ __device__ void sched_step(const DevCtx& c, SchedShared& sh) {
   const bool group = c.chunk_rec && !(c.tune_nw & 0x808000u) && ((c.tune_nw & 0x400000u) || (u64)nrun * c.nkv >= WHOLE_CONTEXT_PAIRS_PER_CU * (u64)c.n_cu);
   const u32 spec_k = (c.flags & 256u) ? c.spec_k : 0u;
   u64 n_ctx = 0;
-  u32 n_multi = 0, n_items = 0;     // sequences that attend like a prompt chunk, their items in the attention with shared KV tiles
+  u32 n_prompts = 0, n_items = 0;   // sequences that process prompt tokens, their items in the attention with shared KV tiles (bf16 models)
   if (kind != KIND_IDLE) {
     for (u32 base = 0; base < c.max_batch; base += BLK_THREADS) {
       const u32 b = base + tid;
@@ -767,12 +767,6 @@ __device__ void sched_step(const DevCtx& c, SchedShared& sh) {
       max_ctx = max(max_ctx, block_max(ctx_after, sh.wave_part));
       max_pref = max(max_pref, block_max(multi ? ctx_after : 0u, sh.wave_part2));
       n_ctx += totx;
-      if (totq && c.chunk_rec) {
-        const u32 per_item = prompt_tiles_per_item(c.nq / c.nkv);
-        u32 o0, o1, ti, tm;
-        block_excl_scan2(multi ? ((ntok + 15) / 16 + per_item - 1) / per_item : 0u, multi ? 1u : 0u, o0, o1, ti, tm, sh.part64);
-        n_items += ti; n_multi += tm;
-      }
       n_seqs += tots;
       n_alloc += tota;
       n_tok += tott;
@@ -827,6 +821,17 @@ __device__ void sched_step(const DevCtx& c, SchedShared& sh) {
         sh.seq_P[s] = c.run[b].P;
       }
       __syncthreads();
+      if (c.chunk_rec) {
+        const u32 per_item = prompt_tiles_per_item(c.nq / c.nkv);
+        u32 items = 0, prompts = 0, o0, o1;
+        for (u32 s = tid; s < n_seqs; s += BLK_THREADS) {
+          if (sh.seq_ring[s] == ~0u) continue;
+          const u32 len = (s + 1 < n_seqs ? sh.seq_tok0[s + 1] : n_tok) - sh.seq_tok0[s];
+          items += ((len + 15) / 16 + per_item - 1) / per_item;
+          prompts += 1;
+        }
+        block_excl_scan2(items, prompts, o0, o1, n_items, n_prompts, sh.part64);
+      }
       for (u32 base = 0; base < n_tok; base += 4 * BLK_THREADS) {
         u32 sq[4], pp[4], blk[4];
         i32 id[4];
@@ -924,7 +929,7 @@ __device__ void sched_step(const DevCtx& c, SchedShared& sh) {
     m->max_pref_ctx = max_pref;
     const u32 kernel_bits = (c.tune_nw >> 16) & 15u;      // 15 forces the shared tiles, other values the other kernel (tests)
     m->prompt_shared = n_items == 0 ? 0u : kernel_bits ? kernel_bits == 15u : max_q >= 32 &&
-        prompt_shared_pays(n_qt, n_multi, n_items, max_pref, n_seqs - n_multi, c.nkv, c.nq / c.nkv, c.hd, c.n_cu);
+        prompt_shared_pays(n_qt, n_prompts, n_items, max_pref, n_seqs - n_prompts, c.nkv, c.nq / c.nkv, c.hd, c.n_cu);
     u32 stopped = 0;
     if (kind != KIND_IDLE) {
       const u64 it = ss->iteration;
