@@ -16,7 +16,7 @@
 // 1.5 ms). With all 512 registers of a SIMD's lanes between the two, nothing else fits on the chip meanwhile, and the small
 // kernels and copies of blink_submit and blink_poll_outputs wait for the end of the launch. So 240 registers per wave at
 // most (the attribute counts half of gfx950's unified file): 32 are left, what those need. Beside prefill iterations of
-// 8000 tokens (32 q / 8 kv heads of 128, d 4096, FFN 14336) a submit takes 33 us instead of 536 and a poll 25 instead of 549, on
+// 8000 tokens (32 q / 8 kv heads of 128, d 4096, FFN 14336) a submit takes 30 us instead of 536 and a poll 25 instead of 549, on
 // average; prefill and decode iterations take what they took with 256.
 #define PHASE_KERNEL8(name, PH) \
   __global__ void __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(120))) name(DevCtx c, u32 layer) PHASE_KERNEL_BODY(PH, false)
