@@ -549,7 +549,7 @@ static int init_impl(const blink_config* cfg, blink_engine* e) {
       if (int rc = dalloc(e, &c.moe_rstd, c.maxT)) return rc;
     } else if (int rc = dalloc(e, &c.hq, tile_tokens * k_pad(c.F))) return rc;
     if (int rc = dalloc(e, &c.ssq, tile_tokens * (c.d / 16))) return rc;
-    if (int rc = dalloc(e, &c.qbuf, (u64)c.maxT * c.nq * c.hd)) return rc;
+    if (int rc = dalloc(e, &c.qbuf, ((u64)c.maxT + 16) * c.nq * c.hd)) return rc;   // (and x: 16 rows for the tokens that fill up a tile)
     {
       c.chunk_cap = c.max_batch * ((c.max_seq_len + ATTN_CHUNK_TOKENS - 1) / ATTN_CHUNK_TOKENS);
       if (int rc = dalloc(e, &c.chunk_rec, 2ull * c.chunk_cap)) return rc;
@@ -571,7 +571,7 @@ static int init_impl(const blink_config* cfg, blink_engine* e) {
   if (int rc = dalloc(e, &kv, e->kv_bytes, true)) return rc;   // zeroed: masked keys multiply cached values by 0
   c.kv = kv;
   // ---- activations ----
-  if (int rc = dalloc(e, &c.x, (u64)c.maxT * c.d)) return rc;
+  if (int rc = dalloc(e, &c.x, ((u64)c.maxT + 16) * c.d)) return rc;
   if (c.dtype == 0) {
     if (int rc = dalloc(e, &c.qkv, (u64)c.maxT * c.qkv_n)) return rc;
     if (int rc = dalloc(e, &c.attn, (u64)c.maxT * c.nq * c.hd)) return rc;

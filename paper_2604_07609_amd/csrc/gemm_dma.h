@@ -171,10 +171,14 @@ __device__ __forceinline__ void gemm_dma(MfmaGemmArgs a, const Items& items, Dma
     fetch_next();
     at = nat;
   };
+  u32 scaled = 0;                                // the block of tokens whose norm scales are in LDS
   for (u32 it = 0; it < n_items; ++it) {
     u32 nb, tb;
     items.at(item_of(it), a, nb, tb);
-    compute_rstd(a, tb * BT, BT, sh.rstd);       // (before the accumulators: it needs registers)
+    // the norm scales of the tokens (before the accumulators: it needs registers). The rounds of a workgroup mostly have the
+    // same tokens (tile_coords), and reading their partial sums anew takes 3 us an item
+    if (it == 0 || (a.ssq_in && tb != scaled)) compute_rstd<BT, 512>(a, tb * BT, sh.rstd);
+    scaled = tb;
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -185,10 +189,20 @@ __device__ __forceinline__ void gemm_dma(MfmaGemmArgs a, const Items& items, Dma
       step(wb, wa, std::integral_constant<bool, true>());
       if (KS == 1) fetch_pair_done();
     }
+    if constexpr (MI == 4 && EPI != EPI_SCALED_STORE) {
+      if (nb * NTW + wn * MI < NT) epilogue_cols<EPI, MJ>(a, acc, nb * NTW + wn * MI, tb * BT + wt * MJ * 16, sh.rstd + wt * MJ * 16);
+      // the next item's first operands, which the last k-step has read already, once more: the epilogue needs their registers
+      // (their k-step stays in its slot: nothing is fetched between two items)
 #pragma unroll
-    for (int i = 0; i < MI; ++i) {
-      const u32 nt = nb * NTW + wn * MI + i;
-      if (nt < NT) epilogue_row<EPI, MJ>(a, acc[i], nt, tb * BT + wt * MJ * 16, sh.rstd + wt * MJ * 16);
+      for (int i = 0; i < MI; ++i) wa[i] = as_f16x8(*(const uint4*)(Lw + at + i * 1024));
+#pragma unroll
+      for (int j = 0; j < MJ; ++j) x[j] = as_f16x8(*(const uint4*)(Lx + at + j * 1024));
+    } else {
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        const u32 nt = nb * NTW + wn * MI + i;
+        if (nt < NT) epilogue_row<EPI, MJ>(a, acc[i], nt, tb * BT + wt * MJ * 16, sh.rstd + wt * MJ * 16);
+      }
     }
   }
   wait_dma_barrier<0>();                         // no fetch may still be on its way when the workgroup's LDS is given to another
@@ -210,11 +224,10 @@ __device__ __forceinline__ void gemm_dma_dense(const MfmaGemmArgs& a, DmaShared&
 // k-step takes `lone` while few compute units are busy and `full` with all of them (shared L2s and the clock under load), and an
 // item's first operands, norm scales and epilogue take `fixed` alone and `fixed_full` with all of them at it. With one workgroup per
 // compute unit nothing runs beside an epilogue, and what it costs depends on what follows the GEMM: a 256 x 256 tile on 128 k-steps
-// takes 187 us with the rotary embedding and KV write, 150 with the residual add, 108 with the gate. So the constants are
-// fitted per kind of epilogue, to launches with every shape forced of 2 to 6 matrices each (1024 to 28672 rows, k 1024 to 14336, weights from HBM)
-// at 65 to 8000 tokens. The fits are within 5 to 11 % (rms) of them, and the shape they choose takes at most 6 % more than the best.
-// (One set for all epilogues took 256 x 256 tiles where 256 x 128 are faster: QKV 6144 x 4096 at 8000 tokens 561 us instead of 464,
-// 5120 x 2048 347 instead of 228, 2048 x 4096 at 6000 tokens 147 instead of 117.)
+// takes 108 us with the rotary embedding and KV write, 131 with the residual add, 98 with the gate. So the epilogues have
+// constants of their own, fitted to launches with every shape forced of 1 to 6 matrices each (1024 to 28672 rows, k 1024 to 14336, weights
+// from HBM) at 65 to 8000 tokens. The fits are within 5 to 13 % (rms) of them, and the shape they choose takes at most 5 % more
+// than the best, 0.1 % on average.
 __device__ __forceinline__ float dma_cost(u32 total, u32 K, float lone, float full, float fixed, float fixed_full, u32 ncu) {
   const u32 rounds = total / ncu, rest = total % ncu;
   const float f = (float)rest / (float)ncu, kt = (float)(K / 32);
@@ -222,13 +235,10 @@ __device__ __forceinline__ float dma_cost(u32 total, u32 K, float lone, float fu
          (rest ? kt * (lone + (full - lone) * f * f * f * f) + fixed + (fixed_full - fixed) * f * f : 0.f);
 }
 
-// The shapes: number, rows x tokens of the workgroup tile, constants.
-#define DMA_SHAPES_STORE(X) X(1, 64, 64, .117f, .111f, 5.7f, 1.9f) X(2, 128, 64, .193f, .192f, 3.7f, 1.2f) X(3, 128, 128, .222f, .255f, 4.9f, 3.7f) \
-                            X(4, 256, 128, .361f, .390f, 5.8f, 7.6f) X(6, 256, 192, .430f, .558f, 11.5f, 11.3f) X(7, 256, 256, .533f, .671f, 14.3f, 17.9f)
-#define DMA_SHAPES_RESIDUAL(X) X(1, 64, 64, .117f, .111f, 2.5f, 1.9f) X(2, 128, 64, .193f, .192f, 2.5f, 2.1f) X(3, 128, 128, .222f, .255f, 4.8f, 7.6f) \
-                               X(4, 256, 128, .361f, .390f, 9.3f, 20.5f) X(6, 256, 192, .430f, .558f, 14.9f, 39.1f) X(7, 256, 256, .533f, .671f, 26.6f, 75.7f)
-#define DMA_SHAPES_ROPE(X) X(1, 64, 64, .363f, .255f, .7f, .7f) X(2, 128, 64, .258f, .204f, 4.3f, 4.3f) X(3, 128, 128, .303f, .309f, 8.4f, 8.4f) \
-                           X(4, 256, 128, .419f, .474f, 14.3f, 14.3f) X(6, 256, 192, .532f, .740f, 24.8f, 24.8f) X(7, 256, 256, .629f, 1.082f, 53.7f, 53.7f)
+// The shapes: number, rows x tokens of the workgroup tile, constants of a k-step, then of an item: store or gate, residual add, rotary embedding.
+#define DMA_SHAPES(X) X(1, 64, 64, .123f, .108f, 6.9f, .7f, 2.2f, 2.0f, 5.8f, 2.2f) X(2, 128, 64, .200f, .179f, 3.2f, .6f, 1.7f, 2.4f, 4.5f, 2.1f) \
+                      X(3, 128, 128, .227f, .243f, 3.6f, 1.6f, 2.9f, 5.7f, 6.0f, 3.7f) X(4, 256, 128, .358f, .386f, 5.1f, 4.9f, 7.2f, 15.7f, 8.6f, 8.3f) \
+                      X(6, 256, 192, .419f, .544f, 9.7f, 7.8f, 12.7f, 26.2f, 14.2f, 14.7f) X(7, 256, 256, .513f, .690f, 11.6f, 10.6f, 16.7f, 39.0f, 16.2f, 20.5f)
 
 // T > 64 tokens. (Bits 12-14 of the tuning word force a shape by its number.)
 template <int EPI>
@@ -236,11 +246,11 @@ __device__ __forceinline__ void gemm_dma_pick(const MfmaGemmArgs& a, DmaShared& 
   u32 best = (a.tune_nw >> 12) & 7u;
   if (best == 0 || best == 5) {
     float least = INFINITY;
-#define OFFER(id, bn, bt, lone, full, fixed, fixed_full) \
-    { const float t = dma_cost(DenseItems(a, bn, bt).total, a.K, lone, full, fixed, fixed_full, nwg); if (t < least) { least = t; best = id; } }
-    if (EPI == EPI_QKV_ROPE) { DMA_SHAPES_ROPE(OFFER) }
-    else if (EPI == EPI_RESIDUAL) { DMA_SHAPES_RESIDUAL(OFFER) }
-    else { DMA_SHAPES_STORE(OFFER) }
+#define OFFER(id, bn, bt, lone, full, store, store_full, residual, residual_full, rope, rope_full) \
+    { const float fixed = EPI == EPI_QKV_ROPE ? rope : EPI == EPI_RESIDUAL ? residual : store;                                    \
+      const float fixed_full = EPI == EPI_QKV_ROPE ? rope_full : EPI == EPI_RESIDUAL ? residual_full : store_full;                \
+      const float t = dma_cost(DenseItems(a, bn, bt).total, a.K, lone, full, fixed, fixed_full, nwg); if (t < least) { least = t; best = id; } }
+    DMA_SHAPES(OFFER)
 #undef OFFER
   }
   switch (best) {
@@ -266,12 +276,10 @@ union GemmShared8 { MfmaShared mfma; DmaShared dma; };
 //     where the matrix has few enough of them. A decode iteration's sums are then taken in the order in which they have
 //     been taken all along (K in eight slices): in another order they round otherwise, and tokens with two nearly equal router
 //     logits go to another expert. The tiles would win 1 % of a decode iteration at 96 sequences of the moe_30b_a3b shape.
-//     The same schedule for the QKV projection of any model at up to 128 tokens, where it is the fastest: 6144 x 4096 at
-//     65 / 128 tokens 34 / 34 us against 39 / 45 (128 x 64 tiles) and 51 (64 x 64).
 template <int EPI>
 __device__ __forceinline__ void gemm_bf16(const MfmaGemmArgs& a, GemmShared8& sh, u32 wg, u32 nwg) {
   if (a.T == 0) return;
-  if (a.T > 64 && (a.ordered ? a.T <= 256 : EPI == EPI_QKV_ROPE && a.T <= 128) && !(a.tune_nw & 0x7000u) && ((a.N + 127) / 128) * ((a.T + 127) / 128) * 4 <= nwg) gemm_stream<EPI, 4, 4, 1, true>(a, sh.mfma, wg, nwg);
+  if (a.T > 64 && a.ordered && a.T <= 256 && !(a.tune_nw & 0x7000u) && ((a.N + 127) / 128) * ((a.T + 127) / 128) * 4 <= nwg) gemm_stream<EPI, 4, 4, 1, true>(a, sh.mfma, wg, nwg);
   else if (a.T > 64) gemm_dma_pick<EPI>(a, sh.dma, wg, nwg);
   else if (((a.N + 127) / 128) * 4 >= nwg * 3 && !(a.tune_nw & 0x807u)) {   // (not where bits 0-2 or 11 of the tuning word ask for streaming)
     if (a.T <= 16) gemm_dma_dense<EPI, 8, 1, 1, 2, true>(a, sh.dma, wg, nwg);        // 128 rows x 16 tokens

@@ -95,48 +95,57 @@ __device__ __forceinline__ f16x8_t ld_op(const f16_t* p) {   // one lane's 16 by
   return as_f16x8(*(const uint4*)p);
 }
 
-// rstd (times the inverse of the weight scale) of `count` (<= 256) tokens starting at column t0 into
-// rstd[0 .. count) (LDS). Sixteen lanes share a token:
-// each reads every sixteenth 16-byte piece of the token's partial sums (256 contiguous bytes per token and load), up to
-// sixteen tokens' loads are in flight per lane, and a butterfly over the sixteen lanes finishes the sum.
-__device__ __forceinline__ void compute_rstd(const MfmaGemmArgs& a, u32 t0, u32 count, float* rstd) {
+// rstd (times the inverse of the weight scale) of COUNT (<= 256) tokens starting at column t0 into
+// rstd[0 .. COUNT) (LDS), by a workgroup of THREADS. Sixteen lanes share a token: each reads every sixteenth 16-byte piece of the
+// token's partial sums (256 contiguous bytes per token and load), and a butterfly over the sixteen lanes finishes the sum.
+// A chain of memory latencies in front of a launch's first product (or, beside its first operands, of its first epilogue), so
+// every load is unconditional (clamped) and a batch of them is written out: with the loads behind a run-time count of tokens
+// they came one at a time, 16 to 64 latencies, wherever the compiler was short of registers (QKV 6144 x 4096 of one
+// token 15 us, 509 tokens 58 us).
+template <int COUNT, int THREADS>
+__device__ __forceinline__ void compute_rstd(const MfmaGemmArgs& a, u32 t0, float* rstd) {
+  constexpr int G = THREADS / 16, P = (COUNT + G - 1) / G, U = P > 8 ? 1 : P == 8 ? 2 : 4;   // tokens at a time, passes, pieces per batch
   const u32 tid = threadIdx.x;
   __syncthreads();   // the previous readers of rstd are done
   if (a.ssq_in == nullptr) {
-    if (tid < count) rstd[tid] = W_SCALE_INV;
-  } else if (tid < BLK_THREADS) {   // threads beyond the first 256 (8-wave launches) only join the barriers
+    if (tid < COUNT) rstd[tid] = W_SCALE_INV;
+  } else {
     const u32 np = a.K / 16, l16 = tid & 15, grp = tid >> 4;
-    const float* pp[16];
-    float s[16];
+    const float* pp[P];
+    float s[P];
 #pragma unroll
-    for (int it = 0; it < 16; ++it) {
-      const u32 t = min(t0 + min(grp + 16 * it, count - 1), a.T - 1);   // clamped: results of padding tokens are dropped
+    for (int it = 0; it < P; ++it) {
+      const u32 t = min(t0 + min(grp + G * it, (u32)COUNT - 1), a.T - 1);   // clamped: results of padding tokens are dropped
       pp[it] = a.ssq_in + (u64)(a.tok_index ? a.tok_index[t] : t) * np;
       s[it] = 0.f;
     }
-    const u32 passes = (count + 15) / 16;
     if ((np & 3u) == 0) {
-      for (u32 q = l16 * 4; q < np; q += 64) {
+      for (u32 q0 = 0; q0 < np; q0 += 64 * U) {
+        float4 v[U][P];
 #pragma unroll
-        for (int it = 0; it < 16; ++it)
-          if ((u32)it < passes) {
-            const float4 v = *(const float4*)(pp[it] + q);
-            s[it] += (v.x + v.y) + (v.z + v.w);
-          }
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int it = 0; it < P; ++it) v[u][it] = *(const float4*)(pp[it] + min(q0 + 64 * u + l16 * 4, np - 4));
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int it = 0; it < P; ++it) s[it] += q0 + 64 * u + l16 * 4 < np ? (v[u][it].x + v[u][it].y) + (v[u][it].z + v[u][it].w) : 0.f;
       }
     } else {
-      for (u32 q = l16; q < np; q += 16) {
+      for (u32 q0 = 0; q0 < np; q0 += 16) {
+        float v[P];
 #pragma unroll
-        for (int it = 0; it < 16; ++it)
-          if ((u32)it < passes) s[it] += pp[it][q];
+        for (int it = 0; it < P; ++it) v[it] = pp[it][min(q0 + l16, np - 1)];
+#pragma unroll
+        for (int it = 0; it < P; ++it) s[it] += q0 + l16 < np ? v[it] : 0.f;
       }
     }
 #pragma unroll
-    for (int it = 0; it < 16; ++it) {
+    for (int it = 0; it < P; ++it) {
       float v = s[it];
       v += __shfl_xor(v, 1); v += __shfl_xor(v, 2); v += __shfl_xor(v, 4); v += __shfl_xor(v, 8);
-      const u32 tl = grp + 16 * it;
-      if (l16 == 0 && tl < count) rstd[tl] = W_SCALE_INV / sqrtf(v / (float)a.K + a.eps);
+      const u32 tl = grp + G * it;
+      if (l16 == 0 && tl < COUNT) rstd[tl] = W_SCALE_INV / sqrtf(v / (float)a.K + a.eps);
     }
   }
   __syncthreads();
@@ -263,6 +272,14 @@ __device__ __forceinline__ void residual_finish(const MfmaGemmArgs& a, floatx4_t
   if (lane < 16 && tv) a.ssq_out[(u64)t * (a.N / 16) + nt] = s;
 }
 
+// All loads of this wave have come. Said to the compiler where it may go on without using what they brought: it keeps their registers
+// apart from then on by waiting before it writes to them again, and where that is inside a loop it waits there in every
+// round, for the tiles on their way to LDS as well, which it knows nothing of.
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0), the other counters at their most
+// The same for one load whose result not every path uses.
+template <typename T>
+__device__ __forceinline__ void loaded(const T& v) { asm volatile("" : : "v"(v)); }
+
 // Epilogue of the TJ accumulator tiles a wave holds for one row tile (tokens t_base + 16 j + lane % 16). The epilogues that
 // read memory (the residual stream, the positions and the rotary table) request the operands of four tiles (two, where a wave has
 // six or eight) first and then compute and store tile by tile: written one tile after the other, every tile's loads would wait behind the
@@ -276,7 +293,7 @@ __device__ __forceinline__ void epilogue_row(const MfmaGemmArgs& a, const floatx
     for (int j = 0; j < TJ; ++j) epilogue_tile<EPI>(a, acc[j], nt, t_base + j * 16, rstd + j * 16);
     return;
   }
-  constexpr int H = TJ > 4 ? 2 : TJ;           // tiles whose operands are requested together
+  constexpr int H = TJ;                        // tiles whose operands are requested together
   // The lane comes anew for every row tile (an empty asm): else the offsets of all token tiles are kept from the first row tile to the
   // last, and beside 128 accumulators and the next item's operands they end in scratch memory, whose loads wait behind every
   // store: 4096 x 14336 at 8000 tokens 771 us instead of 753.
@@ -307,7 +324,171 @@ __device__ __forceinline__ void epilogue_row(const MfmaGemmArgs& a, const floatx
 #pragma unroll
       for (int j = 0; j < H; ++j) cs[j] = *(const float4*)(a.rope_tab + (u64)(rot ? pos[j] : 0) * half + (rot ? p : 0u));   // (cos,sin) of pairs p, p+1
 #pragma unroll
+      for (int j = 0; j < H; ++j) {
+        loaded(cs[j].x); loaded(cs[j].y); loaded(cs[j].z); loaded(cs[j].w);
+        loaded(slot[j]);
+      }
+#pragma unroll
       for (int j = 0; j < H; ++j) rope_finish(a, acc[j0 + j], nt, t[j], rstd[(j0 + j) * 16 + (lane & 15)], slot[j], cs[j]);
+    }
+  }
+}
+
+// Transposes the 4 x 4 matrix M[i][lane / 16] that lanes l, l + 16, l + 32, l + 48 hold as r[i]: afterwards lane group g holds row g,
+// r[c] = M[g][c]. (v_permlane16_swap exchanges the odd groups of its first operand with the even ones of its second,
+// v_permlane32_swap the upper half of the first with the lower half of the second.)
+__device__ __forceinline__ void swap16(u32& a, u32& b) { const auto v = __builtin_amdgcn_permlane16_swap(a, b, false, false); a = v[0]; b = v[1]; }
+__device__ __forceinline__ void swap32(u32& a, u32& b) { const auto v = __builtin_amdgcn_permlane32_swap(a, b, false, false); a = v[0]; b = v[1]; }
+__device__ __forceinline__ void transpose4(u32 (&r)[4]) {
+  swap16(r[0], r[1]); swap16(r[2], r[3]);
+  swap32(r[0], r[2]); swap32(r[1], r[3]);
+}
+
+// Epilogue of the 4 x TJ accumulator tiles (64 rows from row tile nt0, a multiple of four; tokens t_base + 16 j + lane % 16) of a wave
+// of the wide tiles. A column of tiles (16 tokens) at a time, with the operands of the next columns on their way: one row tile
+// after the other, two tiles' loads at a time, an epilogue is a chain of eight to sixteen memory latencies with little in flight
+// (256 x 256 tiles, every compute unit at it: 76 us with the residual add). And the four row tiles of a column are exchanged
+// between the lanes first, so that a lane stores 16 bytes of one row's neighbours instead of four pieces of 4 bytes: the gate's
+// result is a whole packed tile (1 KB) per column, queries and keys are runs of 64 bytes per token.
+// Tokens behind the last one are computed and stored like the others, into rows that the buffers have for it (16 behind the
+// last token's; for keys and values the query buffer's), so that no store stands in a branch, where the loads behind it would
+// have to wait for it. QKV 6144 x 4096 at 509 / 1700 / 8000 tokens 58 / 120 / 466 us before and 45 / 87 / 342 now (with compute_rstd and
+// without waits in the main loop), gate/up 28672 x 4096 at 1700 / 8000 tokens 351 / 1506 and 325 / 1411.
+template <int EPI, int TJ>
+__device__ __forceinline__ void epilogue_cols(const MfmaGemmArgs& a, const floatx4_t (&acc)[4][TJ], u32 nt0, u32 t_base, const float* rstd) {
+  u32 lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));               // (nothing of this is kept in registers from one item to the next)
+  const u32 lc = lane & 15, lg = lane >> 4;
+  constexpr int DMAX = EPI == EPI_QKV_ROPE ? 2 : 3, D = TJ < DMAX ? TJ : DMAX;   // columns whose operands are on their way
+  if (t_base >= a.T) return;
+  if constexpr (EPI == EPI_SILU_GATE) {
+    const u32 tbs = a.TBS_out ? a.TBS_out : a.TBS;
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) {
+      if (t_base + j * 16 >= a.T) return;
+      const u32 t = t_base + j * 16 + lc + a.col0;
+      const float r = rstd[j * 16 + lc];
+      u32 h[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float g0 = acc[i][j][0] * r, u0 = acc[i][j][1] * r, g1 = acc[i][j][2] * r, u1 = acc[i][j][3] * r;
+        const float h0 = g0 / (1.f + __expf(-g0)) * u0, h1 = g1 / (1.f + __expf(-g1)) * u1;
+        h[i] = pack_f16x2(h0, h1);
+      }
+      transpose4(h);                           // this lane: outputs nt0 * 8 + lg * 8 .. + 7 of its token
+      *(uint4*)(a.Hp + ((u64)((nt0 >> 2) * tbs + (t >> 4)) * 64 + (t & 15) + 16 * lg) * 8) = make_uint4(h[0], h[1], h[2], h[3]);
+    }
+  } else if constexpr (EPI == EPI_RESIDUAL) {
+    const u32 NT = a.N / 16;
+    const bool two = nt0 + 2 < NT;             // (rows come in pairs of tiles: the second pair may be behind the last row)
+    float4 g[4], old[D][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) g[i] = *(const float4*)(a.g_next + (i < 2 || two ? nt0 + i : nt0) * 16 + lg * 4);
+    auto request = [&](int j, float4 (&o)[4]) {
+      const float* xp = a.x + (u64)min(t_base + j * 16 + lc, a.T - 1) * a.ldx + nt0 * 16 + lg * 4;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[i] = *(const float4*)(xp + (i < 2 || two ? i * 16 : 0));
+    };
+#pragma unroll
+    for (int j = 0; j < D; ++j) request(j, old[j]);
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) {
+      if (t_base + j * 16 >= a.T) { wait_loads(); return; }
+      const u32 t = t_base + j * 16 + lc;
+      float ss[4];
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        if (p == 1 && !two) break;
+        u32 k[2][2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int i = 2 * p + q;
+          const float4 o = old[j % D][i];
+          const float v0 = o.x + acc[i][j][0] * W_SCALE_INV, v1 = o.y + acc[i][j][1] * W_SCALE_INV;
+          const float v2 = o.z + acc[i][j][2] * W_SCALE_INV, v3 = o.w + acc[i][j][3] * W_SCALE_INV;
+          *(float4*)(a.x + (u64)t * a.ldx + (nt0 + i) * 16 + lg * 4) = make_float4(v0, v1, v2, v3);
+          k[q][0] = pack_f16x2(v0 * g[i].x, v1 * g[i].y);
+          k[q][1] = pack_f16x2(v2 * g[i].z, v3 * g[i].w);
+          float s = v0 * v0 + v1 * v1 + v2 * v2 + v3 * v3;
+          s += __shfl_xor(s, 16);
+          ss[i] = s + __shfl_xor(s, 32);
+        }
+        // even lane groups take eight values of the pair's first row tile, odd ones of its second
+        swap16(k[0][0], k[1][0]); swap16(k[0][1], k[1][1]);
+        *(uint4*)(a.Xp_next + ((u64)(((nt0 + 2 * p) >> 1) * a.TBS + (t >> 4)) * 64 + lc + 16 * ((lg & 1) * 2 + (lg >> 1))) * 8) =
+            make_uint4(k[0][0], k[0][1], k[1][0], k[1][1]);
+      }
+      // the sums of squares of the four row tiles, a tile per lane group
+      const float s01 = lg & 1 ? ss[1] : ss[0], s23 = lg & 1 ? ss[3] : ss[2];
+      if (two) a.ssq_out[(u64)t * NT + nt0 + lg] = lg & 2 ? s23 : s01;
+      else if (lg < 2) a.ssq_out[(u64)t * NT + nt0 + lg] = s01;
+      if (j + D < TJ) request(j + D, old[j % D]);
+    }
+  } else {                                     // EPI_QKV_ROPE: 64 rows are the pairs p0 .. p0 + 31 of one head
+    const u32 hd = a.hd, half = hd / 2, head = nt0 * 16 / hd, p0 = (nt0 * 16 % hd) >> 1;
+    u32 at[TJ], pos[TJ];                       // cache slots (keys and values) and positions (queries and keys)
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) {
+      const u32 t = min(t_base + j * 16 + lc, a.T - 1);
+      at[j] = (u32)a.slot_mapping[t]; pos[j] = (u32)a.positions[t];
+    }
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) { loaded(at[j]); loaded(pos[j]); }
+    auto cache_row = [&](f16_t* cache, u32 h, int j) -> f16_t* {       // the 16-token block's part of kv head h
+      return cache + ((u64)(at[j] / a.bs) * a.nkv + h) * (a.bs * hd);
+    };
+    f16_t* const spare = a.qbuf + ((u64)a.T * a.nq) * hd;              // (rows behind the last token's)
+    if (head < a.nq + a.nkv) {
+      float4 cs[D][4];
+      auto request = [&](int j, float4 (&o)[4]) {
+        const float2* tab = a.rope_tab + (u64)pos[j] * half + p0 + lg * 2;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[i] = *(const float4*)(tab + i * 8);    // (cos, sin) of pairs p, p + 1
+      };
+#pragma unroll
+      for (int j = 0; j < D; ++j) request(j, cs[j]);
+      const float sc = 1.0f / sqrtf((float)hd);
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) {
+        if (t_base + j * 16 >= a.T) { wait_loads(); return; }
+        const u32 t = t_base + j * 16 + lc;
+        const float r = rstd[j * 16 + lc];
+        u32 lo[4], hi[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float lo0 = acc[i][j][0] * r, hi0 = acc[i][j][1] * r, lo1 = acc[i][j][2] * r, hi1 = acc[i][j][3] * r;
+          const float4 w = cs[j % D][i];
+          const float a0 = lo0 * w.x - hi0 * w.y, b0 = hi0 * w.x + lo0 * w.y;
+          const float a1 = lo1 * w.z - hi1 * w.w, b1 = hi1 * w.z + lo1 * w.w;
+          lo[i] = head < a.nq ? pack_f16x2(a0 * sc, a1 * sc) : pack_f16x2(a0, a1);
+          hi[i] = head < a.nq ? pack_f16x2(b0 * sc, b1 * sc) : pack_f16x2(b0, b1);
+        }
+        if (j + D < TJ) request(j + D, cs[j % D]);
+        transpose4(lo);                        // this lane: pairs p0 + lg * 8 .. + 7 of its token
+        transpose4(hi);
+        f16_t* out = a.qbuf + ((u64)t * a.nq + head) * hd;
+        if (head >= a.nq) out = t < a.T ? cache_row(a.Kc, head - a.nq, j) + at[j] % a.bs * hd : spare;
+        out += p0 + lg * 8;
+        *(uint4*)out = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+        *(uint4*)(out + half) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+      }
+    } else {                                   // V: dimension-major inside a block, [hd][16 tokens]
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) {
+        if (t_base + j * 16 >= a.T) return;
+        const bool tv = t_base + j * 16 + lc < a.T;
+        const float r = rstd[j * 16 + lc];
+        f16_t* v = tv ? cache_row(a.Vc, head - a.nq - a.nkv, j) + at[j] % a.bs : spare;
+        const u32 step = tv ? a.bs : 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const u32 p = p0 + i * 8 + lg * 2;
+          v[p * step] = f32_to_f16(acc[i][j][0] * r);
+          v[(p + 1) * step] = f32_to_f16(acc[i][j][2] * r);
+          v[(half + p) * step] = f32_to_f16(acc[i][j][1] * r);
+          v[(half + p + 1) * step] = f32_to_f16(acc[i][j][3] * r);
+        }
+      }
     }
   }
 }
@@ -348,13 +529,13 @@ constexpr int stream_batch(int NW, int TW) {
   return NW == 1 ? (TW == 1 ? 8 : (TW == 2 ? 6 : 4))
        : ((NW * TW >= 8) ? 2 : (NW + TW >= 5 ? 3 : 4));
 }
-template <int EPI, int NW, int TW, int U = stream_batch(NW, TW), bool GRID2D = false>
+template <int EPI, int NW, int TW, int U = stream_batch(NW, TW), bool GRID2D = false, int THREADS = 512>
 __device__ __forceinline__ void gemm_stream(const MfmaGemmArgs& a, MfmaShared& sh, u32 wg, u32 nwg) {
   const u32 lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const u32 NT = (a.N + 15) / 16, KT = gemm_k_tiles(a.K);
   const u32 TG = GRID2D ? (a.T + 63) / 64 : 1u;            // groups of 64 tokens
   const u32 NG = ((NT + NW - 1) / NW) * TG;                // work items: groups of NW tiles x token groups
-  const u32 KS = blockDim.x >> 6;                          // waves of the workgroup: each takes a slice of K
+  constexpr u32 KS = THREADS / 64;                         // waves of the workgroup: each takes a slice of K
   const u32 kb = (u32)((u64)KT * w / KS), ke = (u32)((u64)KT * (w + 1) / KS);
   const u32 nbatch = (KT / KS + (KT % KS ? 1 : 0) + U - 1) / U;   // same count in every wave (loads past `ke` are zeros)
   u32 round = 0;
@@ -402,7 +583,9 @@ __device__ __forceinline__ void gemm_stream(const MfmaGemmArgs& a, MfmaShared& s
 #pragma unroll
     for (int tw = 0; tw < TW; ++tw) acc[i][tw] = floatx4_t{0.f, 0.f, 0.f, 0.f};
   issue(bufA, ng, kb);               // the first loads are in flight while the norm scales are computed
-  compute_rstd(a, 0, 64 * TG, sh.rstd);
+  if constexpr (!GRID2D) compute_rstd<TW * 16, THREADS>(a, 0, sh.rstd);
+  else if (TG <= 2) compute_rstd<128, THREADS>(a, 0, sh.rstd);
+  else compute_rstd<256, THREADS>(a, 0, sh.rstd);
   auto step = [&](StreamBuf<U, NW, TW>& use, StreamBuf<U, NW, TW>& fill) -> bool {
     const bool last = b + 1 >= nbatch;
     const u32 nng = last ? item_of(round + 1) : ng;
@@ -499,18 +682,18 @@ __device__ __forceinline__ void gemm_stream_nw(const MfmaGemmArgs& a, MfmaShared
 template <int EPI>
 __device__ __forceinline__ void gemm_router(const MfmaGemmArgs& a, MfmaShared& sh, u32 wg, u32 nwg) {
   if (a.T == 0) return;
-  if (a.T <= 16) gemm_stream<EPI, 1, 1>(a, sh, wg, nwg);
-  else if (a.T <= 32) gemm_stream<EPI, 1, 2>(a, sh, wg, nwg);
-  else if (a.T <= 48) gemm_stream<EPI, 1, 3>(a, sh, wg, nwg);
-  else if (a.T <= 64) gemm_stream<EPI, 1, 4>(a, sh, wg, nwg);
-  else if (a.T <= 256) gemm_stream<EPI, 1, 4, stream_batch(1, 4), true>(a, sh, wg, nwg);
+  if (a.T <= 16) gemm_stream<EPI, 1, 1, stream_batch(1, 1), false, BLK_THREADS>(a, sh, wg, nwg);
+  else if (a.T <= 32) gemm_stream<EPI, 1, 2, stream_batch(1, 2), false, BLK_THREADS>(a, sh, wg, nwg);
+  else if (a.T <= 48) gemm_stream<EPI, 1, 3, stream_batch(1, 3), false, BLK_THREADS>(a, sh, wg, nwg);
+  else if (a.T <= 64) gemm_stream<EPI, 1, 4, stream_batch(1, 4), false, BLK_THREADS>(a, sh, wg, nwg);
+  else if (a.T <= 256) gemm_stream<EPI, 1, 4, stream_batch(1, 4), true, BLK_THREADS>(a, sh, wg, nwg);
   else {
     const u32 lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
     const u32 NT = (a.N + 15) / 16, KT = gemm_k_tiles(a.K), TB = (a.T + 31) / 32, items = NT * TB;
     constexpr int U = 4;
     for (u32 base = wg * nw; base < items; base += nwg * nw) {     // the waves of a workgroup: neighbouring row tiles, the same tokens
       const u32 item = base + w, nt = min(item, items - 1) % NT, tb = min(item, items - 1) / NT;
-      compute_rstd(a, (base / NT) * 32, NT >= 4 ? 64 : 128, sh.rstd);   // (the four items lie in at most two, or four, blocks of tokens)
+      compute_rstd<128, BLK_THREADS>(a, (base / NT) * 32, sh.rstd);   // (the four items lie in at most two, or four, blocks of tokens)
       const f16_t* wp = a.Wp + (u64)nt * KT * 512 + lane * 8;
       const f16_t* xp = a.Xp + (u64)tb * 1024 + lane * 8;
       const u64 xk = (u64)a.TBS * 512;

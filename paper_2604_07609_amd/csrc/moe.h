@@ -26,7 +26,7 @@ struct MoeShared {
   u32 small_base[MOE_MAX_EXPERTS + 1];
   u32 big_e[MOE_MAX_EXPERTS];     // experts with more tokens, and the blocks of tokens of all of them before each
   u32 big_base[MOE_MAX_EXPERTS + 1];
-  u32 n_small, n_big, shape;      // shape: workgroup tile of the big experts' GEMMs (DMA_SHAPES_STORE)
+  u32 n_small, n_big, shape;      // shape: workgroup tile of the big experts' GEMMs (DMA_SHAPES)
   float wrstd[8][64];             // per wave: norm scales of the tokens of its current item
   DmaShared dma;
 };
@@ -91,11 +91,11 @@ __device__ __forceinline__ void moe_split(const DevCtx& c, MoeShared& sh, u32 N,
     u32 best = (c.tune_nw >> 12) & 7u, width = 0, bt_of_best = 256;
     const bool forced = best != 0 && best != 5;
     float least = INFINITY;
-#define OFFER(id, bn, bt, lone, full, fixed, fixed_full) {                                                                 \
+#define OFFER(id, bn, bt, lone, full, fixed, fixed_full, residual, residual_full, rope, rope_full) {                        \
       width = bt == 64 ? b64 : bt == 128 ? b128 : bt == 192 ? b192 : b256;                                                 \
       const float t = dma_cost((N + bn - 1) / bn * width, K, lone, full, fixed, fixed_full, nwg);                          \
       if (forced ? best == id : t < least) { least = t; best = id; bt_of_best = bt; } }
-    DMA_SHAPES_STORE(OFFER)
+    DMA_SHAPES(OFFER)
 #undef OFFER
     u32 blocks = 0;
 #pragma unroll
