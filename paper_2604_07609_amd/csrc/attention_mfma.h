@@ -628,7 +628,8 @@ __device__ __forceinline__ void attn_prefill(const DevCtx& c, u32 layer, AttnMfm
 // Per launch at 32 q / 8 kv heads of 128, wave-per-tile kernel -> this one: two prompts of 4000 tokens 1130 -> 363 us
 // (of 262 GFLOP: 0.72 PFLOP/s; 530 with 32 keys per step, 515 with 64, 387 without bank conflicts, 363 with the order of the
 // two waves of a SIMD), three of 350-790 tokens 76 -> 40, one of 509 32 -> 30, a chunk of 1850 tokens beside 190 decoding
-// sequences 441 -> 268. Now bound by the softmax's vector instructions beside the matrix instructions.
+// sequences 441 -> 268. Now bound by the softmax's vector instructions beside the matrix instructions. (The wait for an item's
+// queries ahead of its loop and not in it: 356 -> 347, 39 -> 38, 30 -> 28.6, 268 -> 250.)
 template <int HD, int CT>
 __device__ __forceinline__ void attn_prompt(const DevCtx& c, u32 layer, AttnPromptShared& sh, u32 wg, u32 nwg, bool mixed) {
   const u32 ncu = max(1u, nwg / 2);              // one workgroup per compute unit is resident; the launch has two
@@ -711,8 +712,6 @@ __device__ __forceinline__ void attn_prompt(const DevCtx& c, u32 layer, AttnProm
       for (u32 r = 0; r < TPW; ++r) dma_tile<false>(at + r * 1024, src, voff[r]);
       id = bt[min(NB * (s + 1) + fb, last_block)];
     };
-#pragma unroll 1
-    for (u32 s = 0; s < NS - 1; ++s) fetch(s);
     // this wave's queries (columns past the prompt's end repeat its last token; they see key 0 only and are not stored)
     const u32 q0 = p0 + qt * 16;
     const bool live = q0 < P;                                // (uniform in the wave)
@@ -724,6 +723,9 @@ __device__ __forceinline__ void attn_prompt(const DevCtx& c, u32 layer, AttnProm
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
       for (int st = 0; st < HD / 32; ++st) q[ct][st] = ld_tile(c.qbuf + ((u64)qrow * c.nq + g * G + hg * CT + ct) * HD + st * 32 + lg * 8);
+#pragma unroll 1
+    for (u32 s = 0; s < NS - 1; ++s) fetch(s);
+    wait_loads();      // (left to the compiler, the wait for the queries stands in the loop and empties the ring in every step)
     floatx4_t o[CT][HD / 16];
     float m[CT], l[CT];                                      // running maximum, this lane's share of the sum
 #pragma unroll
