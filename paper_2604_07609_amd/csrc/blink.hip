@@ -549,6 +549,26 @@ static int init_impl(const blink_config* cfg, blink_engine* e) {
       if (int rc = dalloc(e, &c.moe_rstd, c.maxT)) return rc;
     } else if (int rc = dalloc(e, &c.hq, tile_tokens * k_pad(c.F))) return rc;
     if (int rc = dalloc(e, &c.ssq, tile_tokens * (c.d / 16))) return rc;
+    {
+      c.gemm_plan_max = std::min(c.maxT, PLAN_MAX_TOKENS);
+      std::vector<GemmPlan> plan(c.gemm_plan_max + 1);
+      const u32 ncu = (u32)e->n_cu, tune = cfg->tune, qo = c.nq * c.hd;
+      const bool moe = c.n_experts != 0;
+      for (u32 t = 1; t <= c.gemm_plan_max; ++t) {
+        plan[t].qkv = gemm_plan(EPI_QKV_ROPE, c.qkv_n, c.d, t, moe, ncu, tune);
+        plan[t].oproj = gemm_plan(EPI_RESIDUAL, c.d, qo, t, moe, ncu, tune);
+        plan[t].gateup = gemm_plan(EPI_SILU_GATE, 2 * c.F, c.d, t, false, ncu, tune);
+        plan[t].down = gemm_plan(EPI_RESIDUAL, c.d, c.F, t, false, ncu, tune);
+        plan[t].lm_head = gemm_plan(EPI_SCALED_STORE, c.V, c.d, t, false, ncu, tune);
+      }
+      u64* dev;
+      static_assert(sizeof(GemmPlan) == 8, "an entry is one word");
+      if (int rc = dalloc(e, &dev, plan.size())) return rc;
+      HIPCHK(hipMemcpy(dev, plan.data(), plan.size() * sizeof(GemmPlan), hipMemcpyHostToDevice));
+      c.gemm_plan = dev;
+    }
+    if (int rc = dalloc(e, &c.gemm_part, (u64)e->n_cu * (256 * 128 / 2), false)) return rc;
+    if (int rc = dalloc(e, &c.gemm_part_count, (u64)e->n_cu)) return rc;
     if (int rc = dalloc(e, &c.qbuf, ((u64)c.maxT + 16) * c.nq * c.hd)) return rc;   // (and x: 16 rows for the tokens that fill up a tile)
     {
       c.chunk_cap = c.max_batch * ((c.max_seq_len + ATTN_CHUNK_TOKENS - 1) / ATTN_CHUNK_TOKENS);

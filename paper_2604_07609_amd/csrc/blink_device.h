@@ -108,6 +108,8 @@ struct IterMeta {
   u32 n_full_chunks;    // decode attention work: chunks of ATTN_CHUNK_TOKENS context tokens that are full, listed first ...
   u32 n_chunks;         // ... and all chunks (the others are the last, partly filled chunk of a context)
   u32 prompt_shared;    // the prompt tokens' attention takes the kernel with shared KV tiles (bf16 models)
+  u32 plan_lm;          // schedules of the GEMMs (GemmPlan, bf16 models): the LM head at n_samples rows ...
+  u32 plan;             // ... and QKV, attention output, gate/up and down (a byte each) at n_tokens
 };
 
 // ---- which of the two prompt attention kernels an iteration takes ---------------------------------------------------------
@@ -299,6 +301,10 @@ struct DevCtx {
   f16_t* qbuf;          // [maxT][nq][hd] rotated queries scaled by 1/sqrt(hd), half precision like the KV cache they meet
   f16_t* hq;            // packed half(silu(gate)*up), inner dimension F
   float* ssq;           // [token][d/16] partial sums of squares of the residual stream
+  const u64* gemm_plan; // [gemm_plan_max + 1] GemmPlan of every token count
+  u32 gemm_plan_max;
+  u64* gemm_part;       // [n_cu][256 * 128 / 2] sums of the slices of GEMMs that split K, two floats each
+  u32* gemm_part_count; // [n_cu] slices that have come to every tile (zeros between launches)
   u32 TBS;              // token-block stride of the packed activation buffers
   u32 tune_nw;          // tuning word (MfmaGemmArgs::tune_nw)
   // mixture of experts

@@ -17,6 +17,7 @@ struct DmaShared {
   // of the grouped GEMMs, every 16-byte read took 60 cycles of the LDS instead of 4 and a launch up to 3.5 times as long.
   alignas(256) unsigned char ring[DMA_RING_BYTES];
   float rstd[256];                      // norm scales of the tokens of the workgroup's tile
+  u32 last;                             // split K: this workgroup is the last of its tile
 };
 
 template <typename T>
@@ -40,6 +41,64 @@ __device__ __forceinline__ void wait_dma_barrier() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(N) : "memory");
 }
 
+// Split K: every workgroup of a tile writes its sums (a wave's MI x MJ accumulator tiles, 1 KB each) and counts itself; the last one gets
+// true and the sum over all slices, in their order, in acc. The L2s of the XCDs are not coherent with each other, and a fence
+// of the device's scope writes back and invalidates a whole L2, once per workgroup (a GEMM took 1.5 to 2 times as long). So
+// nothing here is cached: sums, counter and their reads are relaxed atomics of the device's scope, which pass the L2s, and a
+// store has been written once vmcnt says so; no workgroup waits for another. The last one zeroes the counter for the next launch.
+template <int MI, int MJ>
+__device__ __forceinline__ bool add_slices(const MfmaGemmArgs& a, floatx4_t (&acc)[MI][MJ], DmaShared& sh, u32 tile, u32 slice, u32 slices) {
+  const u32 lane = threadIdx.x & 63, w = (u32)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr u32 WAVE_U64 = MI * MJ * 128, TILE_U64 = 8 * WAVE_U64;
+  u64* const mine = a.part + (u64)tile * slices * TILE_U64 + w * WAVE_U64 + lane;
+  auto at = [&](u32 s, int i, int j, int h) { return mine + (u64)s * TILE_U64 + ((i * MJ + j) * 2 + h) * 64; };
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < MJ; ++j)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        __hip_atomic_store(at(slice, i, j, h), ((u64)__float_as_uint(acc[i][j][2 * h + 1]) << 32) | __float_as_uint(acc[i][j][2 * h]),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const u32 before = __hip_atomic_fetch_add(a.part_count + tile, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    sh.last = before == slices - 1;
+    if (before == slices - 1) __hip_atomic_store(a.part_count + tile, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  if (!__builtin_amdgcn_readfirstlane(sh.last)) return false;
+  // the slices, U of them on their way at a time (past the last: that one again, not added)
+  constexpr int U = MI * MJ >= 16 ? 1 : MI * MJ >= 4 ? 16 / (MI * MJ) : 4;
+#pragma unroll 1
+  for (u32 s0 = 0; s0 < slices; s0 += U) {
+    u64 v[U][MI][MJ][2];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < MJ; ++j)
+#pragma unroll
+          for (int h = 0; h < 2; ++h) v[u][i][j][h] = __hip_atomic_load(at(min(s0 + u, slices - 1), i, j, h), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (s0 + u >= slices) { wait_loads(); break; }
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < MJ; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const float x = __uint_as_float((u32)(v[u][i][j][q >> 1] >> (32 * (q & 1))));
+            acc[i][j][q] = s0 + u == 0 ? x : acc[i][j][q] + x;
+          }
+    }
+  }
+  return true;
+}
+
 // A workgroup tile: WN waves along the rows (8 / WN along the tokens) of MI x MJ tiles of 16 x 16 each. KS: k-steps (of 32) per
 // barrier, 1 or 2 (the smaller tiles have too little work per k-step to hide the barrier behind). ONCE: no other workgroup reads
 // the weights of this one (their loads bypass temporal caching).
@@ -49,9 +108,12 @@ __device__ __forceinline__ void wait_dma_barrier() {
 // products apart, so that the memory pipe takes them without holding up the matrix instructions, and the fetches run on
 // into the next item while the epilogue of the last one stores. Behind the last item they repeat it (into slots nobody
 // reads), so that the number in flight is the same at every barrier and the loop has no branch for its end.
-// Items(NTW, BT).total(a) is their number; Items.at(i, a, nb, tb) completes the arguments of item i and names its block of rows and of tokens.
-template <int EPI, int WN, int MI, int MJ, int KS, bool ONCE, typename Items>
-__device__ __forceinline__ void gemm_dma(MfmaGemmArgs a, const Items& items, DmaShared& sh, u32 wg, u32 nwg) {
+// items.total is their number; items.at(i, a, nb, tb) completes the arguments of item i and names its block of rows and of tokens.
+//
+// SPLIT: K is cut into `slices` of each tile, an item each, at most one per workgroup (gemm_dma_pick says where that pays). The
+// workgroup that comes last to a tile adds the slices up in their order, so the result does not depend on which one that is.
+template <int EPI, int WN, int MI, int MJ, int KS, bool ONCE, bool SPLIT, typename Items>
+__device__ __forceinline__ void gemm_dma(MfmaGemmArgs a, const Items& items, DmaShared& sh, u32 wg, u32 nwg, u32 slices = 1) {
   constexpr u32 WT = 8 / WN, NTW = MI * WN, NXT = MJ * WT, ST = NTW + NXT, BT = 16 * NXT;
   constexpr u32 RING = DMA_RING_BYTES / 1024u / ST, NS = (RING > 18u ? 18u : RING) / KS * KS;   // k-steps the ring holds
   // tiles a wave fetches per k-step: RW weight tiles, then RX activation tiles (past the last one: that one again, the same
@@ -60,17 +122,28 @@ __device__ __forceinline__ void gemm_dma(MfmaGemmArgs a, const Items& items, Dma
   constexpr u32 RW = ONE ? 1 : NTW / 8, RX = ONE ? 0 : (NXT + 7) / 8, R = RW + RX;
   static_assert((ONE || NTW % 8 == 0) && NS >= 3 * KS && NS * R < 63 && BT <= 256, "ring");
   const u32 lane = threadIdx.x & 63, w = (u32)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wn = w % WN, wt = w / WN;
-  const u32 NT = (a.N + 15) / 16, KT = gemm_k_tiles(a.K), total = items.total, rounds = (total + nwg - 1) / nwg;
+  const u32 NT = (a.N + 15) / 16, KT = gemm_k_tiles(a.K), total = SPLIT ? items.total * slices : items.total, rounds = (total + nwg - 1) / nwg;
   if (total == 0) return;
-  auto item_of = [&](u32 r) -> u32 { return xcd_item(r * nwg, total, wg, nwg); };
-  const u32 n_items = item_of(rounds - 1) != ~0u ? rounds : rounds - 1;      // only the last round may have none for this workgroup
+  u32 slice = 0, k_first = 0, k_steps = KT;      // the slice of K (neighbouring workgroups: other tiles of the same slice)
+  if (SPLIT) {
+    const u32 i = xcd_item(0, total, wg, nwg);
+    if (i == ~0u) return;
+    slice = i / items.total;
+    k_first = KT / 2 * slice / slices * 2;
+    k_steps = KT / 2 * (slice + 1) / slices * 2 - k_first;
+  }
+  auto item_of = [&](u32 r) -> u32 {
+    const u32 i = xcd_item(r * nwg, total, wg, nwg);
+    return SPLIT ? i - slice * items.total : i;
+  };
+  const u32 n_items = SPLIT ? 1u : item_of(rounds - 1) != ~0u ? rounds : rounds - 1;   // only the last round may have none for this workgroup
   if (n_items == 0) return;
   const u32 xk_bytes = a.TBS * 1024;
   const u32 lds0 = (u32)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)sh.ring + w * 1024;
   // ---- the fetching side: pointers of this wave's tiles at the k-step that is fetched next ----
   const unsigned char *pw[RW], *px[RX + 1];
-  u32 vx[RX + 1], xslot[RX + 1], wadv = 1024, vw = lane * 16;
-  u32 p_item = 0, p_left = KT, p_at = lds0;
+  u32 vx[RX + 1], xslot[RX + 1], wadv = 1024, xadv = xk_bytes, vw = lane * 16;
+  u32 p_item = 0, p_left = k_steps, p_at = lds0;
   auto x_tile = [&](const MfmaGemmArgs& f, u32 xt, const unsigned char*& ptr, u32& off) {
     if (f.tok_index) {                   // the sixteen tokens of a tile come from arbitrary columns of the operand
       const u32 s = f.tok_index[min(xt * 16 + (lane & 15), f.T - 1)];
@@ -85,28 +158,31 @@ __device__ __forceinline__ void gemm_dma(MfmaGemmArgs a, const Items& items, Dma
     u32 nb, tb;
     MfmaGemmArgs f = a;
     items.at(item_of(min(p_item, n_items - 1)), f, nb, tb);
+    if (p_item >= n_items) wadv = xadv = 0;      // behind the last item: one k-step, again and again, which the L1 has
     if (ONE && w >= 4) {
       x_tile(f, tb * NXT + (w - 4), pw[0], vw);
-      wadv = xk_bytes;
+      if (SPLIT) pw[0] += (u64)k_first * xk_bytes;
+      if (p_item < n_items) wadv = xk_bytes;
       return;
     }
 #pragma unroll
-    for (u32 r = 0; r < RW; ++r) pw[r] = uniform_ptr((const unsigned char*)(f.Wp + (u64)min(nb * NTW + w + 8 * r, NT - 1) * KT * 512));
+    for (u32 r = 0; r < RW; ++r) pw[r] = uniform_ptr((const unsigned char*)(f.Wp + ((u64)min(nb * NTW + w + 8 * r, NT - 1) * KT + (SPLIT ? k_first : 0u)) * 512));
 #pragma unroll
     for (u32 r = 0; r < RX; ++r) {
       const u32 i = min(w + 8 * r, NXT - 1);
       xslot[r] = (NTW + i - w) * 1024;
       x_tile(f, tb * NXT + i, px[r], vx[r]);
+      if (SPLIT) px[r] += (u64)k_first * xk_bytes;
     }
   };
   fetch_item();
   auto fetch_tile = [&](u32 r) {
-    if (r < RW) { dma_tile<ONCE>(p_at + r * 8192, pw[r], ONE ? vw : lane * 16); pw[r] += ONE ? wadv : 1024u; }
-    else { dma_tile<false>(p_at + xslot[r - RW], px[r - RW], vx[r - RW]); px[r - RW] += xk_bytes; }
+    if (r < RW) { dma_tile<ONCE>(p_at + r * 8192, pw[r], ONE ? vw : lane * 16); pw[r] += wadv; }
+    else { dma_tile<false>(p_at + xslot[r - RW], px[r - RW], vx[r - RW]); px[r - RW] += xadv; }
   };
   auto fetch_next = [&]() { p_at = p_at == lds0 + (NS - 1) * (ST * 1024) ? lds0 : p_at + ST * 1024; };
   auto fetch_pair_done = [&]() {         // (an item ends behind a pair of k-steps)
-    if ((p_left -= 2) == 0) { p_left = KT; ++p_item; fetch_item(); }
+    if ((p_left -= 2) == 0) { p_left = k_steps; ++p_item; fetch_item(); }
   };
   // k-steps fetched before the first product. KS = 1: an even number that fits the ring. KS = 2: one less than the ring holds,
   // because the first k-step of a pair fetches before the pair's barrier, when only the slots of the pairs before it are free.
@@ -183,12 +259,13 @@ __device__ __forceinline__ void gemm_dma(MfmaGemmArgs a, const Items& items, Dma
     for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int j = 0; j < MJ; ++j) acc[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-    for (u32 k = 0; k < KT; k += 2) {
+    for (u32 k = 0; k < k_steps; k += 2) {
       step(wa, wb, std::integral_constant<bool, KS == 1>());
       if (KS == 2) fetch_pair_done();
       step(wb, wa, std::integral_constant<bool, true>());
       if (KS == 1) fetch_pair_done();
     }
+    if (SPLIT && !add_slices<MI, MJ>(a, acc, sh, nb * ((a.T + BT - 1) / BT) + tb, slice, slices)) break;
     if constexpr (MI == 4 && EPI != EPI_SCALED_STORE) {
       if (nb * NTW + wn * MI < NT) epilogue_cols<EPI, MJ>(a, acc, nb * NTW + wn * MI, tb * BT + wt * MJ * 16, sh.rstd + wt * MJ * 16);
       // the next item's first operands, which the last k-step has read already, once more: the epilogue needs their registers
@@ -216,7 +293,11 @@ struct DenseItems {
 };
 template <int EPI, int WN, int MI, int MJ, int KS, bool ONCE = false>
 __device__ __forceinline__ void gemm_dma_dense(const MfmaGemmArgs& a, DmaShared& sh, u32 wg, u32 nwg) {
-  gemm_dma<EPI, WN, MI, MJ, KS, ONCE>(a, DenseItems(a, WN * MI * 16, 8 / WN * MJ * 16), sh, wg, nwg);
+  gemm_dma<EPI, WN, MI, MJ, KS, ONCE, false>(a, DenseItems(a, WN * MI * 16, 8 / WN * MJ * 16), sh, wg, nwg);
+}
+template <int EPI, int WN, int MI, int MJ, bool ONCE = false>
+__device__ __forceinline__ void gemm_dma_split(const MfmaGemmArgs& a, DmaShared& sh, u32 wg, u32 nwg, u32 slices) {
+  gemm_dma<EPI, WN, MI, MJ, 2, ONCE, true>(a, DenseItems(a, WN * MI * 16, 8 / WN * MJ * 16), sh, wg, nwg, slices);
 }
 
 // ---- choice of the workgroup tile -----------------------------------------------------------------------------------
@@ -228,7 +309,7 @@ __device__ __forceinline__ void gemm_dma_dense(const MfmaGemmArgs& a, DmaShared&
 // constants of their own, fitted to launches with every shape forced of 1 to 6 matrices each (1024 to 28672 rows, k 1024 to 14336, weights
 // from HBM) at 65 to 8000 tokens. The fits are within 5 to 13 % (rms) of them, and the shape they choose takes at most 5 % more
 // than the best, 0.1 % on average.
-__device__ __forceinline__ float dma_cost(u32 total, u32 K, float lone, float full, float fixed, float fixed_full, u32 ncu) {
+__host__ __device__ __forceinline__ float dma_cost(u32 total, u32 K, float lone, float full, float fixed, float fixed_full, u32 ncu) {
   const u32 rounds = total / ncu, rest = total % ncu;
   const float f = (float)rest / (float)ncu, kt = (float)(K / 32);
   return (float)rounds * (kt * full + fixed_full) +
@@ -240,53 +321,113 @@ __device__ __forceinline__ float dma_cost(u32 total, u32 K, float lone, float fu
                       X(3, 128, 128, .227f, .243f, 3.6f, 1.6f, 2.9f, 5.7f, 6.0f, 3.7f) X(4, 256, 128, .358f, .386f, 5.1f, 4.9f, 7.2f, 15.7f, 8.6f, 8.3f) \
                       X(6, 256, 192, .419f, .544f, 9.7f, 7.8f, 12.7f, 26.2f, 14.2f, 14.7f) X(7, 256, 256, .513f, .690f, 11.6f, 10.6f, 16.7f, 39.0f, 16.2f, 20.5f)
 
-// T > 64 tokens. (Bits 12-14 of the tuning word force a shape by its number.)
-template <int EPI>
-__device__ __forceinline__ void gemm_dma_pick(const MfmaGemmArgs& a, DmaShared& sh, u32 wg, u32 nwg) {
-  u32 best = (a.tune_nw >> 12) & 7u;
-  if (best == 0 || best == 5) {
-    float least = INFINITY;
-#define OFFER(id, bn, bt, lone, full, store, store_full, residual, residual_full, rope, rope_full) \
-    { const float fixed = EPI == EPI_QKV_ROPE ? rope : EPI == EPI_RESIDUAL ? residual : store;                                    \
-      const float fixed_full = EPI == EPI_QKV_ROPE ? rope_full : EPI == EPI_RESIDUAL ? residual_full : store_full;                \
-      const float t = dma_cost(DenseItems(a, bn, bt).total, a.K, lone, full, fixed, fixed_full, nwg); if (t < least) { least = t; best = id; } }
-    DMA_SHAPES(OFFER)
-#undef OFFER
-  }
-  switch (best) {
-    case 1: gemm_dma_dense<EPI, 4, 1, 2, 2>(a, sh, wg, nwg); break;
-    case 2: gemm_dma_dense<EPI, 2, 4, 1, 2>(a, sh, wg, nwg); break;
-    case 3: gemm_dma_dense<EPI, 2, 4, 2, 2>(a, sh, wg, nwg); break;
-    case 4: gemm_dma_dense<EPI, 4, 4, 4, 2>(a, sh, wg, nwg); break;
-    case 6: gemm_dma_dense<EPI, 4, 4, 6, 1>(a, sh, wg, nwg); break;
-    default: gemm_dma_dense<EPI, 4, 4, 8, 1>(a, sh, wg, nwg); break;
-  }
-}
+// ---- the schedule of every GEMM --------------------------------------------------------------------------------------
+// It depends on the matrix and the number of tokens alone, so the library tabulates it when an engine is made (GemmPlan per token count), the
+// scheduler step copies the entry of its iteration into the metadata that the kernels read anyway, and a launch begins with its
+// operands: weighing six shapes in every workgroup took 1.5 us of a launch.
+#define PLAN_STREAM 0u           // streaming schedule
+#define PLAN_TALL 5u             // all tokens (at most 64) in one tile of 128 rows
+#define PLAN_CODE(shape, slices) ((shape) | (slices) << 3)       // 1-4, 6, 7: workgroup tile of that number; slices of K (0: whole)
+#define PLAN_MAX_TOKENS 16384u   // entries: beyond, the rounds are many, and the last entry serves
+struct GemmPlan { unsigned char qkv, oproj, gateup, down, lm_head, pad[3]; };
 
-union GemmShared8 { MfmaShared mfma; DmaShared dma; };
-
-// The GEMMs of a bf16 model.
+static inline u32 dma_tiles(u32 N, u32 T, u32 bn, u32 bt) { return (N + bn - 1) / bn * ((T + bt - 1) / bt); }
+// The entry of a matrix of N rows, inner dimension K, at T tokens. `ordered`: a mixture-of-experts model's GEMM ahead of the router.
 //   T <= 64: a matrix tall enough that its 128-row items occupy three quarters of the compute units goes through LDS with all
 //     tokens in one tile: each workgroup streams whole rows, no reduction over slices of K at the end, and the ring keeps 100 KB and
 //     more of weights on their way per compute unit (28672 x 4096 from HBM at 61 / 16 tokens: 46 / 42 us = 5.1 / 5.6 TB/s with loads that
 //     bypass temporal caching, 49 / 46 us without; streamed through registers with K split over the four waves of a workgroup 61 / 43 us). Narrower matrices would leave compute units idle
 //     and stay with the streaming schedule (4096 x 14336 at 16 tokens: 27 us against 47).
 //   T > 64: the tile whose rounds take the least time.
-//   64 < T <= 256 ahead of the router of a mixture-of-experts model (a.ordered): the streaming schedule over a grid of 64 x 64 items,
+//   64 < T <= 256 ahead of the router of a mixture-of-experts model (ordered): the streaming schedule over a grid of 64 x 64 items,
 //     where the matrix has few enough of them. A decode iteration's sums are then taken in the order in which they have
 //     been taken all along (K in eight slices): in another order they round otherwise, and tokens with two nearly equal router
 //     logits go to another expert. The tiles would win 1 % of a decode iteration at 96 sequences of the moe_30b_a3b shape.
+//   K in slices (QKV, attention output and down projections; not where the order of the sums is kept): where a matrix has too few tiles for
+//     the chip, its tiles are cut along K, two to eight slices each, at most one per compute unit. Half the chip then doesn't stand
+//     idle at 300 to 700 tokens, and at 17 to 256 larger tiles read the activations fewer times (the streaming schedule reads all of
+//     them in every workgroup). Both sides in us: 4096 x 14336 at 33 / 61 / 128 / 256 / 300 / 509 tokens 39 / 45 / 68 / 69 / 103 / 107 whole
+//     and 31 / 32 / 45 / 56 / 68 / 82 in slices, 4096 x 4096 at 128 / 300 tokens 26 / 37 and 22 / 31, 6144 x 4096 at 192 39 and 34, 1024 x 4096 at
+//     256 20 and 16. The last workgroup's reading and adding take 4 us and more, so at 61 tokens 4096 x 4096 stays whole (18 / 18).
+//     The model is within 11 % (rms) of launches with both forced, and its choice 0.7 % from the best of them on average.
+static inline unsigned char gemm_plan(int epi, u32 N, u32 K, u32 T, bool ordered, u32 ncu, u32 tune) {
+  const u32 shape = (tune >> 12) & 7u, slices = (tune >> 24) & 15u;       // forced
+  const bool split = !ordered && (epi == EPI_RESIDUAL || epi == EPI_QKV_ROPE), streams = T <= 64 && !(slices > 1 && shape);
+  float least = INFINITY;
+  u32 best = shape == 5 ? 0 : shape;
+  if (T > 64 && ordered && T <= 256 && !shape && dma_tiles(N, T, 128, 128) * 4 <= ncu) return PLAN_STREAM;
+  // (not where bits 0-2 or 11 of the tuning word ask for streaming)
+  if (streams && dma_tiles(N, T, 128, 64) * 4 >= ncu * 3 && !(tune & 0x807u)) return PLAN_TALL;
+  const float weights_us = (float)N * (float)K * 2.f / 5.6e6f;            // at the rate they come from HBM
+  if (streams) {
+    if (T <= 16 || !split || (tune & 0x7807u)) return PLAN_STREAM;
+    // time of the streaming schedule: the weights, or what a workgroup loads
+    const u32 tiles = (N + 15) / 16, nw = tiles < 320 ? 1 : 2, groups = (tiles + nw - 1) / nw, tb = (T + 15) / 16;
+    const float loads = (float)((groups + ncu - 1) / ncu) * (float)K / 2048.f * (2.39f * (float)nw + .70f * (float)tb);
+    least = (weights_us > loads ? weights_us : loads) + .4f + .7f * (float)tb;
+    best = PLAN_STREAM;
+  }
+#define OFFER(id, bn, bt, lone, full, store, store_full, residual, residual_full, rope, rope_full) {                                  \
+    const float fixed = epi == EPI_QKV_ROPE ? rope : epi == EPI_RESIDUAL ? residual : store;                                          \
+    const float fixed_full = epi == EPI_QKV_ROPE ? rope_full : epi == EPI_RESIDUAL ? residual_full : store_full;                      \
+    const u32 tiles = dma_tiles(N, T, bn, bt);                                                                                        \
+    if (T > 64 && !shape) {                                                                                                           \
+      const float t = dma_cost(tiles, K, lone, full, fixed, fixed_full, ncu);                                                         \
+      if (t < least) { least = t; best = id; }                                                                                        \
+    }                                                                                                                                 \
+    if (split && id <= 4 && (T > 64 || (id <= 2 && (id == 1 || T > 32))) && !shape)                                                   \
+      for (u32 s = 2; s <= 8 && tiles * s <= ncu && s * 2 <= gemm_k_tiles(K); ++s) {                                                  \
+        const float f = (float)(tiles * s) / (float)ncu, fe = (float)tiles / (float)ncu, k_steps = ceilf((float)K / 64.f / (float)s) * 2.f; \
+        const float work = k_steps * (lone + (full - lone) * f * f * f * f), bytes = weights_us / sqrtf(f);                           \
+        const float t = 1.03f * ((work > bytes ? work : bytes) + fixed + (fixed_full - fixed) * fe * fe + 4.1f + .226f * (float)(s * bn * bt) / 4096.f); \
+        if (t < least) { least = t; best = PLAN_CODE(id, s); }                                                                        \
+      }                                                                                                                               \
+    if (split && shape == id && id <= 4 && slices > 1 && slices * 2 <= gemm_k_tiles(K) && tiles * slices <= ncu) best = PLAN_CODE(id, slices); }
+  DMA_SHAPES(OFFER)
+#undef OFFER
+  return (unsigned char)(best == 0 && T > 64 ? 1u : best);
+}
+
+union GemmShared8 { MfmaShared mfma; DmaShared dma; };
+
+// A GEMM of a bf16 model in the schedule that its plan names.
 template <int EPI>
-__device__ __forceinline__ void gemm_bf16(const MfmaGemmArgs& a, GemmShared8& sh, u32 wg, u32 nwg) {
+__device__ __forceinline__ void gemm_bf16(const MfmaGemmArgs& a, u32 plan, GemmShared8& sh, u32 wg, u32 nwg) {
   if (a.T == 0) return;
-  if (a.T > 64 && a.ordered && a.T <= 256 && !(a.tune_nw & 0x7000u) && ((a.N + 127) / 128) * ((a.T + 127) / 128) * 4 <= nwg) gemm_stream<EPI, 4, 4, 1, true>(a, sh.mfma, wg, nwg);
-  else if (a.T > 64) gemm_dma_pick<EPI>(a, sh.dma, wg, nwg);
-  else if (((a.N + 127) / 128) * 4 >= nwg * 3 && !(a.tune_nw & 0x807u)) {   // (not where bits 0-2 or 11 of the tuning word ask for streaming)
-    if (a.T <= 16) gemm_dma_dense<EPI, 8, 1, 1, 2, true>(a, sh.dma, wg, nwg);        // 128 rows x 16 tokens
-    else if (a.T <= 32) gemm_dma_dense<EPI, 4, 2, 1, 2, true>(a, sh.dma, wg, nwg);   // 128 x 32
-    else gemm_dma_dense<EPI, 2, 4, 1, 2, true>(a, sh.dma, wg, nwg);                  // 128 x 64
-  } else if (a.T <= 16) gemm_stream_nw<EPI, 1>(a, sh.mfma, wg, nwg);
-  else if (a.T <= 32) gemm_stream_nw<EPI, 2>(a, sh.mfma, wg, nwg);
-  else if (a.T <= 48) gemm_stream_nw<EPI, 3>(a, sh.mfma, wg, nwg);
-  else gemm_stream_nw<EPI, 4>(a, sh.mfma, wg, nwg);
+  const u32 slices = plan >> 3;
+  if constexpr (EPI == EPI_RESIDUAL || EPI == EPI_QKV_ROPE) {
+    if (slices) {
+      switch (plan & 7u) {
+        case 1: gemm_dma_split<EPI, 4, 1, 2>(a, sh.dma, wg, nwg, slices); break;
+        case 2:
+          if (a.T <= 16) gemm_dma_split<EPI, 8, 1, 1, true>(a, sh.dma, wg, nwg, slices);
+          else if (a.T <= 32) gemm_dma_split<EPI, 4, 2, 1, true>(a, sh.dma, wg, nwg, slices);
+          else gemm_dma_split<EPI, 2, 4, 1>(a, sh.dma, wg, nwg, slices);
+          break;
+        case 3: gemm_dma_split<EPI, 2, 4, 2>(a, sh.dma, wg, nwg, slices); break;
+        default: gemm_dma_split<EPI, 4, 4, 4>(a, sh.dma, wg, nwg, slices); break;
+      }
+      return;
+    }
+  }
+  switch (plan & 7u) {
+    case PLAN_STREAM:
+      if (a.T <= 16) gemm_stream_nw<EPI, 1>(a, sh.mfma, wg, nwg);
+      else if (a.T <= 32) gemm_stream_nw<EPI, 2>(a, sh.mfma, wg, nwg);
+      else if (a.T <= 48) gemm_stream_nw<EPI, 3>(a, sh.mfma, wg, nwg);
+      else if (a.T <= 64) gemm_stream_nw<EPI, 4>(a, sh.mfma, wg, nwg);
+      else gemm_stream<EPI, 4, 4, 1, true>(a, sh.mfma, wg, nwg);
+      break;
+    case PLAN_TALL:
+      if (a.T <= 16) gemm_dma_dense<EPI, 8, 1, 1, 2, true>(a, sh.dma, wg, nwg);        // 128 rows x 16 tokens
+      else if (a.T <= 32) gemm_dma_dense<EPI, 4, 2, 1, 2, true>(a, sh.dma, wg, nwg);   // 128 x 32
+      else gemm_dma_dense<EPI, 2, 4, 1, 2, true>(a, sh.dma, wg, nwg);                  // 128 x 64
+      break;
+    case 1: gemm_dma_dense<EPI, 4, 1, 2, 2>(a, sh.dma, wg, nwg); break;
+    case 2: gemm_dma_dense<EPI, 2, 4, 1, 2>(a, sh.dma, wg, nwg); break;
+    case 3: gemm_dma_dense<EPI, 2, 4, 2, 2>(a, sh.dma, wg, nwg); break;
+    case 4: gemm_dma_dense<EPI, 4, 4, 4, 2>(a, sh.dma, wg, nwg); break;
+    case 6: gemm_dma_dense<EPI, 4, 4, 6, 1>(a, sh.dma, wg, nwg); break;
+    default: gemm_dma_dense<EPI, 4, 4, 8, 1>(a, sh.dma, wg, nwg); break;
+  }
 }

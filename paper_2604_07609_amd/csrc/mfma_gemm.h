@@ -15,7 +15,7 @@
 // The k dimension of both is padded with zeros to a multiple of 64 (an even number of k-steps).
 //
 // out[t][n] = sum_k X[t][k] * W[n][k]. Every GEMM kernel runs eight waves per workgroup and one workgroup per compute unit. The
-// schedule is chosen per launch from the token count T of the iteration and the shape of the matrix (gemm_dma.h: gemm_bf16):
+// schedule is chosen per launch from the token count T of the iteration and the shape of the matrix (gemm_dma.h: gemm_plan):
 //   tiles whose operands go from memory straight to LDS (gemm_dma.h): T > 64, and tall matrices at any T.
 //   stream (T <= 64 otherwise, decode at small batch): a workgroup owns 1 or 2 16-row weight tiles and all token blocks; its
 //     eight waves split K and keep two batches of 1 KB operand loads in flight each; weight loads are non-temporal;
@@ -68,11 +68,12 @@ struct MfmaGemmArgs {
   f16_t* Kc;               // this layer's K cache and V cache (half precision)
   f16_t* Vc;
   u32 nq, nkv, hd, bs;
-  u32 ordered;             // keep the order of the sums at 64 < T <= 256 (gemm_bf16)
+  u64* part;               // split K: the slices' sums, at most one 256 x 128 tile of floats per compute unit, and a count per tile (zeros between launches)
+  u32* part_count;
   u32 tune_nw;             // tests and tuning. Low three bits: 0 automatic choice of weight tiles per workgroup of the streaming schedule, 1/2 forced.
                            // Bit 5 (launcher): never the kernel chain without the decode attention's merge kernels, bit 7: always.
                            // Bit 6: epilogues load their operands tile by tile. Bit 11: tall matrices stream too at T <= 64.
-                           // Bits 12-14: force the tile shape at T > 64 (gemm_dma_pick).
+                           // Bits 12-14: force the tile shape at T > 64, with them bits 24-27 the slices of K (gemm_plan).
                            // Bit 15 (scheduler): the decode attention's work items are always chunks, bit 22: always whole
                            // contexts; bit 23: the decode attention kernel with static items. Bits 16-19: 15 prompt attention with shared KV tiles, 1, 2, 4 or 8 the
                            // other kernel with that many waves per item, other values that kernel. Bit 30: mixed launches run their decode part first in every workgroup.
@@ -677,7 +678,7 @@ __device__ __forceinline__ void gemm_stream_nw(const MfmaGemmArgs& a, MfmaShared
 
 // ---- router of a mixture-of-experts model (four waves per workgroup) ---------------------------------------------------
 // T <= 256: the streaming schedule with K in four slices (its order of the sums decides near-ties between experts: see
-// gemm_bf16). Beyond: independent waves, each with one row tile, 32 tokens and the whole of K in order, two batches of
+// gemm_plan). Beyond: independent waves, each with one row tile, 32 tokens and the whole of K in order, two batches of
 // loads in flight (128 x 2048 at 2100 tokens: 528 wave items).
 template <int EPI>
 __device__ __forceinline__ void gemm_router(const MfmaGemmArgs& a, MfmaShared& sh, u32 wg, u32 nwg) {

@@ -349,12 +349,12 @@ __device__ __forceinline__ void moe_grouped(const DevCtx& c, u32 layer, MoeShare
     return items;
   };
   switch (sh.shape) {
-    case 1: gemm_dma<EPI, 4, 1, 2, 2, false>(a, shaped(64), sh.dma, wg, nwg); break;
-    case 2: gemm_dma<EPI, 2, 4, 1, 2, false>(a, shaped(128), sh.dma, wg, nwg); break;
-    case 3: gemm_dma<EPI, 2, 4, 2, 2, false>(a, shaped(128), sh.dma, wg, nwg); break;
-    case 4: gemm_dma<EPI, 4, 4, 4, 2, false>(a, shaped(256), sh.dma, wg, nwg); break;
-    case 6: gemm_dma<EPI, 4, 4, 6, 1, false>(a, shaped(256), sh.dma, wg, nwg); break;
-    default: gemm_dma<EPI, 4, 4, 8, 1, false>(a, shaped(256), sh.dma, wg, nwg); break;
+    case 1: gemm_dma<EPI, 4, 1, 2, 2, false, false>(a, shaped(64), sh.dma, wg, nwg); break;
+    case 2: gemm_dma<EPI, 2, 4, 1, 2, false, false>(a, shaped(128), sh.dma, wg, nwg); break;
+    case 3: gemm_dma<EPI, 2, 4, 2, 2, false, false>(a, shaped(128), sh.dma, wg, nwg); break;
+    case 4: gemm_dma<EPI, 4, 4, 4, 2, false, false>(a, shaped(256), sh.dma, wg, nwg); break;
+    case 6: gemm_dma<EPI, 4, 4, 6, 1, false, false>(a, shaped(256), sh.dma, wg, nwg); break;
+    default: gemm_dma<EPI, 4, 4, 8, 1, false, false>(a, shaped(256), sh.dma, wg, nwg); break;
   }
 }
 

@@ -100,14 +100,16 @@ __device__ __forceinline__ void run_phase_bf16(const DevCtx& c, u32 layer, typen
   a.TBS = c.TBS;
   a.eps = c.eps;
   a.tune_nw = c.tune_nw;
+  a.part = c.gemm_part;
+  a.part_count = c.gemm_part_count;
   switch (PH) {
     case PH_EMBED: phase_embed_packed(c, wg, nwg); break;
     case PH_QKV:
       a.Wp = P->wqkv; a.Xp = c.xq; a.N = c.qkv_n; a.K = c.d; a.ssq_in = c.ssq;
       a.positions = c.positions; a.slot_mapping = c.slot_mapping; a.rope_tab = c.rope_tab; a.qbuf = c.qbuf;
       a.Kc = (f16_t*)c.kv + (u64)layer * c.kv_layer_stride; a.Vc = a.Kc + c.kv_kv_stride;
-      a.nq = c.nq; a.nkv = c.nkv; a.hd = c.hd; a.bs = c.bs; a.ordered = c.n_experts;
-      gemm_bf16<EPI_QKV_ROPE>(a, *(GemmShared8*)&sh, wg, nwg);
+      a.nq = c.nq; a.nkv = c.nkv; a.hd = c.hd; a.bs = c.bs;
+      gemm_bf16<EPI_QKV_ROPE>(a, m->plan & 0xffu, *(GemmShared8*)&sh, wg, nwg);
       break;
     case PH_ATTN: phase_attention_mfma(c, layer, *(AttnShared8*)&sh, wg, nwg); break;
     case PH_ATTN_COMBINE: attn_decode_combine(c, wg, nwg); break;
@@ -124,23 +126,23 @@ __device__ __forceinline__ void run_phase_bf16(const DevCtx& c, u32 layer, typen
     case PH_MOE_COMBINE: moe_combine(c, layer, *(MoeLists*)&sh, wg, nwg); break;
     case PH_OPROJ:
       a.Wp = P->wo; a.Xp = c.aq; a.N = c.d; a.K = c.nq * c.hd; a.x = c.x; a.ldx = c.d; a.g_next = c.layers[layer].g2;
-      a.Xp_next = c.xq; a.ssq_out = c.ssq; a.ordered = c.n_experts;
-      gemm_bf16<EPI_RESIDUAL>(a, *(GemmShared8*)&sh, wg, nwg);
+      a.Xp_next = c.xq; a.ssq_out = c.ssq;
+      gemm_bf16<EPI_RESIDUAL>(a, (m->plan >> 8) & 0xffu, *(GemmShared8*)&sh, wg, nwg);
       break;
     case PH_GATEUP:
       a.Wp = P->wgu; a.Xp = c.xq; a.N = 2 * c.F; a.K = c.d; a.ssq_in = c.ssq; a.Hp = c.hq;
-      gemm_bf16<EPI_SILU_GATE>(a, *(GemmShared8*)&sh, wg, nwg);
+      gemm_bf16<EPI_SILU_GATE>(a, (m->plan >> 16) & 0xffu, *(GemmShared8*)&sh, wg, nwg);
       break;
     case PH_DOWN:
       a.Wp = P->wd; a.Xp = c.hq; a.N = c.d; a.K = c.F; a.x = c.x; a.ldx = c.d;
       a.g_next = layer + 1 < c.n_layers ? c.layers[layer + 1].g1 : c.gf;
       a.Xp_next = c.xq; a.ssq_out = c.ssq;
-      gemm_bf16<EPI_RESIDUAL>(a, *(GemmShared8*)&sh, wg, nwg);
+      gemm_bf16<EPI_RESIDUAL>(a, m->plan >> 24, *(GemmShared8*)&sh, wg, nwg);
       break;
     case PH_LM_HEAD:
       a.Wp = c.lm_p; a.Xp = c.xq; a.N = c.V; a.K = c.d; a.T = m->n_samples; a.tok_index = c.last_idx; a.ssq_in = c.ssq;
       a.out = c.logits; a.ldo = c.V;
-      gemm_bf16<EPI_SCALED_STORE>(a, *(GemmShared8*)&sh, wg, nwg);
+      gemm_bf16<EPI_SCALED_STORE>(a, m->plan_lm, *(GemmShared8*)&sh, wg, nwg);
       break;
     case PH_SAMPLE:
       if (c.spec_k) phase_sample_publish_spec(c, *(SamplerShared*)&sh, wg, nwg);

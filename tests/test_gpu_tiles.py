@@ -152,6 +152,19 @@ def test_tile_gemms_in_every_shape(lib, shape, model):
         print(model, "shape", shape, "prompts", prompts, "worst relative logit error", worst)
 
 
+@pytest.mark.parametrize("slices", [2, 3])
+@pytest.mark.parametrize("shape", [1, 2, 3, 4])
+def test_tile_gemms_with_k_in_slices(lib, shape, slices):
+    """Bits 24-27 of the tuning word cut K of every tile of the QKV, attention output and down projections into slices, which the workgroup that
+    comes last adds up: K of 3 and 6 pairs of k-steps (slices of one to three pairs, one of them half padding), 17 to 330 tokens and
+    decode iterations, twice over (the counters are zeros again after every launch)."""
+    cfg, raw, blob = ragged(1)
+    eng = dict(synth.engine_config("mini_gqa"), max_batch=24, max_seq_len=400, kv_num_blocks=96, max_prefill_tokens=512, ring_slots=64)
+    for prompts in ([65], [257, 73], [61], [3] * 19):
+        worst = parity.stepwise_check(lib, cfg, eng, raw, blob, _fixed_prompts(cfg, prompts, 3, 264), rtol=RTOL, tune=shape << 12 | slices << 24)
+        print("shape", shape, "slices", slices, "prompts", prompts, "worst relative logit error", worst)
+
+
 @pytest.mark.parametrize("prompts", [[1], [17], [33, 15], [509, 16], [511, 500, 490], [3] * 270])
 def test_fp32_gemms_in_both_schedules(lib, prompts):
     """A workgroup's waves share a tile's K (few tiles) or, from 1025 tiles of 16 x 16 on, take 32 x 32 each with the whole of K: gate/up (44 row
