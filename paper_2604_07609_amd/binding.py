@@ -180,7 +180,7 @@ class Engine:
         _check(self.lib, self.lib.blink_stop(self.h))
 
     def poll(self, cap=4096):
-        buf = np.zeros(cap, dtype=EVENT_DTYPE)
+        buf = np.empty(cap, dtype=EVENT_DTYPE)
         n = C.c_uint32()
         _check(self.lib, self.lib.blink_poll_outputs(self.h, buf.ctypes.data, cap, C.byref(n)))
         return buf[: n.value]
@@ -213,10 +213,11 @@ class Engine:
             max_bytes = 8 + 4 * max(e["max_batch"] * (1 + int(e.get("speculative", 0))) * m["vocab"], e["kv_num_blocks"] + 1, max_t * m["d_model"],
                                     m["n_layers"] * max_t * m.get("n_active", 0),
                                     e["max_batch"] * ((e["max_seq_len"] + 15) // 16), e["ring_slots"])
-        buf = np.zeros(max_bytes, dtype=np.uint8)
+        buf = np.empty(max_bytes, dtype=np.uint8)
         n = C.c_uint64()
         _check(self.lib, self.lib.blink_debug_read(self.h, int(what), buf.ctypes.data, buf.nbytes, C.byref(n)))
-        return buf[: n.value].view(dtype).copy()
+        out = buf[: n.value].view(dtype)
+        return out if 2 * n.value > max_bytes else out.copy()      # (a copy only where it frees most of the buffer)
 
     def time_phase(self, phase):
         _check(self.lib, self.lib.blink_time_phase(self.h, int(phase)))

@@ -156,19 +156,88 @@ __global__ void __launch_bounds__(BLK_THREADS) k_ring_write(const SlotDesc* desc
   }
 }
 
-// The token reader's fetch (section 4.4): the new records of every picked slot into one pinned array, a workgroup per slot; a slot
-// whose last record this is goes back to EMPTY behind them.
-struct OutPick { u32 slot, from, n, at, completed, pad[3]; };
-__global__ void __launch_bounds__(64) k_fetch_outputs(const OutPick* picks, const OutRec* out_arena, u32 max_seq_len, OutRec* to, SlotStatus* status) {
-  const OutPick p = picks[blockIdx.x];
-  const uint4* src = (const uint4*)(out_arena + (u64)p.slot * max_seq_len + p.from);
-  uint4* dst = (uint4*)(to + p.at);
-  for (u32 i = threadIdx.x; i < p.n; i += 64) dst[i] = src[i];
-  if (p.completed && threadIdx.x == 0) {
-    SlotStatus* st = status + p.slot;
-    st->gen_count = 0; st->ticket_lo = 0; st->flags = 0;
-    __hip_atomic_store(&st->state, (u32)BLINK_SLOT_EMPTY, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+// The token reader (section 4.4) in one launch and one wait: the slots' metadata against what the host has had of every slot, the new records
+// of all of them into one pinned array (slot ascending, at most `room` in all), a description of each, and a slot whose
+// last record this is back to EMPTY behind them. One workgroup, small enough (32 registers) to run beside the GEMMs. The host
+// reads nothing of it in between: as a copy of the metadata, a decision there and a fetch a poll waited for the device twice.
+struct OutPick { u32 slot, from, n, completed; };
+struct OutWant { u32 slot, ticket_lo, have, pad; };       // a slot with a request, slot ascending, written by the host
+__global__ void __launch_bounds__(BLK_THREADS) __attribute__((amdgpu_num_vgpr(16))) k_poll_outputs(const OutWant* want, u32 n_want, SlotStatus* status, const OutRec* out_arena, u32 max_seq_len, u32 room,
+                                                             OutRec* to, OutPick* picks, u32* n_picks) {
+  __shared__ u32 part[BLK_THREADS / WAVE], s_slot[BLK_THREADS], s_from[BLK_THREADS], s_n[BLK_THREADS], s_at[BLK_THREADS];
+  const u32 lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
+  u32 staged = 0, listed = 0;
+  for (u32 base = 0; base < n_want && staged < room; base += BLK_THREADS) {
+    u32 slot = 0, n = 0, have = 0;
+    bool done = false;
+    if (base + threadIdx.x < n_want) {
+      const uint4 q = *(const uint4*)(want + base + threadIdx.x);
+      slot = q.x;
+      const SlotStatus* st = status + slot;
+      // state and count in one word, as they are published, behind the records (which are read past the caches too)
+      const u64 word = __hip_atomic_load((const u64*)st, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      if (__hip_atomic_load(&st->ticket_lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == q.y) {
+        have = q.z;
+        done = (u32)word == BLINK_SLOT_DECODE_COMPLETED;
+        n = (u32)(word >> 32) > have ? (u32)(word >> 32) - have : 0u;
+      }
+    }
+    // records and slots before this thread's
+    u32 inc = n;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) { const u32 t = __shfl_up(inc, o); if (lane >= (u32)o) inc += t; }
+    __syncthreads();
+    if (lane == 63u) part[w] = inc;
+    __syncthreads();
+    u32 at = inc - n;
+    for (u32 i = 0; i < w; ++i) at += part[i];
+    const u32 left = room - staged, full = n;
+    n = at >= left ? 0u : min(n, left - at);
+    const unsigned long long some = __ballot(n != 0);
+    u32 place = (u32)__popcll(some & ((1ull << lane) - 1ull));
+    __syncthreads();
+    if (lane == 0) part[w] = (u32)__popcll(some);
+    __syncthreads();
+    u32 strip = 0;
+    for (u32 i = 0; i < BLK_THREADS / WAVE; ++i) { if (i < w) place += part[i]; strip += part[i]; }
+    if (n) {
+      s_slot[place] = slot; s_from[place] = have; s_n[place] = n; s_at[place] = staged + at;
+      OutPick p;
+      p.slot = slot; p.from = have; p.n = n; p.completed = done && n == full;
+      *(uint4*)(picks + listed + place) = *(const uint4*)&p;
+    }
+    __syncthreads();
+    const u32 n_recs = strip ? s_at[strip - 1] + s_n[strip - 1] - staged : 0u;
+    for (u32 r0 = 0; r0 < n_recs; r0 += 2 * BLK_THREADS) {      // a thread per record, two on their way
+      u64 v[2][2];
+#pragma unroll
+      for (u32 u = 0; u < 2; ++u) {
+        const u32 r = staged + min(r0 + u * BLK_THREADS + threadIdx.x, n_recs - 1);
+        u32 lo = 0, hi = strip;                                  // its slot: the last k with s_at[k] <= r
+        while (hi - lo > 1) {
+          const u32 mid = (lo + hi) / 2;
+          if (s_at[mid] <= r) lo = mid; else hi = mid;
+        }
+        const u64* src = (const u64*)(out_arena + (u64)s_slot[lo] * max_seq_len + s_from[lo] + (r - s_at[lo]));
+#pragma unroll
+        for (u32 h = 0; h < 2; ++h) v[u][h] = __hip_atomic_load(src + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      }
+#pragma unroll
+      for (u32 u = 0; u < 2; ++u) {
+        const u32 r = r0 + u * BLK_THREADS + threadIdx.x;
+        if (r < n_recs) *(ulonglong2*)(to + staged + r) = make_ulonglong2(v[u][0], v[u][1]);
+      }
+    }
+    if (strip) staged = s_at[strip - 1] + s_n[strip - 1];
+    listed += strip;
+    __syncthreads();                                             // (every record of the strip has been read)
+    if (done && n && n == full) {
+      SlotStatus* st = status + slot;
+      st->gen_count = 0; st->ticket_lo = 0; st->flags = 0;
+      __hip_atomic_store(&st->state, (u32)BLINK_SLOT_EMPTY, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
   }
+  if (threadIdx.x == 0) *n_picks = listed;
 }
 
 __global__ void k_open_window(SchedState* ss, u64 iter_limit) {
@@ -195,6 +264,11 @@ static int fail(int code, const char* fmt, ...) {
     if (e_ != hipSuccess) return fail(BLINK_ERR_DEVICE, "%s: %s (%s:%d)", #x, hipGetErrorString(e_), __FILE__, __LINE__); \
   } while (0)
 
+// staging of blink_debug_read: the two descriptions, then pieces of the result
+#define DBG_PIECE (512u << 10)
+#define DBG_PIECES 34u             // at most: as many as the largest logits need
+#define DBG_AHEAD (256u << 10)
+
 struct blink_engine {
   blink_config cfg{};
   DevCtx ctx{};
@@ -212,13 +286,18 @@ struct blink_engine {
   std::vector<std::atomic<u32>> shadow_state;   // host view: 0 empty, 1 in flight
   std::vector<u32> delivered;
   std::vector<u64> slot_ticket;
-  SlotStatus* stage_status = nullptr;  // pinned [ring_slots]
+  OutWant* stage_want = nullptr;       // pinned [ring_slots]
+  u32* stage_n_picks = nullptr;        // pinned
   OutRec* stage_out = nullptr;         // pinned
   u64 stage_out_cap = 0;
   OutPick* stage_picks = nullptr;      // pinned [ring_slots]
   u64 iter_limit = 0;                  // of the current window (0: none)
   u64 iter_before = 0;                 // iterations and chains run before the current window
   u32 chains_before = 0;
+  char* stage_dbg = nullptr;           // pinned: staging of blink_debug_read
+  u32 dbg_pieces = 0;
+  hipEvent_t dbg_ev[DBG_PIECES] = {};
+  std::mutex dbg_mu;
   // loop
   std::thread launcher;
   hipGraphExec_t iter_graph = nullptr;        // the kernel chain of one iteration
@@ -288,6 +367,7 @@ static void free_all(blink_engine* e) {
   if (e->iter_graph_whole) (void)hipGraphExecDestroy(e->iter_graph_whole);
   for (hipEvent_t ev : e->events) (void)hipEventDestroy(ev);
   for (hipEvent_t ev : e->phase_ev) (void)hipEventDestroy(ev);
+  for (hipEvent_t ev : e->dbg_ev) if (ev) (void)hipEventDestroy(ev);
   for (void* p : e->dev_allocs) (void)hipFree(p);
   for (void* p : e->host_allocs) (void)hipHostFree(p);
   if (e->compute) (void)hipStreamDestroy(e->compute);
@@ -337,10 +417,19 @@ static int init_impl(const blink_config* cfg, blink_engine* e) {
   if (int rc = halloc(e, &e->hmirror, 1)) return rc;
   c.hctrl = e->hctrl; c.hmirror = e->hmirror;
   if (int rc = halloc(e, &e->stage_in, sizeof(SlotDesc) + sizeof(SlotStatus) + ((u64)c.max_seq_len + 3) / 4 * 16)) return rc;
-  if (int rc = halloc(e, &e->stage_status, c.ring_slots)) return rc;
+  if (int rc = halloc(e, &e->stage_want, c.ring_slots)) return rc;
+  if (int rc = halloc(e, &e->stage_n_picks, 1)) return rc;
   e->stage_out_cap = 1u << 16;
   if (int rc = halloc(e, &e->stage_out, e->stage_out_cap)) return rc;
   if (int rc = halloc(e, &e->stage_picks, c.ring_slots)) return rc;
+  e->dbg_pieces = (u32)std::min<u64>(DBG_PIECES, std::max<u64>(2, (rows_cap * c.V * 4 + DBG_PIECE - 1) / DBG_PIECE));
+  {
+    void* q = nullptr;
+    HIPCHK(hipHostMalloc(&q, 1024 + (u64)DBG_PIECE * e->dbg_pieces, hipHostMallocMapped));
+    e->host_allocs.push_back(q);
+    e->stage_dbg = (char*)q;
+  }
+  for (auto& ev : e->dbg_ev) HIPCHK(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
   e->delivered.assign(c.ring_slots, 0);
   e->slot_ticket.assign(c.ring_slots, 0);
   for (auto& s : e->shadow_state) s.store(0);
@@ -930,39 +1019,20 @@ extern "C" int blink_poll_outputs(blink_engine* e, blink_event* buf, uint32_t ca
   if (e->shut) return fail(BLINK_ERR_STATE, "engine is shut down");
   const DevCtx& c = e->ctx;
   HIPCHK(hipSetDevice(e->cfg.device));
-  // one bulk read of the slot metadata (section 4.4 "Token reader")
-  HIPCHK(hipMemcpyAsync(e->stage_status, c.status, sizeof(SlotStatus) * c.ring_slots, hipMemcpyDeviceToHost, e->s_out));
+  u32 n_want = 0;
+  for (u32 slot = 0; slot < c.ring_slots; ++slot)
+    if (e->shadow_state[slot].load(std::memory_order_acquire) != 0) e->stage_want[n_want++] = OutWant{slot, (u32)e->slot_ticket[slot], e->delivered[slot], 0};
+  if (n_want == 0 || cap == 0) return BLINK_OK;  // (no request is under way)
+  HIPCHK(launch(k_poll_outputs, 1, BLK_THREADS, e->s_out, e->stage_want, n_want, c.status, c.out_arena, c.max_seq_len,
+                (u32)std::min<u64>(cap, e->stage_out_cap), e->stage_out, e->stage_picks, e->stage_n_picks));
   HIPCHK(hipStreamSynchronize(e->s_out));
-  u32 n_picks = 0;
-  u64 staged = 0;
-  u32 budget = cap;
-  for (u32 slot = 0; slot < c.ring_slots && budget > 0; ++slot) {
-    if (e->shadow_state[slot].load(std::memory_order_acquire) == 0) continue;
-    const SlotStatus& st = e->stage_status[slot];
-    if (st.ticket_lo != (u32)e->slot_ticket[slot]) continue;
-    const u32 gen = st.gen_count, have = e->delivered[slot];
-    if (gen <= have) continue;
-    u32 n = std::min(gen - have, budget);
-    if (staged + n > e->stage_out_cap) n = (u32)(e->stage_out_cap - staged);
-    if (n == 0) break;
-    OutPick& p = e->stage_picks[n_picks++];
-    p = OutPick{};
-    p.slot = slot; p.from = have; p.n = n; p.at = (u32)staged;
-    p.completed = st.state == BLINK_SLOT_DECODE_COMPLETED && have + n == gen;
-    staged += n;
-    budget -= n;
-  }
-  if (n_picks == 0) return BLINK_OK;
-  // one kernel fetches the records of all slots and returns the completed slots to EMPTY (the frontend's edge of the life cycle);
-  // a copy per slot cost 3 us each, and another for every completed one
-  HIPCHK(launch(k_fetch_outputs, n_picks, 64, e->s_out, e->stage_picks, c.out_arena, c.max_seq_len, e->stage_out, c.status));
-  HIPCHK(hipStreamSynchronize(e->s_out));
+  const u32 n_picks = *e->stage_n_picks;
   // events across requests ordered by (iteration, ring slot); per request by index
   u32 w = 0;
   for (u32 k = 0; k < n_picks; ++k) {
     const OutPick p = e->stage_picks[k];
     for (u32 i = 0; i < p.n; ++i) {
-      const OutRec& r = e->stage_out[p.at + i];
+      const OutRec& r = e->stage_out[w];         // (the slots' records follow each other)
       blink_event& ev = buf[w++];
       ev.request_id = e->slot_ticket[p.slot];
       ev.index = p.from + i;
@@ -1050,16 +1120,59 @@ extern "C" int blink_get_stats(blink_engine* e, blink_stats* out) {
   return BLINK_OK;
 }
 
+// Device memory into a caller's (pageable) buffer, in pieces through pinned memory: a piece is on its way over the bus while others are
+// copied out of the staging buffer, by several threads where there is much of it, because most of the time is the first touch of the
+// caller's pages. 16.8 MB into new pages: 4.5 ms as one hipMemcpy, 2.0 with four threads; 8 MB 2.2 and 1.1; 2 MB .58 and .35.
+static hipError_t read_back(blink_engine* e, char* to, const char* from, u64 n) {
+  const u32 pieces = (u32)((n + DBG_PIECE - 1) / DBG_PIECE);
+  char* const ring = e->stage_dbg + 1024;
+  for (u32 first = 0; first < pieces; first += e->dbg_pieces) {
+    const u32 end = std::min(pieces, first + e->dbg_pieces);
+    for (u32 i = first; i < end; ++i) {
+      const u64 off = (u64)i * DBG_PIECE;
+      hipError_t er = hipMemcpyAsync(ring + (u64)(i - first) * DBG_PIECE, from + off, std::min<u64>(DBG_PIECE, n - off), hipMemcpyDeviceToHost, e->s_out);
+      if (er == hipSuccess) er = hipEventRecord(e->dbg_ev[i - first], e->s_out);
+      if (er != hipSuccess) { (void)hipStreamSynchronize(e->s_out); return er; }
+    }
+    std::atomic<u32> next{first};
+    std::atomic<int> bad{0};
+    const int device = e->cfg.device;
+    auto work = [&]() {
+      if (hipSetDevice(device) != hipSuccess) bad = 1;
+      for (u32 i; (i = next.fetch_add(1)) < end;) {
+        if (hipEventSynchronize(e->dbg_ev[i - first]) != hipSuccess) { bad = 1; continue; }
+        const u64 off = (u64)i * DBG_PIECE;
+        memcpy(to + off, ring + (u64)(i - first) * DBG_PIECE, std::min<u64>(DBG_PIECE, n - off));
+      }
+    };
+    std::thread helpers[3];
+    for (u32 t = 0; t < 3 && (t + 1) * 4 < end - first; ++t) {
+      try { helpers[t] = std::thread(work); } catch (...) { break; }     // (no thread to be had: this one does it)
+    }
+    work();
+    for (auto& h : helpers) if (h.joinable()) h.join();
+    if (bad) return hipErrorUnknown;
+  }
+  return hipSuccess;
+}
+
 extern "C" int blink_debug_read(blink_engine* e, uint32_t what, void* buf, uint64_t cap_bytes, uint64_t* n_bytes) {
   g_err.clear();
   if (!e || !buf || !n_bytes) return fail(BLINK_ERR_INVAL, "null argument");
   if (e->loop_active.load()) return fail(BLINK_ERR_STATE, "stop the loop before reading device state");
   HIPCHK(hipSetDevice(e->cfg.device));
   const DevCtx& c = e->ctx;
-  IterMeta m;
-  SchedState s;
-  HIPCHK(hipMemcpy(&m, c.meta, sizeof m, hipMemcpyDeviceToHost));
-  HIPCHK(hipMemcpy(&s, c.ss, sizeof s, hipMemcpyDeviceToHost));
+  std::lock_guard<std::mutex> lock(e->dbg_mu);
+  // Both descriptions and, for the logits, the first rows come with one wait: a small result needs no other.
+  IterMeta& m = *(IterMeta*)e->stage_dbg;
+  SchedState& s = *(SchedState*)(e->stage_dbg + 512);
+  static_assert(sizeof(IterMeta) <= 512 && sizeof(SchedState) <= 512, "staging layout");
+  char* const data = e->stage_dbg + 1024;
+  HIPCHK(hipMemcpyAsync(&m, c.meta, sizeof m, hipMemcpyDeviceToHost, e->s_out));
+  HIPCHK(hipMemcpyAsync(&s, c.ss, sizeof s, hipMemcpyDeviceToHost, e->s_out));
+  const u64 ahead = what == BLINK_DBG_LOGITS ? std::min<u64>(std::min<u64>(cap_bytes, DBG_AHEAD), (u64)c.max_batch * (c.spec_k + 1) * c.V * 4) : 0;
+  if (ahead) HIPCHK(hipMemcpyAsync(data, c.logits, ahead, hipMemcpyDeviceToHost, e->s_out));
+  HIPCHK(hipStreamSynchronize(e->s_out));
   const void* src = nullptr;
   u64 n = 0;
   switch (what) {
@@ -1116,7 +1229,8 @@ extern "C" int blink_debug_read(blink_engine* e, uint32_t what, void* buf, uint6
     default: return fail(BLINK_ERR_INVAL, "unknown selector %u", what);
   }
   if (n > cap_bytes) return fail(BLINK_ERR_INVAL, "buffer too small: need %llu bytes", (unsigned long long)n);
-  if (n) HIPCHK(hipMemcpy(buf, src, n, hipMemcpyDeviceToHost));
+  if (n && n <= ahead) memcpy(buf, data, n);
+  else if (n) HIPCHK(read_back(e, (char*)buf, (const char*)src, n));
   *n_bytes = n;
   return BLINK_OK;
 }

@@ -121,3 +121,33 @@ def test_the_last_iteration_of_a_window_is_enqueued_ahead(lib):
     short, long = (np.median(gaps[n][5:]) for n in (2, 6))
     print("gap before the last iteration of 2: %.1f us, of 6: %.1f us" % (short, long))
     assert short < long + 3.0
+
+
+@pytest.mark.parametrize("n,cap", [(1, 2), (8, 5), (9, 4096), (256, 7), (257, 300)])
+def test_poll_in_pieces_and_the_logits_behind_it(lib, n, cap):
+    """Polls of `cap` records (a slot's records in several polls, one strip of 256 slots and one more) bring every token of every request
+    once and in order, completed slots are free again, and the logits of the last iteration (8192 floats a row: within the first
+    256 KB, that and one more row, several pieces of 512 KB) have their maximum at the token that each request got."""
+    cfg = synth.model_config("sched_stress")
+    eng = dict(synth.engine_config("sched_stress"), max_batch=n, ring_slots=512)
+    e = lib.Engine(cfg, eng, synth.pack_blob(cfg, synth.make_weights(cfg, 1000)), flags=lib.FLAG_KEEP_LOGITS)
+    try:
+        for window in range(2):
+            rng = np.random.default_rng(window)
+            ids = [e.submit(rng.integers(0, cfg["vocab"], 5 + i % 4), 3) for i in range(n)]
+            e.run(3)
+            e.wait()
+            got = {i: [] for i in ids}
+            while True:
+                ev = e.poll(cap)
+                if ev.size == 0:
+                    break
+                assert ev.size <= cap
+                for r in ev:
+                    assert r["index"] == len(got[r["request_id"]])
+                    got[r["request_id"]].append(int(r["token"]))
+            assert all(len(t) == 3 for t in got.values())
+            logits = e.debug_read(lib.DBG.LOGITS, np.float32).reshape(n, cfg["vocab"])
+            assert [int(x) for x in logits.argmax(1)] == [got[i][2] for i in ids]
+    finally:
+        e.shutdown()
