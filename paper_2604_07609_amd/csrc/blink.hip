@@ -475,7 +475,7 @@ static int init_impl(const blink_config* cfg, blink_engine* e) {
   if (int rc = dalloc(e, &c.input_ids, c.maxT)) return rc;
   if (int rc = dalloc(e, &c.positions, c.maxT)) return rc;
   if (int rc = dalloc(e, &c.slot_mapping, c.maxT)) return rc;
-  if (int rc = dalloc(e, &c.tok_seq, c.maxT)) return rc;
+  if (int rc = dalloc(e, &c.tok_bslot, c.maxT)) return rc;
   if (int rc = dalloc(e, &c.trace, c.trace_cap)) return rc;
   {
     std::vector<u32> fs(c.n_blocks);

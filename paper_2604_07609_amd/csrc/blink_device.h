@@ -275,7 +275,7 @@ struct DevCtx {
   i32* input_ids;       // [maxT]
   i32* positions;       // [maxT]
   i32* slot_mapping;    // [maxT]
-  u32* tok_seq;         // [maxT]
+  u32* tok_bslot;       // [maxT] batch slot of every token's sequence (fp32 models' attention)
   TraceRec* trace;
   // weights
   const void* embed;

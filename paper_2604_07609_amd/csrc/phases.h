@@ -64,7 +64,7 @@ __device__ __forceinline__ void run_phase_f32(const DevCtx& c, u32 layer, typena
       a.nq = c.nq; a.nkv = c.nkv; a.hd = c.hd; a.bs = c.bs;
       gemm_f32<FA_NORM, FE_ROPE>(a, *(F32GemmShared*)&sh, wg, nwg);
       break;
-    case PH_ATTN: phase_attention<float>(c, layer, *(AttnShared*)&sh, wg, nwg); break;
+    case PH_ATTN: phase_attention_f32(c, layer, *(AttnShared*)&sh, wg, nwg); break;
     case PH_OPROJ:
       a.A = c.attn; a.lda = c.nq * c.hd; a.W = (const float*)L->wo; a.out = c.x; a.ldo = c.d; a.N = c.d; a.K = c.nq * c.hd;
       gemm_f32<FA_PLAIN, FE_ADD>(a, *(F32GemmShared*)&sh, wg, nwg);

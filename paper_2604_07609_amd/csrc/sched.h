@@ -743,13 +743,13 @@ __device__ void sched_step(const DevCtx& c, SchedShared& sh) {
           c.input_ids[toff] = r.last_token;
           c.positions[toff] = (i32)pos0;
           c.slot_mapping[toff] = (i32)(bt[pos0 / c.bs] * c.bs + pos0 % c.bs);
-          c.tok_seq[toff] = si;
+          c.tok_bslot[toff] = b;
           for (u32 j = 1; j < ntok; ++j) {          // the drafts behind the last token, at the next positions
             const u32 p = pos0 + j;
             c.input_ids[toff + j] = c.spec_tok[(u64)b * SPEC_MAX_DRAFTS + j - 1];
             c.positions[toff + j] = (i32)p;
             c.slot_mapping[toff + j] = (i32)(bt[p / c.bs] * c.bs + p % c.bs);
-            c.tok_seq[toff + j] = si;
+            c.tok_bslot[toff + j] = b;
           }
           if (r.paused) {
             set_slot_state(&c.status[r.ring_slot], SLOT_DECODE_PROCESSING);
@@ -861,7 +861,7 @@ __device__ void sched_step(const DevCtx& c, SchedShared& sh) {
             c.input_ids[tk] = id[u];
             c.positions[tk] = (i32)pp[u];
             c.slot_mapping[tk] = (i32)(blk[u] * c.bs + pp[u] % c.bs);
-            c.tok_seq[tk] = sq[u];
+            c.tok_bslot[tk] = sh.seq_bslot[sq[u]];
           }
         }
       }

@@ -177,3 +177,17 @@ def test_fp32_gemms_in_both_schedules(lib, prompts):
                ring_slots=16 if n < 16 else 512)
     worst = parity.stepwise_check(lib, cfg, eng, raw, blob, _fixed_prompts(cfg, prompts, 2, 263), rtol=1e-5)
     print("fp32", prompts if n < 16 else n, "worst relative logit error", worst)
+
+
+@pytest.mark.parametrize("heads", [(2, 2, 64), (4, 2, 64), (3, 1, 64), (8, 1, 64), (6, 1, 64), (2, 2, 128), (3, 1, 128), (8, 2, 128)])
+def test_fp32_attention(lib, heads):
+    """1, 2, 3, 4, 6 and 8 q heads per kv head of 64 and 128 dimensions (whole and partly filled groups of heads): contexts of one
+    key, around a block of 16, around the four blocks of the four waves (64), around a step of every wave (256 and 128 keys) and behind it; prompts, then
+    decode iterations that cross those edges. Tolerance: the rounding of sums of up to 600 products (sqrt(600) * 2^-24) in each of some ten steps."""
+    nq, nkv, hd = heads
+    cfg = dict(synth.model_config("mini_gqa"), d_model=96, n_q_heads=nq, n_kv_heads=nkv, head_dim=hd, d_ffn=192, vocab=1003, dtype=0)
+    raw = synth.make_weights(cfg, 66, gain_jitter=0.1)
+    prompts = [1, 15, 16, 62, 65, 126, 254, 257, 530]
+    eng = dict(synth.engine_config("mini_gqa"), max_batch=len(prompts), max_seq_len=560, kv_num_blocks=140, max_prefill_tokens=2048, ring_slots=16)
+    worst = parity.stepwise_check(lib, cfg, eng, raw, synth.pack_blob(cfg, raw), _fixed_prompts(cfg, prompts, 5, 266), rtol=1.5e-5)
+    print("fp32 attention", heads, "worst relative logit error", worst)
