@@ -684,7 +684,7 @@ static int init_impl(const blink_config* cfg, blink_engine* e) {
   if (c.dtype == 0) {
     if (int rc = dalloc(e, &c.qkv, (u64)c.maxT * c.qkv_n)) return rc;
     if (int rc = dalloc(e, &c.attn, (u64)c.maxT * c.nq * c.hd)) return rc;
-    if (int rc = dalloc(e, &c.gu, (u64)c.maxT * 2 * c.F)) return rc;
+    if (int rc = dalloc(e, &c.gu, (u64)c.maxT * c.F)) return rc;
   }
   if (int rc = dalloc(e, &c.logits, rows_cap * c.V)) return rc;
   HIPCHK(hipStreamSynchronize(e->compute));
@@ -832,11 +832,12 @@ static int launch_phase(blink_engine* e, const DevCtx& ctx, hipStream_t st, int 
     e->phase_rec[slot] = 1;
     HIPCHK(hipEventRecord(a, st));
   }
-  // the GEMMs of a bf16 model run one eight-wave workgroup per compute unit
+  // the GEMMs of a bf16 model run one eight-wave workgroup per compute unit, and so does the down projection of an fp32 model
   const bool gemm = ph == PH_QKV || ph == PH_OPROJ || ph == PH_GATEUP || ph == PH_DOWN || ph == PH_LM_HEAD || ph == PH_MOE_GATEUP || ph == PH_MOE_DOWN;
   const bool bf16 = e->ctx.dtype == 1;
-  const u32 threads = bf16 && (gemm || ph == PH_ATTN) ? 512u : (u32)BLK_THREADS;
-  HIPCHK(launch(phase_kernel(ph, !bf16), bf16 && gemm ? (u32)e->n_cu : e->grid, threads, st, ctx, layer));
+  const bool down_f32 = !bf16 && ph == PH_DOWN;
+  const u32 threads = down_f32 ? 64u * F32_DOWN_WAVES : bf16 && (gemm || ph == PH_ATTN) ? 512u : (u32)BLK_THREADS;
+  HIPCHK(launch(phase_kernel(ph, !bf16), (bf16 && gemm) || down_f32 ? (u32)e->n_cu : e->grid, threads, st, ctx, layer));
   if (timed) HIPCHK(hipEventRecord(b, st));
   return 0;
 }

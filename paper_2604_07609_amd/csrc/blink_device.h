@@ -291,7 +291,7 @@ struct DevCtx {
   float* x;             // [maxT][d] residual stream
   float* qkv;           // [maxT][qkv_n]
   float* attn;          // [maxT][nq*hd]
-  float* gu;            // [maxT][2F]
+  float* gu;            // [maxT][F] silu(gate) * up
   float* logits;        // [max_batch][V]
   // bf16 path: packed weights and packed activation operands
   const LayerWP* players;

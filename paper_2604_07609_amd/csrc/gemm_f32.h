@@ -7,8 +7,12 @@
 // rotary step was a launch of its own (5 us each). Here the operands come straight from memory into registers, 16 bytes
 // per lane: lane l holds row (or token) l % 16 and k = 4 (l / 16) .. + 3 of sixteen k, and the four matrix instructions of the
 // sixteen take element 0, 1, 2, 3 of both (the order of k inside a sum is free as long as both operands agree). Two schedules:
-//   few tiles: a workgroup of four waves per (row tile, 16 tokens), K in four slices, partial sums joined through LDS;
-//   many tiles (more than twice as many as workgroups): a wave per 32 rows x 32 tokens with the whole of K.
+//   few tiles: a workgroup per (row tile, 16 tokens), K in a slice per wave, partial sums joined through LDS. Four waves, and
+//     eight in the down projection, whose K is the FFN's width (256 x 1024 at 8 tokens 6.5 us, 6.7 with sixteen; the
+//     others, whose loads are one batch per wave already, take 1 to 2 us longer with eight);
+//   many tiles (more than 1024): a wave per 32 rows x 32 tokens with the whole of K.
+// The gate is applied once, where gate and up are computed (as the down projection's operand it was computed anew for every row
+// tile: 256 x 1024 at 8 tokens, with K in four slices, 10.2 us).
 // The norm: its gain multiplies the operand as it is loaded, its scale (one number per token) the finished sum; the
 // squares are summed on the way.
 #pragma once
@@ -17,10 +21,12 @@
 
 #define FA_PLAIN 0
 #define FA_NORM 1       // a(t,k) = x[t][k] * gain[k], the sum scaled by 1 / rms(x[t])
-#define FA_SILU_MUL 2   // a(t,k) = silu(A[t][k]) * A[t][K + k]   (A has 2K columns: gate | up)
 #define FE_STORE 0
 #define FE_ADD 1        // out += result (residual connection, in place)
 #define FE_ROPE 2       // rotary embedding; q to out, k and v into the paged cache
+#define FE_GATE 3       // rows are N/2 gates, then N/2 ups: out[t][j] = silu(gate j) * up j
+#define F32_WAVES 4        // waves per workgroup
+#define F32_DOWN_WAVES 8   // ... in the down projection
 
 struct F32GemmArgs {
   const float* A; u32 lda;
@@ -37,14 +43,17 @@ struct F32GemmArgs {
   u32 nq, nkv, hd, bs;
 };
 
+template <int WAVES>
 struct F32GemmShared {
-  float red[4][2][64][4];   // [wave][row tile][lane][4]
-  float ss[4][16];          // [wave][token]
+  float red[WAVES][2][64][4];       // [wave][row tile][lane][4]
+  float ss[WAVES][16];              // [wave][token]
 };
 
-// Row tiles of 16 come in groups: for FE_ROPE the two tiles whose rows pair up in the rotary embedding (half a head apart).
+// Row tiles of 16 come in groups: for FE_ROPE the two tiles whose rows pair up in the rotary embedding (half a head apart), for
+// FE_GATE a tile of gates and the tile of their ups.
 template <int EMODE>
 __device__ __forceinline__ u32 f32_row(const F32GemmArgs& a, u32 group, u32 tile, u32 per_group) {
+  if (EMODE == FE_GATE) return group * 16 + tile * (a.N / 2);
   if (EMODE != FE_ROPE) return (group * per_group + tile) * 16;
   const u32 half = a.hd / 2, per_head = half / 16;
   return (group / per_head) * a.hd + (group % per_head) * 16 + tile * half;
@@ -63,6 +72,10 @@ __device__ __forceinline__ void f32_store(const F32GemmArgs& a, u32 row, u32 t, 
     for (int i = 0; i < 4; ++i)
       if (row + i < a.N) o[i] = EMODE == FE_ADD ? o[i] + e[i] : e[i];
   }
+}
+__device__ __forceinline__ void f32_store_gate(const F32GemmArgs& a, u32 row, u32 t, float4 g, float4 u) {
+  *(float4*)(a.out + (u64)t * a.ldo + row) = make_float4(g.x / (1.f + __expf(-g.x)) * u.x, g.y / (1.f + __expf(-g.y)) * u.y,
+                                                         g.z / (1.f + __expf(-g.z)) * u.z, g.w / (1.f + __expf(-g.w)) * u.w);
 }
 __device__ __forceinline__ void f32_store_rope(const F32GemmArgs& a, u32 row, u32 t, float4 lo, float4 hi) {
   const u32 half = a.hd / 2, head = row / a.hd, p = row % a.hd;
@@ -86,17 +99,14 @@ __device__ __forceinline__ void f32_store_rope(const F32GemmArgs& a, u32 row, u3
 // One sixteen of k of the operands in flight: RT row tiles, TT token tiles.
 template <int AMODE, int RT, int TT>
 struct F32Chunk {
-  float4 w[RT], x[TT], u[AMODE == FA_SILU_MUL ? TT : 1], g;
+  float4 w[RT], x[TT], g;
 };
 template <int AMODE, int RT, int TT>
 __device__ __forceinline__ void f32_load(const F32GemmArgs& a, const float* const (&wp)[RT], const float* const (&xp)[TT], u32 k, F32Chunk<AMODE, RT, TT>& c) {
 #pragma unroll
   for (int i = 0; i < RT; ++i) c.w[i] = *(const float4*)(wp[i] + k);
 #pragma unroll
-  for (int j = 0; j < TT; ++j) {
-    c.x[j] = *(const float4*)(xp[j] + k);
-    if (AMODE == FA_SILU_MUL) c.u[j] = *(const float4*)(xp[j] + a.K + k);
-  }
+  for (int j = 0; j < TT; ++j) c.x[j] = *(const float4*)(xp[j] + k);
   if (AMODE == FA_NORM) c.g = *(const float4*)(a.gain + k + 4 * ((threadIdx.x & 63) >> 4));
 }
 template <int AMODE, int RT, int TT>
@@ -104,11 +114,6 @@ __device__ __forceinline__ void f32_mul(const F32Chunk<AMODE, RT, TT>& c, floatx
 #pragma unroll
   for (int j = 0; j < TT; ++j) {
     float x[4] = {c.x[j].x, c.x[j].y, c.x[j].z, c.x[j].w};
-    if (AMODE == FA_SILU_MUL) {
-      const float u[4] = {c.u[j].x, c.u[j].y, c.u[j].z, c.u[j].w};
-#pragma unroll
-      for (int i = 0; i < 4; ++i) x[i] = x[i] / (1.f + __expf(-x[i])) * u[i];
-    }
     if (AMODE == FA_NORM) {
       const float g[4] = {c.g.x, c.g.y, c.g.z, c.g.w};
 #pragma unroll
@@ -148,16 +153,24 @@ __device__ __forceinline__ void f32_run(const F32GemmArgs& a, const float* const
   }
 }
 
-template <int AMODE, int EMODE>
-__device__ __forceinline__ void gemm_f32(const F32GemmArgs& a, F32GemmShared& sh, u32 wg, u32 nwg) {
+// the sum of v[0 .. N), in a fixed order, by halves
+template <int N, typename T>
+__device__ __forceinline__ T tree_sum(const T* v) {
+  if constexpr (N == 1) return v[0];
+  else return tree_sum<N / 2>(v) + tree_sum<N / 2>(v + N / 2);
+}
+
+template <int AMODE, int EMODE, int WAVES>
+__device__ __forceinline__ void gemm_f32(const F32GemmArgs& a, F32GemmShared<WAVES>& sh, u32 wg, u32 nwg) {
   if (a.T == 0) return;
   const u32 lane = threadIdx.x & 63, w = threadIdx.x >> 6, lc = lane & 15, lg = lane >> 4;
   const u32 NT = (a.N + 15) / 16, TB = (a.T + 15) / 16, KQ = a.K / 16;
   auto w_ptr = [&](u32 row) { return a.W + (u64)min(row + lc, a.N - 1) * a.K + 4 * lg; };        // (rows and tokens past the end
   auto x_ptr = [&](u32 t) { const u32 r = min(t + lc, a.T - 1); return a.A + (u64)(a.rows ? a.rows[r] : r) * a.lda + 4 * lg; };   // repeat the last one)
   auto scale = [&](float ss) { return 1.0f / sqrtf(ss / (float)a.K + a.eps); };
-  if (NT * TB > 2 * nwg) {
-    const u32 RG = (NT + 1) / 2, TG = (TB + 1) / 2, nw = blockDim.x >> 6;
+  if (NT * TB > 1024) {
+    constexpr u32 nw = WAVES;
+    const u32 RG = (NT + 1) / 2, TG = (TB + 1) / 2;
     for (u32 item = wg * nw + w; item < RG * TG; item += nwg * nw) {
       const u32 rg = item / TG, t0 = (item % TG) * 32;
       const u32 row[2] = {f32_row<EMODE>(a, rg, 0, 2), f32_row<EMODE>(a, rg, 1, 2)};
@@ -184,6 +197,7 @@ __device__ __forceinline__ void gemm_f32(const F32GemmArgs& a, F32GemmShared& sh
 #pragma unroll
           for (int i = 0; i < 2; ++i) v[i] = make_float4(acc[i][j][0] * r, acc[i][j][1] * r, acc[i][j][2] * r, acc[i][j][3] * r);
           if (EMODE == FE_ROPE) f32_store_rope(a, row[0] + 4 * lg, t, v[0], v[1]);
+          else if (EMODE == FE_GATE) f32_store_gate(a, row[0] + 4 * lg, t, v[0], v[1]);
           else {
 #pragma unroll
             for (int i = 0; i < 2; ++i) f32_store<EMODE>(a, row[i] + 4 * lg, t, v[i]);
@@ -193,9 +207,9 @@ __device__ __forceinline__ void gemm_f32(const F32GemmArgs& a, F32GemmShared& sh
     }
     return;
   }
-  constexpr int RT = EMODE == FE_ROPE ? 2 : 1;
-  const u32 RG = NT / RT;                         // (the QKV projection has whole heads)
-  const u32 kb = KQ * w / 4, ke = KQ * (w + 1) / 4;
+  constexpr int RT = EMODE == FE_ROPE || EMODE == FE_GATE ? 2 : 1;
+  const u32 RG = NT / RT;                         // (the QKV projection has whole heads, gate/up whole pairs of tiles)
+  const u32 kb = KQ * w / WAVES, ke = KQ * (w + 1) / WAVES;
   for (u32 item = wg; item < RG * TB; item += nwg) {
     const u32 rg = item / TB, t0 = (item % TB) * 16;
     u32 row[RT];
@@ -221,15 +235,23 @@ __device__ __forceinline__ void gemm_f32(const F32GemmArgs& a, F32GemmShared& sh
     const u32 t = t0 + lc;
     if (w == 0 && t < a.T) {
       float r = 1.f;
-      if (AMODE == FA_NORM) r = scale((sh.ss[0][lc] + sh.ss[1][lc]) + (sh.ss[2][lc] + sh.ss[3][lc]));
+      if (AMODE == FA_NORM) {
+        float p[WAVES];
+#pragma unroll
+        for (int k = 0; k < WAVES; ++k) p[k] = sh.ss[k][lc];
+        r = scale(tree_sum<WAVES>(p));
+      }
       float4 v[RT];
 #pragma unroll
       for (int i = 0; i < RT; ++i) {
-        const floatx4_t s = (*(floatx4_t*)&sh.red[0][i][lane][0] + *(floatx4_t*)&sh.red[1][i][lane][0]) +
-                            (*(floatx4_t*)&sh.red[2][i][lane][0] + *(floatx4_t*)&sh.red[3][i][lane][0]);
+        floatx4_t p[WAVES];
+#pragma unroll
+        for (int k = 0; k < WAVES; ++k) p[k] = *(floatx4_t*)&sh.red[k][i][lane][0];
+        const floatx4_t s = tree_sum<WAVES>(p);
         v[i] = make_float4(s[0] * r, s[1] * r, s[2] * r, s[3] * r);
       }
       if (EMODE == FE_ROPE) f32_store_rope(a, row[0] + 4 * lg, t, v[0], v[RT - 1]);
+      else if (EMODE == FE_GATE) f32_store_gate(a, row[0] + 4 * lg, t, v[0], v[RT - 1]);
       else f32_store<EMODE>(a, row[0] + 4 * lg, t, v[0]);
     }
   }

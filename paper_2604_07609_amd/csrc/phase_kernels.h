@@ -9,9 +9,11 @@
     __shared__ PhaseSharedOf<PH, F32>::type sh;                  \
     run_phase<PH, F32>(c, layer, sh, blockIdx.x, gridDim.x);     \
   }
-// small phases and the phases of an fp32 model: four waves, two workgroups per compute unit
+// small phases and the other phases of an fp32 model: four waves, two workgroups per compute unit
 #define PHASE_KERNEL(name, PH) __global__ void __launch_bounds__(BLK_THREADS, 2) name(DevCtx c, u32 layer) PHASE_KERNEL_BODY(PH, false)
 #define PHASE_KERNEL_F32(name, PH) __global__ void __launch_bounds__(BLK_THREADS, 2) name(DevCtx c, u32 layer) PHASE_KERNEL_BODY(PH, true)
+// the down projection of an fp32 model: eight waves (gemm_f32.h)
+#define PHASE_KERNEL_F32_DOWN(name, PH) __global__ void __launch_bounds__(64 * F32_DOWN_WAVES) name(DevCtx c, u32 layer) PHASE_KERNEL_BODY(PH, true)
 // The GEMMs and the attention of a bf16 model: eight waves, two per SIMD, which stay on their compute unit for the whole launch (up to
 // 1.5 ms). With all 512 registers of a SIMD's lanes between the two, nothing else fits on the chip meanwhile, and the small
 // kernels and copies of blink_submit and blink_poll_outputs wait for the end of the launch. So 240 registers per wave at

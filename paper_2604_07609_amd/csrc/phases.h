@@ -39,11 +39,11 @@ template <> struct PhaseSharedOf<PH_MOE_GATEUP, false> { typedef MoeShared type;
 template <> struct PhaseSharedOf<PH_MOE_DOWN, false> { typedef MoeShared type; };
 template <> struct PhaseSharedOf<PH_MOE_COMBINE, false> { typedef MoeLists type; };
 template <> struct PhaseSharedOf<PH_MOE_PERMUTE, false> { typedef MoeLists type; };
-template <> struct PhaseSharedOf<PH_QKV, true> { typedef F32GemmShared type; };
-template <> struct PhaseSharedOf<PH_OPROJ, true> { typedef F32GemmShared type; };
-template <> struct PhaseSharedOf<PH_GATEUP, true> { typedef F32GemmShared type; };
-template <> struct PhaseSharedOf<PH_DOWN, true> { typedef F32GemmShared type; };
-template <> struct PhaseSharedOf<PH_LM_HEAD, true> { typedef F32GemmShared type; };
+template <> struct PhaseSharedOf<PH_QKV, true> { typedef F32GemmShared<F32_WAVES> type; };
+template <> struct PhaseSharedOf<PH_OPROJ, true> { typedef F32GemmShared<F32_WAVES> type; };
+template <> struct PhaseSharedOf<PH_GATEUP, true> { typedef F32GemmShared<F32_WAVES> type; };
+template <> struct PhaseSharedOf<PH_DOWN, true> { typedef F32GemmShared<F32_DOWN_WAVES> type; };
+template <> struct PhaseSharedOf<PH_LM_HEAD, true> { typedef F32GemmShared<F32_WAVES> type; };
 template <> struct PhaseSharedOf<PH_ATTN, true> { typedef AttnShared type; };
 template <> struct PhaseSharedOf<PH_SAMPLE, true> { typedef SamplerShared type; };
 
@@ -62,25 +62,25 @@ __device__ __forceinline__ void run_phase_f32(const DevCtx& c, u32 layer, typena
       a.positions = c.positions; a.slot_mapping = c.slot_mapping; a.rope_tab = c.rope_tab;
       a.Kc = (float*)c.kv + (u64)layer * c.kv_layer_stride; a.Vc = a.Kc + c.kv_kv_stride;
       a.nq = c.nq; a.nkv = c.nkv; a.hd = c.hd; a.bs = c.bs;
-      gemm_f32<FA_NORM, FE_ROPE>(a, *(F32GemmShared*)&sh, wg, nwg);
+      gemm_f32<FA_NORM, FE_ROPE, F32_WAVES>(a, *(F32GemmShared<F32_WAVES>*)&sh, wg, nwg);
       break;
     case PH_ATTN: phase_attention_f32(c, layer, *(AttnShared*)&sh, wg, nwg); break;
     case PH_OPROJ:
       a.A = c.attn; a.lda = c.nq * c.hd; a.W = (const float*)L->wo; a.out = c.x; a.ldo = c.d; a.N = c.d; a.K = c.nq * c.hd;
-      gemm_f32<FA_PLAIN, FE_ADD>(a, *(F32GemmShared*)&sh, wg, nwg);
+      gemm_f32<FA_PLAIN, FE_ADD, F32_WAVES>(a, *(F32GemmShared<F32_WAVES>*)&sh, wg, nwg);
       break;
     case PH_GATEUP:
-      a.A = c.x; a.lda = c.d; a.gain = L->g2; a.W = (const float*)L->wgu; a.out = c.gu; a.ldo = 2 * c.F; a.N = 2 * c.F; a.K = c.d;
-      gemm_f32<FA_NORM, FE_STORE>(a, *(F32GemmShared*)&sh, wg, nwg);
+      a.A = c.x; a.lda = c.d; a.gain = L->g2; a.W = (const float*)L->wgu; a.out = c.gu; a.ldo = c.F; a.N = 2 * c.F; a.K = c.d;
+      gemm_f32<FA_NORM, FE_GATE, F32_WAVES>(a, *(F32GemmShared<F32_WAVES>*)&sh, wg, nwg);
       break;
     case PH_DOWN:
-      a.A = c.gu; a.lda = 2 * c.F; a.W = (const float*)L->wd; a.out = c.x; a.ldo = c.d; a.N = c.d; a.K = c.F;
-      gemm_f32<FA_SILU_MUL, FE_ADD>(a, *(F32GemmShared*)&sh, wg, nwg);
+      a.A = c.gu; a.lda = c.F; a.W = (const float*)L->wd; a.out = c.x; a.ldo = c.d; a.N = c.d; a.K = c.F;
+      gemm_f32<FA_PLAIN, FE_ADD, F32_DOWN_WAVES>(a, *(F32GemmShared<F32_DOWN_WAVES>*)&sh, wg, nwg);
       break;
     case PH_LM_HEAD:      // one row per sampling sequence (its last token)
       a.T = m->n_samples; a.rows = c.last_idx; a.A = c.x; a.lda = c.d; a.gain = c.gf; a.W = (const float*)c.lm; a.out = c.logits; a.ldo = c.V;
       a.N = c.V; a.K = c.d;
-      gemm_f32<FA_NORM, FE_STORE>(a, *(F32GemmShared*)&sh, wg, nwg);
+      gemm_f32<FA_NORM, FE_STORE, F32_WAVES>(a, *(F32GemmShared<F32_WAVES>*)&sh, wg, nwg);
       break;
     case PH_SAMPLE:
       if (c.spec_k) phase_sample_publish_spec(c, *(SamplerShared*)&sh, wg, nwg);
