@@ -134,6 +134,7 @@ struct AttnMfmaShared {
   float o[ATTN_WAVES][16][128];  // [wave][q head of the group (decode) or query of the tile (prefill)][dim]
   u32 cu_chunks[ATTN_META_MAX + 1], tok[ATTN_META_MAX], ctx[ATTN_META_MAX], bslot[ATTN_META_MAX], pos0[ATTN_META_MAX];
   u32 next_item;   // items taken through a work counter: the next one (prompts), the one after it (decode)
+  u32 last;        // this workgroup is the last of its context's chunks
 };
 
 // Prompt attention with shared KV tiles: a ring of stages of four KV blocks (64 keys), and where every sequence's items begin.
@@ -258,6 +259,53 @@ __device__ __forceinline__ void attn_decode(const DevCtx& c, u32 layer, AttnMfma
   }
 }
 
+// The partial results of a context's chunks merged by the workgroup that finishes the last of them (launches without the
+// merge kernel behind them, see the launcher): every chunk's result has been written past the caches, which are not coherent between
+// the XCDs, before its workgroup counts itself (relaxed atomics of the device's scope and the wave's own counter: a fence of that scope
+// would write back and invalidate a whole L2 each time). No workgroup waits for another, the chunks are added in their order, and the
+// counter is zero again for the next launch.
+__device__ __forceinline__ void st_past_caches(float* p, float v) { __hip_atomic_store((u32*)p, __float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float ld_past_caches(const float* p) { return __uint_as_float(__hip_atomic_load((const u32*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)); }
+template <int HD>
+__device__ __forceinline__ void merge_chunks(const DevCtx& c, AttnMfmaShared& sh, u32 c0, u32 nch, u32 bslot, u32 t, u32 g, u32 G) {
+  asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    u32* const ctr = c.attn_merge_ctr + (u64)bslot * c.nkv + g;
+    const u32 before = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    sh.last = before == nch - 1;
+    if (before == nch - 1) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  if (!__builtin_amdgcn_readfirstlane(sh.last)) return;
+  for (u32 idx = threadIdx.x; idx < G * HD; idx += blockDim.x) {
+    const u32 h = idx / HD, dim = idx % HD;
+    const float* ml = c.attn_part_ml + (((u64)c0 * c.nkv + g) * G + h) * 2;
+    const float* o = c.attn_part_o + (((u64)c0 * c.nkv + g) * G + h) * HD + dim;
+    const u64 step = (u64)c.nkv * G;
+    float M = -INFINITY, L = 0.f, O = 0.f;
+    for (u32 p0 = 0; p0 < nch; p0 += 4) {          // four chunks' results on their way; a new maximum rescales what is there
+      float m[4], l[4], v[4];
+#pragma unroll
+      for (u32 u = 0; u < 4; ++u) {
+        const u64 p = min(p0 + u, nch - 1) * step;
+        m[u] = ld_past_caches(ml + 2 * p); l[u] = ld_past_caches(ml + 2 * p + 1); v[u] = ld_past_caches(o + p * HD);
+      }
+      float Mn = M;
+#pragma unroll
+      for (u32 u = 0; u < 4; ++u) Mn = fmaxf(Mn, m[u]);      // (past the last: that one again)
+      const float f0 = __expf(M - Mn);                       // (exp(-inf) = 0 in the first round: a chunk has a visible key)
+      L *= f0; O *= f0; M = Mn;
+#pragma unroll
+      for (u32 u = 0; u < 4; ++u) {
+        const float f = p0 + u < nch ? __expf(m[u] - Mn) : 0.f;
+        L += l[u] * f; O += v[u] * f;
+      }
+    }
+    c.aq[packed_off(t, (g * G + h) * HD + dim, c.TBS)] = f32_to_f16(O / L);
+  }
+}
+
 // The decode items taken from the scheduler's work list through a counter. What a launch loses against a plain
 // stream of the same tiles is fixed cost, not bandwidth (measured: a launch took 26 us + 11.1 us per full item and
 // compute unit, and 11.1 us per 256 KB item is what a load-only kernel reaches): a second generation of workgroups
@@ -326,6 +374,7 @@ __device__ __forceinline__ void attn_decode_dyn(const DevCtx& c, u32 layer, Attn
   };
   u32 nitem = wg + nwg_eff;
   if (wg >= total_items) return;
+  const bool merge_here = (c.tune_nw & 0x10u) != 0;
   f16x8_t q[1][HD / 32];
   KVTile<HD> t0, t1, t2, t3;
   Round cur = first_round(wg);
@@ -356,11 +405,15 @@ __device__ __forceinline__ void attn_decode_dyn(const DevCtx& c, u32 layer, Attn
       }
       if (it.nch == 1) {
         c.aq[packed_off(it.t, (it.g * G + h) * HD + dim, c.TBS)] = f32_to_f16(O / L);
+      } else if (merge_here) {
+        st_past_caches(po + h * HD + dim, O);
+        if (dim == 0) { st_past_caches(pml + h * 2, M); st_past_caches(pml + h * 2 + 1, L); }
       } else {
         po[(u64)h * HD + dim] = O;
         if (dim == 0) { pml[h * 2] = M; pml[h * 2 + 1] = L; }
       }
     }
+    if (merge_here && it.nch > 1) merge_chunks<HD>(c, sh, it.ci - it.b_lo / ATTN_CHUNK_BLOCKS, it.nch, it.bslot, it.t, it.g, G);
   };
   AttnAcc<HD, 1> acc;
   attn_init(acc);

@@ -300,9 +300,8 @@ struct blink_engine {
   std::mutex dbg_mu;
   // loop
   std::thread launcher;
-  hipGraphExec_t iter_graph = nullptr;        // the kernel chain of one iteration
-  hipGraphExec_t iter_graph_whole = nullptr;  // the chain without the merge kernels of the decode attention (whole_chain_ok)
-  bool whole_chain_ok = false;                // the shorter chain exists for this engine
+  hipGraphExec_t iter_graph[3] = {};          // the kernel chains of one iteration (Chain)
+  bool whole_chain_ok = false, merge_in_ok = false;   // which of the shorter chains exist for this engine
   char *host_step_h = nullptr, *host_step_d = nullptr;   // BLINK_FLAG_HOST_STEP: pinned and device ends of the per-step copies
   u64 host_step_bytes = 0;
   int timed_phase = -1;                 // phase whose launches are bracketed by HIP events (-1: none)
@@ -363,8 +362,7 @@ static u64 expected_weight_bytes(const blink_config* c) {
 }
 
 static void free_all(blink_engine* e) {
-  if (e->iter_graph) (void)hipGraphExecDestroy(e->iter_graph);
-  if (e->iter_graph_whole) (void)hipGraphExecDestroy(e->iter_graph_whole);
+  for (hipGraphExec_t g : e->iter_graph) if (g) (void)hipGraphExecDestroy(g);
   for (hipEvent_t ev : e->events) (void)hipEventDestroy(ev);
   for (hipEvent_t ev : e->phase_ev) (void)hipEventDestroy(ev);
   for (hipEvent_t ev : e->dbg_ev) if (ev) (void)hipEventDestroy(ev);
@@ -644,6 +642,7 @@ static int init_impl(const blink_config* cfg, blink_engine* e) {
       const u32 ncu = (u32)e->n_cu, tune = cfg->tune, qo = c.nq * c.hd;
       const bool moe = c.n_experts != 0;
       for (u32 t = 1; t <= c.gemm_plan_max; ++t) {
+        if (t > 65 && (t - 1) % 64) { plan[t] = plan[t - 1]; continue; }     // (every tile is a multiple of 64 tokens wide)
         plan[t].qkv = gemm_plan(EPI_QKV_ROPE, c.qkv_n, c.d, t, moe, ncu, tune);
         plan[t].oproj = gemm_plan(EPI_RESIDUAL, c.d, qo, t, moe, ncu, tune);
         plan[t].gateup = gemm_plan(EPI_SILU_GATE, 2 * c.F, c.d, t, false, ncu, tune);
@@ -668,6 +667,7 @@ static int init_impl(const blink_config* cfg, blink_engine* e) {
       const u64 chunks = (u64)c.max_batch * ((c.max_seq_len + ATTN_CHUNK_TOKENS - 1) / ATTN_CHUNK_TOKENS), G = c.nq / c.nkv;
       if (int rc = dalloc(e, &c.attn_part_o, chunks * c.nkv * G * c.hd)) return rc;
       if (int rc = dalloc(e, &c.attn_part_ml, chunks * c.nkv * G * 2)) return rc;
+      if (int rc = dalloc(e, &c.attn_merge_ctr, (u64)c.max_batch * c.nkv)) return rc;
     }
   }
   if (int rc = dalloc(e, &e->calib_src, e->calib_bytes)) return rc;
@@ -842,14 +842,16 @@ static int launch_phase(blink_engine* e, const DevCtx& ctx, hipStream_t st, int 
   return 0;
 }
 
-// The kernel chain of one iteration.
-// whole_chain: the chain for iterations whose decode attention takes whole contexts as its items. The scheduler step
-// of this chain is told to make them so whatever the batch (bit 22 of its tuning word), no item leaves a partial
-// result, and the merge kernel behind every attention launch is left out: 32 launches less per iteration on a
-// 32-layer model (an empty kernel costs 4-5 us here, the gap before the next one 2-3 us).
-static int enqueue_iteration_kernels(blink_engine* e, hipStream_t st, u64 enq_index, bool whole_chain) {
+// The kernel chains of one iteration. The merge kernel behind every attention launch (32 per iteration of a 32-layer model; an empty
+// kernel costs 4-5 us here, the gap before the next one 2-3 us) is there in the first only.
+// CHAIN_WHOLE: for iterations whose decode attention takes whole contexts as its items. The scheduler step of this chain is told to
+// make them so whatever the batch (bit 22 of its tuning word), and no item leaves a partial result.
+// CHAIN_MERGE_IN: the attention kernel merges the chunks of a context itself (bit 4).
+enum Chain { CHAIN_MERGE_KERNEL, CHAIN_WHOLE, CHAIN_MERGE_IN };
+static int enqueue_iteration_kernels(blink_engine* e, hipStream_t st, u64 enq_index, Chain kind) {
   DevCtx c = e->ctx;
-  if (whole_chain) c.tune_nw |= 0x400000u;
+  if (kind == CHAIN_WHOLE) c.tune_nw |= 0x400000u;
+  if (kind == CHAIN_MERGE_IN) c.tune_nw |= 0x10u;
   if (c.spec_k) HIPCHK(launch(k_spec_draft, (c.max_batch + 3) / 4, BLK_THREADS, st, c));
   HIPCHK(launch(k_sched, 1, BLK_THREADS, st, c));
   if (int rc = launch_phase(e, c, st, PH_EMBED, 0, enq_index)) return rc;
@@ -859,17 +861,17 @@ static int enqueue_iteration_kernels(blink_engine* e, hipStream_t st, u64 enq_in
   const int *const chain = c.n_experts ? experts : dense, n = (int)(c.n_experts ? sizeof experts : sizeof dense) / (int)sizeof(int);
   for (u32 l = 0; l < c.n_layers; ++l)
     for (int i = 0; i < n; ++i) {
-      if (chain[i] == PH_ATTN_COMBINE && (c.dtype == 0 || whole_chain)) continue;
+      if (chain[i] == PH_ATTN_COMBINE && (c.dtype == 0 || kind != CHAIN_MERGE_KERNEL)) continue;
       if (int rc = launch_phase(e, c, st, chain[i], l, enq_index)) return rc;
     }
   if (int rc = launch_phase(e, c, st, PH_LM_HEAD, 0, enq_index)) return rc;
   return launch_phase(e, c, st, PH_SAMPLE, 0, enq_index);
 }
 
-static int capture_chain(blink_engine* e, bool whole_chain, hipGraphExec_t* out) {
+static int capture_chain(blink_engine* e, Chain kind, hipGraphExec_t* out) {
   hipGraph_t g = nullptr;
   HIPCHK(hipStreamBeginCapture(e->compute, hipStreamCaptureModeThreadLocal));
-  const int rc = enqueue_iteration_kernels(e, e->compute, ~0ull, whole_chain);
+  const int rc = enqueue_iteration_kernels(e, e->compute, ~0ull, kind);
   hipError_t er = hipStreamEndCapture(e->compute, &g);
   if (rc) return rc;
   HIPCHK(er);
@@ -879,36 +881,40 @@ static int capture_chain(blink_engine* e, bool whole_chain, hipGraphExec_t* out)
 }
 
 static int build_graph(blink_engine* e) {
-  // The shorter chain exists where the scheduler can make whole contexts the items of every decode iteration: bf16
+  // The chain for whole contexts exists where the scheduler can make whole contexts the items of every decode iteration: bf16
   // models in the plain mode, unless the tuning word forces chunk items or the static kernel (bits 15, 23) or rules
-  // the chain out (bit 5).
+  // the chain out (bit 5). The one that merges in the attention kernel exists in every mode (not with bits 5 and 23).
   const u32 ext = BLINK_FLAG_CHUNKED_PREFILL | BLINK_FLAG_PREEMPTION | BLINK_FLAG_PREFIX_CACHE | BLINK_FLAG_SPECULATIVE;
   e->whole_chain_ok = e->ctx.dtype == 1 && e->ctx.chunk_rec && !(e->cfg.flags & ext) && !(e->cfg.tune & 0x808020u);
+  e->merge_in_ok = e->ctx.dtype == 1 && e->ctx.chunk_rec && !(e->cfg.tune & 0x800020u);
   if (e->cfg.flags & BLINK_FLAG_NO_GRAPH) return 0;
-  if (int rc = capture_chain(e, false, &e->iter_graph)) return rc;
+  if (int rc = capture_chain(e, CHAIN_MERGE_KERNEL, &e->iter_graph[CHAIN_MERGE_KERNEL])) return rc;
   if (e->whole_chain_ok)
-    if (int rc = capture_chain(e, true, &e->iter_graph_whole)) return rc;
+    if (int rc = capture_chain(e, CHAIN_WHOLE, &e->iter_graph[CHAIN_WHOLE])) return rc;
+  if (e->merge_in_ok)
+    if (int rc = capture_chain(e, CHAIN_MERGE_IN, &e->iter_graph[CHAIN_MERGE_IN])) return rc;
   return 0;
 }
 
 // Which chain the next iteration runs is the launcher's choice, and the only one it makes: from the number of running
-// sequences the scheduler step last mirrored to the host (a plain read of pinned memory, several iterations old, a hint
-// and nothing more) it takes the shorter chain when the device would make whole contexts the items anyway (the same
-// threshold). Either chain is correct for any iteration; a stale hint costs a few iterations with the other item shape.
-static bool pick_whole_chain(const blink_engine* e) {
-  if (!e->whole_chain_ok) return false;
-  if (e->cfg.tune & 0x80u) return true;          // bit 7 of the tuning word: always (tests)
-  const u32 nrun = *(volatile const u32*)&e->hmirror->n_running;
-  return (u64)nrun * e->ctx.nkv >= WHOLE_CONTEXT_PAIRS_PER_CU * (u64)e->ctx.n_cu;
+// sequences and of attention items that the scheduler step last mirrored to the host (plain reads of pinned memory, several iterations old,
+// hints and nothing more) it takes the chain for whole contexts when the device would make those the items anyway (the same
+// threshold), and the one that merges in the attention kernel where that is cheaper (merge_in_attention). Any chain is correct
+// for any iteration; a stale hint costs a few iterations with the other one.
+static Chain pick_chain(const blink_engine* e) {
+  const u32 nrun = *(volatile const u32*)&e->hmirror->n_running, items = *(volatile const u32*)&e->hmirror->attn_items;
+  if (e->whole_chain_ok && ((e->cfg.tune & 0x80u) || (u64)nrun * e->ctx.nkv >= WHOLE_CONTEXT_PAIRS_PER_CU * (u64)e->ctx.n_cu)) return CHAIN_WHOLE;
+  if (e->merge_in_ok && ((e->cfg.tune & 0x8u) || merge_in_attention(items, e->ctx.hd, (u32)e->ctx.n_cu))) return CHAIN_MERGE_IN;
+  return CHAIN_MERGE_KERNEL;
 }
 
 static int enqueue_iteration(blink_engine* e, u64 enq_index) {
-  const bool whole = pick_whole_chain(e);
-  if (e->iter_graph && e->timed_phase < 0) {
-    HIPCHK(hipGraphLaunch(whole ? e->iter_graph_whole : e->iter_graph, e->compute));
+  const Chain kind = pick_chain(e);
+  if (e->iter_graph[kind] && e->timed_phase < 0) {
+    HIPCHK(hipGraphLaunch(e->iter_graph[kind], e->compute));
     return 0;
   }
-  return enqueue_iteration_kernels(e, e->compute, enq_index, whole);
+  return enqueue_iteration_kernels(e, e->compute, enq_index, kind);
 }
 
 // durations of the timed phase for the iteration enqueued at enq_index (its events have completed). A phase without kernels in

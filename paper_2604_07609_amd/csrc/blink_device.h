@@ -152,6 +152,13 @@ __host__ __device__ __forceinline__ bool prompt_shared_pays(u32 tiles, u32 seqs,
 // (sequence, kv head) pairs per compute unit from which the decode attention's work items are whole contexts; the
 // launcher takes the kernel chain without the merge kernels from the same count (read from the host mirror)
 #define WHOLE_CONTEXT_PAIRS_PER_CU 4ull
+// Whether the attention kernel merges a context's chunks itself (the launcher's choice of chain, from the items mirrored to the host):
+// with heads of 128 whenever there are chunks, with heads of 64 up to three items per compute unit. An item of 64-wide heads
+// is half as long, and what a merge costs a workgroup (its stores, a count, two barriers: 2 us per item) is then more than the merge
+// kernel, 7 us a launch. Decode iteration with / without the merge kernel, ms: 32 q / 8 kv heads of 128, 4 layers, 16 sequences at 900 / 1700 keys .547 / .606 and
+// .545 / .588, 61 sequences .791 / .951 and .792 / .936, 32 / 4 heads of 128, 96 sequences .787 / .867 and .776 / .842; 16 / 16 of 64, 8 layers, 16 sequences
+// at 900 / 1700 / 2500 keys .521 / .586 / .649 and .520 / .588 / .677.
+__host__ __forceinline__ bool merge_in_attention(u32 items, u32 hd, u32 ncu) { return hd >= 128 || items <= 3 * ncu; }
 
 // One work item of the decode attention (times the kv heads), as the kernel takes it from the scheduler (32 bytes: one
 // scalar load of a wave): a run of KV blocks of one decoding sequence that one workgroup walks, ATTN_CHUNK_TOKENS at a
@@ -190,6 +197,8 @@ struct HostMirror {
   u32 n_running;
   u32 idle;
   u64 clock_probe;      // device clock written by the clock probe kernel
+  u32 attn_items;       // work items of the decode attention in the last iteration (kv heads included)
+  u32 pad;
   u64 progress;         // chains whose scheduler step has run (upper half) and iterations begun (lower half), one store
 };
 
@@ -322,6 +331,7 @@ struct DevCtx {
   // decode attention: partial (max, sum, output) of every chunk of a context longer than one chunk
   float* attn_part_o;   // [chunk][kv head][G][hd]
   float* attn_part_ml;  // [chunk][kv head][G][2]
+  u32* attn_merge_ctr;  // [max_batch][nkv] chunks of a context that are done, where the attention kernel merges them itself (zeros between launches)
 };
 
 __device__ __forceinline__ u64 dev_now_ns() { return wall_clock64() * 10ull; }  // 100 MHz constant clock

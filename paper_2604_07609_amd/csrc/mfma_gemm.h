@@ -71,7 +71,8 @@ struct MfmaGemmArgs {
   u64* part;               // split K: the slices' sums, at most one 256 x 128 tile of floats per compute unit, and a count per tile (zeros between launches)
   u32* part_count;
   u32 tune_nw;             // tests and tuning. Low three bits: 0 automatic choice of weight tiles per workgroup of the streaming schedule, 1/2 forced.
-                           // Bit 5 (launcher): never the kernel chain without the decode attention's merge kernels, bit 7: always.
+                           // Bit 5 (launcher): never a kernel chain without the decode attention's merge kernels, bit 7: always the one for whole contexts, bit 3: always
+                           // the one whose attention merges chunks itself. Bit 4 (set in that chain): it does.
                            // Bit 6: epilogues load their operands tile by tile. Bit 11: tall matrices stream too at T <= 64.
                            // Bits 12-14: force the tile shape at T > 64, with them bits 24-27 the slices of K (gemm_plan).
                            // Bit 15 (scheduler): the decode attention's work items are always chunks, bit 22: always whole

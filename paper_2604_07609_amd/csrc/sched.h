@@ -978,6 +978,7 @@ __device__ void sched_step(const DevCtx& c, SchedShared& sh) {
     c.hmirror->tokens_out = ss->tokens_out;
     c.hmirror->n_running = nrun;
     c.hmirror->error = ss->error;
+    c.hmirror->attn_items = (n_full + n_part) * c.nkv;
     c.hmirror->idle = kind == KIND_IDLE;
     __hip_atomic_store(&c.hmirror->stopped, stopped, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }

@@ -191,3 +191,14 @@ def test_fp32_attention(lib, heads):
     eng = dict(synth.engine_config("mini_gqa"), max_batch=len(prompts), max_seq_len=560, kv_num_blocks=140, max_prefill_tokens=2048, ring_slots=16)
     worst = parity.stepwise_check(lib, cfg, eng, raw, synth.pack_blob(cfg, raw), _fixed_prompts(cfg, prompts, 5, 266), rtol=1.5e-5)
     print("fp32 attention", heads, "worst relative logit error", worst)
+
+
+@pytest.mark.parametrize("name,prompts", [("mini_gqa128", [1030, 2070, 7, 511, 1023]), ("mini_gqa", [6300, 512, 40]), ("mini_kv8", [1030] * 24)])
+def test_decode_attention_merges_chunks_itself(lib, name, prompts):
+    """Bit 3 of the tuning word: always the chain without the merge kernel whose attention kernel merges a context's chunks. One chunk, two
+    to thirteen, contexts that grow by a chunk on the way, and more items than workgroups (24 sequences x 8 kv heads x 3 chunks)."""
+    cfg, eng, raw, blob = setup(name, 67)
+    blocks = sum((n + 20) // 16 + 1 for n in prompts)
+    eng = dict(eng, max_batch=len(prompts), max_seq_len=max(prompts) + 16, kv_num_blocks=blocks, max_prefill_tokens=8192, ring_slots=32)
+    worst = parity.stepwise_check(lib, cfg, eng, raw, blob, _fixed_prompts(cfg, prompts, 5, 267), rtol=RTOL, tune=0x8)
+    print(name, "chunks merged in the attention kernel, worst relative logit error", worst)
