@@ -133,12 +133,69 @@ __device__ __forceinline__ void bitonic_sort_desc(unsigned long long* v, u32 n) 
   }
 }
 
-// Leaves the k largest composite keys (order_key(logit) << 32 | ~id) of the row in sh.cand[0..k), descending, the
-// rest of sh.cand[0..npow) holding smaller keys or zero padding. Returns npow (a power of two >= k).
+// ---- the 64 largest of four keys per lane, in one wave without barriers ------------------------------------------------
+// the value of lane l ^ X
+template <int X>
+__device__ __forceinline__ u32 lane_xor(u32 lane, u32 v) {
+  if constexpr (X == 1) return (u32)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true);
+  else if constexpr (X == 2) return (u32)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true);
+  else if constexpr (X == 4) return (u32)__builtin_amdgcn_ds_swizzle((int)v, 0x101F);
+  else if constexpr (X == 8) return (u32)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xF, 0xF, true);     // a row of sixteen lanes rotated by eight
+  else if constexpr (X == 16) { const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false); return (lane & 16u) ? a[0] : a[1]; }
+  else { const auto a = __builtin_amdgcn_permlane32_swap(v, v, false, false); return (lane & 32u) ? a[0] : a[1]; }
+}
+template <int X>
+__device__ __forceinline__ unsigned long long lane_xor64(u32 lane, unsigned long long v) {
+  return ((unsigned long long)lane_xor<X>(lane, (u32)(v >> 32)) << 32) | lane_xor<X>(lane, (u32)v);
+}
+// One step of a bitonic network on N lists of 64 (an element per lane); `first`: this lane, the one without bit X, gets the larger key.
+template <int X, int N>
+__device__ __forceinline__ void bitonic_step(u32 lane, unsigned long long (&v)[N], const bool (&larger_first)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const unsigned long long p = lane_xor64<X>(lane, v[i]);
+    const bool keep_larger = ((lane & X) == 0) == larger_first[i];
+    v[i] = (v[i] > p) == keep_larger ? v[i] : p;
+  }
+}
+// bitonic lists (of which each half is sorted, one way up and one down) into order: descending or ascending per list
+template <int N>
+__device__ __forceinline__ void bitonic_merge(u32 lane, unsigned long long (&v)[N], const bool (&desc)[N]) {
+  bitonic_step<32>(lane, v, desc); bitonic_step<16>(lane, v, desc); bitonic_step<8>(lane, v, desc);
+  bitonic_step<4>(lane, v, desc); bitonic_step<2>(lane, v, desc); bitonic_step<1>(lane, v, desc);
+}
+template <int N>
+__device__ __forceinline__ void bitonic_sort(u32 lane, unsigned long long (&v)[N], const bool (&desc)[N]) {
+  auto dir = [&](u32 size, bool (&d)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) d[i] = ((lane & size) == 0) == desc[i];
+  };
+  bool d[N];
+  dir(2, d); bitonic_step<1>(lane, v, d);
+  dir(4, d); bitonic_step<2>(lane, v, d); bitonic_step<1>(lane, v, d);
+  dir(8, d); bitonic_step<4>(lane, v, d); bitonic_step<2>(lane, v, d); bitonic_step<1>(lane, v, d);
+  dir(16, d); bitonic_step<8>(lane, v, d); bitonic_step<4>(lane, v, d); bitonic_step<2>(lane, v, d); bitonic_step<1>(lane, v, d);
+  dir(32, d); bitonic_step<16>(lane, v, d); bitonic_step<8>(lane, v, d); bitonic_step<4>(lane, v, d); bitonic_step<2>(lane, v, d); bitonic_step<1>(lane, v, d);
+  bitonic_merge(lane, v, desc);
+}
+// Of four lists sorted descending, ascending, descending, ascending: the 64 largest of all, sorted. (The larger of each pair of a descending
+// and an ascending list are the 64 largest of the two, and bitonic.)
+__device__ __forceinline__ unsigned long long top64_of_four(u32 lane, const unsigned long long (&v)[4], bool desc) {
+  unsigned long long h[2] = {v[0] > v[1] ? v[0] : v[1], v[2] > v[3] ? v[2] : v[3]};
+  const bool dirs[2] = {true, false};
+  bitonic_merge(lane, h, dirs);
+  unsigned long long m[1] = {h[0] > h[1] ? h[0] : h[1]};
+  const bool dir1[1] = {desc};
+  bitonic_merge(lane, m, dir1);
+  return m[0];
+}
+
+// Leaves the k largest composite keys (order_key(logit) << 32 | ~id) of the row in sh.cand[0..k), descending. Returns npow, a power of
+// two >= k, by which the candidates are dealt to the threads (what lies behind the k largest is not read).
 __device__ __forceinline__ u32 select_top_k(const float* row, u32 V, u32 k, SamplerShared& sh) {
   const u32 tid = threadIdx.x;
   // (1) One pass: every thread keeps the four largest keys among the elements it visits and the largest logit it
-  // dropped. The 1024 kept keys are sorted; their k-th largest is the exact threshold unless some thread dropped
+  // dropped. Of the 1024 kept keys the largest are sorted; their k-th largest is the exact threshold unless some thread dropped
   // a logit at or above its logit (a tie with the threshold's logit goes to the exact stages below).
   if (k <= 256) {
     // Sorted by (logit descending, id ascending): a thread meets its ids in ascending order, so among equal logits the
@@ -152,13 +209,30 @@ __device__ __forceinline__ u32 select_top_k(const float* row, u32 V, u32 k, Samp
 #undef TOPK_PLACE
       dropped = max(dropped, xk);      // the logit key of whatever fell out at the bottom
     });
+    unsigned long long v[4] = {q0 ? ((unsigned long long)q0 << 32) | (u32)~i0 : 0ull, q1 ? ((unsigned long long)q1 << 32) | (u32)~i1 : 0ull,
+                               q2 ? ((unsigned long long)q2 << 32) | (u32)~i2 : 0ull, q3 ? ((unsigned long long)q3 << 32) | (u32)~i3 : 0ull};
     __syncthreads();
-    sh.cand[tid * 4] = q0 ? ((unsigned long long)q0 << 32) | (u32)~i0 : 0ull;
-    sh.cand[tid * 4 + 1] = q1 ? ((unsigned long long)q1 << 32) | (u32)~i1 : 0ull;
-    sh.cand[tid * 4 + 2] = q2 ? ((unsigned long long)q2 << 32) | (u32)~i2 : 0ull;
-    sh.cand[tid * 4 + 3] = q3 ? ((unsigned long long)q3 << 32) | (u32)~i3 : 0ull;
-    __syncthreads();
-    bitonic_sort_desc(sh.cand, SAMPLER_MAX_K);
+    if (k <= 64) {
+      // every wave's 64 largest of its 256, in registers, then the 64 largest of the four waves' by the first wave (the sort of
+      // all 1024 in LDS is 55 steps behind a barrier each: 14 us of a launch of 25 at 16 rows of 8192)
+      u32 lane = tid & 63u;
+      asm volatile("" : "+v"(lane));      // (or the masks of all steps are made at the start of the kernel, also of a launch that needs none)
+      const bool dirs[4] = {true, false, true, false};
+      bitonic_sort(lane, v, dirs);
+      const unsigned long long mine = top64_of_four(lane, v, (tid & 64u) == 0);
+      sh.cand[tid] = mine;
+      __syncthreads();
+      if (tid < 64) {
+        const unsigned long long w[4] = {mine, sh.cand[64 + tid], sh.cand[128 + tid], sh.cand[192 + tid]};
+        sh.cand[tid] = top64_of_four(lane, w, true);
+      }
+      __syncthreads();
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) sh.cand[tid * 4 + j] = v[j];
+      __syncthreads();
+      bitonic_sort_desc(sh.cand, SAMPLER_MAX_K);
+    }
     const u32 thr = (u32)(sh.cand[k - 1] >> 32);
     const u32 worst = block_max(dropped, sh.misc);
     if (worst < thr) return SAMPLER_MAX_K;      // every dropped logit lies strictly below the k-th kept one
@@ -304,10 +378,11 @@ __device__ __forceinline__ void phase_sample_publish(const DevCtx& c, SamplerSha
     if (tid == 0) {
       const u32 idx = r.gen;
       const u32 slot = r.ring_slot;
-      OutRec* o = c.out_arena + (u64)slot * c.max_seq_len + idx;
-      o->token = token;
-      o->iteration = meta->iteration;
-      o->device_ns = dev_now_ns();
+      // The record, then, once it has been written, state and generation count as one 64-bit word: all past the caches (relaxed, system
+      // scope), so that no fence has to write back an L2 (two of them a row).
+      u64* const o = (u64*)(c.out_arena + (u64)slot * c.max_seq_len + idx);
+      __hip_atomic_store(o, (u64)(u32)token | ((u64)meta->iteration << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      __hip_atomic_store(o + 1, dev_now_ns(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
       r.gen = idx + 1;
       r.last_token = token;
       r.paused = 0;             // the status word written below says PROCESSING or COMPLETED (a resumed request was PAUSED until now)
@@ -317,10 +392,9 @@ __device__ __forceinline__ void phase_sample_publish(const DevCtx& c, SamplerSha
         r.finished = 1;
         state = SLOT_DECODE_COMPLETED;
       }
-      __threadfence_system();
-      // state and generation count are published together as one 64-bit word
       const u64 word = (u64)state | ((u64)(idx + 1) << 32);
-      __hip_atomic_store((u64*)&c.status[slot], word, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+      asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+      __hip_atomic_store((u64*)&c.status[slot], word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
     __syncthreads();
   }

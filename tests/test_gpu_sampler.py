@@ -110,3 +110,20 @@ def test_parameter_errors(lib):
         with pytest.raises(lib.BlinkError) as ei:
             lib.sample_rows(rows, [bad], [0])
         assert ei.value.code == lib.ERR_INVAL
+
+
+@pytest.mark.parametrize("V", [70, 300, 4099, 8192])
+def test_top_k_around_a_wave(lib, V):
+    """Up to 64 candidates are sorted in the registers of a wave, more in LDS: top_k of 1, 2, 63, 64 and 65 on continuous rows, on rows of few distinct
+    values (ties across the cut, decided by the id) and on rows whose largest values all meet one thread."""
+    rng = np.random.default_rng(V)
+    ks = [1, 2, 63, 64, 65]
+    rows, params = [], []
+    for i, k in enumerate(ks):
+        one_thread = rng.normal(0.0, 0.1, V)
+        one_thread[: 4 * 12 : 4] += 3.0
+        for j, row in enumerate((rng.normal(0.0, 1.5, V), rng.integers(0, 40, V) / 8.0, one_thread)):
+            rows.append(row)
+            params.append(P(top_k=k, top_p=[0.95, 1.0, 0.6][j], seed=77 + 10 * i + j))
+    n = check(lib, np.stack(rows), params, np.arange(len(rows)) % 5)
+    print("decided", n, "of", len(rows))
