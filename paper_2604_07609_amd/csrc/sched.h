@@ -48,6 +48,7 @@ struct SchedShared {
   alignas(16) u32 dec_key[SCHED_MAX_BATCH];   // per batch slot: sort key of a decoding sequence (0: none), its chunk id ...
   u32 dec_si[SCHED_MAX_BATCH];
   u32 dec_tok[SCHED_MAX_BATCH];      // ... and the index of its token
+  u32 scan_part[BLK_THREADS / WAVE][16];      // block_scan_many
   u32 flag;
   u32 exit_idle;
   u64 chain;
@@ -216,6 +217,65 @@ __device__ __forceinline__ u64 block_max64(u64 v, u64* part) {
   return m;
 }
 
+// Whether the predicate holds for any thread.
+__device__ __forceinline__ bool block_any(bool pred, u32* part) {
+  const bool wave = __ballot(pred) != 0;
+  __syncthreads();
+  if ((threadIdx.x & 63u) == 0) part[threadIdx.x >> 6] = wave;
+  __syncthreads();
+  u32 any = 0;
+#pragma unroll
+  for (u32 i = 0; i < BLK_THREADS / WAVE; ++i) any |= part[i];
+  return any != 0;
+}
+
+// Inclusive prefix sum (or running maximum) over the lanes of a wave by DPP: shifts by 1, 2, 4, 8 inside the rows of sixteen lanes, then the last
+// lane of a row to the row behind it, and of the lower half to the upper one.
+template <bool MAX, int CTRL, int ROWS>
+__device__ __forceinline__ u32 dpp_step(u32 v) {
+  const u32 x = (u32)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+  return MAX ? max(v, x) : v + x;
+}
+template <bool MAX>
+__device__ __forceinline__ u32 wave_incl(u32 v) {
+  v = dpp_step<MAX, 0x111, 0xF>(v); v = dpp_step<MAX, 0x112, 0xF>(v); v = dpp_step<MAX, 0x114, 0xF>(v); v = dpp_step<MAX, 0x118, 0xF>(v);
+  v = dpp_step<MAX, 0x142, 0xA>(v);
+  return dpp_step<MAX, 0x143, 0xC>(v);
+}
+// NS exclusive prefix sums with their totals, and NM maxima, over the 256 threads behind one pair of barriers. v: values in, sums out.
+template <int NS, int NM>
+__device__ __forceinline__ void block_scan_many(u32 (&v)[NS], u32 (&total)[NS], u32 (&mx)[NM], u32 (&part)[BLK_THREADS / WAVE][16]) {
+  static_assert(NS + NM <= 16, "room in part");
+  const u32 lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
+  u32 inc[NS];
+#pragma unroll
+  for (int i = 0; i < NS; ++i) inc[i] = wave_incl<false>(v[i]);
+#pragma unroll
+  for (int i = 0; i < NM; ++i) mx[i] = wave_incl<true>(mx[i]);
+  __syncthreads();
+  if (lane == 63u) {
+#pragma unroll
+    for (int i = 0; i < NS; ++i) part[w][i] = inc[i];
+#pragma unroll
+    for (int i = 0; i < NM; ++i) part[w][NS + i] = mx[i];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NS; ++i) {
+    u32 base = 0;
+    total[i] = 0;
+#pragma unroll
+    for (u32 k = 0; k < BLK_THREADS / WAVE; ++k) { const u32 x = part[k][i]; base += k < w ? x : 0u; total[i] += x; }
+    v[i] = base + inc[i] - v[i];
+  }
+#pragma unroll
+  for (int i = 0; i < NM; ++i) {
+    mx[i] = 0;
+#pragma unroll
+    for (u32 k = 0; k < BLK_THREADS / WAVE; ++k) mx[i] = max(mx[i], part[k][NS + i]);
+  }
+}
+
 // Number of leading threads (thread 0 upwards) whose predicate holds.
 __device__ __forceinline__ u32 block_prefix_count(bool pred, u32* part) {
   const u32 w = threadIdx.x >> 6;
@@ -243,22 +303,33 @@ __device__ void sched_step(const DevCtx& c, SchedShared& sh) {
   const u32 tid = threadIdx.x;
   SchedState* ss = c.ss;
 
+  // The step is a chain of memory latencies with little work between them, so what can be asked for is asked for here, while the host's
+  // control word (a read over the bus, 1.5 us) is on its way: the state, the requests' entries (into the caches) and the
+  // slots of the next tickets.
+  u32 top = ss->free_top, committed = ss->committed, nrun = ss->n_running, lo = ss->free_lo, pinned = ss->pinned;
+  const u64 next0 = ss->next_ticket;
+  const bool running = nrun != 0;
+  const u32* const entry = (const u32*)(c.run + min(tid, c.max_batch - 1));
+  const u32 warm0 = entry[0], warm1 = entry[sizeof(RunEntry) / 4 - 1];
+  const u32 slot_state = __hip_atomic_load(&c.status[(u32)(next0 + tid) & (c.ring_slots - 1)].state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   // ---- window gate -----------------------------------------------------------------------------------
   if (tid == 0) {
+    const u64 ctrl = __hip_atomic_load((const u64*)c.hctrl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);     // both words at once
+    static_assert(offsetof(HostCtrl, stop) == 0 && offsetof(HostCtrl, exit_when_idle) == 4 && sizeof(HostCtrl) == 8, "control words");
     const u64 chain = ss->chains;
     ss->chains = chain + 1;
     sh.chain = chain;
     u32 stop = ss->stopped | ss->error;
     const u64 iter_limit = ss->iter_limit;
     if (iter_limit != 0 && ss->iteration >= iter_limit) stop = 1;
-    if (__hip_atomic_load(&c.hctrl->stop, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_SYSTEM)) stop = 1;
+    if ((u32)ctrl) stop = 1;
     // ---- idle poll: nothing is running, so only a new arrival can give this iteration work. One thread watches the
     // slot of the next ticket (and the stop word) until the slot turns pending or the time allowed has passed; the
     // wait is bounded by the device clock, so the kernel always ends.
-    const u32 exit_idle = __hip_atomic_load(&c.hctrl->exit_when_idle, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    const u32 exit_idle = (u32)(ctrl >> 32);
     sh.exit_idle = exit_idle;
-    if (!stop && ss->n_running == 0 && !exit_idle) {
-      const u64 t0 = dev_now_ns(), next = ss->next_ticket;
+    if (!stop && !running && !exit_idle) {
+      const u64 t0 = dev_now_ns(), next = next0;
       const u32 slot = (u32)(next & (u64)(c.ring_slots - 1));
       for (;;) {
         if (__hip_atomic_load(&c.status[slot].state, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_SYSTEM) == SLOT_PREFILL_PENDING &&
@@ -286,12 +357,10 @@ __device__ void sched_step(const DevCtx& c, SchedShared& sh) {
     return;
   }
 
-  u32 top = ss->free_top, committed = ss->committed, nrun = ss->n_running;
-  const u64 next0 = ss->next_ticket;
+  asm volatile("" : : "v"(warm0), "v"(warm1));
   const u32 mbs = c.max_blocks_per_seq;
   const bool pcache = (c.flags & 128u) != 0;
-  u32 lo = ss->free_lo, pinned = ss->pinned, hits = 0;
-  __syncthreads();
+  u32 hits = 0;
 
   // ---- (1) retire, batch slot ascending; blocks go back in block-table order ------------------------------
   if (pcache) {
@@ -353,6 +422,7 @@ __device__ void sched_step(const DevCtx& c, SchedShared& sh) {
   for (u32 base = 0; base < c.max_batch; base += BLK_THREADS) {
     const u32 b = base + tid;
     const bool fin = b < c.max_batch && c.run[b].valid && c.run[b].finished;
+    if (!block_any(fin, sh.wave_part)) continue;
     const u32 nb = fin ? c.run[b].n_blocks : 0u;
     u32 tot, tot_resv, tot_fin;
     const u32 off = block_excl_scan(nb, tot, sh.wave_part);
@@ -366,17 +436,22 @@ __device__ void sched_step(const DevCtx& c, SchedShared& sh) {
   }
   __syncthreads();
 
-  // ---- free batch slots, ascending -----------------------------------------------------------------------
+  // ---- free batch slots, ascending (listed when the first request asks for one) ---------------------------
   u32 n_free = 0;
-  for (u32 base = 0; base < c.max_batch; base += BLK_THREADS) {
-    const u32 b = base + tid;
-    const bool fr = b < c.max_batch && !c.run[b].valid;
-    u32 tot;
-    const u32 off = block_excl_scan(fr ? 1u : 0u, tot, sh.wave_part);
-    if (fr) sh.free_list[n_free + off] = b;
-    n_free += tot;
-  }
-  __syncthreads();
+  bool listed = false;
+  auto list_free = [&]() {
+    if (listed) return;
+    listed = true;
+    for (u32 base = 0; base < c.max_batch; base += BLK_THREADS) {
+      const u32 b = base + tid;
+      const bool fr = b < c.max_batch && !c.run[b].valid;
+      u32 tot;
+      const u32 off = block_excl_scan(fr ? 1u : 0u, tot, sh.wave_part);
+      if (fr) sh.free_list[n_free + off] = b;
+      n_free += tot;
+    }
+    __syncthreads();
+  };
 
   // ---- chunked prefill: the token budget of the iteration goes first to the running requests (one token per decoding
   // request, then the one request that may be part-way through its prompt); admissions take what is left ----------
@@ -406,6 +481,7 @@ __device__ void sched_step(const DevCtx& c, SchedShared& sh) {
   const bool preempt = (c.flags & 64u) != 0;
   u32 resumed = 0, promised = 0, tokens_admitted = 0, n_pre = preempt ? ss->n_preempted : 0u;
   bool blocked = false;
+  if (n_pre > 0) list_free();
   while (n_pre > 0 && !blocked) {
     u64 key = 0;                                   // smallest ticket = largest inverted ticket; low bits: the entry's index
     for (u32 i = tid; i < n_pre; i += BLK_THREADS) {
@@ -451,14 +527,18 @@ __device__ void sched_step(const DevCtx& c, SchedShared& sh) {
     bool pend = false;
     u32 P = 0, max_new = 0;
     if (tid < c.ring_slots) {
-      const u32 st = __hip_atomic_load(&c.status[slot].state, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_SYSTEM);
-      if (st == SLOT_PREFILL_PENDING) {
+      // (the state asked for at the beginning says whether there is anything to acquire; an idle poll is newer than that)
+      const bool early = admitted == 0 && running;
+      if ((!early || slot_state == SLOT_PREFILL_PENDING) &&
+          __hip_atomic_load(&c.status[slot].state, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_SYSTEM) == SLOT_PREFILL_PENDING) {
         const u64 tk = __hip_atomic_load(&c.desc[slot].ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         pend = tk == t;
       }
     }
     const u32 vis = block_prefix_count(pend, sh.wave_part);
     tail = next0 + admitted + vis;
+    if (vis == 0) break;
+    list_free();
     const bool cand = tid < vis;
     if (cand) {
       P = __hip_atomic_load(&c.desc[slot].n_prompt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -693,18 +773,17 @@ __device__ void sched_step(const DevCtx& c, SchedShared& sh) {
         else ntok = 0;
         nrow = smp ? ((spec_k && !pref) ? ntok : 1u) : 0u;    // logits rows: the last token; every token of a decoding sequence when drafts are verified
       }
-      u32 tots, tota, tott, totq, totc, totm, totx, totf, totp, totr, totd;
       const u32 ctx_after = in ? pos0 + ntok : 0u;
       const bool dec_seq = in && !multi;
       const u32 nch = !dec_seq ? 0u : group ? 1u : (ctx_after + ATTN_CHUNK_TOKENS - 1) / ATTN_CHUNK_TOKENS;
       const u32 nfull = (!dec_seq || group) ? 0u : ctx_after / ATTN_CHUNK_TOKENS;
-      u32 foff, poff, coff, qoff, si, mi, aoff, toff, ri, doff;
-      block_excl_scan2(nfull, nch - nfull, foff, poff, totf, totp, sh.part64);
-      block_excl_scan2(nch, multi ? (ntok + 15) / 16 : 0u, coff, qoff, totc, totq, sh.part64);
-      block_excl_scan2(in ? 1u : 0u, smp ? 1u : 0u, si, mi, tots, totm, sh.part64);
-      block_excl_scan2(nalloc, ntok, aoff, toff, tota, tott, sh.part64);
-      block_excl_scan2(nrow, (in && !pref) ? 1u : 0u, ri, doff, totr, totd, sh.part64);
-      block_excl_scan(ctx_after, totx, sh.wave_part);     // context tokens the attention of this iteration reads
+      // offsets: full and partly filled chunks, all chunks, query tiles, sequences, sampling ones, blocks, tokens, logits rows, decoding
+      // sequences, context tokens the attention reads (their total)
+      u32 sum[11] = {nfull, nch - nfull, nch, multi ? (ntok + 15) / 16 : 0u, in ? 1u : 0u, smp ? 1u : 0u, nalloc, ntok, nrow, (in && !pref) ? 1u : 0u, ctx_after};
+      u32 tot[11], mx[3] = {ntok, ctx_after, multi ? ctx_after : 0u};
+      block_scan_many(sum, tot, mx, sh.scan_part);
+      u32 foff = sum[0], poff = sum[1], coff = sum[2], qoff = sum[3], si = sum[4], mi = sum[5], aoff = sum[6], toff = sum[7], ri = sum[8];
+      const u32 totf = tot[0], totp = tot[1], totc = tot[2], totq = tot[3], tots = tot[4], totm = tot[5], tota = tot[6], tott = tot[7], totr = tot[8], totd = tot[9], totx = tot[10];
       foff += n_full; poff += n_part; coff += n_ch; qoff += n_qt; si += n_seqs; mi += n_smp; aoff += n_alloc; toff += n_tok; ri += n_rows;
       n_dec_seq += totd;
       if (in) {
@@ -763,9 +842,9 @@ __device__ void sched_step(const DevCtx& c, SchedShared& sh) {
       }
       // (sort key of a decoding sequence: context length, then the lower batch slot first; unique, 0 for no sequence)
       if (group && b < SCHED_MAX_BATCH) { sh.dec_key[b] = (b < c.max_batch && dec_seq) ? (ctx_after << 10) | (1023u - b) : 0u; sh.dec_si[b] = coff; sh.dec_tok[b] = toff; }
-      max_q = max(max_q, block_max(ntok, sh.wave_part2));
-      max_ctx = max(max_ctx, block_max(ctx_after, sh.wave_part));
-      max_pref = max(max_pref, block_max(multi ? ctx_after : 0u, sh.wave_part2));
+      max_q = max(max_q, mx[0]);
+      max_ctx = max(max_ctx, mx[1]);
+      max_pref = max(max_pref, mx[2]);
       n_ctx += totx;
       n_seqs += tots;
       n_alloc += tota;
@@ -980,6 +1059,7 @@ __device__ void sched_step(const DevCtx& c, SchedShared& sh) {
     c.hmirror->error = ss->error;
     c.hmirror->attn_items = (n_full + n_part) * c.nkv;
     c.hmirror->idle = kind == KIND_IDLE;
-    __hip_atomic_store(&c.hmirror->stopped, stopped, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    // (the launcher reads it behind the chain's event, which orders it: a release here would write back an L2 first)
+    __hip_atomic_store(&c.hmirror->stopped, stopped, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
