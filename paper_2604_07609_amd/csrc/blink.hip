@@ -628,7 +628,7 @@ static int init_impl(const blink_config* cfg, blink_engine* e) {
       if (int rc = dalloc(e, &c.xq_moe, (u64)c.moe_TBS * 16 * k_pad(c.d))) return rc;
       if (int rc = dalloc(e, &c.y_moe, (u64)c.moe_TBS * 16 * c.d, false)) return rc;
       if (int rc = dalloc(e, &c.moe_logits, (u64)c.maxT * c.n_experts, false)) return rc;
-      if (int rc = dalloc(e, &c.moe_count, c.n_experts)) return rc;
+      if (int rc = dalloc(e, &c.moe_count, (u64)c.n_experts * MOE_COUNT_STRIDE)) return rc;
       if (int rc = dalloc(e, &c.moe_list, (u64)c.n_experts * c.maxT)) return rc;
       if (int rc = dalloc(e, &c.moe_sel, (u64)c.n_layers * c.maxT * c.n_active)) return rc;
       if (int rc = dalloc(e, &c.moe_pos, (u64)c.maxT * c.n_active)) return rc;

@@ -318,7 +318,7 @@ struct DevCtx {
   u32 tune_nw;          // tuning word (MfmaGemmArgs::tune_nw)
   // mixture of experts
   float* moe_logits;    // [maxT][n_experts] router logits
-  u32* moe_count;       // [n_experts] tokens routed to every expert in the current layer
+  u32* moe_count;       // [n_experts][MOE_COUNT_STRIDE] (first word) tokens routed to every expert in the current layer
   u32* moe_list;        // [n_experts][maxT] their token indices (order inside a list depends on timing, results do not)
   u32* moe_sel;         // [n_layers][maxT * n_active] selected expert of every (token, slot), kept per layer for tests
   u32* moe_pos;         // [maxT * n_active] place of the pair in its expert's list

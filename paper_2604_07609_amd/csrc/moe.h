@@ -14,6 +14,9 @@
 #define MOE_MAX_EXPERTS 256
 #define MOE_MAX_ACTIVE 8
 
+// words from one expert's counter to the next: a cache line each. Side by side the counters of 128 experts are four lines, whose atomic adds
+// go one after the other (2100 tokens, eight experts each: 38 us for the selection, 13.6 with a line each; 96 tokens 7.5 and 7.1).
+#define MOE_COUNT_STRIDE 32u
 #define MOE_WAVE_MAX_TOKENS 64   // experts with at most this many tokens are run by independent waves (see moe_wave_item)
 
 struct MoeLists {
@@ -49,7 +52,7 @@ __device__ __forceinline__ void moe_offsets(const DevCtx& c, MoeLists& l) {
 #pragma unroll
     for (u32 j = 0; j < EL; ++j) {
       const u32 e = threadIdx.x * EL + j;
-      n[j] = e < c.n_experts ? c.moe_count[e] : 0;
+      n[j] = e < c.n_experts ? c.moe_count[e * MOE_COUNT_STRIDE] : 0;
     }
 #pragma unroll
     for (u32 j = 0; j < EL; ++j) sum += (n[j] + 15u) & ~15u;
@@ -164,7 +167,7 @@ __device__ __forceinline__ void moe_route(const DevCtx& c, u32 layer, u32 wg, u3
     }
     if (lane < k) {
       const u32 q = t * k + lane;
-      const u32 pos = atomicAdd(&c.moe_count[sel_e], 1u);
+      const u32 pos = atomicAdd(&c.moe_count[sel_e * MOE_COUNT_STRIDE], 1u);
       c.moe_list[(u64)sel_e * c.maxT + pos] = t;
       c.moe_sel[(u64)layer * c.maxT * k + q] = sel_e;
       c.moe_pos[q] = pos;

@@ -115,7 +115,7 @@ __device__ __forceinline__ void run_phase_bf16(const DevCtx& c, u32 layer, typen
     case PH_ATTN_COMBINE: attn_decode_combine(c, wg, nwg); break;
     case PH_ROUTER:     // router logits of every token; its first workgroup also clears the experts' counters for this layer
       if (wg == 0)
-        for (u32 e = threadIdx.x; e < c.n_experts; e += blockDim.x) c.moe_count[e] = 0;
+        for (u32 e = threadIdx.x; e < c.n_experts; e += blockDim.x) c.moe_count[e * MOE_COUNT_STRIDE] = 0;
       a.Wp = P->wr; a.Xp = c.xq; a.N = c.n_experts; a.K = c.d; a.ssq_in = c.ssq; a.out = c.moe_logits; a.ldo = c.n_experts;
       gemm_router<EPI_SCALED_STORE>(a, *(MfmaShared*)&sh, wg, nwg);
       break;
