@@ -13,8 +13,8 @@
  * on the device for a bounded time, so a request that reaches an idle engine is claimed
  * within microseconds. The host side of this ABI stands in for the paper's
  * SmartNIC frontend (section 4.4): blink_submit plays the RDMA datapath (payload first,
- * then the slot state), blink_poll_outputs plays the token reader (one bulk read of the
- * slot metadata, compare generation counts, fetch new tokens).
+ * then the slot state), blink_poll_outputs plays the token reader (compare the slots'
+ * generation counts, fetch new tokens).
  *
  * All functions return 0 on success or a negative BLINK_ERR_* code. Nothing throws.
  * All pointers are HOST pointers. The engine owns every byte of device memory; the caller

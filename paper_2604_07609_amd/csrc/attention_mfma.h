@@ -318,7 +318,7 @@ __device__ __forceinline__ void merge_chunks(const DevCtx& c, AttnMfmaShared& sh
 // load instead of a search in metadata staged through LDS. An item is a run of KV blocks of one sequence and one kv head,
 // walked in rounds of 32 blocks (four tile slots per wave) with the running maxima, sums and outputs kept in registers
 // from round to round, and merged across the waves once, at its end: one chunk of a context (its partial result is
-// merged with the other chunks' by the combine kernel) or, when the scheduler has many sequences to hand out, a whole
+// merged with the other chunks' by the workgroup that finishes the last of them, or by the combine kernel) or, when the scheduler has many sequences to hand out, a whole
 // context (no partial results). A wave refills each tile slot with the tile of the next round (of the same item or of
 // the next one) as soon as it has consumed the slot; the next round's description and queries are fetched first (loads
 // complete in order, so the queries must not queue behind the refills); the workgroup's last round runs without the

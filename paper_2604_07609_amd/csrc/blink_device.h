@@ -163,7 +163,7 @@ __host__ __forceinline__ bool merge_in_attention(u32 items, u32 hd, u32 ncu) { r
 // One work item of the decode attention (times the kv heads), as the kernel takes it from the scheduler (32 bytes: one
 // scalar load of a wave): a run of KV blocks of one decoding sequence that one workgroup walks, ATTN_CHUNK_TOKENS at a
 // time, into one result. With few sequences an item is one chunk of a context (so that the chip has enough items; the
-// chunks' partial results are merged by the combine kernel): full chunks are listed first (DevCtx::chunk_rec[0 ..
+// chunks' partial results are merged by the attention kernel or by the combine kernel behind it): full chunks are listed first (DevCtx::chunk_rec[0 ..
 // n_full_chunks)), the partly filled ones behind them from DevCtx::chunk_rec[chunk_cap]. With many sequences an item is
 // a whole context (no partial results, fewer merges), listed longest first. The workgroups take the list in order.
 struct ChunkRec {

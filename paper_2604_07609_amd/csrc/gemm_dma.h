@@ -110,7 +110,7 @@ __device__ __forceinline__ bool add_slices(const MfmaGemmArgs& a, floatx4_t (&ac
 // reads), so that the number in flight is the same at every barrier and the loop has no branch for its end.
 // items.total is their number; items.at(i, a, nb, tb) completes the arguments of item i and names its block of rows and of tokens.
 //
-// SPLIT: K is cut into `slices` of each tile, an item each, at most one per workgroup (gemm_dma_pick says where that pays). The
+// SPLIT: K is cut into `slices` of each tile, an item each, at most one per workgroup (gemm_plan says where that pays). The
 // workgroup that comes last to a tile adds the slices up in their order, so the result does not depend on which one that is.
 template <int EPI, int WN, int MI, int MJ, int KS, bool ONCE, bool SPLIT, typename Items>
 __device__ __forceinline__ void gemm_dma(MfmaGemmArgs a, const Items& items, DmaShared& sh, u32 wg, u32 nwg, u32 slices = 1) {
