@@ -411,7 +411,8 @@ __device__ __forceinline__ void epilogue_cols(const MfmaGemmArgs& a, const float
           *(float4*)(a.x + (u64)t * a.ldx + (nt0 + i) * 16 + lg * 4) = make_float4(v0, v1, v2, v3);
           k[q][0] = pack_f16x2(v0 * g[i].x, v1 * g[i].y);
           k[q][1] = pack_f16x2(v2 * g[i].z, v3 * g[i].w);
-          float s = v0 * v0 + v1 * v1 + v2 * v2 + v3 * v3;
+          // (written out: which square comes first must not depend on the schedule, a last bit here moves near ties of a router)
+          float s = fmaf(v3, v3, fmaf(v2, v2, fmaf(v1, v1, v0 * v0)));
           s += __shfl_xor(s, 16);
           ss[i] = s + __shfl_xor(s, 32);
         }
