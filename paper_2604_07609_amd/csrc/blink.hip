@@ -637,18 +637,7 @@ static int init_impl(const blink_config* cfg, blink_engine* e) {
     } else if (int rc = dalloc(e, &c.hq, tile_tokens * k_pad(c.F))) return rc;
     if (int rc = dalloc(e, &c.ssq, tile_tokens * (c.d / 16))) return rc;
     {
-      c.gemm_plan_max = std::min(c.maxT, PLAN_MAX_TOKENS);
-      std::vector<GemmPlan> plan(c.gemm_plan_max + 1);
-      const u32 ncu = (u32)e->n_cu, tune = cfg->tune, qo = c.nq * c.hd;
-      const bool moe = c.n_experts != 0;
-      for (u32 t = 1; t <= c.gemm_plan_max; ++t) {
-        if (t > 65 && (t - 1) % 64) { plan[t] = plan[t - 1]; continue; }     // (every tile is a multiple of 64 tokens wide)
-        plan[t].qkv = gemm_plan(EPI_QKV_ROPE, c.qkv_n, c.d, t, moe, ncu, tune);
-        plan[t].oproj = gemm_plan(EPI_RESIDUAL, c.d, qo, t, moe, ncu, tune);
-        plan[t].gateup = gemm_plan(EPI_SILU_GATE, 2 * c.F, c.d, t, false, ncu, tune);
-        plan[t].down = gemm_plan(EPI_RESIDUAL, c.d, c.F, t, false, ncu, tune);
-        plan[t].lm_head = gemm_plan(EPI_SCALED_STORE, c.V, c.d, t, false, ncu, tune);
-      }
+      const std::vector<GemmPlan> plan = gemm_plan_table(c.maxT, c.qkv_n, c.d, c.nq * c.hd, c.F, c.V, c.n_experts != 0, (u32)e->n_cu, cfg->tune);
       u64* dev;
       static_assert(sizeof(GemmPlan) == 8, "an entry is one word");
       if (int rc = dalloc(e, &dev, plan.size())) return rc;

@@ -310,8 +310,7 @@ struct DevCtx {
   f16_t* qbuf;          // [maxT][nq][hd] rotated queries scaled by 1/sqrt(hd), half precision like the KV cache they meet
   f16_t* hq;            // packed half(silu(gate)*up), inner dimension F
   float* ssq;           // [token][d/16] partial sums of squares of the residual stream
-  const u64* gemm_plan; // [gemm_plan_max + 1] GemmPlan of every token count
-  u32 gemm_plan_max;
+  const u64* gemm_plan; // [gemm_plan_entry(maxT) + 1] GemmPlan of every token count
   u64* gemm_part;       // [n_cu][256 * 128 / 2] sums of the slices of GEMMs that split K, two floats each
   u32* gemm_part_count; // [n_cu] slices that have come to every tile (zeros between launches)
   u32 TBS;              // token-block stride of the packed activation buffers

@@ -15,7 +15,7 @@
 // The k dimension of both is padded with zeros to a multiple of 64 (an even number of k-steps).
 //
 // out[t][n] = sum_k X[t][k] * W[n][k]. Every GEMM kernel runs eight waves per workgroup and one workgroup per compute unit. The
-// schedule is chosen per launch from the token count T of the iteration and the shape of the matrix (gemm_dma.h: gemm_plan):
+// schedule is chosen per launch from the token count T of the iteration and the shape of the matrix (gemm_plan.h):
 //   tiles whose operands go from memory straight to LDS (gemm_dma.h): T > 64, and tall matrices at any T.
 //   stream (T <= 64 otherwise, decode at small batch): a workgroup owns 1 or 2 16-row weight tiles and all token blocks; its
 //     eight waves split K and keep two batches of 1 KB operand loads in flight each; weight loads are non-temporal;
@@ -25,6 +25,7 @@
 // the result as the next GEMM's activation operand together with the partial sums of squares the next RMSNorm needs.
 #pragma once
 #include "blink_device.h"
+#include "gemm_plan.h"
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
@@ -32,12 +33,6 @@ typedef float floatx4_t __attribute__((ext_vector_type(4)));
 
 #define W_SCALE 256.0f            // packed weights hold W * 2^8 (keeps small weights in the normal range of a half)
 #define W_SCALE_INV (1.0f / 256.0f)
-
-#define EPI_SCALED_STORE 0   // out[t][n] = rstd[t] * acc                      (QKV projection, LM head)
-#define EPI_RESIDUAL 1       // x[t][n] += acc; emit packed half(x * g_next) and sum-of-squares partials
-#define EPI_SILU_GATE 2      // rows interleaved (gate_j, up_j): emit packed half(silu(r*g) * (r*u))
-#define EPI_QKV_ROPE 3       // rows of every head interleaved (dim p, dim p+hd/2): rotary embedding, then q to the query
-                             // buffer, k and v straight into the paged cache through the slot mapping
 
 struct MfmaGemmArgs {
   const f16_t* Wp;         // packed weights (half precision, scaled by W_SCALE)
@@ -85,8 +80,6 @@ struct MfmaShared {
   float red[GEMM_MAX_WAVES][4][64][4];       // [wave][token block][lane][4]
   float rstd[256];                           // norm scales of the tokens
 };
-
-__host__ __device__ __forceinline__ u32 gemm_k_tiles(u32 K) { return ((K + 63) / 64) * 2; }   // k-steps of the packed operands
 
 __device__ __forceinline__ u64 packed_off(u32 t, u32 k, u32 TBS) {
   return ((u64)((k >> 5) * TBS + (t >> 4)) * 64 + (t & 15) + 16 * ((k & 31) >> 3)) * 8 + (k & 7);

@@ -17,6 +17,7 @@
 // (pc_bucket / pc_next); an evicted block's node stays in its chain, marked stale, until the block is entered again.
 #pragma once
 #include "blink_device.h"
+#include "gemm_plan.h"
 
 #define SLOT_EMPTY 0u
 #define SLOT_PREFILL_PENDING 1u
@@ -985,8 +986,8 @@ __device__ void sched_step(const DevCtx& c, SchedShared& sh) {
   if (c.attn_ctr)
     for (u32 l = tid; l < 2 * c.n_layers; l += BLK_THREADS) c.attn_ctr[l] = 0; // work counters of this iteration's attention launches
   if (tid == WAVE && c.gemm_plan) {      // (another wave than the rest: its loads are beside that, not in front of it)
-    c.meta->plan = (u32)c.gemm_plan[min(n_tok, c.gemm_plan_max)];
-    c.meta->plan_lm = (u32)(c.gemm_plan[min(n_rows, c.gemm_plan_max)] >> 32) & 0xffu;
+    c.meta->plan = (u32)c.gemm_plan[gemm_plan_entry(n_tok)];
+    c.meta->plan_lm = (u32)(c.gemm_plan[gemm_plan_entry(n_rows)] >> 32) & 0xffu;
   }
   if (tid == 0) {
     const u64 now = dev_now_ns();
