@@ -259,11 +259,19 @@ __device__ __forceinline__ void attn_decode(const DevCtx& c, u32 layer, AttnMfma
   }
 }
 
+// Adds one chunk's result (maximum, sum, output) to the merge of its context, whose maximum over all chunks is M: written out, and M
+// taken ahead of the first sum, for every merge here, so that the launcher's choice between them moves no bit.
+__device__ __forceinline__ void merge_add(float m, float l, float o, float M, float& L, float& O) {
+  const float f = __expf(m - M);
+  L = fmaf(l, f, L);
+  O = fmaf(o, f, O);
+}
+
 // The partial results of a context's chunks merged by the workgroup that finishes the last of them (launches without the
 // merge kernel behind them, see the launcher): every chunk's result has been written past the caches, which are not coherent between
 // the XCDs, before its workgroup counts itself (relaxed atomics of the device's scope and the wave's own counter: a fence of that scope
 // would write back and invalidate a whole L2 each time). No workgroup waits for another, the chunks are added in their order, and the
-// counter is zero again for the next launch.
+// counter is zero again for the next launch. The result has the bits of the merge kernel's.
 __device__ __forceinline__ void st_past_caches(float* p, float v) { __hip_atomic_store((u32*)p, __float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ float ld_past_caches(const float* p) { return __uint_as_float(__hip_atomic_load((const u32*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)); }
 template <int HD>
@@ -284,23 +292,28 @@ __device__ __forceinline__ void merge_chunks(const DevCtx& c, AttnMfmaShared& sh
     const float* o = c.attn_part_o + (((u64)c0 * c.nkv + g) * G + h) * HD + dim;
     const u64 step = (u64)c.nkv * G;
     float M = -INFINITY, L = 0.f, O = 0.f;
-    for (u32 p0 = 0; p0 < nch; p0 += 4) {          // four chunks' results on their way; a new maximum rescales what is there
+    if (nch > 4)
+      for (u32 p0 = 0; p0 < nch; p0 += 8) {        // (eight loads on their way; past the last chunk: that one again)
+        float m[8];
+#pragma unroll
+        for (u32 u = 0; u < 8; ++u) m[u] = ld_past_caches(ml + 2 * (min(p0 + u, nch - 1) * step));
+#pragma unroll
+        for (u32 u = 0; u < 8; ++u) M = fmaxf(M, m[u]);
+      }
+    for (u32 p0 = 0; p0 < nch; p0 += 4) {          // four chunks' results on their way
       float m[4], l[4], v[4];
 #pragma unroll
       for (u32 u = 0; u < 4; ++u) {
         const u64 p = min(p0 + u, nch - 1) * step;
         m[u] = ld_past_caches(ml + 2 * p); l[u] = ld_past_caches(ml + 2 * p + 1); v[u] = ld_past_caches(o + p * HD);
       }
-      float Mn = M;
+      if (nch <= 4) {
 #pragma unroll
-      for (u32 u = 0; u < 4; ++u) Mn = fmaxf(Mn, m[u]);      // (past the last: that one again)
-      const float f0 = __expf(M - Mn);                       // (exp(-inf) = 0 in the first round: a chunk has a visible key)
-      L *= f0; O *= f0; M = Mn;
-#pragma unroll
-      for (u32 u = 0; u < 4; ++u) {
-        const float f = p0 + u < nch ? __expf(m[u] - Mn) : 0.f;
-        L += l[u] * f; O += v[u] * f;
+        for (u32 u = 0; u < 4; ++u) M = fmaxf(M, m[u]);
       }
+#pragma unroll
+      for (u32 u = 0; u < 4; ++u)
+        if (p0 + u < nch) merge_add(m[u], l[u], v[u], M, L, O);
     }
     c.aq[packed_off(t, (g * G + h) * HD + dim, c.TBS)] = f32_to_f16(O / L);
   }
@@ -485,11 +498,7 @@ __device__ __forceinline__ void attn_combine_pair(const DevCtx& c, u32 c0, u32 n
         if (p < nch) M = fmaxf(M, ml[e][p].x);
 #pragma unroll
       for (u32 p = 0; p < MAXC; ++p)
-        if (p < nch) {
-          const float f = __expf(ml[e][p].x - M);
-          L += ml[e][p].y * f;
-          O += ov[e][p] * f;
-        }
+        if (p < nch) merge_add(ml[e][p].x, ml[e][p].y, ov[e][p], M, L, O);
       if (idx < n) c.aq[packed_off(t, g * n + idx, c.TBS)] = f32_to_f16(O / L);
     }
   }
@@ -512,9 +521,7 @@ __device__ __forceinline__ void attn_decode_combine(const DevCtx& c, u32 wg, u32
         for (u32 p = 0; p < nch; ++p) M = fmaxf(M, c.attn_part_ml[(((u64)(c0 + p) * c.nkv + g) * G + h) * 2]);
         for (u32 p = 0; p < nch; ++p) {
           const u64 base = ((u64)(c0 + p) * c.nkv + g) * G;
-          const float f = __expf(c.attn_part_ml[(base + h) * 2] - M);
-          L += c.attn_part_ml[(base + h) * 2 + 1] * f;
-          O += c.attn_part_o[(base + h) * HD + dim] * f;
+          merge_add(c.attn_part_ml[(base + h) * 2], c.attn_part_ml[(base + h) * 2 + 1], c.attn_part_o[(base + h) * HD + dim], M, L, O);
         }
         c.aq[packed_off(t, (g * G + h) * HD + dim, c.TBS)] = f32_to_f16(O / L);
       }

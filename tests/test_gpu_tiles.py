@@ -223,3 +223,30 @@ def test_decode_attention_merges_chunks_itself(lib, name, prompts):
     eng = dict(eng, max_batch=len(prompts), max_seq_len=max(prompts) + 16, kv_num_blocks=blocks, max_prefill_tokens=8192, ring_slots=32)
     worst = parity.stepwise_check(lib, cfg, eng, raw, blob, _fixed_prompts(cfg, prompts, 5, 267), rtol=RTOL, tune=0x8)
     print(name, "chunks merged in the attention kernel, worst relative logit error", worst)
+
+
+@pytest.mark.parametrize("name,prompts", [("mini_gqa128", [1030, 2070, 4090, 6300, 7]), ("mini_gqa", [1030, 2070, 4090, 6300, 7]), ("mini_kv8", [2600] * 12)])
+def test_where_chunks_are_merged_does_not_move_a_bit(lib, name, prompts):
+    """The launcher chooses from a hint of the host, which is some iterations old, whether the attention kernel merges a context's chunks (bit 3
+    of the tuning word: always) or a kernel behind it does (bit 5: always), so the two give the same bits: contexts of one to thirteen
+    chunks, up to four of them in one batch of loads, more in several; logits of five decode iterations."""
+    cfg, eng, raw, blob = setup(name, 67)
+    blocks = sum((n + 20) // 16 + 1 for n in prompts)
+    eng = dict(eng, max_batch=len(prompts), max_seq_len=max(prompts) + 16, kv_num_blocks=blocks, max_prefill_tokens=1 << 15, ring_slots=32)
+    logits = []
+    for tune in (0x20, 0x8, 0):
+        e = lib.Engine(cfg, eng, blob, tune=tune, flags=lib.FLAG_KEEP_LOGITS)
+        try:
+            for r in _fixed_prompts(cfg, prompts, 6, 267):
+                e.submit(r["prompt"], 6)
+            rows = []
+            for _ in range(6):
+                e.run(1)
+                e.wait()
+                rows.append(e.debug_read(lib.DBG.LOGITS, np.uint32).reshape(len(prompts), cfg["vocab"]))
+            logits.append(np.stack(rows))
+        finally:
+            e.shutdown()
+    assert (logits[0][0] == logits[1][0]).all()
+    for other in logits[1:]:
+        assert (logits[0] == other).all(), "%d of %d rows differ" % ((logits[0] != other).any(axis=2).sum(), 6 * len(prompts))
