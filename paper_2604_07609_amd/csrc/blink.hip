@@ -886,7 +886,7 @@ static int build_graph(blink_engine* e) {
 }
 
 // Which chain the next iteration runs is the launcher's choice, and the only one it makes: from the number of running
-// sequences and of attention items that the scheduler step last mirrored to the host (plain reads of pinned memory, several iterations old,
+// sequences and of the attention items ahead that the scheduler step last mirrored to the host (plain reads of pinned memory, several iterations old,
 // hints and nothing more) it takes the chain for whole contexts when the device would make those the items anyway (the same
 // threshold), and the one that merges in the attention kernel where that is cheaper (merge_in_attention). Any chain is correct
 // for any iteration; a stale hint costs a few iterations with the other one.

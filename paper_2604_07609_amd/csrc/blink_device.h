@@ -197,7 +197,8 @@ struct HostMirror {
   u32 n_running;
   u32 idle;
   u64 clock_probe;      // device clock written by the clock probe kernel
-  u32 attn_items;       // work items of the decode attention in the last iteration (kv heads included)
+  u32 attn_items;       // chunks of the contexts that decode in the next iteration, times the kv heads (a prefill iteration has none itself, and
+                        // the launcher chooses the chain of the decode iterations behind it from what it leaves here)
   u32 pad;
   u64 progress;         // chains whose scheduler step has run (upper half) and iterations begun (lower half), one store
 };

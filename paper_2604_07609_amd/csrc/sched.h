@@ -738,12 +738,13 @@ __device__ void sched_step(const DevCtx& c, SchedShared& sh) {
   const bool group = c.chunk_rec && !(c.tune_nw & 0x808000u) && ((c.tune_nw & 0x400000u) || (u64)nrun * c.nkv >= WHOLE_CONTEXT_PAIRS_PER_CU * (u64)c.n_cu);
   const u32 spec_k = (c.flags & 256u) ? c.spec_k : 0u;
   u64 n_ctx = 0;
+  u32 n_next = 0;                 // chunks of the contexts that decode in the next iteration, for the launcher
   u32 n_prompts = 0, n_items = 0;   // sequences that process prompt tokens, their items in the attention with shared KV tiles (bf16 models)
   if (kind != KIND_IDLE) {
     for (u32 base = 0; base < c.max_batch; base += BLK_THREADS) {
       const u32 b = base + tid;
       bool in = false, pref = false, smp = false, multi = false;   // multi: several tokens of one sequence attend like a prompt chunk
-      u32 nalloc = 0, ntok = 0, pos0 = 0, nb = 0, nrow = 0;
+      u32 nalloc = 0, ntok = 0, pos0 = 0, nb = 0, nrow = 0, nnext = 0;
       if (b < c.max_batch && c.run[b].valid) {
         RunEntry& r = c.run[b];
         nb = r.n_blocks;
@@ -773,15 +774,16 @@ __device__ void sched_step(const DevCtx& c, SchedShared& sh) {
         if (in) nalloc = max((pos0 + ntok + c.bs - 1) / c.bs, nb) - nb;
         else ntok = 0;
         nrow = smp ? ((spec_k && !pref) ? ntok : 1u) : 0u;    // logits rows: the last token; every token of a decoding sequence when drafts are verified
+        if (smp || !in) nnext = ((in ? pos0 + ntok : r.ctx_len) + ATTN_CHUNK_TOKENS) / ATTN_CHUNK_TOKENS;    // (one token more than now)
       }
       const u32 ctx_after = in ? pos0 + ntok : 0u;
       const bool dec_seq = in && !multi;
       const u32 nch = !dec_seq ? 0u : group ? 1u : (ctx_after + ATTN_CHUNK_TOKENS - 1) / ATTN_CHUNK_TOKENS;
       const u32 nfull = (!dec_seq || group) ? 0u : ctx_after / ATTN_CHUNK_TOKENS;
       // offsets: full and partly filled chunks, all chunks, query tiles, sequences, sampling ones, blocks, tokens, logits rows, decoding
-      // sequences, context tokens the attention reads (their total)
-      u32 sum[11] = {nfull, nch - nfull, nch, multi ? (ntok + 15) / 16 : 0u, in ? 1u : 0u, smp ? 1u : 0u, nalloc, ntok, nrow, (in && !pref) ? 1u : 0u, ctx_after};
-      u32 tot[11], mx[3] = {ntok, ctx_after, multi ? ctx_after : 0u};
+      // sequences; of context tokens the attention reads and the next iteration's chunks the totals
+      u32 sum[12] = {nfull, nch - nfull, nch, multi ? (ntok + 15) / 16 : 0u, in ? 1u : 0u, smp ? 1u : 0u, nalloc, ntok, nrow, (in && !pref) ? 1u : 0u, ctx_after, nnext};
+      u32 tot[12], mx[3] = {ntok, ctx_after, multi ? ctx_after : 0u};
       block_scan_many(sum, tot, mx, sh.scan_part);
       u32 foff = sum[0], poff = sum[1], coff = sum[2], qoff = sum[3], si = sum[4], mi = sum[5], aoff = sum[6], toff = sum[7], ri = sum[8];
       const u32 totf = tot[0], totp = tot[1], totc = tot[2], totq = tot[3], tots = tot[4], totm = tot[5], tota = tot[6], tott = tot[7], totr = tot[8], totd = tot[9], totx = tot[10];
@@ -856,6 +858,7 @@ __device__ void sched_step(const DevCtx& c, SchedShared& sh) {
       n_part += totp;
       n_smp += totm;
       n_rows += totr;
+      n_next += tot[11];
     }
     top -= n_alloc;
     __syncthreads();
@@ -1058,7 +1061,7 @@ __device__ void sched_step(const DevCtx& c, SchedShared& sh) {
     c.hmirror->tokens_out = ss->tokens_out;
     c.hmirror->n_running = nrun;
     c.hmirror->error = ss->error;
-    c.hmirror->attn_items = (n_full + n_part) * c.nkv;
+    c.hmirror->attn_items = n_next * c.nkv;
     c.hmirror->idle = kind == KIND_IDLE;
     // (the launcher reads it behind the chain's event, which orders it: a release here would write back an L2 first)
     __hip_atomic_store(&c.hmirror->stopped, stopped, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);

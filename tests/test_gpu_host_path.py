@@ -151,3 +151,36 @@ def test_poll_in_pieces_and_the_logits_behind_it(lib, n, cap):
             assert [int(x) for x in logits.argmax(1)] == [got[i][2] for i in ids]
     finally:
         e.shutdown()
+
+
+def test_decode_iterations_behind_a_prefill_run_their_own_batch_s_chain(lib):
+    """40 sequences x 8 kv heads of 64 x 3 chunks are more than three attention items per compute unit, where a kernel behind the
+    attention merges the chunks: it is there (phase 12) from the first decode iteration behind the prefill iterations, although those
+    had no decode attention themselves, and is not there for 4 sequences."""
+    cfg = synth.model_config("mini_kv8")
+    eng = dict(synth.engine_config("mini_kv8"), max_prefill_tokens=16384)
+    e = lib.Engine(cfg, eng, synth.pack_blob(cfg, synth.make_weights(cfg, 50)))
+    rng = np.random.default_rng(50)
+    try:
+        for n in (40, 4):
+            for _ in range(n):
+                e.submit(rng.integers(0, cfg["vocab"], 1100), 12)
+            first = 0
+            while first < n:
+                e.run(1)
+                e.wait()
+                first += len(e.drain())
+            e.time_phase(12)
+            e.run(4)
+            e.wait()
+            t = e.phase_times_ms()[:4]
+            print(n, "sequences, merge kernel in the first four decode iterations, us:", t * 1e3)
+            assert (t > 0).all() if n == 40 else not t.any(), (n, t)
+            e.time_phase(-1)
+            e.set_exit_when_idle(True)
+            e.run(0)
+            e.wait()
+            e.drain()
+            e.set_exit_when_idle(False)
+    finally:
+        e.shutdown()
