@@ -146,6 +146,18 @@ __device__ __forceinline__ void compute_rstd(const MfmaGemmArgs& a, u32 t0, floa
   __syncthreads();
 }
 
+// What several epilogues compute is written out once: left to the compiler, which product is rounded and which goes into a fused
+// multiply-add depends on what it is inlined into, and a last bit here moves near ties of a router.
+// Sum of the squares of a lane's four values of the residual stream.
+__device__ __forceinline__ float sum_squares(float v0, float v1, float v2, float v3) { return fmaf(v3, v3, fmaf(v2, v2, fmaf(v1, v1, v0 * v0))); }
+
+// A pair of the rotary embedding, (c, s) the cosine and sine of its angle.
+__device__ __forceinline__ void rotate(float& lo, float& hi, float c, float s) {
+  const float a = fmaf(lo, c, -(hi * s));
+  hi = fmaf(hi, c, lo * s);
+  lo = a;
+}
+
 // Epilogue of one 16(n) x 16(t) accumulator tile held by one wave. rl: index of the tile's first token in sh.rstd.
 template <int EPI>
 __device__ __forceinline__ void epilogue_tile(const MfmaGemmArgs& a, floatx4_t acc, u32 nt, u32 t_base, const float* rstd16) {
@@ -175,7 +187,7 @@ __device__ __forceinline__ void epilogue_tile(const MfmaGemmArgs& a, floatx4_t a
       const float4 g = *(const float4*)(a.g_next + n0);
       *(uint2*)(a.Xp_next + packed_off(t, n0, a.TBS)) = make_uint2(pack_f16x2(v[0] * g.x, v[1] * g.y), pack_f16x2(v[2] * g.z, v[3] * g.w));
     }
-    float s = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+    float s = sum_squares(v[0], v[1], v[2], v[3]);
     s += __shfl_xor(s, 16);
     s += __shfl_xor(s, 32);
     if (lane < 16 && tv) a.ssq_out[(u64)t * (a.N / 16) + nt] = s;
@@ -186,9 +198,8 @@ __device__ __forceinline__ void epilogue_tile(const MfmaGemmArgs& a, floatx4_t a
     float lo0 = acc[0] * r, hi0 = acc[1] * r, lo1 = acc[2] * r, hi1 = acc[3] * r;
     if (head < a.nq + a.nkv) {
       const float4 cs = *(const float4*)(a.rope_tab + (u64)a.positions[t] * half + p);   // (cos,sin) of pairs p, p+1
-      const float a0 = lo0 * cs.x - hi0 * cs.y, b0 = hi0 * cs.x + lo0 * cs.y;
-      const float a1 = lo1 * cs.z - hi1 * cs.w, b1 = hi1 * cs.z + lo1 * cs.w;
-      lo0 = a0; hi0 = b0; lo1 = a1; hi1 = b1;
+      rotate(lo0, hi0, cs.x, cs.y);
+      rotate(lo1, hi1, cs.z, cs.w);
     }
     if (head < a.nq) {
       const float sc = 1.0f / sqrtf((float)hd);
@@ -227,9 +238,8 @@ __device__ __forceinline__ void rope_finish(const MfmaGemmArgs& a, floatx4_t acc
   const u32 hd = a.hd, half = hd / 2, head = n0 / hd, p = (n0 % hd) >> 1;   // rows: (p, p+half, p+1, p+1+half)
   float lo0 = acc[0] * r, hi0 = acc[1] * r, lo1 = acc[2] * r, hi1 = acc[3] * r;
   if (head < a.nq + a.nkv) {
-    const float a0 = lo0 * cs.x - hi0 * cs.y, b0 = hi0 * cs.x + lo0 * cs.y;
-    const float a1 = lo1 * cs.z - hi1 * cs.w, b1 = hi1 * cs.z + lo1 * cs.w;
-    lo0 = a0; hi0 = b0; lo1 = a1; hi1 = b1;
+    rotate(lo0, hi0, cs.x, cs.y);
+    rotate(lo1, hi1, cs.z, cs.w);
   }
   if (head < a.nq) {
     const float sc = 1.0f / sqrtf((float)hd);
@@ -261,7 +271,7 @@ __device__ __forceinline__ void residual_finish(const MfmaGemmArgs& a, floatx4_t
     *(float4*)(a.x + (u64)t * a.ldx + n0) = make_float4(v[0], v[1], v[2], v[3]);
     *(uint2*)(a.Xp_next + packed_off(t, n0, a.TBS)) = make_uint2(pack_f16x2(v[0] * g.x, v[1] * g.y), pack_f16x2(v[2] * g.z, v[3] * g.w));
   }
-  float s = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+  float s = sum_squares(v[0], v[1], v[2], v[3]);
   s += __shfl_xor(s, 16);
   s += __shfl_xor(s, 32);
   if (lane < 16 && tv) a.ssq_out[(u64)t * (a.N / 16) + nt] = s;
@@ -404,8 +414,7 @@ __device__ __forceinline__ void epilogue_cols(const MfmaGemmArgs& a, const float
           *(float4*)(a.x + (u64)t * a.ldx + (nt0 + i) * 16 + lg * 4) = make_float4(v0, v1, v2, v3);
           k[q][0] = pack_f16x2(v0 * g[i].x, v1 * g[i].y);
           k[q][1] = pack_f16x2(v2 * g[i].z, v3 * g[i].w);
-          // (written out: which square comes first must not depend on the schedule, a last bit here moves near ties of a router)
-          float s = fmaf(v3, v3, fmaf(v2, v2, fmaf(v1, v1, v0 * v0)));
+          float s = sum_squares(v0, v1, v2, v3);
           s += __shfl_xor(s, 16);
           ss[i] = s + __shfl_xor(s, 32);
         }
@@ -452,12 +461,12 @@ __device__ __forceinline__ void epilogue_cols(const MfmaGemmArgs& a, const float
         u32 lo[4], hi[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const float lo0 = acc[i][j][0] * r, hi0 = acc[i][j][1] * r, lo1 = acc[i][j][2] * r, hi1 = acc[i][j][3] * r;
+          float lo0 = acc[i][j][0] * r, hi0 = acc[i][j][1] * r, lo1 = acc[i][j][2] * r, hi1 = acc[i][j][3] * r;
           const float4 w = cs[j % D][i];
-          const float a0 = lo0 * w.x - hi0 * w.y, b0 = hi0 * w.x + lo0 * w.y;
-          const float a1 = lo1 * w.z - hi1 * w.w, b1 = hi1 * w.z + lo1 * w.w;
-          lo[i] = head < a.nq ? pack_f16x2(a0 * sc, a1 * sc) : pack_f16x2(a0, a1);
-          hi[i] = head < a.nq ? pack_f16x2(b0 * sc, b1 * sc) : pack_f16x2(b0, b1);
+          rotate(lo0, hi0, w.x, w.y);
+          rotate(lo1, hi1, w.z, w.w);
+          lo[i] = head < a.nq ? pack_f16x2(lo0 * sc, lo1 * sc) : pack_f16x2(lo0, lo1);
+          hi[i] = head < a.nq ? pack_f16x2(hi0 * sc, hi1 * sc) : pack_f16x2(hi0, hi1);
         }
         if (j + D < TJ) request(j + D, cs[j % D]);
         transpose4(lo);                        // this lane: pairs p0 + lg * 8 .. + 7 of its token

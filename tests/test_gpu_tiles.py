@@ -250,3 +250,72 @@ def test_where_chunks_are_merged_does_not_move_a_bit(lib, name, prompts):
     assert (logits[0][0] == logits[1][0]).all()
     for other in logits[1:]:
         assert (logits[0] == other).all(), "%d of %d rows differ" % ((logits[0] != other).any(axis=2).sum(), 6 * len(prompts))
+
+
+def one_product_per_sum(cfg, seed):
+    """Weights with which every sum over K has one term that is not zero, so that no order of summation shows: what an output projection
+    adds to the residual stream is zero, and every row of gate, up and down has a single element."""
+    raw = synth.make_weights(cfg, seed, gain_jitter=0.1)
+    rng = np.random.default_rng(seed)
+    for name, w in raw.items():
+        what = name.split(".")[-1]
+        if what == "wo":
+            w[:] = 0
+        elif what in ("wg", "wu", "wd"):
+            row = np.arange(w.shape[0])
+            w[:] = 0
+            w[row, rng.integers(0, w.shape[1], w.shape[0])] = synth.f32_to_bf16_bits(rng.uniform(0.5, 1.5, w.shape[0]).astype(np.float32))
+    return raw
+
+
+@pytest.mark.parametrize("tune", [0, 2, 0x40, 0x1000, 0x1040, 0x2000, 0x3000, 0x4000, 0x6000, 0x7000, 0x1000 | 2 << 24, 0x1040 | 2 << 24, 0x4000 | 2 << 24])
+def test_every_residual_epilogue_sums_the_squares_in_one_order(lib, tune):
+    """Without an order of summation over K to tell them apart the streaming schedule (one to four blocks of tokens), its and the tiles' epilogues
+    tile by tile (bit 6), the tiles of every shape and K in slices give a token the same norm scales: the residual stream of
+    the last token of prompts of 1 to 700 tokens has the bits of the prompt that is this token alone."""
+    cfg = dict(synth.model_config("mini_gqa128"))
+    blob = synth.pack_blob(cfg, one_product_per_sum(cfg, 69))
+    eng = dict(synth.engine_config("mini_gqa128"), max_batch=2, max_seq_len=720, kv_num_blocks=100, max_prefill_tokens=1024, ring_slots=16)
+    rng = np.random.default_rng(69)
+    tokens = rng.integers(0, cfg["vocab"], 4)
+
+    def hidden(tune, lengths):
+        e = lib.Engine(cfg, eng, blob, tune=tune)
+        out = {}
+        try:
+            for n in lengths:
+                for tok in tokens:
+                    e.submit(np.concatenate([rng.integers(0, cfg["vocab"], n - 1), [tok]]), 1)
+                    e.run(1)
+                    e.wait()
+                    e.drain()
+                    out.setdefault(n, []).append(e.debug_read(lib.DBG.HIDDEN, np.uint32).reshape(n, cfg["d_model"])[-1])
+        finally:
+            e.shutdown()
+        return {n: np.stack(v) for n, v in out.items()}
+
+    alone = hidden(0, [1])[1]
+    assert len(np.unique(alone)) > alone.size // 2
+    for n, got in hidden(tune, [1, 16, 33, 61, 65, 127, 300, 700]).items():
+        assert (got == alone).all(), "%d tokens: %d of %d values differ" % (n, (got != alone).sum(), alone.size)
+
+
+@pytest.mark.parametrize("prompts", [[1], [40], [130], [530, 477]])
+def test_epilogues_tile_by_tile_do_not_move_a_bit(lib, prompts):
+    """Bit 6 of the tuning word: epilogues that load their operands tile by tile. The residual stream of a mixture of experts behind prompts that take the
+    streaming schedule, its grid of 64 x 64 items and (forced) 64 x 64 tiles has the same bits with and without it: the rotary
+    embedding and the sums of squares are one computation in both."""
+    cfg, eng, raw, blob = setup("mini_moe16", 62)
+    eng = dict(eng, max_batch=6, max_seq_len=600, kv_num_blocks=160, max_prefill_tokens=2048, ring_slots=16)
+    out = []
+    for tune in (1 << 12, 1 << 12 | 0x40):
+        e = lib.Engine(cfg, eng, blob, tune=tune if sum(prompts) > 256 else tune & 0x40)
+        try:
+            for r in _fixed_prompts(cfg, prompts, 1, 270):
+                e.submit(r["prompt"], 1)
+            e.run(1)
+            e.wait()
+            out.append(e.debug_read(lib.DBG.HIDDEN, np.uint32))
+        finally:
+            e.shutdown()
+    assert out[0].size == sum(prompts) * cfg["d_model"] and (out[0] == out[1]).all(), "%d values differ" % (out[0] != out[1]).sum()
