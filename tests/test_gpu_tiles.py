@@ -319,3 +319,25 @@ def test_epilogues_tile_by_tile_do_not_move_a_bit(lib, prompts):
         finally:
             e.shutdown()
     assert out[0].size == sum(prompts) * cfg["d_model"] and (out[0] == out[1]).all(), "%d values differ" % (out[0] != out[1]).sum()
+
+
+def test_fp32_down_projection_with_few_tokens_has_the_chip_to_itself(lib):
+    """Down 1024 x 4096 at 509 tokens is 512 items of 32 x 32, at 2036 tokens 2048, one for every wave of the chip: the quarter of the work may take
+    two thirds of the time (117 us against 250; with eight neighbouring items per workgroup it was 64 busy compute units and 246)."""
+    cfg = dict(synth.model_config("mini_gqa"), n_layers=2, d_model=1024, n_q_heads=8, n_kv_heads=8, head_dim=128, d_ffn=4096, vocab=512, dtype=0)
+    eng = dict(synth.engine_config("mini_gqa"), max_batch=2, max_seq_len=2048, kv_num_blocks=256, max_prefill_tokens=2048, ring_slots=16)
+    e = lib.Engine(cfg, eng, synth.pack_blob(cfg, synth.make_weights(cfg, 71)))
+    us = {}
+    try:
+        e.time_phase(8)
+        for tokens in (509, 2036):
+            for rep in range(5):
+                e.submit(np.zeros(tokens, np.int32), 1)
+                e.run(1)
+                e.wait()
+                e.drain()
+                us[tokens] = min(us.get(tokens, np.inf), float(e.phase_times_ms()[0]) * 1e3 / 2)
+    finally:
+        e.shutdown()
+    print(us)
+    assert us[509] < us[2036] * 2 / 3, us
