@@ -254,14 +254,14 @@ def test_where_chunks_are_merged_does_not_move_a_bit(lib, name, prompts):
 
 def one_product_per_sum(cfg, seed):
     """Weights with which every sum over K has one term that is not zero, so that no order of summation shows: what an output projection
-    adds to the residual stream is zero, and every row of gate, up and down has a single element."""
+    adds to the residual stream is zero, and every row of gate, up, down and the LM head has a single element."""
     raw = synth.make_weights(cfg, seed, gain_jitter=0.1)
     rng = np.random.default_rng(seed)
     for name, w in raw.items():
         what = name.split(".")[-1]
         if what == "wo":
             w[:] = 0
-        elif what in ("wg", "wu", "wd"):
+        elif what in ("wg", "wu", "wd", "lm"):
             row = np.arange(w.shape[0])
             w[:] = 0
             w[row, rng.integers(0, w.shape[1], w.shape[0])] = synth.f32_to_bf16_bits(rng.uniform(0.5, 1.5, w.shape[0]).astype(np.float32))
@@ -271,33 +271,33 @@ def one_product_per_sum(cfg, seed):
 @pytest.mark.parametrize("tune", [0, 2, 0x40, 0x1000, 0x1040, 0x2000, 0x3000, 0x4000, 0x6000, 0x7000, 0x1000 | 2 << 24, 0x1040 | 2 << 24, 0x4000 | 2 << 24])
 def test_every_residual_epilogue_sums_the_squares_in_one_order(lib, tune):
     """Without an order of summation over K to tell them apart the streaming schedule (one to four blocks of tokens), its and the tiles' epilogues
-    tile by tile (bit 6), the tiles of every shape and K in slices give a token the same norm scales: the residual stream of
-    the last token of prompts of 1 to 700 tokens has the bits of the prompt that is this token alone."""
+    tile by tile (bit 6), the tiles of every shape and K in slices give a token the same norm scales: the logits behind 64 last
+    tokens, which the last of these scales multiplies, have the same bits in iterations of 1 to 704 tokens. (A sum of squares that was contracted
+    in another order in some tile shapes moved two rows of the 64.)"""
     cfg = dict(synth.model_config("mini_gqa128"))
     blob = synth.pack_blob(cfg, one_product_per_sum(cfg, 69))
-    eng = dict(synth.engine_config("mini_gqa128"), max_batch=2, max_seq_len=720, kv_num_blocks=100, max_prefill_tokens=1024, ring_slots=16)
+    eng = dict(synth.engine_config("mini_gqa128"), max_batch=64, max_seq_len=32, kv_num_blocks=128, max_prefill_tokens=1024, ring_slots=256)
     rng = np.random.default_rng(69)
-    tokens = rng.integers(0, cfg["vocab"], 4)
+    last = rng.integers(0, cfg["vocab"], 64)
 
-    def hidden(tune, lengths):
-        e = lib.Engine(cfg, eng, blob, tune=tune)
-        out = {}
+    def logits(tune, shapes):
+        """Of every (sequences, tokens of each), an iteration after the other."""
+        e = lib.Engine(cfg, eng, blob, tune=tune, flags=lib.FLAG_KEEP_LOGITS)
         try:
-            for n in lengths:
-                for tok in tokens:
-                    e.submit(np.concatenate([rng.integers(0, cfg["vocab"], n - 1), [tok]]), 1)
-                    e.run(1)
-                    e.wait()
-                    e.drain()
-                    out.setdefault(n, []).append(e.debug_read(lib.DBG.HIDDEN, np.uint32).reshape(n, cfg["d_model"])[-1])
+            for first, n, each in shapes:
+                for tok in last[first:first + n]:
+                    e.submit(np.concatenate([rng.integers(0, cfg["vocab"], each - 1), [tok]]), 1)
+                e.run(1)
+                e.wait()
+                assert len(e.drain()) == n
+                yield e.debug_read(lib.DBG.LOGITS, np.uint32).reshape(n, cfg["vocab"])
         finally:
             e.shutdown()
-        return {n: np.stack(v) for n, v in out.items()}
 
-    alone = hidden(0, [1])[1]
-    assert len(np.unique(alone)) > alone.size // 2
-    for n, got in hidden(tune, [1, 16, 33, 61, 65, 127, 300, 700]).items():
-        assert (got == alone).all(), "%d tokens: %d of %d values differ" % (n, (got != alone).sum(), alone.size)
+    alone = np.concatenate(list(logits(0, [(i, 1, 1) for i in range(64)])))
+    shapes = [(0, 1, 1), (0, 16, 1), (16, 33, 1), (3, 61, 1), (0, 64, 1), (0, 64, 2), (0, 64, 5), (0, 64, 11)]
+    for (first, n, each), got in zip(shapes, logits(tune, shapes)):
+        assert (got == alone[first:first + n]).all(), "%d x %d tokens: %d rows differ" % (n, each, (got != alone[first:first + n]).any(axis=1).sum())
 
 
 @pytest.mark.parametrize("prompts", [[1], [40], [130], [530, 477]])
