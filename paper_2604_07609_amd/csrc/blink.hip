@@ -160,7 +160,12 @@ __global__ void __launch_bounds__(BLK_THREADS) k_ring_write(const SlotDesc* desc
 // of all of them into one pinned array (slot ascending, at most `room` in all), a description of each, and a slot whose
 // last record this is back to EMPTY behind them. One workgroup, small enough (32 registers) to run beside the GEMMs. The host
 // reads nothing of it in between: as a copy of the metadata, a decision there and a fetch a poll waited for the device twice.
-struct OutPick { u32 slot, from, n, completed; };
+// Where 256 slots have more than POLL_HERE new records between them, their records are left to k_fetch_outputs, a second launch and
+// wait: one workgroup takes 512 records to the host in 2.3 us and more. 512 slots with 8 / 16 / 64 / 120 records each, us a poll: all of it here
+// 46 / 62 / 160 / 288, with the second launch 43 / 52 / 84 / 138 (the metadata copied and then one fetch, as it once was: 59 / 65 / 91 / 178).
+#define POLL_HERE 2048u
+struct OutPick { u32 slot, from, n : 30, left : 1, completed : 1, at; };
+static_assert(sizeof(OutPick) == 16, "written as one store");
 struct OutWant { u32 slot, ticket_lo, have, pad; };       // a slot with a request, slot ascending, written by the host
 __global__ void __launch_bounds__(BLK_THREADS) __attribute__((amdgpu_num_vgpr(16))) k_poll_outputs(const OutWant* want, u32 n_want, SlotStatus* status, const OutRec* out_arena, u32 max_seq_len, u32 room,
                                                              OutRec* to, OutPick* picks, u32* n_picks) {
@@ -189,9 +194,10 @@ __global__ void __launch_bounds__(BLK_THREADS) __attribute__((amdgpu_num_vgpr(16
     __syncthreads();
     if (lane == 63u) part[w] = inc;
     __syncthreads();
-    u32 at = inc - n;
-    for (u32 i = 0; i < w; ++i) at += part[i];
+    u32 at = inc - n, sum = 0;
+    for (u32 i = 0; i < BLK_THREADS / WAVE; ++i) { if (i < w) at += part[i]; sum += part[i]; }
     const u32 left = room - staged, full = n;
+    const bool left_over = min(sum, left) > POLL_HERE;
     n = at >= left ? 0u : min(n, left - at);
     const unsigned long long some = __ballot(n != 0);
     u32 place = (u32)__popcll(some & ((1ull << lane) - 1ull));
@@ -203,12 +209,12 @@ __global__ void __launch_bounds__(BLK_THREADS) __attribute__((amdgpu_num_vgpr(16
     if (n) {
       s_slot[place] = slot; s_from[place] = have; s_n[place] = n; s_at[place] = staged + at;
       OutPick p;
-      p.slot = slot; p.from = have; p.n = n; p.completed = done && n == full;
+      p.slot = slot; p.from = have; p.n = n; p.left = left_over; p.completed = done && n == full; p.at = staged + at;
       *(uint4*)(picks + listed + place) = *(const uint4*)&p;
     }
     __syncthreads();
-    const u32 n_recs = strip ? s_at[strip - 1] + s_n[strip - 1] - staged : 0u;
-    for (u32 r0 = 0; r0 < n_recs; r0 += 2 * BLK_THREADS) {      // a thread per record, two on their way
+    const u32 n_recs = strip ? s_at[strip - 1] + s_n[strip - 1] - staged : 0u, n_here = left_over ? 0u : n_recs;
+    for (u32 r0 = 0; r0 < n_here; r0 += 2 * BLK_THREADS) {      // a thread per record, two on their way
       u64 v[2][2];
 #pragma unroll
       for (u32 u = 0; u < 2; ++u) {
@@ -228,16 +234,44 @@ __global__ void __launch_bounds__(BLK_THREADS) __attribute__((amdgpu_num_vgpr(16
         if (r < n_recs) *(ulonglong2*)(to + staged + r) = make_ulonglong2(v[u][0], v[u][1]);
       }
     }
-    if (strip) staged = s_at[strip - 1] + s_n[strip - 1];
+    staged += n_recs;
     listed += strip;
     __syncthreads();                                             // (every record of the strip has been read)
-    if (done && n && n == full) {
+    if (done && n && n == full && !left_over) {
       SlotStatus* st = status + slot;
       st->gen_count = 0; st->ticket_lo = 0; st->flags = 0;
       __hip_atomic_store(&st->state, (u32)BLINK_SLOT_EMPTY, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
   }
   if (threadIdx.x == 0) *n_picks = listed;
+}
+
+// The records that k_poll_outputs has left, a workgroup per FETCH_PIECE records of a slot (`pieces` of them per slot; the host waits
+// for the launch before the slot can be taken again, so it is EMPTY whichever piece ends last).
+#define FETCH_PIECE 1024u
+__global__ void __launch_bounds__(BLK_THREADS) __attribute__((amdgpu_num_vgpr(16))) k_fetch_outputs(const OutPick* picks, u32 pieces, SlotStatus* status, const OutRec* out_arena, u32 max_seq_len, OutRec* to) {
+  const OutPick p = picks[blockIdx.x / pieces];
+  const u32 first = blockIdx.x % pieces * FETCH_PIECE;
+  if (!p.left || first >= p.n) return;
+  const u32 last = min(p.n, first + FETCH_PIECE) - 1;
+  const u64* const src = (const u64*)(out_arena + (u64)p.slot * max_seq_len + p.from);
+  for (u32 r0 = first; r0 <= last; r0 += 2 * BLK_THREADS) {
+    u64 v[2][2];
+#pragma unroll
+    for (u32 u = 0; u < 2; ++u)
+#pragma unroll
+      for (u32 h = 0; h < 2; ++h) v[u][h] = __hip_atomic_load(src + 2 * (u64)min(r0 + u * BLK_THREADS + threadIdx.x, last) + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+#pragma unroll
+    for (u32 u = 0; u < 2; ++u) {
+      const u32 r = r0 + u * BLK_THREADS + threadIdx.x;
+      if (r <= last) *(ulonglong2*)(to + p.at + r) = make_ulonglong2(v[u][0], v[u][1]);
+    }
+  }
+  if (p.completed && first == 0 && threadIdx.x == 0) {
+    SlotStatus* st = status + p.slot;
+    st->gen_count = 0; st->ticket_lo = 0; st->flags = 0;
+    __hip_atomic_store(&st->state, (u32)BLINK_SLOT_EMPTY, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
 }
 
 __global__ void k_open_window(SchedState* ss, u64 iter_limit) {
@@ -1023,6 +1057,14 @@ extern "C" int blink_poll_outputs(blink_engine* e, blink_event* buf, uint32_t ca
                 (u32)std::min<u64>(cap, e->stage_out_cap), e->stage_out, e->stage_picks, e->stage_n_picks));
   HIPCHK(hipStreamSynchronize(e->s_out));
   const u32 n_picks = *e->stage_n_picks;
+  u32 longest = 0;                               // of the slots whose records are still there
+  for (u32 k = 0; k < n_picks; ++k)
+    if (e->stage_picks[k].left) longest = std::max<u32>(longest, e->stage_picks[k].n);
+  if (longest) {
+    const u32 pieces = (longest + FETCH_PIECE - 1) / FETCH_PIECE;
+    HIPCHK(launch(k_fetch_outputs, n_picks * pieces, BLK_THREADS, e->s_out, e->stage_picks, pieces, c.status, c.out_arena, c.max_seq_len, e->stage_out));
+    HIPCHK(hipStreamSynchronize(e->s_out));
+  }
   // events across requests ordered by (iteration, ring slot); per request by index
   u32 w = 0;
   for (u32 k = 0; k < n_picks; ++k) {

@@ -153,6 +153,75 @@ def test_poll_in_pieces_and_the_logits_behind_it(lib, n, cap):
         e.shutdown()
 
 
+@pytest.mark.parametrize("n,out,cap", [(300, 9, 1 << 16), (300, 9, 2500), (40, 60, 1 << 16), (512, 40, 1 << 16), (3, 1500, 1 << 16), (2, 1100, 2100)])
+def test_polls_of_many_records(lib, n, out, cap):
+    """More than 2048 new records of 256 slots come with a second launch, a workgroup per 1024 of a slot: strips of slots on either side of
+    that, polls that end inside a slot, slots with more records than one workgroup takes. Every token once and in order, and the
+    slots can be taken again afterwards."""
+    cfg = synth.model_config("sched_stress")
+    eng = dict(synth.engine_config("sched_stress"), max_batch=n, max_seq_len=out + 8, kv_num_blocks=n * (out // 16 + 2), ring_slots=512)
+    e = lib.Engine(cfg, eng, synth.pack_blob(cfg, synth.make_weights(cfg, 1000)))
+    rng = np.random.default_rng(n)
+    try:
+        for window in range(2):
+            ids = [e.submit(rng.integers(0, cfg["vocab"], 3 + i % 3), out) for i in range(n)]
+            e.run(out)
+            e.wait()
+            got, polls = [], 0
+            while True:
+                ev = e.poll(cap)
+                if ev.size == 0:
+                    break
+                assert ev.size <= cap
+                got.append(ev)
+                polls += 1
+            assert polls == -(-n * out // cap)
+            ev = np.concatenate(got)
+            order = np.lexsort((np.arange(len(ev)), ev["request_id"]))
+            assert (ev["request_id"][order].reshape(n, out) == np.array(ids)[:, None]).all()
+            ev = ev[order].reshape(n, out)
+            assert (ev["index"] == np.arange(out)).all() and (np.diff(ev["iteration"].astype(np.int64), axis=1) == 1).all()
+            assert (ev["flags"] == np.where(np.arange(out) == 0, lib.EVENT_FIRST, 0) + np.where(np.arange(out) == out - 1, lib.EVENT_LAST, 0)).all()
+            if window == 0:
+                first = ev["token"]
+                rng = np.random.default_rng(n)
+            else:
+                assert (ev["token"] == first).all()
+            e.set_exit_when_idle(True)
+            e.run(0)
+            e.wait()
+            e.set_exit_when_idle(False)
+    finally:
+        e.shutdown()
+
+
+def test_a_poll_of_many_records_takes_no_longer_than_two_launches(lib):
+    """512 slots with 120 records each: 61440 records are 1 MB over the bus and 2 MB of events, 140 us a poll (one workgroup for all of
+    them took 290)."""
+    cfg = synth.model_config("sched_stress")
+    eng = dict(synth.engine_config("sched_stress"), max_seq_len=128, kv_num_blocks=512 * 8, ring_slots=512)
+    e = lib.Engine(cfg, eng, synth.pack_blob(cfg, synth.make_weights(cfg, 1000)))
+    took = []
+    try:
+        for _ in range(5):
+            for i in range(512):
+                e.submit(np.full(4, i), 120)
+            e.run(120)
+            e.wait()
+            t0 = time.perf_counter()
+            ev = e.poll(1 << 16)
+            took.append((time.perf_counter() - t0) * 1e6)
+            assert len(ev) == 512 * 120
+            e.set_exit_when_idle(True)
+            e.run(0)
+            e.wait()
+            e.set_exit_when_idle(False)
+    finally:
+        e.shutdown()
+    print("61440 records: %.0f us a poll" % min(took))
+    assert min(took) < 230
+
+
 def test_decode_iterations_behind_a_prefill_run_their_own_batch_s_chain(lib):
     """40 sequences x 8 kv heads of 64 x 3 chunks are more than three attention items per compute unit, where a kernel behind the
     attention merges the chunks: it is there (phase 12) from the first decode iteration behind the prefill iterations, although those
