@@ -298,9 +298,11 @@ static int fail(int code, const char* fmt, ...) {
     if (e_ != hipSuccess) return fail(BLINK_ERR_DEVICE, "%s: %s (%s:%d)", #x, hipGetErrorString(e_), __FILE__, __LINE__); \
   } while (0)
 
-// staging of blink_debug_read: the two descriptions, then pieces of the result
+// staging of blink_debug_read, 4 MB: the two descriptions, then DBG_SLOTS pieces of the result for each thread that copies them out (one on
+// its way while the other is copied)
 #define DBG_PIECE (512u << 10)
-#define DBG_PIECES 34u             // at most: as many as the largest logits need
+#define DBG_THREADS 4u
+#define DBG_SLOTS 2u
 #define DBG_AHEAD (256u << 10)
 
 struct blink_engine {
@@ -328,9 +330,8 @@ struct blink_engine {
   u64 iter_limit = 0;                  // of the current window (0: none)
   u64 iter_before = 0;                 // iterations and chains run before the current window
   u32 chains_before = 0;
-  char* stage_dbg = nullptr;           // pinned: staging of blink_debug_read
-  u32 dbg_pieces = 0;
-  hipEvent_t dbg_ev[DBG_PIECES] = {};
+  char* stage_dbg = nullptr;           // pinned: staging of blink_debug_read (one call at a time: dbg_mu)
+  hipEvent_t dbg_ev[DBG_THREADS * DBG_SLOTS] = {};
   std::mutex dbg_mu;
   // loop
   std::thread launcher;
@@ -454,10 +455,9 @@ static int init_impl(const blink_config* cfg, blink_engine* e) {
   e->stage_out_cap = 1u << 16;
   if (int rc = halloc(e, &e->stage_out, e->stage_out_cap)) return rc;
   if (int rc = halloc(e, &e->stage_picks, c.ring_slots)) return rc;
-  e->dbg_pieces = (u32)std::min<u64>(DBG_PIECES, std::max<u64>(2, (rows_cap * c.V * 4 + DBG_PIECE - 1) / DBG_PIECE));
   {
     void* q = nullptr;
-    HIPCHK(hipHostMalloc(&q, 1024 + (u64)DBG_PIECE * e->dbg_pieces, hipHostMallocMapped));
+    HIPCHK(hipHostMalloc(&q, 1024 + (u64)DBG_PIECE * DBG_THREADS * DBG_SLOTS, hipHostMallocMapped));
     e->host_allocs.push_back(q);
     e->stage_dbg = (char*)q;
   }
@@ -1159,44 +1159,49 @@ extern "C" int blink_get_stats(blink_engine* e, blink_stats* out) {
 }
 
 // Device memory into a caller's (pageable) buffer, in pieces through pinned memory: a piece is on its way over the bus while others are
-// copied out of the staging buffer, by several threads where there is much of it, because most of the time is the first touch of the
-// caller's pages. 16.8 MB into new pages: 4.5 ms as one hipMemcpy, 2.0 with four threads; 8 MB 2.2 and 1.1; 2 MB .58 and .35.
+// copied out of the staging buffer, by up to four threads where there is much of it, because most of the time is the first touch of the
+// caller's pages. Each thread has its own places of the buffer and fills them again as it has copied them out, so that any size goes
+// through the same few megabytes. Into new pages, as one hipMemcpy / like this: 8 MB .80 / .46 ms, 16.8 MB 3.4 / .87, 33 MB 5.9 / 1.6, 131 MB
+// 21.8 / 6.1.
 static hipError_t read_back(blink_engine* e, char* to, const char* from, u64 n) {
-  const u32 pieces = (u32)((n + DBG_PIECE - 1) / DBG_PIECE);
-  char* const ring = e->stage_dbg + 1024;
-  for (u32 first = 0; first < pieces; first += e->dbg_pieces) {
-    const u32 end = std::min(pieces, first + e->dbg_pieces);
-    for (u32 i = first; i < end; ++i) {
-      const u64 off = (u64)i * DBG_PIECE;
-      hipError_t er = hipMemcpyAsync(ring + (u64)(i - first) * DBG_PIECE, from + off, std::min<u64>(DBG_PIECE, n - off), hipMemcpyDeviceToHost, e->s_out);
-      if (er == hipSuccess) er = hipEventRecord(e->dbg_ev[i - first], e->s_out);
-      if (er != hipSuccess) { (void)hipStreamSynchronize(e->s_out); return er; }
-    }
-    std::atomic<u32> next{first};
-    std::atomic<int> bad{0};
-    const int device = e->cfg.device;
-    auto work = [&]() {
-      if (hipSetDevice(device) != hipSuccess) bad = 1;
-      for (u32 i; (i = next.fetch_add(1)) < end;) {
-        if (hipEventSynchronize(e->dbg_ev[i - first]) != hipSuccess) { bad = 1; continue; }
-        const u64 off = (u64)i * DBG_PIECE;
-        memcpy(to + off, ring + (u64)(i - first) * DBG_PIECE, std::min<u64>(DBG_PIECE, n - off));
-      }
+  const u32 pieces = (u32)((n + DBG_PIECE - 1) / DBG_PIECE), threads = std::min(DBG_THREADS, (pieces + 3) / 4);
+  auto part = [=](u32 t) -> hipError_t {         // pieces t, t + threads, ..
+    hipError_t er = hipSetDevice(e->cfg.device);
+    auto slot = [=](u32 i) { return t * DBG_SLOTS + i / threads % DBG_SLOTS; };
+    auto place = [=](u32 i) { return e->stage_dbg + 1024 + (u64)slot(i) * DBG_PIECE; };
+    auto bytes = [=](u32 i) { return std::min<u64>(DBG_PIECE, n - (u64)i * DBG_PIECE); };
+    auto ask = [&](u32 i) {
+      if (er == hipSuccess) er = hipMemcpyAsync(place(i), from + (u64)i * DBG_PIECE, bytes(i), hipMemcpyDeviceToHost, e->s_out);
+      if (er == hipSuccess) er = hipEventRecord(e->dbg_ev[slot(i)], e->s_out);
     };
-    std::thread helpers[3];
-    for (u32 t = 0; t < 3 && (t + 1) * 4 < end - first; ++t) {
-      try { helpers[t] = std::thread(work); } catch (...) { break; }     // (no thread to be had: this one does it)
+    for (u32 i = t; i < pieces && i < t + DBG_SLOTS * threads; i += threads) ask(i);
+    for (u32 i = t; i < pieces && er == hipSuccess; i += threads) {
+      er = hipEventSynchronize(e->dbg_ev[slot(i)]);
+      if (er != hipSuccess) break;
+      memcpy(to + (u64)i * DBG_PIECE, place(i), bytes(i));
+      if (i + DBG_SLOTS * threads < pieces) ask(i + DBG_SLOTS * threads);
     }
-    work();
-    for (auto& h : helpers) if (h.joinable()) h.join();
-    if (bad) return hipErrorUnknown;
+    return er;
+  };
+  hipError_t result[DBG_THREADS] = {};
+  std::thread helpers[DBG_THREADS];
+  for (u32 t = 1; t < threads; ++t) {
+    try { helpers[t] = std::thread([&result, &part, t]() { result[t] = part(t); }); } catch (...) {}   // (no thread to be had: below)
   }
+  result[0] = part(0);
+  for (u32 t = 1; t < threads; ++t) {
+    if (helpers[t].joinable()) helpers[t].join();
+    else result[t] = part(t);
+  }
+  for (hipError_t er : result)
+    if (er != hipSuccess) { (void)hipStreamSynchronize(e->s_out); return er; }      // (nothing on its way into the staging buffer any more)
   return hipSuccess;
 }
 
 extern "C" int blink_debug_read(blink_engine* e, uint32_t what, void* buf, uint64_t cap_bytes, uint64_t* n_bytes) {
   g_err.clear();
   if (!e || !buf || !n_bytes) return fail(BLINK_ERR_INVAL, "null argument");
+  if (e->shut) return fail(BLINK_ERR_STATE, "engine is shut down");
   if (e->loop_active.load()) return fail(BLINK_ERR_STATE, "stop the loop before reading device state");
   HIPCHK(hipSetDevice(e->cfg.device));
   const DevCtx& c = e->ctx;
