@@ -677,9 +677,13 @@ static int init_impl(const blink_config* cfg, blink_engine* e) {
       if (int rc = dalloc(e, &dev, plan.size())) return rc;
       HIPCHK(hipMemcpy(dev, plan.data(), plan.size() * sizeof(GemmPlan), hipMemcpyHostToDevice));
       c.gemm_plan = dev;
+      bool cut = false;                          // (K in slices: not in a mixture of experts, nor in matrices that are large enough)
+      for (const GemmPlan& p : plan) cut = cut || p.qkv >> 3 || p.oproj >> 3 || p.down >> 3;
+      if (cut) {
+        if (int rc = dalloc(e, &c.gemm_part, (u64)e->n_cu * (256 * 128 / 2), false)) return rc;
+        if (int rc = dalloc(e, &c.gemm_part_count, (u64)e->n_cu)) return rc;
+      }
     }
-    if (int rc = dalloc(e, &c.gemm_part, (u64)e->n_cu * (256 * 128 / 2), false)) return rc;
-    if (int rc = dalloc(e, &c.gemm_part_count, (u64)e->n_cu)) return rc;
     if (int rc = dalloc(e, &c.qbuf, ((u64)c.maxT + 16) * c.nq * c.hd)) return rc;   // (and x: 16 rows for the tokens that fill up a tile)
     {
       c.chunk_cap = c.max_batch * ((c.max_seq_len + ATTN_CHUNK_TOKENS - 1) / ATTN_CHUNK_TOKENS);
@@ -911,7 +915,9 @@ static int build_graph(blink_engine* e) {
   e->whole_chain_ok = e->ctx.dtype == 1 && e->ctx.chunk_rec && !(e->cfg.flags & ext) && !(e->cfg.tune & 0x808020u);
   e->merge_in_ok = e->ctx.dtype == 1 && e->ctx.chunk_rec && !(e->cfg.tune & 0x800020u);
   if (e->cfg.flags & BLINK_FLAG_NO_GRAPH) return 0;
-  if (int rc = capture_chain(e, CHAIN_MERGE_KERNEL, &e->iter_graph[CHAIN_MERGE_KERNEL])) return rc;
+  // (the one with the merge kernel is never taken where the attention kernel merges whatever the number of items)
+  if (!e->merge_in_ok || !((e->cfg.tune & 0x8u) || merge_in_attention(~0u, e->ctx.hd, (u32)e->n_cu)))
+    if (int rc = capture_chain(e, CHAIN_MERGE_KERNEL, &e->iter_graph[CHAIN_MERGE_KERNEL])) return rc;
   if (e->whole_chain_ok)
     if (int rc = capture_chain(e, CHAIN_WHOLE, &e->iter_graph[CHAIN_WHOLE])) return rc;
   if (e->merge_in_ok)

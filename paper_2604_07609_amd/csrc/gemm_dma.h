@@ -295,9 +295,9 @@ template <int EPI, int WN, int MI, int MJ, int KS, bool ONCE = false>
 __device__ __forceinline__ void gemm_dma_dense(const MfmaGemmArgs& a, DmaShared& sh, u32 wg, u32 nwg) {
   gemm_dma<EPI, WN, MI, MJ, KS, ONCE, false>(a, DenseItems(a, WN * MI * 16, 8 / WN * MJ * 16), sh, wg, nwg);
 }
-template <int EPI, int WN, int MI, int MJ, bool ONCE = false>
+template <int EPI, int WN, int MI, int MJ>
 __device__ __forceinline__ void gemm_dma_split(const MfmaGemmArgs& a, DmaShared& sh, u32 wg, u32 nwg, u32 slices) {
-  gemm_dma<EPI, WN, MI, MJ, 2, ONCE, true>(a, DenseItems(a, WN * MI * 16, 8 / WN * MJ * 16), sh, wg, nwg, slices);
+  gemm_dma<EPI, WN, MI, MJ, 2, false, true>(a, DenseItems(a, WN * MI * 16, 8 / WN * MJ * 16), sh, wg, nwg, slices);
 }
 
 // ---- dispatch: the schedule of a launch comes from the table of gemm_plan.h -----------------------------------------------
@@ -312,11 +312,7 @@ __device__ __forceinline__ void gemm_bf16(const MfmaGemmArgs& a, u32 plan, GemmS
     if (slices) {
       switch (plan & 7u) {
         case 1: gemm_dma_split<EPI, 4, 1, 2>(a, sh.dma, wg, nwg, slices); break;
-        case 2:
-          if (a.T <= 16) gemm_dma_split<EPI, 8, 1, 1, true>(a, sh.dma, wg, nwg, slices);
-          else if (a.T <= 32) gemm_dma_split<EPI, 4, 2, 1, true>(a, sh.dma, wg, nwg, slices);
-          else gemm_dma_split<EPI, 2, 4, 1>(a, sh.dma, wg, nwg, slices);
-          break;
+        case 2: gemm_dma_split<EPI, 2, 4, 1>(a, sh.dma, wg, nwg, slices); break;
         case 3: gemm_dma_split<EPI, 2, 4, 2>(a, sh.dma, wg, nwg, slices); break;
         default: gemm_dma_split<EPI, 4, 4, 4>(a, sh.dma, wg, nwg, slices); break;
       }
