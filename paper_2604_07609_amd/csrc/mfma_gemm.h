@@ -68,7 +68,7 @@ struct MfmaGemmArgs {
   u32 tune_nw;             // tests and tuning. Low three bits: 0 automatic choice of weight tiles per workgroup of the streaming schedule, 1/2 forced.
                            // Bit 5 (launcher): never a kernel chain without the decode attention's merge kernels, bit 7: always the one for whole contexts, bit 3: always
                            // the one whose attention merges chunks itself. Bit 4 (set in that chain): it does.
-                           // Bit 6: epilogues load their operands tile by tile. Bit 11: tall matrices stream too at T <= 64.
+                           // Bit 6: epilogues load their operands tile by tile (not in waves with four row tiles, epilogue_cols). Bit 11: tall matrices stream too at T <= 64.
                            // Bits 12-14: force the tile shape at T > 64, with them bits 24-27 the slices of K (gemm_plan).
                            // Bit 15 (scheduler): the decode attention's work items are always chunks, bit 22: always whole
                            // contexts; bit 23: the decode attention kernel with static items. Bits 16-19: 15 prompt attention with shared KV tiles, 1, 2, 4 or 8 the
@@ -285,10 +285,10 @@ __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70
 template <typename T>
 __device__ __forceinline__ void loaded(const T& v) { asm volatile("" : : "v"(v)); }
 
-// Epilogue of the TJ accumulator tiles a wave holds for one row tile (tokens t_base + 16 j + lane % 16). The epilogues that
-// read memory (the residual stream, the positions and the rotary table) request the operands of four tiles (two, where a wave has
-// six or eight) first and then compute and store tile by tile: written one tile after the other, every tile's loads would wait behind the
-// previous tile's stores (the compiler has to assume that they may alias), a chain of TJ memory latencies per row tile.
+// Epilogue of the TJ accumulator tiles a wave holds for one row tile (tokens t_base + 16 j + lane % 16); a residual add or rotary embedding comes
+// here from waves with one or two row tiles (with four: epilogue_cols). Those read memory (the residual stream, the
+// positions and the rotary table), and request the operands of all tiles first: written one tile after the other, every tile's loads would wait
+// behind the previous tile's stores (the compiler has to assume that they may alias), a chain of TJ memory latencies.
 // Tokens behind the last one read the last token's operands (an unconditional load) and store nothing.
 // (Bit 6 of the tuning word: tile by tile, for comparison.)
 template <int EPI, int TJ>
@@ -298,44 +298,34 @@ __device__ __forceinline__ void epilogue_row(const MfmaGemmArgs& a, const floatx
     for (int j = 0; j < TJ; ++j) epilogue_tile<EPI>(a, acc[j], nt, t_base + j * 16, rstd + j * 16);
     return;
   }
-  constexpr int H = TJ;                        // tiles whose operands are requested together
-  // The lane comes anew for every row tile (an empty asm): else the offsets of all token tiles are kept from the first row tile to the
-  // last, and beside 128 accumulators and the next item's operands they end in scratch memory, whose loads wait behind every
-  // store: 4096 x 14336 at 8000 tokens 771 us instead of 753.
-  u32 lane = threadIdx.x & 63;
-  asm volatile("" : "+v"(lane));
-  const u32 n0 = nt * 16 + (lane >> 4) * 4;
+  const u32 lane = threadIdx.x & 63, n0 = nt * 16 + (lane >> 4) * 4;
   const u32 hd = a.hd, half = hd / 2, head = EPI == EPI_QKV_ROPE ? n0 / hd : 0u, p = EPI == EPI_QKV_ROPE ? (n0 % hd) >> 1 : 0u;   // rows: (p, p+half, p+1, p+1+half)
   const bool rot = head < a.nq + a.nkv;
-  float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (EPI == EPI_RESIDUAL) g = *(const float4*)(a.g_next + n0);
+  u32 t[TJ], tc[TJ];
 #pragma unroll
-  for (int j0 = 0; j0 < TJ; j0 += H) {
-    u32 t[H], tc[H];
+  for (int j = 0; j < TJ; ++j) { t[j] = t_base + j * 16 + (lane & 15); tc[j] = min(t[j], a.T - 1); }
+  if (EPI == EPI_RESIDUAL) {
+    const float4 g = *(const float4*)(a.g_next + n0);
+    float4 old[TJ];
 #pragma unroll
-    for (int j = 0; j < H; ++j) { t[j] = t_base + (j0 + j) * 16 + (lane & 15); tc[j] = min(t[j], a.T - 1); }
-    if (EPI == EPI_RESIDUAL) {
-      float4 old[H];
+    for (int j = 0; j < TJ; ++j) old[j] = *(const float4*)(a.x + (u64)tc[j] * a.ldx + n0);
 #pragma unroll
-      for (int j = 0; j < H; ++j) old[j] = *(const float4*)(a.x + (u64)tc[j] * a.ldx + n0);
+    for (int j = 0; j < TJ; ++j) residual_finish(a, acc[j], nt, t[j], old[j], g);
+  } else {   // EPI_QKV_ROPE
+    i32 pos[TJ];
+    u32 slot[TJ];
 #pragma unroll
-      for (int j = 0; j < H; ++j) residual_finish(a, acc[j0 + j], nt, t[j], old[j], g);
-    } else {   // EPI_QKV_ROPE
-      i32 pos[H];
-      u32 slot[H];
+    for (int j = 0; j < TJ; ++j) { pos[j] = a.positions[tc[j]]; slot[j] = (u32)a.slot_mapping[tc[j]]; }
+    float4 cs[TJ];
 #pragma unroll
-      for (int j = 0; j < H; ++j) { pos[j] = a.positions[tc[j]]; slot[j] = (u32)a.slot_mapping[tc[j]]; }
-      float4 cs[H];
+    for (int j = 0; j < TJ; ++j) cs[j] = *(const float4*)(a.rope_tab + (u64)(rot ? pos[j] : 0) * half + (rot ? p : 0u));   // (cos,sin) of pairs p, p+1
 #pragma unroll
-      for (int j = 0; j < H; ++j) cs[j] = *(const float4*)(a.rope_tab + (u64)(rot ? pos[j] : 0) * half + (rot ? p : 0u));   // (cos,sin) of pairs p, p+1
-#pragma unroll
-      for (int j = 0; j < H; ++j) {
-        loaded(cs[j].x); loaded(cs[j].y); loaded(cs[j].z); loaded(cs[j].w);
-        loaded(slot[j]);
-      }
-#pragma unroll
-      for (int j = 0; j < H; ++j) rope_finish(a, acc[j0 + j], nt, t[j], rstd[(j0 + j) * 16 + (lane & 15)], slot[j], cs[j]);
+    for (int j = 0; j < TJ; ++j) {
+      loaded(cs[j].x); loaded(cs[j].y); loaded(cs[j].z); loaded(cs[j].w);
+      loaded(slot[j]);
     }
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) rope_finish(a, acc[j], nt, t[j], rstd[j * 16 + (lane & 15)], slot[j], cs[j]);
   }
 }
 

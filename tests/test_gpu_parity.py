@@ -89,11 +89,11 @@ def test_bf16_wide_matrices(lib, name, max_batch, n_req, tune):
 
 
 @pytest.mark.parametrize("max_batch,tune", [(100, 0), (200, 0), (250, 0x1000), (150, 0x2000), (250, 0x3000), (140, 0x6000), (250, 0x7000), (120, 0x4000),
-                                            (200, 0x40)])
+                                            (200, 0x40), (200, 0x1040)])
 def test_bf16_decode_batches_beyond_64(lib, max_batch, tune):
-    """Decode iterations of 65..256 tokens: QKV as 64 x 64 streaming items over a (rows, token groups) grid up to 128 tokens, else and in the
-    other projections the tile the cost model picks, or with bits 12-14 of the tuning word one of the six shapes
-    everywhere; the LM head reads its tokens through the indirection. Bit 6: epilogues that load their operands tile by tile."""
+    """Decode iterations of 65..256 tokens: the tile that the cost model picks, with K in slices or whole, or with bits 12-14 of the tuning word
+    one of the six shapes everywhere; the LM head reads its tokens through the indirection. Bit 6: epilogues that load their operands
+    tile by tile, in the 64 x 64 tiles (0x1040) and where a wave has one row tile otherwise."""
     tune_word = tune
     cfg, eng, raw, blob = setup("mini_wide2", 35)
     eng = dict(eng, max_batch=max_batch, kv_num_blocks=3 * max_batch + 64, ring_slots=512, max_prefill_tokens=2048)
@@ -120,11 +120,12 @@ def test_bf16_forced_tiles_per_workgroup(lib, nw):
     print("forced", nw, "tiles per workgroup: worst relative logit error", worst)
 
 
-@pytest.mark.parametrize("tune", [0, 0x40, 0x1000, 0x2000, 0x3000, 0x4000, 0x6000, 0x7000, 0x7040])
+@pytest.mark.parametrize("tune", [0, 0x40, 0x1000, 0x1040, 0x2000, 0x3000, 0x4000, 0x6000, 0x7000, 0x7040])
 def test_bf16_large_prefill_iterations(lib, tune):
     """Prefill iterations of ~1000 tokens (a ragged last token tile, a ragged last row block) with the shape the cost model picks and
     with each shape forced (bits 12-14 of the tuning word: 64 x 64, 128 x 64, 128 x 128, 256 x 128, 256 x 192, 256 x 256); bit 6:
-    epilogues that load their operands tile by tile."""
+    epilogues that load their operands tile by tile (0x1040; the other shapes' waves have four row tiles and an epilogue of their own, in
+    which the bit has no effect)."""
     tune_word = tune
     cfg, eng, raw, blob = setup("mini_wide4", 39)
     eng = dict(eng, max_batch=40, max_prefill_tokens=1100, kv_num_blocks=200)
