@@ -341,3 +341,25 @@ def test_fp32_down_projection_with_few_tokens_has_the_chip_to_itself(lib):
         e.shutdown()
     print(us)
     assert us[509] < us[2036] * 2 / 3, us
+
+
+@pytest.mark.parametrize("slices", [5, 8])
+@pytest.mark.parametrize("shape", [1, 2, 3])
+def test_tile_gemms_with_k_in_many_slices(lib, shape, slices):
+    """The workgroup that comes last adds four slices of 128 x 64 tiles at a time, eight of 64 x 64 and one of 128 x 128: five and eight slices,
+    so that there are second and partly filled batches; K of 9 and 11 pairs of k-steps (slices of one to three pairs)."""
+    cfg = dict(synth.model_config("mini_gqa"), n_layers=1, d_model=576, n_q_heads=9, n_kv_heads=3, head_dim=64, d_ffn=704, vocab=1003)
+    raw = synth.make_weights(cfg, 72, gain_jitter=0.1)
+    eng = dict(synth.engine_config("mini_gqa"), max_batch=24, max_seq_len=400, kv_num_blocks=96, max_prefill_tokens=512, ring_slots=64)
+    for prompts in ([65], [61], [128], [3] * 19):
+        worst = parity.stepwise_check(lib, cfg, eng, raw, synth.pack_blob(cfg, raw), _fixed_prompts(cfg, prompts, 3, 272), rtol=RTOL, tune=shape << 12 | slices << 24)
+        print("shape", shape, "slices", slices, "prompts", prompts, "worst relative logit error", worst)
+
+
+@pytest.mark.parametrize("prompts", [[17], [61], [65], [257, 73], [400, 109]])
+def test_eight_slices_by_the_planner_s_own_choice(lib, prompts):
+    """Down 256 x 6400 (100 pairs of k-steps) is in eight slices from 17 tokens on without being asked to."""
+    cfg, eng, raw, blob = setup("mini_wide2", 73)
+    eng = dict(eng, max_batch=4, max_seq_len=420, kv_num_blocks=96)
+    worst = parity.stepwise_check(lib, cfg, eng, raw, blob, _fixed_prompts(cfg, prompts, 2, 273), rtol=RTOL)
+    print("prompts", prompts, "worst relative logit error", worst)
