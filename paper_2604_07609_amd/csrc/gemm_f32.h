@@ -10,7 +10,7 @@
 //   few tiles: a workgroup per (row tile, 16 tokens), K in a slice per wave, partial sums joined through LDS. Four waves, and
 //     eight in the down projection, whose K is the FFN's width (256 x 1024 at 8 tokens 6.5 us, 6.7 with sixteen; the
 //     others, whose loads are one batch per wave already, take 1 to 2 us longer with eight);
-//   many tiles (more than 1024): a wave per 32 rows x 32 tokens with the whole of K.
+//   many tiles (more than four per compute unit): a wave per 32 rows x 32 tokens with the whole of K.
 // The gate is applied once, where gate and up are computed (as the down projection's operand it was computed anew for every row
 // tile: 256 x 1024 at 8 tokens, with K in four slices, 10.2 us).
 // The norm: its gain multiplies the operand as it is loaded, its scale (one number per token) the finished sum; the
@@ -168,7 +168,7 @@ __device__ __forceinline__ void gemm_f32(const F32GemmArgs& a, F32GemmShared<WAV
   auto w_ptr = [&](u32 row) { return a.W + (u64)min(row + lc, a.N - 1) * a.K + 4 * lg; };        // (rows and tokens past the end
   auto x_ptr = [&](u32 t) { const u32 r = min(t + lc, a.T - 1); return a.A + (u64)(a.rows ? a.rows[r] : r) * a.lda + 4 * lg; };   // repeat the last one)
   auto scale = [&](float ss) { return 1.0f / sqrtf(ss / (float)a.K + a.eps); };
-  if (NT * TB > 1024) {
+  if (NT * TB > nwg * WAVES / 2) {         // (eight waves per compute unit in either launch: 1024 tiles on 256 of them)
     constexpr u32 nw = WAVES;
     const u32 RG = (NT + 1) / 2, TG = (TB + 1) / 2;
     // four neighbouring items per workgroup, of eight waves the other four as many workgroups further on: eight neighbours would leave half
