@@ -312,8 +312,12 @@ __device__ __forceinline__ void merge_chunks(const DevCtx& c, AttnMfmaShared& sh
         for (u32 u = 0; u < 4; ++u) M = fmaxf(M, m[u]);
       }
 #pragma unroll
-      for (u32 u = 0; u < 4; ++u)
-        if (p0 + u < nch) merge_add(m[u], l[u], v[u], M, L, O);
+      for (u32 u = 0; u < 4; ++u) {                // (computed in any case: a branch would wait for its chunk's loads)
+        float Ln = L, On = O;
+        merge_add(m[u], l[u], v[u], M, Ln, On);
+        L = p0 + u < nch ? Ln : L;
+        O = p0 + u < nch ? On : O;
+      }
     }
     c.aq[packed_off(t, (g * G + h) * HD + dim, c.TBS)] = f32_to_f16(O / L);
   }
