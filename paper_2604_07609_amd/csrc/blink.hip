@@ -1170,34 +1170,36 @@ extern "C" int blink_get_stats(blink_engine* e, blink_stats* out) {
 // through the same few megabytes. Into new pages, as one hipMemcpy / like this: 8 MB .80 / .46 ms, 16.8 MB 3.4 / .87, 33 MB 5.9 / 1.6, 131 MB
 // 21.8 / 6.1.
 static hipError_t read_back(blink_engine* e, char* to, const char* from, u64 n) {
-  const u32 pieces = (u32)((n + DBG_PIECE - 1) / DBG_PIECE), threads = std::min(DBG_THREADS, (pieces + 3) / 4);
-  auto part = [=](u32 t) -> hipError_t {         // pieces t, t + threads, ..
+  const u32 pieces = (u32)((n + DBG_PIECE - 1) / DBG_PIECE), threads = std::min(DBG_THREADS, (pieces + 3) / 4), ahead = threads * DBG_SLOTS;
+  auto slot = [=](u32 i) { return i % threads * DBG_SLOTS + i / threads % DBG_SLOTS; };
+  auto place = [=](u32 i) { return e->stage_dbg + 1024 + (u64)slot(i) * DBG_PIECE; };
+  auto bytes = [=](u32 i) { return std::min<u64>(DBG_PIECE, n - (u64)i * DBG_PIECE); };
+  auto ask = [=](u32 i) -> hipError_t {
+    const hipError_t er = hipMemcpyAsync(place(i), from + (u64)i * DBG_PIECE, bytes(i), hipMemcpyDeviceToHost, e->s_out);
+    return er != hipSuccess ? er : hipEventRecord(e->dbg_ev[slot(i)], e->s_out);
+  };
+  auto part = [=](u32 t) -> hipError_t {         // pieces t, t + threads, .., of which the first DBG_SLOTS have been asked for
     hipError_t er = hipSetDevice(e->cfg.device);
-    auto slot = [=](u32 i) { return t * DBG_SLOTS + i / threads % DBG_SLOTS; };
-    auto place = [=](u32 i) { return e->stage_dbg + 1024 + (u64)slot(i) * DBG_PIECE; };
-    auto bytes = [=](u32 i) { return std::min<u64>(DBG_PIECE, n - (u64)i * DBG_PIECE); };
-    auto ask = [&](u32 i) {
-      if (er == hipSuccess) er = hipMemcpyAsync(place(i), from + (u64)i * DBG_PIECE, bytes(i), hipMemcpyDeviceToHost, e->s_out);
-      if (er == hipSuccess) er = hipEventRecord(e->dbg_ev[slot(i)], e->s_out);
-    };
-    for (u32 i = t; i < pieces && i < t + DBG_SLOTS * threads; i += threads) ask(i);
     for (u32 i = t; i < pieces && er == hipSuccess; i += threads) {
       er = hipEventSynchronize(e->dbg_ev[slot(i)]);
       if (er != hipSuccess) break;
       memcpy(to + (u64)i * DBG_PIECE, place(i), bytes(i));
-      if (i + DBG_SLOTS * threads < pieces) ask(i + DBG_SLOTS * threads);
+      if (i + ahead < pieces) er = ask(i + ahead);
     }
     return er;
   };
   hipError_t result[DBG_THREADS] = {};
-  std::thread helpers[DBG_THREADS];
-  for (u32 t = 1; t < threads; ++t) {
-    try { helpers[t] = std::thread([&result, &part, t]() { result[t] = part(t); }); } catch (...) {}   // (no thread to be had: below)
-  }
-  result[0] = part(0);
-  for (u32 t = 1; t < threads; ++t) {
-    if (helpers[t].joinable()) helpers[t].join();
-    else result[t] = part(t);
+  for (u32 i = 0; i < std::min(pieces, ahead) && result[0] == hipSuccess; ++i) result[0] = ask(i);
+  if (result[0] == hipSuccess) {
+    std::thread helpers[DBG_THREADS];
+    for (u32 t = 1; t < threads; ++t) {
+      try { helpers[t] = std::thread([&result, &part, t]() { result[t] = part(t); }); } catch (...) {}   // (no thread to be had: below)
+    }
+    result[0] = part(0);
+    for (u32 t = 1; t < threads; ++t) {
+      if (helpers[t].joinable()) helpers[t].join();
+      else result[t] = part(t);
+    }
   }
   for (hipError_t er : result)
     if (er != hipSuccess) { (void)hipStreamSynchronize(e->s_out); return er; }      // (nothing on its way into the staging buffer any more)
