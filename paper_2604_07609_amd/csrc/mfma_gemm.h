@@ -688,7 +688,9 @@ __device__ __forceinline__ void gemm_router(const MfmaGemmArgs& a, MfmaShared& s
     constexpr int U = 4;
     for (u32 base = wg * nw; base < items; base += nwg * nw) {     // the waves of a workgroup: neighbouring row tiles, the same tokens
       const u32 item = base + w, nt = min(item, items - 1) % NT, tb = min(item, items - 1) / NT;
-      compute_rstd<128, BLK_THREADS>(a, (base / NT) * 32, sh.rstd);   // (the four items lie in at most two, or four, blocks of tokens)
+      // (the four items lie in at most two, or four, blocks of tokens)
+      if (NT >= 4) compute_rstd<64, BLK_THREADS>(a, (base / NT) * 32, sh.rstd);
+      else compute_rstd<128, BLK_THREADS>(a, (base / NT) * 32, sh.rstd);
       const f16_t* wp = a.Wp + (u64)nt * KT * 512 + lane * 8;
       const f16_t* xp = a.Xp + (u64)tb * 1024 + lane * 8;
       const u64 xk = (u64)a.TBS * 512;
