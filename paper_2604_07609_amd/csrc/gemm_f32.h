@@ -8,8 +8,9 @@
 // per lane: lane l holds row (or token) l % 16 and k = 4 (l / 16) .. + 3 of sixteen k, and the four matrix instructions of the
 // sixteen take element 0, 1, 2, 3 of both (the order of k inside a sum is free as long as both operands agree). Two schedules:
 //   few tiles: a workgroup per (row tile, 16 tokens), K in a slice per wave, partial sums joined through LDS. Four waves, and
-//     eight in the down projection, whose K is the FFN's width (256 x 1024 at 8 tokens 6.5 us, 6.7 with sixteen; the
-//     others, whose loads are one batch per wave already, take 1 to 2 us longer with eight);
+//     eight in the down projection, whose K is the FFN's width (256 x 1024 at 8 tokens 6.5 us, 6.7 with sixteen; 1024 x 4096 at 1 / 16 /
+//     64 / 200 tokens 15 / 21 / 21 / 66 us, with four 25 / 30 / 31 / 97; the others, whose loads are one batch per wave
+//     already, take 1 to 2 us longer with eight);
 //   many tiles (more than four per compute unit): a wave per 32 rows x 32 tokens with the whole of K.
 // The gate is applied once, where gate and up are computed (as the down projection's operand it was computed anew for every row
 // tile: 256 x 1024 at 8 tokens, with K in four slices, 10.2 us).

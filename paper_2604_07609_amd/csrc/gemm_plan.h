@@ -59,7 +59,8 @@ constexpr u32 dma_tiles(u32 N, u32 T, u32 bn, u32 bt) { return (N + bn - 1) / bn
 //     idle at 300 to 700 tokens, and at 17 to 256 larger tiles read the activations fewer times (the streaming schedule reads all of
 //     them in every workgroup). Both sides in us: 4096 x 14336 at 33 / 61 / 128 / 256 / 300 / 509 tokens 39 / 45 / 68 / 69 / 103 / 107 whole
 //     and 31 / 32 / 45 / 56 / 68 / 82 in slices, 4096 x 4096 at 128 / 300 tokens 26 / 37 and 22 / 31, 6144 x 4096 at 192 39 and 34, 1024 x 4096 at
-//     256 20 and 16. The last workgroup's reading and adding take 4 us and more, so at 61 tokens 4096 x 4096 stays whole (18 / 18).
+//     256 20 and 16. The last workgroup's reading and adding take 4 us and more, so 4096 x 4096 stays whole up to 48 tokens (16 us) and takes
+//     18 either way at 61.
 //     The model is within 11 % (rms) of launches with both forced, and its choice 0.7 % from the best of them on average.
 static inline unsigned char gemm_plan(int epi, u32 N, u32 K, u32 T, bool ordered, u32 ncu, u32 tune) {
   const u32 shape = (tune >> 12) & 7u, slices = (tune >> 24) & 15u;       // forced

@@ -352,8 +352,8 @@ __device__ __forceinline__ void transpose4(u32 (&r)[4]) {
 // result is a whole packed tile (1 KB) per column, queries and keys are runs of 64 bytes per token.
 // Tokens behind the last one are computed and stored like the others, into rows that the buffers have for it (16 behind the
 // last token's; for keys and values the query buffer's), so that no store stands in a branch, where the loads behind it would
-// have to wait for it. QKV 6144 x 4096 at 509 / 1700 / 8000 tokens 58 / 120 / 466 us before and 45 / 87 / 342 now (with compute_rstd and
-// without waits in the main loop), gate/up 28672 x 4096 at 1700 / 8000 tokens 351 / 1506 and 325 / 1411.
+// have to wait for it. QKV 6144 x 4096 at 509 / 1700 / 8000 tokens 58 / 120 / 466 us before and 45 / 92 / 346 now (with compute_rstd and
+// without waits in the main loop), gate/up 28672 x 4096 at 1700 / 8000 tokens 351 / 1506 and 341 / 1452 (means of a pass).
 template <int EPI, int TJ>
 __device__ __forceinline__ void epilogue_cols(const MfmaGemmArgs& a, const floatx4_t (&acc)[4][TJ], u32 nt0, u32 t_base, const float* rstd) {
   u32 lane = threadIdx.x & 63;
