@@ -363,3 +363,30 @@ def test_eight_slices_by_the_planner_s_own_choice(lib, prompts):
     eng = dict(eng, max_batch=4, max_seq_len=420, kv_num_blocks=96)
     worst = parity.stepwise_check(lib, cfg, eng, raw, blob, _fixed_prompts(cfg, prompts, 2, 273), rtol=RTOL)
     print("prompts", prompts, "worst relative logit error", worst)
+
+
+def test_iterations_beyond_16384_tokens(lib):
+    """Down 160 x 9216 has K in slices up to 16384 tokens, exactly one item per compute unit, and whole beyond: 42 prompts of 400 tokens in one
+    iteration of 16800 give the logits that they give in iterations of 4000."""
+    cfg = dict(synth.model_config("mini_gqa"), n_layers=2, d_model=160, n_q_heads=4, n_kv_heads=4, head_dim=64, d_ffn=9216, vocab=1003)
+    blob = synth.pack_blob(cfg, synth.make_weights(cfg, 74, gain_jitter=0.1))
+    rows = []
+    for budget in (4000, 20000):
+        eng = dict(synth.engine_config("mini_gqa"), max_batch=42, max_seq_len=416, kv_num_blocks=42 * 26, max_prefill_tokens=budget, ring_slots=64)
+        e = lib.Engine(cfg, eng, blob, flags=lib.FLAG_KEEP_LOGITS)
+        try:
+            for r in _fixed_prompts(cfg, [400] * 42, 1, 274):
+                e.submit(r["prompt"], 1)
+            got = []
+            while sum(len(g) for g in got) < 42:
+                e.run(1)
+                e.wait()
+                e.drain()
+                got.append(e.debug_read(lib.DBG.LOGITS, np.float32).reshape(-1, cfg["vocab"]))
+            rows.append(np.concatenate(got))
+        finally:
+            e.shutdown()
+    assert len(got) == 1
+    error = np.abs(rows[0] - rows[1]).max(axis=1) / np.abs(rows[0]).max(axis=1)
+    print("worst relative difference", error.max())
+    assert error.max() < RTOL
